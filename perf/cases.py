@@ -1,0 +1,643 @@
+"""The workloads whose speed this repository watches: the entry points of the
+package at the sizes its configurations, tests and benchmark use them, from
+the smallest mesh to the largest.
+
+A case names an entry point ("kind") and its sizes:
+
+* matvec        y = F_h x (`KKTOperator.matvec`)
+* ras_apply     z = M^{-1} r, one-level RAS (`RAS.apply`)
+* ras_setup     a new operator's subdomain factorisation and its first
+                application (`KKTOperator`, `RAS`, `RAS.apply`)
+* coarse_apply  the exact coarse correction of q vectors (`Coarse.apply` for
+                q = 1, else `Coarse.apply_multi`)
+* coarse_setup  the block elimination of a coarse level and its first
+                application (`Coarse`, `Coarse.apply`)
+* solve         new sensor data on a kept operator: right-hand side, then
+                restarted (F)GMRES to rtol 1e-6 (`KKTOperator.rhs`, `solve`)
+* solve_batch   several uneven instances solved together (`solve_batch`)
+
+Problems are synthetic and seeded: a smooth positive diffusivity, moving
+Gaussian sources seen by point sensors with 1% noise, random Krylov-like
+vectors.  `exact` evaluates the same quantities in plain torch FP64.
+"""
+import math
+from types import SimpleNamespace
+
+import numpy as np
+import torch
+
+import paper_1508_06103_amd as st
+from paper_1508_06103_amd import tune
+
+DTO, OTD = 0, 1
+F64, F32 = "f64", "f32"
+HOST_NODES = 1000       # largest spatial mesh whose exact solve is formed densely
+EXACT_ROWS = 2_500_000  # largest sum of box rows factored by `exact`
+
+
+def listed():
+    return [
+        # the smallest configuration's operator (cube8x16): launch latency
+        dict(name="matvec_8x16", kind="matvec", n0=8, n1=8, n2=8, M=16, variant=DTO, reg=0, faces=3, seed=0),
+        # an anisotropic mesh with odd node counts, the Appendix A variant and the H1-L2 regularisation
+        dict(name="matvec_ragged", kind="matvec", n0=37, n1=22, n2=29, M=41, variant=OTD, reg=1, faces=3, seed=0),
+        # the largest configuration (cube48x96), two per FGMRES step of the two-level method
+        dict(name="matvec_48x96", kind="matvec", n0=48, n1=48, n2=48, M=96, variant=DTO, reg=0, faces=3, seed=0),
+        # the benchmark preconditioner (cube32x64): 512 boxes, overlap 2, FP64 factors
+        dict(name="ras_f64_32x64", kind="ras_apply", n0=32, n1=32, n2=32, M=64, p0=4, p1=4, p2=4, p3=8, overlap=2,
+             precision=F64, variant=DTO, reg=0, faces=3, seed=0),
+        # an instance of the uneven batch (24^3 x 48) with mixed-precision (FP32) factors
+        dict(name="ras_f32_24x48", kind="ras_apply", n0=24, n1=24, n2=24, M=48, p0=3, p1=3, p2=3, p3=4, overlap=1,
+             precision=F32, variant=DTO, reg=0, faces=3, seed=0),
+        # a new operator: its factors, before the first solve on it can start
+        dict(name="ras_setup_24x48", kind="ras_setup", n0=24, n1=24, n2=24, M=48, p0=3, p1=3, p2=3, p3=4, overlap=1,
+             precision=F64, variant=DTO, reg=0, faces=3, seed=0),
+        # one coarse correction per FGMRES step of a two-level solve (32^3 x 64 over 8^3 x 16)
+        dict(name="coarse_f64_32x64", kind="coarse_apply", n0=32, n1=32, n2=32, M=64, f0=4, f1=4, f2=4, f3=4, q=1,
+             precision=F64, variant=DTO, reg=0, faces=3, seed=0),
+        # requests in flight on one operator share a coarse pass (served stream)
+        dict(name="coarse_f32_q6_32x64", kind="coarse_apply", n0=32, n1=32, n2=32, M=64, f0=4, f1=4, f2=4, f3=4, q=6,
+             precision=F32, variant=DTO, reg=0, faces=3, seed=0),
+        # the coarse level of a new operator
+        dict(name="coarse_setup_32x64", kind="coarse_setup", n0=32, n1=32, n2=32, M=64, f0=4, f1=4, f2=4, f3=4,
+             precision=F64, variant=DTO, reg=0, faces=3, seed=0),
+        # the smallest whole solve (cube8x16, one-level GMRES(30)): latency of every launch of a step
+        dict(name="solve_8x16", kind="solve", n0=8, n1=8, n2=8, M=16, p0=2, p1=2, p2=2, p3=2, overlap=1, precision=F64,
+             f=0, restart=30, variant=DTO, reg=0, faces=3, seed=0, steps=20),
+        # a served two-level request: FP32 preconditioners inside FP64 FGMRES(50)
+        dict(name="solve_two_level_32x64", kind="solve", n0=32, n1=32, n2=32, M=64, p0=4, p1=4, p2=4, p3=8, overlap=1,
+             precision=F32, f=4, restart=50, variant=DTO, reg=0, faces=3, seed=0, steps=56),
+        # uneven instances together, tuned partitions, FP32 preconditioners
+        dict(name="batch_12_uneven", kind="solve_batch", count=12, max_n=24, max_M=48, precision=F32, restart=50,
+             seed=0, steps=40),
+    ]
+
+
+# --------------------------------------------------------------------------
+# drawn cases
+# --------------------------------------------------------------------------
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _model(rng):
+    # Dirichlet faces: x = 0 and x = 1 as in the benchmark problems, or one face, or both x and z
+    return dict(variant=rng.choice([DTO, DTO, OTD]), reg=rng.choice([0, 0, 1]), faces=rng.choice([3, 3, 1, 51]),
+                seed=rng.randrange(1 << 20))
+
+
+def _boxes(rng, n, M):
+    """Overlap 0 to 2, parts with owned boxes of about 6 to 12 nodes per axis (9 to 12 with overlap 2)."""
+    overlap = rng.choice([0, 1, 1, 2])
+    parts = [max(1, round((k + 1) / rng.uniform(9 if overlap == 2 else 6, 12))) for k in (*n, M)]
+    return dict(zip(("p0", "p1", "p2", "p3"), parts), overlap=overlap)
+
+
+def draw(rng):
+    kind = rng.choice(["matvec", "matvec", "ras_apply", "ras_apply", "ras_setup", "coarse_apply", "coarse_apply",
+                       "coarse_setup", "solve", "solve", "solve_batch"])
+    prec = rng.choice([F64, F32])
+    if kind == "matvec":
+        n = [_log(rng, 4, 48) for _ in range(3)]
+        return dict(kind=kind, n0=n[0], n1=n[1], n2=n[2], M=_log(rng, 4, 96), **_model(rng))
+    if kind in ("ras_apply", "ras_setup"):
+        n = [_log(rng, 5, 28 if kind == "ras_apply" else 24) for _ in range(3)]
+        M = _log(rng, 6, 48)
+        return dict(kind=kind, n0=n[0], n1=n[1], n2=n[2], M=M, **_boxes(rng, n, M), precision=prec, **_model(rng))
+    if kind in ("coarse_apply", "coarse_setup"):
+        f = [rng.choice([2, 3, 4]) for _ in range(4)]
+        c = [rng.randint(3, 8) for _ in range(3)]
+        out = dict(kind=kind, n0=f[0] * c[0], n1=f[1] * c[1], n2=f[2] * c[2], M=f[3] * rng.randint(3, 16),
+                   f0=f[0], f1=f[1], f2=f[2], f3=f[3], precision=prec, **_model(rng))
+        if kind == "coarse_apply":
+            out["q"] = rng.choice([1, 1, rng.randint(2, 16)])
+        return out
+    if kind == "solve":
+        two = rng.random() < 0.5
+        if two:   # nested coarse mesh of factor 2 in every axis
+            n = [2 * rng.randint(3, 8) for _ in range(3)]
+            M = 2 * rng.randint(4, 16)
+        else:
+            n = [_log(rng, 5, 20) for _ in range(3)]
+            M = _log(rng, 8, 40)
+        return dict(kind=kind, n0=n[0], n1=n[1], n2=n[2], M=M, **_boxes(rng, n, M), precision=prec, f=2 if two else 0,
+                    restart=rng.choice([30, 50]), **{**_model(rng), "faces": 3}, steps=20)
+    return dict(kind=kind, count=rng.randint(2, 10), max_n=rng.choice([12, 16, 20]), max_M=rng.choice([16, 24, 32]),
+                precision=prec, restart=rng.choice([30, 50]), seed=rng.randrange(1 << 20), steps=30)
+
+
+# --------------------------------------------------------------------------
+# problems
+# --------------------------------------------------------------------------
+def _problem(n, M, seed, *, variant=DTO, reg=0, faces=3, coarse=(1, 1, 1), beta=1e-4, sensors=64, nsrc=2):
+    """A seeded instance; sensors sit on interior nodes of the mesh coarsened by `coarse`."""
+    rng = np.random.default_rng(seed)
+    ax = [(np.arange(n[d]) + 0.5) / n[d] for d in range(3)]
+    g = np.zeros((n[2], n[1], n[0]))
+    for _ in range(8):
+        m, c, phi = rng.integers(0, 3, 3), rng.standard_normal(), rng.uniform(0, 2 * np.pi)
+        g += c * np.cos(2 * np.pi * (m[0] * ax[0][None, None, :] + m[1] * ax[1][None, :, None]
+                                     + m[2] * ax[2][:, None, None]) + phi)
+    a = np.exp(0.5 * g / max(np.abs(g).max(), 1e-12))
+    # distinct interior nodes of the (coarse) mesh
+    grid = [np.arange(c, n[d], c) for d, c in zip(range(3), coarse)]
+    ids = (grid[0][None, None, :] + (n[0] + 1) * (grid[1][None, :, None] + (n[1] + 1) * grid[2][:, None, None])).ravel()
+    sn = np.sort(rng.choice(ids, size=min(sensors, ids.size), replace=False)).astype(np.int32)
+    pos = np.stack([sn % (n[0] + 1) / n[0], sn // (n[0] + 1) % (n[1] + 1) / n[1],
+                    sn // ((n[0] + 1) * (n[1] + 1)) / n[2]], 1)
+    return SimpleNamespace(n=tuple(n), M=M, a_elem=a.ravel(), v=(1.0, 0.5, 0.25), beta1=beta, beta2=beta,
+                           sensor_node=sn, data=_data(pos, M, rng, nsrc), pos=pos, length=(1.0, 1.0, 1.0), T=1.0,
+                           dirichlet_faces=faces, variant=variant, reg=reg)
+
+
+def _data(pos, M, rng, nsrc=2, noise=0.01):
+    """Concentrations of moving plumes at the sensors, levels 0..M, with multiplicative noise."""
+    t = np.linspace(0.0, 1.0, M + 1)
+    c = np.zeros((M + 1, len(pos)))
+    for _ in range(nsrc):
+        p, q = rng.uniform(0.2, 0.8, (2, 3))
+        at = p + t[:, None] * (q - p)
+        c += np.exp(-((pos[None] - at[:, None]) ** 2).sum(-1) / 0.2 ** 2)
+    c *= 0.05 * np.sin(np.pi * t)[:, None] ** 2
+    return c * (1 + noise * rng.uniform(-1, 1, c.shape))
+
+
+def _sizes(case):
+    return (case["n0"], case["n1"], case["n2"]), case["M"]
+
+
+def _factor(case):
+    return (case["f0"], case["f1"], case["f2"], case["f3"]) if "f0" in case else (case["f"],) * 4
+
+
+def _case_problem(case, seed):
+    n, M = _sizes(case)
+    coarse = _factor(case)[:3] if "f0" in case or case.get("f") else (1, 1, 1)
+    return _problem(n, M, case["seed"] + 7919 * seed, variant=case["variant"], reg=case["reg"], faces=case["faces"],
+                    coarse=coarse)
+
+
+def _batch_problems(case, seed):
+    rng = np.random.default_rng([case["seed"], seed])
+    # the size classes are the case's own: the seed draws the instances in them
+    sizes = np.random.default_rng(case["seed"])
+    out = []
+    for _ in range(case["count"]):
+        n = int(sizes.choice([k for k in (8, 12, 16, 20, 24) if k <= case["max_n"]]))
+        M = int(sizes.choice([k for k in (16, 24, 32, 48) if k <= case["max_M"]]))
+        out.append(_problem((n, n, n), M, int(rng.integers(1 << 30)), beta=float(sizes.choice([1e-4, 1e-3])),
+                            sensors=int(sizes.integers(27, 65)), nsrc=int(sizes.integers(1, 4))))
+    return out
+
+
+def _vectors(q, size, seed):
+    g = torch.Generator(device="cuda").manual_seed(int(seed) & 0x7FFFFFFF)
+    v = torch.randn(q, size, dtype=torch.float64, device="cuda", generator=g)
+    return v / v.norm(dim=1, keepdim=True)   # Krylov vectors have unit norm
+
+
+def _prec(case):
+    return st.F32 if case["precision"] == F32 else st.F64
+
+
+def _parts(case):
+    return (case["p0"], case["p1"], case["p2"], case["p3"])
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    if kind == "solve_batch":
+        probs = _batch_problems(case, seed)
+        ops = [st.KKTOperator(p) for p in probs]
+        pres = []
+        for p, op in zip(probs, ops):
+            parts, overlap = tune.parts_for(p)
+            pres.append(st.RAS(op, parts, overlap, precision=_prec(case)))
+        return dict(kind=kind, case=case, ops=ops, pres=pres)
+    prob = _case_problem(case, seed)
+    if kind == "ras_setup":
+        size = 3 * (prob.M + 1) * math.prod(k + 1 for k in prob.n)
+        return dict(kind=kind, case=case, prob=prob, x=_vectors(1, size, seed)[0])
+    op = st.KKTOperator(prob)
+    state = dict(kind=kind, case=case, op=op)
+    if kind == "matvec":
+        state.update(x=_vectors(1, op.n, seed)[0])
+    elif kind == "ras_apply":
+        state.update(x=_vectors(1, op.n, seed)[0], pre=st.RAS(op, _parts(case), case["overlap"], precision=_prec(case)))
+    elif kind == "coarse_apply":
+        x = _vectors(case["q"], op.n, seed)
+        state.update(x=x[0] if case["q"] == 1 else x, coarse=st.Coarse(op, _factor(case), precision=_prec(case)))
+    elif kind == "coarse_setup":
+        state.update(x=_vectors(1, op.n, seed)[0])
+    else:
+        state.update(pre=st.RAS(op, _parts(case), case["overlap"], precision=_prec(case)), data=prob.data,
+                     coarse=st.Coarse(op, _factor(case), precision=_prec(case)) if case["f"] else None)
+    return state
+
+
+def run(state):
+    kind, case = state["kind"], state["case"]
+    if kind == "matvec":
+        return state["op"].matvec(state["x"])
+    if kind == "ras_apply":
+        return state["pre"].apply(state["x"])
+    if kind == "ras_setup":
+        op = st.KKTOperator(state["prob"])
+        return {"b": op.b, "z": st.RAS(op, _parts(case), case["overlap"], precision=_prec(case)).apply(state["x"])}
+    if kind == "coarse_apply":
+        return state["coarse"].apply(state["x"]) if case["q"] == 1 else state["coarse"].apply_multi(state["x"])
+    if kind == "coarse_setup":
+        return st.Coarse(state["op"], _factor(case), precision=_prec(case)).apply(state["x"])
+    if kind == "solve":
+        b = state["op"].rhs(state["data"])
+        x, _ = st.solve(state["op"], state["pre"], b, coarse=state["coarse"], restart=case["restart"], rtol=1e-6,
+                        flexible=state["coarse"] is not None)
+        return {"b": b, "x": x}
+    xs, _ = st.solve_batch(state["ops"], state["pres"], restart=case["restart"], rtol=1e-6)
+    return xs
+
+
+# --------------------------------------------------------------------------
+# the work of one pass
+# --------------------------------------------------------------------------
+MATVEC_FLOPS = 330   # per space-time node: two 27-point diffusion sums, the 1-D mass, stiffness and convection factors
+
+
+def _box_dims(n, M, parts, overlap):
+    """Per axis, the box lengths of the node-based split extended by the overlap."""
+    dims = []
+    for length, p in zip((n[0] + 1, n[1] + 1, n[2] + 1, M + 1), parts):
+        q, r = divmod(length, p)
+        cut = [k * q + min(k, r) for k in range(p + 1)]
+        dims.append([min(length, cut[k + 1] + overlap) - max(0, cut[k] - overlap) for k in range(p)])
+    return dims
+
+
+def _blocks(n, M, parts, overlap):
+    """3x3 factor blocks and rows of all boxes."""
+    dims = _box_dims(n, M, parts, overlap)
+    return math.prod(sum(3 * v - 2 for v in d) for d in dims), math.prod(sum(d) for d in dims)
+
+
+def _nodes(n, M):
+    N = math.prod(k + 1 for k in n)
+    return N, N * (M + 1)
+
+
+def _coarse_sizes(n, M, f):
+    return 3 * math.prod(n[d] // f[d] + 1 for d in range(3)), M // f[3] + 1
+
+
+def _ras_work(n, M, parts, overlap, prec):
+    blocks, rows = _blocks(n, M, parts, overlap)
+    _, V = _nodes(n, M)
+    return (4 if prec == F32 else 8) * 9 * blocks + 48 * V, 18 * blocks
+
+
+def _coarse_work(n, M, f, prec, q):
+    nb, levels = _coarse_sizes(n, M, f)
+    _, V = _nodes(n, M)
+    # one dense block per level and the fine vectors in and out
+    return (4 if prec == F32 else 8) * levels * nb * nb + 48 * V * q, 4 * levels * nb * nb * q
+
+
+def _step_work(n, M, parts, overlap, prec, f, restart):
+    """One Arnoldi step: preconditioner, matvec, Gram-Schmidt against half a cycle of vectors (two passes)."""
+    _, V = _nodes(n, M)
+    rb, rf = _ras_work(n, M, parts, overlap, prec)
+    b, fl = rb + 48 * V + 24 * V * restart, rf + MATVEC_FLOPS * V + 12 * V * restart
+    if f:
+        cb, cf = _coarse_work(n, M, (f,) * 4, prec, 1)
+        b, fl = b + cb + 48 * V, fl + cf + MATVEC_FLOPS * V
+    return b, fl
+
+
+def work(case):
+    kind = case["kind"]
+    if kind == "solve_batch":
+        b = fl = 0
+        for p in _batch_problems(case, 0):
+            parts, overlap = tune.parts_for(p)
+            sb, sf = _step_work(p.n, p.M, parts, overlap, case["precision"], 0, min(case["steps"], case["restart"]))
+            b, fl = b + case["steps"] * sb, fl + case["steps"] * sf
+        return dict(bytes=b, flops=fl)
+    n, M = _sizes(case)
+    N, V = _nodes(n, M)
+    if kind == "matvec":
+        return dict(bytes=48 * V + 16 * N, flops=MATVEC_FLOPS * V)
+    if kind == "ras_apply":
+        b, fl = _ras_work(n, M, _parts(case), case["overlap"], case["precision"])
+        return dict(bytes=b, flops=fl)
+    if kind == "ras_setup":
+        blocks, rows = _blocks(n, M, _parts(case), case["overlap"])
+        b, fl = _ras_work(n, M, _parts(case), case["overlap"], case["precision"])
+        # an interior row eliminates its 40 lower neighbours: 760 block products (54 flops each)
+        return dict(bytes=2 * b, flops=fl + 54 * 760 * rows * (blocks / (81 * rows)) ** 2)
+    if kind == "coarse_apply":
+        b, fl = _coarse_work(n, M, _factor(case), case["precision"], case["q"])
+        return dict(bytes=b, flops=fl)
+    if kind == "coarse_setup":
+        nb, levels = _coarse_sizes(n, M, _factor(case))
+        b, fl = _coarse_work(n, M, _factor(case), case["precision"], 1)
+        return dict(bytes=2 * b, flops=fl + 2 * levels * nb ** 3)
+    b, fl = _step_work(n, M, _parts(case), case["overlap"], case["precision"], case["f"],
+                       min(case["steps"], case["restart"]))
+    return dict(bytes=case["steps"] * b, flops=case["steps"] * fl)
+
+
+# --------------------------------------------------------------------------
+# the same quantities in plain torch, FP64
+# --------------------------------------------------------------------------
+def _line(nn, h, kind):
+    """1-D finite-element matrices of hat functions: mass, stiffness, convection (phi_i, phi_j')."""
+    a = torch.zeros(nn, nn, dtype=torch.float64)
+    e = {"m": ((h / 3, h / 6), (h / 6, h / 3)), "k": ((1 / h, -1 / h), (-1 / h, 1 / h)),
+         "c": ((-0.5, 0.5), (-0.5, 0.5))}[kind]
+    for i in range(nn - 1):
+        a[i:i + 2, i:i + 2] += torch.tensor(e, dtype=torch.float64)
+    return a.cuda()
+
+
+class _Model:
+    """F_h of a problem, applied through its Kronecker factors (space-time vectors as [M+1, z, y, x, 3])."""
+
+    def __init__(self, p):
+        self.p, self.nn, self.L = p, tuple(k + 1 for k in p.n), p.M + 1
+        self.h = [p.length[d] / p.n[d] for d in range(3)]
+        self.tau = p.T / p.M
+        self.line = {k: [_line(self.nn[d], self.h[d], k) for d in range(3)] for k in "mkc"}
+        self.Tm, self.Ts = _line(self.L, self.tau, "m"), _line(self.L, self.tau, "k")
+        P = torch.ones(self.nn[2], self.nn[1], self.nn[0], dtype=torch.float64, device="cuda")
+        for bit, (axis, at) in enumerate([(2, 0), (2, -1), (1, 0), (1, -1), (0, 0), (0, -1)]):
+            if p.dirichlet_faces >> bit & 1:
+                P.select(axis, at).zero_()
+        self.P = P
+        S = torch.zeros(P.numel(), dtype=torch.float64, device="cuda")
+        S[torch.as_tensor(p.sensor_node, dtype=torch.int64, device="cuda")] = 1.0
+        self.S = S.reshape(P.shape)
+        self.a = torch.as_tensor(p.a_elem, dtype=torch.float64, device="cuda").reshape(p.n[2], p.n[1], p.n[0])
+
+    def _ax(self, u, d, mat):
+        """Apply a 1-D matrix along axis x, y, z (d = 0, 1, 2) of [L, z, y, x]."""
+        return torch.movedim(torch.movedim(u, 3 - d, -1) @ mat.T.contiguous(), -1, 3 - d)
+
+    def _prod(self, u, kinds, T=False):
+        for d in range(3):
+            m = self.line[kinds[d]][d]
+            u = self._ax(u, d, m.T if T and kinds[d] == "c" else m)
+        return u
+
+    def B(self, u):
+        return self._prod(u, "mmm")
+
+    def K(self, u):
+        return self._prod(u, "kmm") + self._prod(u, "mkm") + self._prod(u, "mmk")
+
+    def N(self, u, T=False):
+        v = self.p.v
+        return v[0] * self._prod(u, "cmm", T) + v[1] * self._prod(u, "mcm", T) + v[2] * self._prod(u, "mmc", T)
+
+    def A(self, u):
+        """Diffusion with one coefficient per element, element by element corner pairs."""
+        h, n, out = self.h, self.p.n, torch.zeros_like(u)
+        m = [((h[d] / 3, h[d] / 6), (h[d] / 6, h[d] / 3)) for d in range(3)]
+        k = [((1 / h[d], -1 / h[d]), (-1 / h[d], 1 / h[d])) for d in range(3)]
+
+        def at(t, c):
+            return t[:, c[2]:c[2] + n[2], c[1]:c[1] + n[1], c[0]:c[0] + n[0]]
+
+        corners = [(x, y, z) for z in (0, 1) for y in (0, 1) for x in (0, 1)]
+        for r in corners:
+            acc = 0.0
+            for c in corners:
+                e = [(k[d][r[d]][c[d]], m[d][r[d]][c[d]]) for d in range(3)]
+                acc = acc + (e[0][0] * e[1][1] * e[2][1] + e[0][1] * e[1][0] * e[2][1]
+                             + e[0][1] * e[1][1] * e[2][0]) * at(u, c)
+            at(out, r).add_(self.a * acc)
+        return out
+
+    def __call__(self, x):
+        p, P, ht, dto = self.p, self.P, 0.5 * self.tau, self.p.variant == DTO
+        X = x.reshape(self.L, *self.P.shape, 3)
+        c, g, f = X[..., 0], X[..., 1], X[..., 2]
+        prev = lambda u: torch.cat([torch.zeros_like(u[:1]), u[:-1]])   # noqa: E731
+        nxt = lambda u: torch.cat([u[1:], torch.zeros_like(u[:1])])     # noqa: E731
+        time = lambda m, u: torch.tensordot(m, u, 1)                     # noqa: E731
+        S1 = P * (c + prev(c))
+        yc = self.B(P * (c - prev(c)) - ht * (f + prev(f))) + ht * (self.A(S1) + self.N(S1))
+        yc = P * yc + (1 - P) * c
+        yc[0] = c[0]
+        own = torch.cat([torch.zeros_like(g[:1]), g[1:]]) if dto else g
+        S2 = P * (own + nxt(g))
+        yg = self.B(P * (own - nxt(g))) + ht * (self.A(S2) + self.N(S2, T=True))
+        if dto:
+            w = torch.full((self.L, 1, 1, 1), self.tau, dtype=torch.float64, device="cuda")
+            w[0] = w[-1] = ht
+            yg = yg + w * self.S * c
+            yg[0] += g[0]
+        else:
+            yg = yg + ht * self.S * (c + nxt(c))
+        yg = P * yg + (1 - P) * g
+        if not dto:
+            yg[-1] = g[-1]
+        Tf = p.beta2 * time(self.Tm, f)
+        yf = self.B(p.beta1 * time(self.Ts, f) - (ht * S2 if dto else P * time(self.Tm, g)) + (Tf if p.reg else 0.0))
+        if not p.reg:
+            yf = yf + self.K(Tf)
+        return torch.stack([yc, yg, yf], -1).reshape(-1)
+
+    def rhs(self, data):
+        d = torch.as_tensor(data, dtype=torch.float64, device="cuda")
+        b = torch.zeros(self.L, self.P.numel(), 3, dtype=torch.float64, device="cuda")
+        at = torch.as_tensor(self.p.sensor_node, dtype=torch.int64, device="cuda")
+        if self.p.variant == DTO:
+            w = torch.full((self.L, 1), self.tau, dtype=torch.float64, device="cuda")
+            w[0] = w[-1] = 0.5 * self.tau
+            b[:, at, 1] = w * d
+        else:
+            b[:-1, at, 1] = 0.5 * self.tau * (d[:-1] + d[1:])
+        return b.reshape(-1)
+
+    def stencil(self):
+        """[M+1, z, y, x, 81, 3, 3]: every row's blocks by offset (x fastest), from products with 3-coloured vectors."""
+        shape = (self.L, self.nn[2], self.nn[1], self.nn[0])
+        co = torch.stack(torch.meshgrid(*(torch.arange(k, device="cuda") for k in shape), indexing="ij"), -1)
+        W = torch.zeros(*shape, 81, 3, 3, dtype=torch.float64, device="cuda")
+        flat = W.view(-1, 81, 3, 3)
+        rows = torch.arange(flat.shape[0], device="cuda")
+        for colour in range(81):
+            ct, cz, cy, cx = colour // 27, colour // 9 % 3, colour // 3 % 3, colour % 3
+            want = torch.tensor([ct, cz, cy, cx], device="cuda")
+            mask = (co % 3 == want).all(-1)
+            off = (want - co + 1) % 3   # offset + 1 of the neighbour with this colour
+            slot = (off[..., 3] + 3 * off[..., 2] + 9 * off[..., 1] + 27 * off[..., 0]).reshape(-1)
+            for s in range(3):
+                e = torch.zeros(*shape, 3, dtype=torch.float64, device="cuda")
+                e[..., s] = mask.to(torch.float64)
+                flat[rows, slot, :, s] = self(e.reshape(-1)).reshape(-1, 3)
+        return W
+
+    def solve(self, b):
+        """F_h^{-1} b by block elimination in time with dense levels; b: [size] or [size, columns]."""
+        nb, W = 3 * self.P.numel(), self.stencil()
+        nn, dev = self.nn, "cuda"
+        j = torch.arange(self.P.numel(), device=dev)
+        jx, jy, jz = j % nn[0], j // nn[0] % nn[1], j // (nn[0] * nn[1])
+
+        def dense(level, dt):
+            D = torch.zeros(nb // 3, 3, nb // 3, 3, dtype=torch.float64, device=dev)
+            w = W[level].reshape(-1, 81, 3, 3)
+            for k in range(27):
+                dx, dy, dz = k % 3 - 1, k // 3 % 3 - 1, k // 9 - 1
+                ok = ((jx + dx >= 0) & (jx + dx < nn[0]) & (jy + dy >= 0) & (jy + dy < nn[1]) & (jz + dz >= 0)
+                      & (jz + dz < nn[2]))
+                r = j[ok]
+                D[r, :, r + dx + nn[0] * (dy + nn[1] * dz), :] = w[r, 27 * (dt + 1) + k]
+            return D.reshape(nb, nb)
+
+        shape, b = b.shape, b.reshape(self.L, nb, -1)
+        ys, Es, E = [], [], None
+        for k in range(self.L):
+            D, r = dense(k, 0), b[k]
+            if k:
+                low = dense(k, -1)
+                D, r = D - low @ E, r - low @ ys[-1]
+            U = dense(k, 1)
+            X = torch.linalg.solve(D, torch.cat([U, r], 1))
+            E = X[:, :nb].contiguous()
+            Es.append(E)
+            ys.append(X[:, nb:].contiguous())
+        for k in range(self.L - 2, -1, -1):
+            ys[k] = ys[k] - Es[k] @ ys[k + 1]
+        return torch.cat(ys).reshape(shape)
+
+
+def _offsets():
+    return [(k % 3 - 1, k // 3 % 3 - 1, k // 9 % 3 - 1, k // 27 - 1) for k in range(81)]
+
+
+def _mul(a, b):
+    """Products of 3x3 blocks."""
+    return (a[..., :, :, None] * b[..., None, :, :]).sum(-2)
+
+
+def _exact_ras(model, parts, overlap, r):
+    """Restricted additive Schwarz with point-block ILU(0) in every box, all boxes at once (padded to one size)."""
+    dev, full = "cuda", (model.nn[0], model.nn[1], model.nn[2], model.L)
+    cuts = []
+    for length, p in zip(full, parts):
+        q, rem = divmod(length, p)
+        cuts.append([k * q + min(k, rem) for k in range(p + 1)])
+    dims = [max(min(n, c[k + 1] + overlap) - max(0, c[k] - overlap) for k in range(len(c) - 1))
+            for n, c in zip(full, cuts)]
+    vol = math.prod(dims)
+    loc = torch.arange(vol, device=dev)
+    xyz = torch.stack([loc % dims[0], loc // dims[0] % dims[1], loc // (dims[0] * dims[1]) % dims[2],
+                       loc // (dims[0] * dims[1] * dims[2])], 1)
+    boxes = [[(max(0, c[k] - overlap), min(n, c[k + 1] + overlap), c[k], c[k + 1]) for k in range(len(c) - 1)]
+             for n, c in zip(full, cuts)]
+    todo = torch.tensor([[boxes[0][i], boxes[1][j], boxes[2][k], boxes[3][m]] for m in range(parts[3])
+                         for k in range(parts[2]) for j in range(parts[1]) for i in range(parts[0])], device=dev)
+    nbox = todo.shape[0]
+    g = todo[:, None, :, 0] + xyz[None]                      # global coordinates [box, row, 4]
+    real = (g < todo[:, None, :, 1]).all(-1)                 # rows of the box, not of the padding
+    own = real & (g >= todo[:, None, :, 2]).all(-1) & (g < todo[:, None, :, 3]).all(-1)
+    node = g[..., 0] + full[0] * (g[..., 1] + full[1] * (g[..., 2] + full[2] * g[..., 3]))
+    node = torch.where(real, node, torch.zeros_like(node))
+    offs = _offsets()
+    sten = model.stencil().reshape(-1, 81, 3, 3)
+    W = torch.zeros(nbox, vol + 1, 81, 3, 3, dtype=torch.float64, device=dev)   # row `vol`: outside every box
+    nbr = torch.full((vol, 81), vol, dtype=torch.int64, device=dev)
+    span = todo[:, None, :, 1] - todo[:, None, :, 0]
+    for s, o in enumerate(offs):
+        at = xyz + torch.tensor(o, device=dev)
+        ok = (at >= 0).all(-1) & (at < torch.tensor(dims, device=dev)).all(-1)
+        to = at[:, 0] + dims[0] * (at[:, 1] + dims[1] * (at[:, 2] + dims[2] * at[:, 3]))
+        nbr[:, s] = torch.where(ok, to, torch.full_like(to, vol))
+        has = real & ok[None] & (at[None] < span).all(-1)
+        W[:, :vol, s] = sten[node, s] * has[..., None, None]
+    del sten
+    eye = torch.eye(3, dtype=torch.float64, device=dev)
+    W[:, :vol, 40] = torch.where(real[..., None, None], W[:, :vol, 40], eye)
+    where = {o: s for s, o in enumerate(offs)}
+    pairs = []
+    for sk in range(40):
+        ok = [(su, where[t]) for su in range(41, 81)
+              if (t := tuple(a + b for a, b in zip(offs[sk], offs[su]))) in where]
+        pairs.append((torch.tensor([a for a, _ in ok], device=dev), torch.tensor([b for _, b in ok], device=dev)))
+    level = xyz[:, 0] + 2 * xyz[:, 1] + 4 * xyz[:, 2] + 8 * xyz[:, 3]
+    rows = [torch.nonzero(level == k)[:, 0] for k in range(int(level.max()) + 1)]
+    y = torch.zeros(nbox, vol + 1, 3, dtype=torch.float64, device=dev)
+    rr = r.reshape(-1, 3)[node] * real[..., None]
+    for R in rows:
+        w = W[:, R]
+        acc = rr[:, R]
+        for sk in range(40):
+            k = nbr[R, sk]
+            low = _mul(w[:, :, sk], W[:, k, 40])
+            w[:, :, sk] = low
+            su, target = pairs[sk]
+            w[:, :, target] -= _mul(low[:, :, None], W[:, k][:, :, su])
+            acc = acc - (low * y[:, k][:, :, None, :]).sum(-1)
+        w[:, :, 40] = torch.linalg.inv(w[:, :, 40])
+        W[:, R] = w
+        y[:, R] = acc
+    for R in reversed(rows):
+        acc = y[:, R]
+        for s in range(41, 81):
+            acc = acc - (W[:, R, s] * y[:, nbr[R, s]][:, :, None, :]).sum(-1)
+        y[:, R] = (W[:, R, 40] * acc[:, :, None, :]).sum(-1)
+    z = torch.zeros(r.numel() // 3, 3, dtype=torch.float64, device=dev)
+    z[node[own]] = y[:, :vol][own]
+    return z.reshape(-1)
+
+
+def _hat(nf, f):
+    """[fine, coarse] linear interpolation of an axis of nf fine elements coarsened by f."""
+    i, c = torch.arange(nf + 1, dtype=torch.float64), torch.arange(nf // f + 1, dtype=torch.float64)
+    return (1 - (i[:, None] - f * c[None]).abs() / f).clamp(min=0).cuda()
+
+
+def _exact_coarse(p, f, x):
+    """I_c^h F_c^{-1} (I_c^h)^T of the rows of x, the coarse problem rediscretised with averaged coefficients."""
+    n, M = p.n, p.M
+    nc = tuple(n[d] // f[d] for d in range(3))
+    a = p.a_elem.reshape(nc[2], f[2], nc[1], f[1], nc[0], f[0]).mean((1, 3, 5))
+    s = p.sensor_node
+    at = (s % (n[0] + 1) // f[0] + (nc[0] + 1) * (s // (n[0] + 1) % (n[1] + 1) // f[1]
+                                                  + (nc[1] + 1) * (s // ((n[0] + 1) * (n[1] + 1)) // f[2])))
+    pc = SimpleNamespace(**{**vars(p), "n": nc, "M": M // f[3], "a_elem": a.ravel(), "sensor_node": at})
+    mats = [_hat(M, f[3]), _hat(n[2], f[2]), _hat(n[1], f[1]), _hat(n[0], f[0])]
+
+    def along(u, which):
+        for axis, m in enumerate(mats, 1):
+            u = torch.movedim(torch.movedim(u, axis, -1) @ (m if which == "down" else m.T.contiguous()), -1, axis)
+        return u
+
+    r = along(x.reshape(-1, M + 1, n[2] + 1, n[1] + 1, n[0] + 1, 3), "down")
+    y = _Model(pc).solve(r.reshape(len(x), -1).T.contiguous()).T.reshape(r.shape)
+    return along(y, "up").reshape(x.shape)
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "solve_batch":
+        return [_Model(p).solve(_Model(p).rhs(p.data)) if math.prod(k + 1 for k in p.n) <= HOST_NODES else None
+                for p in _batch_problems(case, seed)]
+    p = _case_problem(case, seed)
+    n, M = _sizes(case)
+    N, V = _nodes(n, M)
+    model = _Model(p)
+    if kind == "matvec":
+        return model(_vectors(1, 3 * V, seed)[0])
+    if kind in ("ras_apply", "ras_setup"):
+        dims = _box_dims(n, M, _parts(case), case["overlap"])
+        if math.prod(max(d) for d in dims) * math.prod(len(d) for d in dims) > EXACT_ROWS:
+            return {"b": model.rhs(p.data), "z": None} if kind == "ras_setup" else None
+        z = _exact_ras(model, _parts(case), case["overlap"], _vectors(1, 3 * V, seed)[0])
+        return {"b": model.rhs(p.data), "z": z} if kind == "ras_setup" else z
+    if kind in ("coarse_apply", "coarse_setup"):
+        y = _exact_coarse(p, _factor(case), _vectors(case.get("q", 1), 3 * V, seed))
+        return y[0] if len(y) == 1 else y
+    b = model.rhs(p.data)
+    return {"b": b, "x": model.solve(b) if N <= HOST_NODES else None}
