@@ -63,13 +63,13 @@ def listed():
              precision=F64, variant=DTO, reg=0, faces=3, seed=0),
         # the smallest whole solve (cube8x16, one-level GMRES(30)): latency of every launch of a step
         dict(name="solve_8x16", kind="solve", n0=8, n1=8, n2=8, M=16, p0=2, p1=2, p2=2, p3=2, overlap=1, precision=F64,
-             f=0, restart=30, variant=DTO, reg=0, faces=3, seed=0, steps=20),
+             f=0, restart=30, variant=DTO, reg=0, faces=3, seed=0, steps=18),
         # a served two-level request: FP32 preconditioners inside FP64 FGMRES(50)
         dict(name="solve_two_level_32x64", kind="solve", n0=32, n1=32, n2=32, M=64, p0=4, p1=4, p2=4, p3=8, overlap=1,
-             precision=F32, f=4, restart=50, variant=DTO, reg=0, faces=3, seed=0, steps=56),
+             precision=F32, f=4, restart=50, variant=DTO, reg=0, faces=3, seed=0, steps=66),
         # uneven instances together, tuned partitions, FP32 preconditioners
         dict(name="batch_12_uneven", kind="solve_batch", count=12, max_n=24, max_M=48, precision=F32, restart=50,
-             seed=0, steps=40),
+             seed=0, steps=90),
     ]
 
 
@@ -123,7 +123,7 @@ def draw(rng):
         return dict(kind=kind, n0=n[0], n1=n[1], n2=n[2], M=M, **_boxes(rng, n, M), precision=prec, f=2 if two else 0,
                     restart=rng.choice([30, 50]), **{**_model(rng), "faces": 3}, steps=20)
     return dict(kind=kind, count=rng.randint(2, 10), max_n=rng.choice([12, 16, 20]), max_M=rng.choice([16, 24, 32]),
-                precision=prec, restart=rng.choice([30, 50]), seed=rng.randrange(1 << 20), steps=30)
+                precision=prec, restart=rng.choice([30, 50]), seed=rng.randrange(1 << 20), steps=60)
 
 
 # --------------------------------------------------------------------------
