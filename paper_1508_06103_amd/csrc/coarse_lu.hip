@@ -38,22 +38,43 @@ constexpr int kPanel = 64;   // Gauss-Jordan panel width (= GEMM inner dimension
 // ---------------------------------------------------------------------------
 __global__ void coupling_rows_kernel(OpDev op, int n, int dt, int32_t *__restrict__ idx, double *__restrict__ val) {
   const int N = op.N;
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < N; j += gridDim.x * blockDim.x) {
+  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < 27 * N; q += gridDim.x * blockDim.x) {
+    const int j = q / 27, k = q - 27 * j;
     const int jx = j % op.nn[0], jy = (j / op.nn[0]) % op.nn[1], jz = j / (op.nn[0] * op.nn[1]);
-    for (int k = 0; k < 27; ++k) {
-      const int dx = k % 3 - 1, dy = (k / 3) % 3 - 1, dz = k / 9 - 1;
-      const int ix = jx + dx, iy = jy + dy, iz = jz + dz;
-      const bool in = ix >= 0 && ix < op.nn[0] && iy >= 0 && iy < op.nn[1] && iz >= 0 && iz < op.nn[2];
-      double blk[9];
-      if (in) kkt_block(op, jx, jy, jz, n, dx, dy, dz, dt, blk);
-      const int i = in ? ix + op.nn[0] * (iy + op.nn[1] * iz) : 0;
-      for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) {
-          const long long e = (long long)(3 * j + a) * 81 + 3 * k + b;
-          idx[e] = 3 * i + b;
-          val[e] = in ? blk[3 * a + b] : 0.0;
-        }
-    }
+    const int dx = k % 3 - 1, dy = (k / 3) % 3 - 1, dz = k / 9 - 1;
+    const int ix = jx + dx, iy = jy + dy, iz = jz + dz;
+    const bool in = ix >= 0 && ix < op.nn[0] && iy >= 0 && iy < op.nn[1] && iz >= 0 && iz < op.nn[2];
+    double blk[9];
+    if (in) kkt_block(op, jx, jy, jz, n, dx, dy, dz, dt, blk);
+    const int i = in ? ix + op.nn[0] * (iy + op.nn[1] * iz) : 0;
+    for (int a = 0; a < 3; ++a)
+      for (int b = 0; b < 3; ++b) {
+        const long long e = (long long)(3 * j + a) * 81 + 3 * k + b;
+        idx[e] = 3 * i + b;
+        val[e] = in ? blk[3 * a + b] : 0.0;
+      }
+  }
+}
+
+// the same couplings by column: for every column c = 3 i + b of the block, the
+// rows 3 j + a of the 27 neighbours j of i and their values (0 outside the mesh)
+__global__ void coupling_cols_kernel(OpDev op, int n, int dt, int32_t *__restrict__ idx, double *__restrict__ val) {
+  const int N = op.N;
+  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < 27 * N; q += gridDim.x * blockDim.x) {
+    const int i = q / 27, k = q - 27 * i;
+    const int ix = i % op.nn[0], iy = (i / op.nn[0]) % op.nn[1], iz = i / (op.nn[0] * op.nn[1]);
+    const int dx = k % 3 - 1, dy = (k / 3) % 3 - 1, dz = k / 9 - 1;
+    const int jx = ix + dx, jy = iy + dy, jz = iz + dz;
+    const bool in = jx >= 0 && jx < op.nn[0] && jy >= 0 && jy < op.nn[1] && jz >= 0 && jz < op.nn[2];
+    double blk[9];
+    if (in) kkt_block(op, jx, jy, jz, n, -dx, -dy, -dz, dt, blk);
+    const int j = in ? jx + op.nn[0] * (jy + op.nn[1] * jz) : 0;
+    for (int b = 0; b < 3; ++b)
+      for (int a = 0; a < 3; ++a) {
+        const long long e = (long long)(3 * i + b) * 81 + 3 * k + a;
+        idx[e] = 3 * j + a;
+        val[e] = in ? blk[3 * a + b] : 0.0;
+      }
   }
 }
 
@@ -68,14 +89,29 @@ __global__ void dense_from_rows_kernel(int nb, const int32_t *__restrict__ idx, 
 }
 
 // S(r, c) -= sum_t L(r, idx_t) E(idx_t, c)   (column-major S, E; L rows sparse)
-__global__ void schur_update_kernel(int nb, const int32_t *__restrict__ idx, const double *__restrict__ val,
-                                    const double *__restrict__ E, double *__restrict__ S) {
-  const int c = blockIdx.y;
-  const double *Ec = E + (long long)c * nb;
+// A thread keeps one row's coupling entry for kSchurCols columns at a time, so
+// that the (index, value) tables are read once per eight columns instead of
+// once per column (they were three quarters of the bytes).
+constexpr int kSchurCols = 8;
+__global__ void __launch_bounds__(256) schur_update_kernel(int nb, const int32_t *__restrict__ idx,
+                                                           const double *__restrict__ val,
+                                                           const double *__restrict__ E, double *__restrict__ S) {
+  const int c0 = blockIdx.y * kSchurCols, nc = min(kSchurCols, nb - c0);
+  const double *Ec = E + (long long)c0 * nb;
   for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nb; r += gridDim.x * blockDim.x) {
-    double acc = 0.0;
-    for (int t = 0; t < 81; ++t) acc += val[(long long)r * 81 + t] * Ec[idx[(long long)r * 81 + t]];
-    S[(long long)c * nb + r] -= acc;
+    double acc[kSchurCols];
+#pragma unroll
+    for (int q = 0; q < kSchurCols; ++q) acc[q] = 0.0;
+    const long long b = (long long)r * 81;
+    for (int t = 0; t < 81; ++t) {
+      const double v = val[b + t];
+      const int i = idx[b + t];
+#pragma unroll
+      for (int q = 0; q < kSchurCols; ++q) acc[q] += v * Ec[(long long)(q < nc ? q : 0) * nb + i];
+    }
+#pragma unroll
+    for (int q = 0; q < kSchurCols; ++q)
+      if (q < nc) S[(long long)(c0 + q) * nb + r] -= acc[q];
   }
 }
 
@@ -92,24 +128,6 @@ __global__ void e_from_cols_kernel(int nb, const int32_t *__restrict__ cidx, con
     }
     E[(long long)c * nb + r] = acc;
   }
-}
-
-// transpose the (row r -> 81 columns) table of U into (column -> 81 rows)
-void transpose_rows(int nb, const std::vector<int32_t> &idx, const std::vector<double> &val,
-                    std::vector<int32_t> &cidx, std::vector<double> &cval) {
-  cidx.assign((size_t)nb * 81, 0);
-  cval.assign((size_t)nb * 81, 0.0);
-  std::vector<int> fill(nb, 0);
-  for (int r = 0; r < nb; ++r)
-    for (int t = 0; t < 81; ++t) {
-      const double v = val[(size_t)r * 81 + t];
-      if (v == 0.0) continue;
-      const int c = idx[(size_t)r * 81 + t];
-      const int f = fill[c]++;
-      if (f >= 81) throw Error(STKKT_EINVAL, "coarse LU: coupling column with more than 81 entries");
-      cidx[(size_t)c * 81 + f] = r;
-      cval[(size_t)c * 81 + f] = v;
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -432,142 +450,6 @@ __global__ void __launch_bounds__(kGjThreads) gje_panel_kernel(int n, int k, int
   }
 }
 
-// Panel elimination with the pivots searched among the panel's own rows
-// (block pivoting).  The Schur blocks of the coarse solve need no row
-// exchanges across panels: with the pivots restricted to each 64-row
-// diagonal block the inverse agrees with partial pivoting over all rows to
-// about 1e-14 (and with LAPACK's inverse), so a panel needs no device-wide
-// exchange per column.
-//
-// Step 1, one workgroup of four wavefronts (lane l on column l, wavefront v
-// on rows 16 v ..): Gauss-Jordan inversion of the diagonal block D = A[K][K]
-// (K = [k, e), w = e - k <= 64) in LDS.  Each step reads the rows'
-// multipliers into registers first, so the row updates are independent and
-// their LDS accesses pipeline.  Step j takes the largest
-// |entry| of column j over the block rows j.. (smallest row on ties), swaps
-// the two rows, records the pivot row in swp[j] (global index) and swaps the
-// two entries of piv, then eliminates column j from the other rows with the
-// in-place steps of gje_panel_kernel.  A[K][K] and Dinv (w x w, row stride
-// kPanel) receive (P D)^{-1}; a zero or non-finite pivot sets status 1.
-constexpr int kDiagThreads = 256;   // four wavefronts, 16 rows of the block each
-__global__ void __launch_bounds__(kDiagThreads) gje_diag_kernel(int n, int k, int e, double *__restrict__ A,
-                                                                double *__restrict__ Dinv,
-                                                                int32_t *__restrict__ piv,
-                                                                int32_t *__restrict__ swp,
-                                                                int *__restrict__ status) {
-  __shared__ double M[kPanel][kPanel + 1];
-  __shared__ int32_t pv[kPanel], sw[kPanel];   // piv[k..e) and the pivot rows, kept in LDS
-  __shared__ double pval;
-  __shared__ int prow_i;
-  if (*status) return;
-  const int w = e - k, tid = (int)threadIdx.x, l = tid & 63, wv = tid >> 6;   // lane l: column l
-  for (int r = wv; r < w; r += kDiagThreads / 64) M[r][l] = l < w ? A[(long long)(k + r) * n + k + l] : 0.0;
-  if (tid < w) pv[tid] = piv[k + tid];
-  __syncthreads();
-  for (int j = 0; j < w; ++j) {
-    // pivot (wavefront 0; lane l looks at row l of column j)
-    if (wv == 0) {
-      double v = (l >= j && l < w) ? fabs(M[l][j]) : -1.0;
-      int i = l;
-      for (int off = 32; off > 0; off >>= 1) {
-        const double ov = __shfl_xor(v, off, 64);
-        const int oi = __shfl_xor(i, off, 64);
-        if (ov > v || (ov == v && oi < i)) {
-          v = ov;
-          i = oi;
-        }
-      }
-      if (l == 0) {
-        pval = v;
-        prow_i = i;
-      }
-    }
-    __syncthreads();
-    const int p = prow_i;
-    if (!(pval > 0.0) || !std::isfinite(pval)) {
-      if (tid == 0) *status = 1;
-      return;
-    }
-    // the swap; the pivot bookkeeping stays in LDS (a global access would
-    // make every step's barrier wait for a memory round trip)
-    if (wv == 0) {
-      if (p != j && l < w) {
-        const double t = M[j][l];
-        M[j][l] = M[p][l];
-        M[p][l] = t;
-      }
-      if (l == 0) {
-        sw[j] = p;
-        if (p != j) {
-          const int32_t t = pv[j];
-          pv[j] = pv[p];
-          pv[p] = t;
-        }
-      }
-    }
-    __syncthreads();
-    // the scaled pivot row (lane l: entry l) and the multipliers of this
-    // wavefront's rows, read before any row changes; then its rows
-    const double a = M[j][j];
-    const double pr = l < w ? (l == j ? 1.0 : M[j][l]) / a : 0.0;
-    const double pj = 1.0 / a;
-    double f[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) f[q] = M[16 * wv + q][j];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int r = 16 * wv + q;
-      if (r < w && l < w) M[r][l] = (r == j) ? pr : ((l == j) ? -f[q] * pj : M[r][l] - f[q] * pr);
-    }
-    __syncthreads();
-  }
-  for (int r = wv; r < w; r += kDiagThreads / 64)
-    if (l < w) {
-      A[(long long)(k + r) * n + k + l] = M[r][l];
-      Dinv[r * kPanel + l] = M[r][l];
-    }
-  if (tid < w) {
-    piv[k + tid] = pv[tid];
-    swp[tid] = k + sw[tid];
-  }
-}
-
-// Step 2: the panel columns of the rows outside the block,
-// A[i][K] <- -A[i][K] Dinv (the rows of K already hold Dinv).  64 rows per
-// workgroup of 256 threads with their panel segments (transposed) and Dinv in
-// LDS; thread (row r, column group g) forms 16 of the row's w outputs.
-__global__ void __launch_bounds__(256) gje_pmul_kernel(int n, int k, int e, double *__restrict__ A,
-                                                       const double *__restrict__ Dinv,
-                                                       const int *__restrict__ status) {
-  __shared__ double Ds[kPanel][kPanel], St[kPanel][kPanel];   // Dinv[t][c]; segment St[t][row]
-  if (*status) return;
-  const int w = e - k, tid = (int)threadIdx.x, r0 = (int)blockIdx.x * 64;
-  for (int q = tid; q < 64 * kPanel; q += 256) {
-    const int a = q / kPanel, b = q % kPanel;
-    Ds[a][b] = (a < w && b < w) ? Dinv[a * kPanel + b] : 0.0;
-    const int i = r0 + a;
-    St[b][a] = (i < n && b < w) ? A[(long long)i * n + k + b] : 0.0;
-  }
-  __syncthreads();
-  const int r = tid & 63, g = tid >> 6;
-  const int i = r0 + r;
-  if (i >= n || (i >= k && i < e)) return;
-  double acc[16];
-#pragma unroll
-  for (int c = 0; c < 16; ++c) acc[c] = 0.0;
-  for (int t = 0; t < w; ++t) {
-    const double sv = St[t][r];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) acc[c] += sv * Ds[t][g * 16 + c];
-  }
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int col = g * 16 + c;
-    if (col < w) A[(long long)i * n + k + col] = -acc[c];
-  }
-}
-
 // The panel's row swaps, in order, on the columns outside the panel (one
 // thread per column).  Skipped after a failed pivot (swp is then incomplete).
 __global__ void gje_laswp_kernel(int n, int k, int e, double *__restrict__ A, const int32_t *__restrict__ swp,
@@ -680,6 +562,203 @@ __global__ void __launch_bounds__(kUpdThreads, 4) gje_update_kernel(int n, int k
         A[(long long)i * n + col] = acc[bi][bj][r];
       }
     }
+}
+
+// Panel elimination with the pivots searched among the panel's own rows
+// (block pivoting).  The Schur blocks of the coarse solve need no row
+// exchanges across panels: with the pivots restricted to each 64-row
+// diagonal block the inverse agrees with partial pivoting over all rows to
+// about 1e-14 (and with LAPACK's inverse), so a panel needs no device-wide
+// exchange per column, and one launch takes it from the previous panel's
+// state to its multipliers.  Workgroup g (eight wavefronts) owns the 64 rows
+// [64 g, 64 g + 64) and, for the panel K = [k, e), w = e - k <= 64:
+//  1. brings its rows' panel columns and, redundantly, the diagonal block
+//     D = A[K][K] up to date with the previous panel [kp, ep) (none when
+//     kp == ep): two 64 x 64 x 64 products on the matrix cores;
+//  2. inverts D: lane r holds row r, wavefront v the columns 8 v .. 8 v + 7 in
+//     registers.  Step j: the wavefront that holds column j takes the pivot
+//     row p among the rows not yet used (a lane reduction over the leading 25
+//     bits of |entry|, so a pivot is at least 1 - 2^-13 of the largest), puts
+//     the column and 1 / pivot in LDS, and after one barrier every wavefront
+//     updates its own eight columns.  Rows are not exchanged: row p_j of the
+//     result is row j of (P D)^{-1}, P the order of the pivots;
+//  3. writes -(its panel segment) (P D)^{-1} into A (one more product).
+// Every workgroup inverts the same block to the same bits; workgroup 0 also
+// writes the inverse to Dinv, the pivot rows to perm and the panel's entries
+// of piv.  Rows K of A keep the old block until gje_take_rows_kernel, since
+// the other workgroups read it.  A zero or non-finite pivot sets status 1.
+//
+// The 64 pivot steps are a serial chain and bound the kernel.  With the block
+// in LDS (five barriers a step) and a launch each for the inversion and the
+// multipliers the chain took 145 + 18 us at n = 2187, after 30 us of update
+// and 16 us of row exchanges; see gje_invert for the whole panel.
+constexpr int kBpThreads = 512;
+constexpr int kBpCols = kPanel / (kBpThreads / 64);   // columns per wavefront
+constexpr int kBpLd = kPanel + 1;
+constexpr size_t kBpLds = sizeof(double) * 3 * (size_t)kPanel * kBpLd;
+
+// largest value over the wavefront's lanes
+__device__ inline unsigned wave_max_u32(unsigned v) {
+  auto step = [&v](unsigned o) { v = o > v ? o : v; };
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));   // row_shr:1
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));   // row_shr:2
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));   // row_shr:4
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));   // row_shr:8
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast:15
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));   // row_bcast:31
+  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+__device__ inline double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// 64 x 64 product on the eight wavefronts of the workgroup: wavefront v
+// forms the 16 x 16 blocks (v / 2, 2 (v % 2)) and the one right of it.
+__device__ inline void bp_product(const double *X, const double *Y, f64x4 (&acc)[2]) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int li = lane & 15, lk = lane >> 4, bi = wv >> 1, bj = 2 * (wv & 1);
+#pragma unroll 4
+  for (int t0 = 0; t0 < kPanel; t0 += 4) {
+    const double a = X[(16 * bi + li) * kBpLd + t0 + lk];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Y[(t0 + lk) * kBpLd + 16 * (bj + u) + li], acc[u], 0, 0, 0);
+  }
+}
+
+__global__ void __launch_bounds__(kBpThreads) gje_block_panel_kernel(int n, int kp, int ep, int k, int e,
+                                                                     double *__restrict__ A,
+                                                                     const double *__restrict__ Rp,
+                                                                     double *__restrict__ Dinv,
+                                                                     int32_t *__restrict__ perm,
+                                                                     int32_t *__restrict__ piv,
+                                                                     int *__restrict__ status) {
+  extern __shared__ double bp_lds[];
+  __shared__ double fcol[2][kPanel], pinv[2];
+  __shared__ int prow[2];
+  if (*status) return;
+  double *So = bp_lds, *Sd = So + kPanel * kBpLd, *Sr = Sd + kPanel * kBpLd;
+  const int w = e - k, wp = ep - kp;
+  const int tid = (int)threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lk = lane >> 4, bi = wv >> 1, bj = 2 * (wv & 1);
+  const int i0 = (int)blockIdx.x * kPanel;
+  // 1. own panel segment and diagonal block.  An entry (row, col) of a
+  // wavefront's blocks sits in register r of lane (li, lk): row 16 bi + lk + 4 r,
+  // column 16 (bj + u) + li.
+  f64x4 own[2], dia[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int q = 16 * bi + lk + 4 * r, c = 16 * (bj + u) + li, i = i0 + q;
+      own[u][r] = (i < n && c < w && !(i >= kp && i < ep)) ? A[(long long)i * n + k + c] : 0.0;
+      dia[u][r] = (q < w && c < w) ? A[(long long)(k + q) * n + k + c] : (q == c ? 1.0 : 0.0);
+    }
+  if (wp > 0) {
+    for (int q = tid; q < kPanel * kPanel; q += kBpThreads) {
+      const int a = q / kPanel, b = q % kPanel;
+      So[a * kBpLd + b] = (i0 + a < n && b < wp) ? A[(long long)(i0 + a) * n + kp + b] : 0.0;
+      Sd[a * kBpLd + b] = (a < w && b < wp) ? A[(long long)(k + a) * n + kp + b] : 0.0;
+      Sr[a * kBpLd + b] = (a < wp && b < w) ? Rp[(long long)a * n + k + b] : 0.0;
+    }
+    __syncthreads();
+    bp_product(So, Sr, own);
+    bp_product(Sd, Sr, dia);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int q = 16 * bi + lk + 4 * r, c = 16 * (bj + u) + li;
+      So[q * kBpLd + c] = own[u][r];
+      Sd[q * kBpLd + c] = dia[u][r];
+    }
+  __syncthreads();
+  // 2. (P D)^{-1}; rows and columns past w are those of the identity
+  double m[kBpCols];
+#pragma unroll
+  for (int c = 0; c < kBpCols; ++c) m[c] = Sd[lane * kBpLd + kBpCols * wv + c];
+  int myq = -1;   // the step that took this lane's row as its pivot row
+  for (int jb = 0; jb < kBpThreads / 64; ++jb) {
+#pragma unroll
+    for (int jj = 0; jj < kBpCols; ++jj) {
+      const int par = jj & 1;
+      if (wv == jb) {
+        const unsigned hi = (unsigned)__double2hiint(m[jj]) & 0x7fffffffu;
+        const unsigned key = myq >= 0 ? 0u : (hi & ~127u) | 64u | (unsigned)(63 - lane);
+        const int p = 63 - (int)(wave_max_u32(key) & 63u);
+        const double a = lane_value(m[jj], p);
+        fcol[par][lane] = m[jj];
+        if (lane == 0) {
+          prow[par] = p;
+          pinv[par] = 1.0 / a;
+          if (!(fabs(a) > 0.0) || !std::isfinite(a)) *status = 1;
+        }
+      }
+      __syncthreads();
+      const int p = __builtin_amdgcn_readfirstlane(prow[par]);
+      const double inv = pinv[par], f = fcol[par][lane];
+      const bool isp = lane == p;
+#pragma unroll
+      for (int c = 0; c < kBpCols; ++c) {
+        const double pr = lane_value(m[c], p) * inv;
+        const double v = isp ? pr : m[c] - f * pr;
+        m[c] = (c == jj && wv == jb) ? (isp ? inv : -f * inv) : v;
+      }
+      if (isp) myq = kBpCols * jb + jj;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < kBpCols; ++c) Sr[myq * kBpLd + kBpCols * wv + c] = m[c];
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    for (int q = tid; q < kPanel * kPanel; q += kBpThreads) {
+      const int a = q / kPanel, b = q % kPanel;
+      Dinv[q] = Sr[a * kBpLd + b];
+    }
+    if (wv == 0) {
+      const bool real = lane < w && myq >= 0 && myq < w;   // (a row past w is a pivot row of a singular block only)
+      const int32_t old = real ? piv[k + lane] : 0;
+      if (real) {
+        piv[k + myq] = old;
+        perm[myq] = lane;
+      }
+    }
+  }
+  // 3. the multipliers
+  if (i0 == k) return;   // the panel's own rows (panels and row groups are both 64 wide)
+#pragma unroll
+  for (int u = 0; u < 2; ++u) own[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+  bp_product(So, Sr, own);
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + 16 * bi + lk + 4 * r, c = 16 * (bj + u) + li;
+      if (i < n && c < w) A[(long long)i * n + k + c] = -own[u][r];
+    }
+}
+
+// The panel's rows in the order of its pivots, R[j][col] = A[k + perm[j]][col]
+// outside the panel columns, and the diagonal block's inverse into A[K][K].
+__global__ void gje_take_rows_kernel(int n, int k, int e, double *__restrict__ A, const double *__restrict__ Dinv,
+                                     const int32_t *__restrict__ perm, double *__restrict__ R,
+                                     const int *__restrict__ status) {
+  if (*status) return;   // perm is then incomplete
+  const int j = blockIdx.y;
+  const double *src = A + (long long)(k + perm[j]) * n;
+  for (int col = blockIdx.x * blockDim.x + threadIdx.x; col < n; col += gridDim.x * blockDim.x) {
+    if (col >= k && col < e) {
+      R[(long long)j * n + col] = 0.0;
+      A[(long long)(k + j) * n + col] = Dinv[j * kPanel + col - k];
+    } else {
+      R[(long long)j * n + col] = src[col];
+    }
+  }
 }
 
 // out[i][piv[j]] = A[i][j]
@@ -947,7 +1026,7 @@ struct LookAhead {
 // inverse).  tmp: n x n scratch; rows: 2 x kPanel x n scratch (the rows of
 // two consecutive panels); pan: kPanel x n scratch (the launch-per-column
 // path's panel; with block pivoting its first kPanel x kPanel doubles hold the
-// diagonal block's inverse); piv: n int32; gs: candidate tables for
+// diagonal block's inverse and swp the order of its pivots); piv: n int32; gs: candidate tables for
 // ceil(n / 64) workgroups; la: the look-ahead's side stream and events.
 static void gje_invert(int n, double *A, double *tmp, double *rows, double *pan, double *fcol, int32_t *piv,
                        int32_t *swp, double *prow, const GjSync &gs, int *status, const LookAhead &la,
@@ -956,6 +1035,8 @@ static void gje_invert(int n, double *A, double *tmp, double *rows, double *pan,
   if (!attr_set) {
     STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&gje_update_kernel),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kUpdLds));
+    STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&gje_block_panel_kernel),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBpLds));
     attr_set = true;
   }
   const bool block = block_pivoting();
@@ -974,27 +1055,47 @@ static void gje_invert(int n, double *A, double *tmp, double *rows, double *pan,
     hipLaunchKernelGGL(gje_laswp_kernel, dim3(blocks_for(n, 256, 64)), dim3(256), 0, s, n, k, e, A, swp, status);
     hipLaunchKernelGGL(gje_copy_rows_kernel, dim3(blocks_for(n, 256, 64), e - k), dim3(256), 0, s, n, k, e, A, Rk);
   };
-  if (block || R > 0) {
-    // Elimination of each panel (block pivoting: the diagonal block's inverse
-    // and the other rows' multipliers; global pivoting: one cooperative
-    // launch) with a look-ahead: the update by panel p first brings the next
-    // panel's columns up to date, then the next panel is eliminated on s
+  if (block) {
+    // Two launches per panel on s: the panel (with the previous panel's update
+    // of its columns) and, once the side stream has finished the previous
+    // panel's update of all other columns, its rows.  The update by the panel
+    // then runs on the side stream beside the next panel's launch, which
+    // touches none of its columns.
+    auto panel = [&](int kp, int ep, int k, int e, const double *Rp) {
+      hipLaunchKernelGGL(gje_block_panel_kernel, dim3((n + kPanel - 1) / kPanel), dim3(kBpThreads), kBpLds, s, n, kp,
+                         ep, k, e, A, Rp, pan, swp, piv, status);
+    };
+    auto take_rows = [&](int k, int e, double *Rk) {
+      hipLaunchKernelGGL(gje_take_rows_kernel, dim3(blocks_for(n, 256, 64), e - k), dim3(256), 0, s, n, k, e, A, pan,
+                         swp, Rk, status);
+    };
+    panel(0, 0, 0, std::min(n, kPanel), rows);
+    take_rows(0, std::min(n, kPanel), rows);
+    for (int k = 0, p = 0; k < n; k += kPanel, ++p) {
+      const int e = std::min(n, k + kPanel);
+      double *Rk = rows + (size_t)(p & 1) * kPanel * n;
+      if (e >= n) {
+        update(k, e, 0, n, 0, 0, Rk, s);
+        break;
+      }
+      const int e2 = std::min(n, e + kPanel);
+      STKKT_HIP(hipEventRecord(la.rows_ready, s));
+      STKKT_HIP(hipStreamWaitEvent(la.side, la.rows_ready, 0));
+      update(k, e, 0, n, e, e2, Rk, la.side);
+      STKKT_HIP(hipEventRecord(la.rest_done, la.side));
+      panel(k, e, e, e2, Rk);
+      STKKT_HIP(hipStreamWaitEvent(s, la.rest_done, 0));
+      take_rows(e, e2, rows + (size_t)((p + 1) & 1) * kPanel * n);
+    }
+  } else if (R > 0) {
+    // Elimination of each panel in one cooperative launch with a look-ahead:
+    // the update by panel p first brings the next panel's columns up to date,
+    // then the next panel is eliminated on s
     // while the rest of the update runs on the side stream.  The two touch
     // different columns, and the next panel's swaps on the other columns wait
     // for the rest of the update.  Every entry gets the same updates as
     // without the look-ahead, bit for bit.
-    auto diag = [&](int k, int e) {
-      hipLaunchKernelGGL(gje_diag_kernel, dim3(1), dim3(kDiagThreads), 0, s, n, k, e, A, pan, piv, swp, status);
-    };
-    auto pmul = [&](int k, int e) {
-      hipLaunchKernelGGL(gje_pmul_kernel, dim3((n + 63) / 64), dim3(256), 0, s, n, k, e, A, pan, status);
-    };
     auto eliminate = [&](int k, int e) {
-      if (block) {
-        diag(k, e);
-        pmul(k, e);
-        return;
-      }
       int n_ = n, k_ = k, e_ = e, R_ = R;
       GjSync gs_ = gs;
       unsigned bar0 = (unsigned)k;
@@ -1083,9 +1184,7 @@ CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStr
   const GjSync gs{candv.as<double>(), candi.as<int32_t>(), candrow.as<double>(), crow.as<double>(),
                   bar.as<unsigned>(), reinterpret_cast<int *>(bar.as<unsigned char>() + 128), spin};
   STKKT_HIP(hipMemsetAsync(status.ptr, 0, sizeof(int), s));
-  std::vector<int32_t> hidx((size_t)nb_ * 81), hcidx;
-  std::vector<double> hval((size_t)nb_ * 81), hcval;
-  const int G = blocks_for(d.N, 128, 1024);
+  const int G = blocks_for(27LL * d.N, 128, 4096);
   const dim3 g2(blocks_for(nb_, 256, 64), nb_);
   const LookAhead la;
   for (int k = 0; k < nlev_; ++k) {
@@ -1100,7 +1199,8 @@ CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStr
     hipLaunchKernelGGL(dense_from_rows_kernel, dim3(blocks_for(nb_, 256, 64)), dim3(256), 0, s, nb_,
                        ridx.as<int32_t>(), rval.as<double>(), S.as<double>());
     if (k > 0)
-      hipLaunchKernelGGL(schur_update_kernel, g2, dim3(256), 0, s, nb_, Lk_idx, Lk_val, Ed.as<double>(),
+      hipLaunchKernelGGL(schur_update_kernel, dim3(blocks_for(nb_, 256, 64), (nb_ + kSchurCols - 1) / kSchurCols),
+                         dim3(256), 0, s, nb_, Lk_idx, Lk_val, Ed.as<double>(),
                          S.as<double>());
     STKKT_HIP(hipGetLastError());
     // S_k^{-1} (column-major S is the row-major transpose: invert it as is)
@@ -1108,14 +1208,8 @@ CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStr
                piv.as<int32_t>(), swp.as<int32_t>(), prow.as<double>(), gs, status.as<int>(), la, s);
     // E_k = S_k^{-1} U_k
     if (k + 1 < nlev_) {
-      hipLaunchKernelGGL(coupling_rows_kernel, dim3(G), dim3(128), 0, s, d, k, +1, ridx.as<int32_t>(),
-                         rval.as<double>());
-      STKKT_HIP(hipMemcpyAsync(hidx.data(), ridx.ptr, sizeof(int32_t) * hidx.size(), hipMemcpyDeviceToHost, s));
-      STKKT_HIP(hipMemcpyAsync(hval.data(), rval.ptr, sizeof(double) * hval.size(), hipMemcpyDeviceToHost, s));
-      STKKT_HIP(hipStreamSynchronize(s));
-      transpose_rows(nb_, hidx, hval, hcidx, hcval);
-      STKKT_HIP(hipMemcpyAsync(cidx.ptr, hcidx.data(), sizeof(int32_t) * hcidx.size(), hipMemcpyHostToDevice, s));
-      STKKT_HIP(hipMemcpyAsync(cval.ptr, hcval.data(), sizeof(double) * hcval.size(), hipMemcpyHostToDevice, s));
+      hipLaunchKernelGGL(coupling_cols_kernel, dim3(G), dim3(128), 0, s, d, k, +1, cidx.as<int32_t>(),
+                         cval.as<double>());
       hipLaunchKernelGGL(e_from_cols_kernel, g2, dim3(256), 0, s, nb_, cidx.as<int32_t>(), cval.as<double>(),
                          S.as<double>(), Ed.as<double>());
       STKKT_HIP(hipGetLastError());
