@@ -18,6 +18,7 @@
 #include <map>
 #include <memory>
 #include <tuple>
+#include <type_traits>
 
 #include "block33.hpp"
 #include "iluk.hpp"
@@ -42,6 +43,13 @@ __host__ __device__ inline bool inside(int x, int y, int z, int t, const int32_t
   return x >= 0 && x < dims[0] && y >= 0 && y < dims[1] && z >= 0 && z < dims[2] && t >= 0 && t < dims[3];
 }
 
+// The faces through which slot offset (dx, dy, dz, dt) leaves a box: bit k the
+// low face of dimension k, bit 4 + k the high one.
+__host__ __device__ inline int slot_faces(int dx, int dy, int dz, int dt) {
+  return (dx < 0 ? 1 : 0) | (dy < 0 ? 2 : 0) | (dz < 0 ? 4 : 0) | (dt < 0 ? 8 : 0) | (dx > 0 ? 16 : 0) |
+         (dy > 0 ? 32 : 0) | (dz > 0 ? 64 : 0) | (dt > 0 ? 128 : 0);
+}
+
 __host__ __device__ inline void unpack(uint64_t c, int &x, int &y, int &z, int &t) {
   x = (int)(c & 0xffff);
   y = (int)((c >> 16) & 0xffff);
@@ -55,6 +63,12 @@ __host__ __device__ inline void unpack(uint64_t c, int &x, int &y, int &z, int &
 // lane reads its block with two 16-byte loads plus one (FP32) or four plus
 // one (FP64).
 constexpr int kGroupAlign = 4;
+
+// Most rows a workgroup of factor_lines_kernel factors together (whole x lines),
+// and the packed coordinates of an x line.  Line tables exist only for boxes with
+// lines of at most kFactorRows nodes and fewer than 1024 nodes on the other axes.
+constexpr int kFactorRows = 54;
+__host__ __device__ inline int32_t pack_line(int y, int z, int t) { return y | (z << 10) | (t << 20); }
 __host__ __device__ inline int64_t blk_pos(int e, int64_t k, int64_t cnt) {
   return e < 4 ? 4 * k + e : e < 8 ? 4 * cnt + 4 * k + (e - 4) : 8 * cnt + k;
 }
@@ -106,25 +120,37 @@ ShapeHost make_shape(const int dims[4]) {
     for (auto c : lev[L]) sh.coords.push_back(c);
   }
   sh.nchunk = (sh.rmax + 63) / 64;
-  const int32_t d32[4] = {lx, ly, lz, lt};
   // chunk-major factor layout: for level L, 64-row chunk c of the level, slot s,
   // the group of the blocks of the chunk's rows that have neighbour s (block k
   // = rank of its row among them), entry e of block k at ctab.off + blk_pos(e, k, ctab.cnt)
   if ((size_t)sh.nlev * sh.nchunk * 81 * 2 > (size_t)INT32_MAX) throw Error(STKKT_EINVAL, "ras_setup: subdomain too large");
   sh.ctab.assign((size_t)sh.nlev * sh.nchunk * 81 * 2, 0);
+  // a row has neighbour s unless it lies on a face through which s leaves the box
+  std::vector<uint8_t> code(sh.vol);
+  for (int i = 0; i < sh.vol; ++i) {
+    int x, y, z, t;
+    unpack(sh.coords[i], x, y, z, t);
+    code[i] = (uint8_t)((x == 0 ? 1 : 0) | (y == 0 ? 2 : 0) | (z == 0 ? 4 : 0) | (t == 0 ? 8 : 0) |
+                        (x == lx - 1 ? 16 : 0) | (y == ly - 1 ? 32 : 0) | (z == lz - 1 ? 64 : 0) |
+                        (t == lt - 1 ? 128 : 0));
+  }
+  uint8_t faces[81];
+  for (int s = 0; s < 81; ++s) {
+    int dx, dy, dz, dt;
+    slot_off(s, dx, dy, dz, dt);
+    faces[s] = (uint8_t)slot_faces(dx, dy, dz, dt);
+  }
   int64_t off = 0;
   for (int L = 0; L < sh.nlev; ++L) {
     const int r0 = sh.lvl_start[L], R = sh.lvl_start[L + 1] - r0;
-    for (int c = 0; c * 64 < R; ++c)
+    for (int c = 0; c * 64 < R; ++c) {
+      const uint8_t *cd = code.data() + r0 + c * 64;
+      const int rows = std::min(64, R - c * 64);
       for (int s = 0; s < 81; ++s) {
-        int dx, dy, dz, dt;
-        slot_off(s, dx, dy, dz, dt);
-        int cnt = 0;
-        for (int q = c * 64; q < std::min(R, c * 64 + 64); ++q) {
-          int x, y, z, t;
-          unpack(sh.coords[r0 + q], x, y, z, t);
-          if (inside(x + dx, y + dy, z + dz, t + dt, d32)) ++cnt;
-        }
+        const uint8_t fs = faces[s];
+        uint8_t n = 0;   // (at most 64: counted in bytes, so that the loop vectorises)
+        for (int q = 0; q < rows; ++q) n = (uint8_t)(n + ((cd[q] & fs) == 0));
+        const int cnt = n;
         const int64_t len = (9 * (int64_t)cnt + kGroupAlign - 1) / kGroupAlign * kGroupAlign;
         if (off + len > INT32_MAX) throw Error(STKKT_EINVAL, "ras_setup: subdomain too large");
         const size_t i = (((size_t)L * sh.nchunk + c) * 81 + s) * 2;
@@ -133,6 +159,7 @@ ShapeHost make_shape(const int dims[4]) {
         off += len;
         sh.nblocks += cnt;
       }
+    }
   }
   sh.felems = off;
   // tzpref[L][t][z]: rows of level L in earlier (t, z) groups (rows of a level
@@ -150,14 +177,32 @@ ShapeHost make_shape(const int dims[4]) {
       }
     if (cnt != sh.lvl_start[L + 1] - sh.lvl_start[L]) throw Error(STKKT_EINVAL, "ras_setup: level table mismatch");
   }
+  // x lines by level y + 2z + 4t (every lower line has a smaller level)
+  if (lx <= kFactorRows && ly < 1024 && lz < 1024 && lt < 1024) {
+    const int nline = (ly - 1) + 2 * (lz - 1) + 4 * (lt - 1) + 1;
+    sh.line_lvl.assign(nline + 1, 0);
+    for (int t = 0; t < lt; ++t)
+      for (int z = 0; z < lz; ++z)
+        for (int y = 0; y < ly; ++y) ++sh.line_lvl[y + 2 * z + 4 * t + 1];
+    for (int k = 0; k < nline; ++k) sh.line_lvl[k + 1] += sh.line_lvl[k];
+    std::vector<int32_t> at(sh.line_lvl.begin(), sh.line_lvl.end() - 1);
+    sh.lines.resize((size_t)ly * lz * lt);
+    for (int t = 0; t < lt; ++t)
+      for (int z = 0; z < lz; ++z)
+        for (int y = 0; y < ly; ++y) sh.lines[at[y + 2 * z + 4 * t]++] = pack_line(y, z, t);
+  }
   return sh;
 }
 
 // --------------------------------------------------------------------------
 // setup: subdomain matrix from the operator formula, then ILU(0), one
 // workgroup per subdomain, rows of a level in parallel (one thread per row).
-// W holds the subdomain's rows padded to 81 blocks: W[rho][s][e].
+// W holds the subdomain's rows padded to 81 blocks: W[rho][s][e], kWStride
+// doubles per row (rows 16-byte aligned).  This form serves boxes with more
+// than kFactorRows nodes along x; factor_lines_kernel the others.
 // --------------------------------------------------------------------------
+constexpr int kWStride = 730;
+
 __global__ void __launch_bounds__(256) factor_kernel(OpDev op, const SubInfo *__restrict__ subs,
                                                      const ShapeInfo *__restrict__ shapes,
                                                      const int32_t *__restrict__ lvl_start,
@@ -175,7 +220,7 @@ __global__ void __launch_bounds__(256) factor_kernel(OpDev op, const SubInfo *__
       int x, y, z, t;
       unpack(coords[sh.coord_off + q], x, y, z, t);
       const long long rho = x + (long long)lx * (y + (long long)ly * (z + (long long)lz * t));
-      double *Wr = Wb + rho * 729;
+      double *Wr = Wb + rho * kWStride;
       const int gx = sd.org[0] + x, gy = sd.org[1] + y, gz = sd.org[2] + z, gn = sd.org[3] + t;
       for (int s = 0; s < 81; ++s) {
         int dx, dy, dz, dt;
@@ -201,7 +246,7 @@ __global__ void __launch_bounds__(256) factor_kernel(OpDev op, const SubInfo *__
           if (!inside(x + kx, y + ky, z + kz, t + kt, sh.dims)) continue;
           const long long rk = rho + kx + (long long)lx * (ky + (long long)ly * (kz + (long long)lz * kt));
           const double *Lik = Wr + 9 * sk;
-          const double *Ukt = Wb + rk * 729 + 9 * su;
+          const double *Ukt = Wb + rk * kWStride + 9 * su;
           double l[9], u[9];
           for (int e = 0; e < 9; ++e) {
             l[e] = Lik[e];
@@ -213,7 +258,7 @@ __global__ void __launch_bounds__(256) factor_kernel(OpDev op, const SubInfo *__
         }
         if (st < 40) {
           const long long rt = rho + tx + (long long)lx * (ty + (long long)ly * (tz + (long long)lz * tt));
-          const double *D = Wb + rt * 729 + 9 * 40;
+          const double *D = Wb + rt * kWStride + 9 * 40;
           double d[9], o[9];
           for (int e = 0; e < 9; ++e) d[e] = D[e];
           for (int a = 0; a < 3; ++a)
@@ -237,45 +282,421 @@ __global__ void __launch_bounds__(256) factor_kernel(OpDev op, const SubInfo *__
   }
 }
 
+// The same factorisation by x lines.  Row i needs its 39 lower neighbours in
+// other lines and then i - 1 in its own; every lower line has a smaller line
+// level y + 2z + 4t, and within a line the slots ascend line by line with the
+// own line last.  So the rows of a line, and all lines of a level, are taken
+// together through the 13 lower lines (dt, dz, dy ascending; three neighbours
+// dx = -1, 0, 1 each), and only the last step (i - 1, inversion of the
+// diagonal block) runs along x.  Every entry sees the products of the
+// sequential IKJ elimination in its order.
+//
+// One launch takes one line level of every box; a workgroup takes whole lines
+// of one box, ROWS rows (27 in four wavefronts, so that two workgroups share a
+// compute unit, or 54 in eight).  Nine lanes hold a row: lane q owns the
+// targets with (dx, dy) = (q % 3 - 1, q / 3 - 1), nine blocks over (dz, dt), in
+// registers.  For one (dy, dz, dt) the blocks U_k and inv(U_kk) of the lower
+// lines' rows are copied into LDS, where three rows use each of them, by
+// direct loads in two pieces: dt = 0 columns with the diagonal (piece 0) and
+// dt = +1 columns (piece 1); the load of one piece overlaps the products of the
+// other.  Slots that no row of the line can use (dz outside -1..1) are left out.
+//
+// What bounds it: the LDS reads (72 B per block product, about 760 a row) and
+// the waits between the 26 pieces, which the second workgroup fills; below
+// them the U blocks read, about 30 KB per row from HBM (a row's own blocks are
+// 6 KB), since a box's window of lines does not fit in L2.
+constexpr int kFlUnits0 = 63, kFlUnits1 = 122;   // 16-byte units per row: slots 40..53, 54..80
+template <int ROWS> struct FlCfg {
+  static constexpr int threads = ROWS > 28 ? 512 : 256;
+  // a row's blocks, and its lanes' exchange of one block
+  static constexpr size_t lds = (16 * (size_t)(kFlUnits0 + kFlUnits1) + 72) * ROWS;
+  static constexpr int max_lines = ROWS / 2;   // (their rows in transit along x fit the blocks' place)
+  static_assert(ROWS <= 7 * (threads / 64), "seven rows per wavefront");
+  static_assert(lds * (ROWS > 28 ? 1 : 2) <= kRingLdsLimit, "LDS of a compute unit");
+  static_assert(sizeof(double) * max_lines * 2 * 9 * 41 <= 16 * (size_t)(kFlUnits0 + kFlUnits1) * ROWS, "rows in transit");
+};
+static_assert(kFactorRows == 54, "the widest workgroup");
+
+typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
+
+// 3x3 block at p (8-byte aligned)
+__device__ inline void ld_blk(const double *p, double (&f)[9]) {
+#pragma unroll
+  for (int e = 0; e < 9; ++e) f[e] = p[e];
+}
+
+__device__ inline void mul_blk(const double (&a)[9], const double (&b)[9], double (&o)[9]) {
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) o[3 * r + c] = a[3 * r] * b[c] + a[3 * r + 1] * b[3 + c] + a[3 * r + 2] * b[6 + c];
+}
+
+__device__ inline void sub_mul_blk(double (&acc)[9], const double (&l)[9], const double (&u)[9]) {
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      acc[3 * r + c] -= l[3 * r] * u[c] + l[3 * r + 1] * u[3 + c] + l[3 * r + 2] * u[6 + c];
+}
+
+// one thread's row position in the workgroup and its target column (dx, dy)
+struct FlLane {
+  int row;        // LDS row: line of the workgroup * lx + x (0 when idle)
+  int x, lx;
+  int q, tx, ty;
+  bool on;        // holds a row
+  double *xch;    // the row's nine doubles of exchange space (its lanes are in one wavefront)
+};
+
+// block v of lane `from` to the row's nine lanes; all lanes of the wavefront
+// take part (lane 63 reads row 6's block)
+__device__ inline void fl_share(const FlLane &f, int from, const double (&v)[9], double (&out)[9]) {
+  if (f.q == from && f.on) {
+#pragma unroll
+    for (int e = 0; e < 9; ++e) f.xch[e] = v[e];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int e = 0; e < 9; ++e) out[e] = f.xch[e];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// (dz, dt) = (KZ, KT), lower line dy = ky, piece 0: L_ik for dx = -1, 0, 1 and
+// the dt = KT targets.
+template <int KZ, int KT>
+__device__ inline void fl_piece0(const FlLane &f, int ky, bool line_ok, const double *b0, double (&acc)[9][9]) {
+  constexpr int jk = (KT + 1) * 3 + KZ + 1;
+  const int uy = f.ty - ky;
+#pragma unroll 1
+  for (int kx = -1; kx <= 1; ++kx) {
+    const int qk = (kx + 1) + 3 * (ky + 1);
+    const bool ok = f.on && line_ok && f.x + kx >= 0 && f.x + kx < f.lx;
+    double a[9], d[9], l[9];
+    fl_share(f, qk, acc[jk], a);
+    const double *rowk = b0 + (f.row + (ok ? kx : 0)) * (2 * kFlUnits0);
+    if (ok) {
+      ld_blk(rowk, d);
+      mul_blk(a, d, l);
+      if (f.q == qk) {
+#pragma unroll
+        for (int e = 0; e < 9; ++e) acc[jk][e] = l[e];
+      }
+      const int ux = f.tx - kx;
+      if (ux >= -1 && ux <= 1 && uy >= -1 && uy <= 1) {
+        const double *uk = rowk + 9 * (ux + 3 * uy);
+        double u[9];
+        if (uy > 0 || (uy == 0 && ux > 0)) {   // uz = 0: upper columns only
+          ld_blk(uk, u);
+          sub_mul_blk(acc[jk], l, u);
+        }
+        if (KZ < 1) {   // uz = 1
+          ld_blk(uk + 81, u);
+          sub_mul_blk(acc[KZ < 1 ? jk + 1 : jk], l, u);
+        }
+      }
+    }
+  }
+}
+
+// piece 1: the dt = KT + 1 targets.  b1 holds slots 54.. (KZ >= 0) or the 8
+// bytes before slot 63 and slots 63.. (KZ = -1) of every row.
+template <int KZ, int KT>
+__device__ inline void fl_piece1(const FlLane &f, int ky, bool line_ok, const double *b1, double (&acc)[9][9]) {
+  constexpr int jk = (KT + 1) * 3 + KZ + 1;
+  const int uy = f.ty - ky;
+#pragma unroll 1
+  for (int kx = -1; kx <= 1; ++kx) {
+    const int qk = (kx + 1) + 3 * (ky + 1);
+    const bool ok = f.on && line_ok && f.x + kx >= 0 && f.x + kx < f.lx;
+    double l[9];
+    fl_share(f, qk, acc[jk], l);
+    const int ux = f.tx - kx;
+    if (ok && ux >= -1 && ux <= 1 && uy >= -1 && uy <= 1) {
+      // block (ux, uy, uz = 0, ut = 1) is slot 67 + ux + 3 uy
+      const double *uk = b1 + (f.row + kx) * (2 * kFlUnits1) + 9 * (ux + 3 * uy) + (KZ < 0 ? 1 + 9 * 4 : 9 * 13);
+      double u[9];
+      if (KZ > -1) {
+        ld_blk(uk - 81, u);
+        sub_mul_blk(acc[KZ > -1 ? jk + 3 - 1 : jk], l, u);
+      }
+      ld_blk(uk, u);
+      sub_mul_blk(acc[jk + 3], l, u);
+      if (KZ < 1) {
+        ld_blk(uk + 81, u);
+        sub_mul_blk(acc[KZ < 1 ? jk + 3 + 1 : jk], l, u);
+      }
+    }
+  }
+}
+
+// Copy units [u0, u0 + nu) (16 bytes each, from the row's start) of the lower
+// lines' rows into rows of `stride` units of LDS by direct loads, a wavefront
+// writing up to 64 consecutive units of one row at a time.  Lane l of every
+// wavefront knows row l of the workgroup: bit l of `has` tells whether the lower
+// line exists, `rho` is the row's place in W (there the lower line's row).
+// Nothing here waits on memory: the addresses come from lane reads.
+template <int THREADS>
+__device__ inline void fl_copy(const double *Wb, int rows, int u0, int nu, int stride, double *lds,
+                               unsigned long long has, int rho) {
+  const int lane = (int)__lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  for (int rr = wave; rr < rows; rr += THREADS / 64) {
+    if (!((has >> rr) & 1)) continue;
+    const double *row = Wb + (long long)__builtin_amdgcn_readlane(rho, rr) * kWStride + 2 * u0;
+    double *dst = lds + rr * stride * 2;
+    if (lane < nu)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + 2 * lane),
+                                       (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+    if (lane + 64 < nu)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + 128 + 2 * lane),
+                                       (__attribute__((address_space(3))) void *)(dst + 128), 16, 0, 0);
+  }
+}
+
+template <int ROWS>
+__global__ void __launch_bounds__(FlCfg<ROWS>::threads, 2) factor_lines_kernel(
+    OpDev op, const double *__restrict__ atab, const SubInfo *__restrict__ subs, const ShapeInfo *__restrict__ shapes,
+    const int32_t *__restrict__ lines, const int32_t *__restrict__ line_lvl, int sub0, int nsub, int nsub8, int L,
+    double *W, int *status) {
+  extern __shared__ __align__(16) double fl_lds[];
+  constexpr int kThreads = FlCfg<ROWS>::threads;
+  // boxes are dealt so that a box stays on one XCD (nsub8 is a multiple of 8)
+  const int box = (int)blockIdx.x % nsub8, group = (int)blockIdx.x / nsub8;
+  if (box >= nsub) return;
+  const SubInfo sd = load_uniform(subs + sub0 + box);
+  const ShapeInfo sh = load_uniform(shapes + sd.shape);
+  if (L >= sh.nline) return;
+  const int lx = sh.dims[0], ly = sh.dims[1], lz = sh.dims[2], lt = sh.dims[3];
+  const int per_round = min(ROWS / lx, FlCfg<ROWS>::max_lines);   // lines
+  const cptr<int32_t> lvl = as_const(line_lvl) + sh.ll_off;
+  const int first = lvl[L] + group * per_round, l1 = lvl[L + 1];
+  if (first >= l1) return;
+  double *Wb = W + sd.wbase;
+  double *b0 = fl_lds, *b1 = fl_lds + (size_t)ROWS * kFlUnits0 * 2;
+  const int lane = (int)__lane_id(), wave = (int)(threadIdx.x >> 6);
+
+  FlLane f;
+  f.lx = lx;
+  const int rw = min(lane / 9, 6);
+  f.q = lane - 9 * rw;   // (lane 63: 9, owns nothing)
+  f.tx = f.q % 3 - 1;
+  f.ty = f.q / 3 - 1;
+  const int slot = 7 * wave + rw;
+  const int lr = slot / lx;   // line of this row
+  f.x = slot - lr * lx;
+  const int nl = min(per_round, l1 - first), rows = nl * lx;
+  f.on = lane < 63 && lr < nl;
+  f.row = f.on ? slot : 0;
+  f.xch = fl_lds + (size_t)ROWS * (kFlUnits0 + kFlUnits1) * 2 + 9 * min(slot, ROWS - 1);
+  const int32_t pk = lines[sh.ln_off + first + (f.on ? lr : 0)];
+  const int y = pk & 1023, z = (pk >> 10) & 1023, t = pk >> 20;
+  // lane l: row l of the workgroup, for the copies
+  const int cl = lane / lx, cx = lane - cl * lx;
+  const int32_t cp = lines[sh.ln_off + first + (cl < nl ? cl : 0)];
+  const int cy = cp & 1023, cz = (cp >> 10) & 1023, ct = cp >> 20;
+  const int crho = cx + lx * (cy + ly * (cz + lz * ct));
+  auto issue = [&](int ky, int kz, int kt, int u0, int nu, int stride, double *lds) {
+    const bool in = cl < nl && cy + ky >= 0 && cy + ky < ly && cz + kz >= 0 && cz + kz < lz && ct + kt >= 0;
+    fl_copy<kThreads>(Wb, rows, u0, nu, stride, lds, __ballot(in), crho + lx * (ky + ly * (kz + lz * kt)));
+  };
+  auto issue0 = [&](int ky, int kz, int kt) { issue(ky, kz, kt, 180, kz < 1 ? 63 : 23, kFlUnits0, b0); };
+  auto issue1 = [&](int ky, int kz, int kt) {
+    issue(ky, kz, kt, kz < 0 ? 283 : 243, kz < 0 ? 82 : kz == 0 ? 122 : 81, kFlUnits1, b1);
+  };
+  issue0(-1, -1, -1);
+  // the rows' blocks of F_h (overlaps the first copy)
+  double acc[9][9];
+  const int gx = sd.org[0] + f.x, gy = sd.org[1] + y, gz = sd.org[2] + z, gn = sd.org[3] + t;
+#pragma unroll
+  for (int tz = -1; tz <= 1; ++tz) {
+    const bool in3 = f.on && f.x + f.tx >= 0 && f.x + f.tx < lx && y + f.ty >= 0 && y + f.ty < ly && z + tz >= 0 &&
+                     z + tz < lz;
+    SpatialCoef c{};
+    if (in3) {
+      const long long node = gx + (long long)op.nn[0] * (gy + (long long)op.nn[1] * gz);
+      c = spatial_coef_with(op, gx, gy, gz, f.tx, f.ty, tz, atab[27 * node + f.q + 9 * (tz + 1)]);
+    }
+#pragma unroll
+    for (int tt = -1; tt <= 1; ++tt) {
+      const int j = (tt + 1) * 3 + tz + 1;
+      if (in3 && t + tt >= 0 && t + tt < lt) {
+        kkt_block_c(op, c, gx, gy, gz, gn, f.tx, f.ty, tz, tt, acc[j]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 9; ++e) acc[j][e] = 0.0;
+      }
+    }
+  }
+  auto wait_copies = [] {
+    __builtin_amdgcn_s_waitcnt(0);   // the direct loads of this wavefront have reached LDS
+    __syncthreads();
+  };
+  auto line_ok = [&](int ky, int kz, int kt) {
+    return y + ky >= 0 && y + ky < ly && z + kz >= 0 && z + kz < lz && t + kt >= 0;
+  };
+  // the lower lines (dt, dz, dy) ascending; (nky, nkz, nkt): the one after
+  auto step = [&](auto KZc, auto KTc, int ky, int nky, int nkz, int nkt, bool last) {
+    constexpr int KZ = decltype(KZc)::value, KT = decltype(KTc)::value;
+    wait_copies();
+    issue1(ky, KZ, KT);
+    fl_piece0<KZ, KT>(f, ky, line_ok(ky, KZ, KT), b0, acc);
+    wait_copies();
+    if (!last) issue0(nky, nkz, nkt);
+    fl_piece1<KZ, KT>(f, ky, line_ok(ky, KZ, KT), b1, acc);
+  };
+  using M1 = std::integral_constant<int, -1>;
+  using Z0 = std::integral_constant<int, 0>;
+  using P1 = std::integral_constant<int, 1>;
+#pragma unroll 1
+  for (int ky = -1; ky <= 1; ++ky) step(M1{}, M1{}, ky, ky < 1 ? ky + 1 : -1, ky < 1 ? -1 : 0, -1, false);
+#pragma unroll 1
+  for (int ky = -1; ky <= 1; ++ky) step(Z0{}, M1{}, ky, ky < 1 ? ky + 1 : -1, ky < 1 ? 0 : 1, -1, false);
+#pragma unroll 1
+  for (int ky = -1; ky <= 1; ++ky) step(P1{}, M1{}, ky, ky < 1 ? ky + 1 : -1, ky < 1 ? 1 : -1, ky < 1 ? -1 : 0, false);
+#pragma unroll 1
+  for (int ky = -1; ky <= 1; ++ky) step(M1{}, Z0{}, ky, ky < 1 ? ky + 1 : -1, ky < 1 ? -1 : 0, 0, false);
+  step(Z0{}, Z0{}, -1, 0, 0, 0, true);
+  // own line, along x: a row's inverse and U blocks pass to the next row
+  // through LDS (line's slots 40..80 in piece-0 layout from b0 on, 41
+  // blocks per line, two lines' rows alternating by parity of x)
+  __syncthreads();
+  double *pass = fl_lds + (size_t)(f.on ? lr : 0) * 2 * (9 * 41);
+  for (int xs = 0; xs < lx; ++xs) {
+    if (f.on && f.x == xs) {
+      const double *pv = pass + ((xs + 1) & 1) * (9 * 41);
+      double *pw = pass + (xs & 1) * (9 * 41);
+      constexpr int jk = 4;   // (dz, dt) = (0, 0)
+      if (xs > 0) {
+        double a[9], d[9], l[9], u[9];
+        const int qk = 3;   // (dx, dy) = (-1, 0)
+        fl_share(f, qk, acc[jk], a);
+        ld_blk(pv, d);
+        mul_blk(a, d, l);
+        if (f.q == qk) {
+#pragma unroll
+          for (int e = 0; e < 9; ++e) acc[jk][e] = l[e];
+        }
+        const int ux = f.tx + 1, uy = f.ty;
+        if (ux <= 1) {
+          const double *uk = pv + 9 * (ux + 3 * uy);
+          if (uy > 0 || (uy == 0 && ux > 0)) {
+            ld_blk(uk, u);
+            sub_mul_blk(acc[4], l, u);
+          }
+          ld_blk(uk + 81, u);
+          sub_mul_blk(acc[5], l, u);
+          ld_blk(uk + 9 * 18, u);
+          sub_mul_blk(acc[6], l, u);
+          ld_blk(uk + 9 * 27, u);
+          sub_mul_blk(acc[7], l, u);
+          ld_blk(uk + 9 * 36, u);
+          sub_mul_blk(acc[8], l, u);
+        }
+      }
+      if (f.q == 4) {   // the diagonal block
+        double o[9];
+        bool ok;
+        inv33_pivot(acc[jk], o, ok);
+        if (!ok) {
+          atomicMax(status, 1);
+#pragma unroll
+          for (int e = 0; e < 9; ++e) o[e] = 0.0;
+        }
+#pragma unroll
+        for (int e = 0; e < 9; ++e) acc[jk][e] = o[e];
+      }
+      if (f.q >= 4) {   // slots 40..44
+#pragma unroll
+        for (int e = 0; e < 9; ++e) pw[9 * (f.q - 4) + e] = acc[jk][e];
+      }
+#pragma unroll
+      for (int j = 5; j < 9; ++j)
+#pragma unroll
+        for (int e = 0; e < 9; ++e) pw[9 * (f.q + 9 * (j - 4) - 4) + e] = acc[j][e];
+    }
+    __syncthreads();
+  }
+  if (f.on) {
+    double *Wr = Wb + (f.x + (long long)lx * (y + (long long)ly * (z + (long long)lz * t))) * kWStride + 9 * f.q;
+#pragma unroll
+    for (int j = 0; j < 9; ++j) {
+      double *o = Wr + 81 * j;
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) *reinterpret_cast<dbl2u *>(o + e) = dbl2u{acc[j][e], acc[j][e + 1]};
+      o[8] = acc[j][8];
+    }
+  }
+}
+
 __device__ inline unsigned lanes_below(unsigned long long mask) {
   const unsigned lane = __lane_id();
   return (unsigned)__popcll(mask & ((1ull << lane) - 1ull));
 }
 
+// Block `v` into place k of a group of cnt blocks (blk_pos layout, 16-byte aligned quads).
+__device__ inline void store_block(double *g, int64_t k, int64_t cnt, const double *v) {
+  *reinterpret_cast<double2 *>(g + 4 * k) = make_double2(v[0], v[1]);
+  *reinterpret_cast<double2 *>(g + 4 * k + 2) = make_double2(v[2], v[3]);
+  *reinterpret_cast<double2 *>(g + 4 * cnt + 4 * k) = make_double2(v[4], v[5]);
+  *reinterpret_cast<double2 *>(g + 4 * cnt + 4 * k + 2) = make_double2(v[6], v[7]);
+  g[8 * cnt + k] = v[8];
+}
+__device__ inline void store_block(float *g, int64_t k, int64_t cnt, const double *v) {
+  *reinterpret_cast<float4 *>(g + 4 * k) = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+  *reinterpret_cast<float4 *>(g + 4 * cnt + 4 * k) = make_float4((float)v[4], (float)v[5], (float)v[6], (float)v[7]);
+  g[8 * cnt + k] = (float)v[8];
+}
+
+// W (rows of 81 blocks) into the chunk-major layout.  A workgroup takes nine
+// slots of one 64-row chunk at a time: the rows' 648 bytes come in with
+// coalesced reads and are turned around in LDS, where lane = row.  Bound by
+// the bytes of W read and F written.  Every box gets kCompactSplit workgroups
+// (its levels in turn): with one per box and each lane reading its own row the
+// 24^3 x 48 case (108 boxes, 14 GB) took 7.1 ms.
+constexpr int kCompactSplit = 16;
 template <typename T>
-__global__ void __launch_bounds__(512) compact_kernel(const SubInfo *__restrict__ subs,
+__global__ void __launch_bounds__(256) compact_kernel(const SubInfo *__restrict__ subs,
                                                       const ShapeInfo *__restrict__ shapes,
                                                       const int32_t *__restrict__ lvl_start,
                                                       const uint64_t *__restrict__ coords,
                                                       const int32_t *__restrict__ ctab, int sub0,
                                                       const double *__restrict__ W, T *__restrict__ F) {
-  const SubInfo sd = subs[sub0 + blockIdx.x];
-  const ShapeInfo sh = shapes[sd.shape];
+  __shared__ double tile[64 * 81];
+  __shared__ int32_t rhos[64];
+  const SubInfo sd = load_uniform(subs + sub0 + blockIdx.x);
+  const ShapeInfo sh = load_uniform(shapes + sd.shape);
   const int lx = sh.dims[0], ly = sh.dims[1], lz = sh.dims[2];
-  const int lane = (int)__lane_id(), wave = (int)(threadIdx.x >> 6), nwaves = (int)(blockDim.x >> 6);
+  const int tid = (int)threadIdx.x, lane = (int)__lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const double *Wb = W + sd.wbase;
-  for (int L = 0; L < sh.nlev; ++L) {
-    const int r0 = lvl_start[sh.lvl_off + L], r1 = lvl_start[sh.lvl_off + L + 1];
-    const int R = r1 - r0, nch = (R + 63) / 64;
-    for (int item = wave; item < nch * 9; item += nwaves) {
-      const int c = item / 9, g = item % 9;
-      const int q = c * 64 + lane;
-      const bool valid = q < R;
+  for (int L = blockIdx.y; L < sh.nlev; L += gridDim.y) {
+    const int r0 = lvl_start[sh.lvl_off + L], R = lvl_start[sh.lvl_off + L + 1] - r0;
+    for (int c = 0; c * 64 < R; ++c) {
+      const int rows = min(64, R - 64 * c);
       int x = 0, y = 0, z = 0, t = 0;
-      if (valid) unpack(coords[sh.coord_off + r0 + q], x, y, z, t);
-      const long long rho = x + (long long)lx * (y + (long long)ly * (z + (long long)lz * t));
-      for (int j = 0; j < 9; ++j) {
-        const int s = 9 * g + j;
-        int dx, dy, dz, dt;
-        slot_off(s, dx, dy, dz, dt);
-        const bool has = valid && inside(x + dx, y + dy, z + dz, t + dt, sh.dims);
-        const unsigned long long mask = __ballot(has);
-        if (has) {
-          const int32_t *ct = ctab + sh.ct_off + (((int64_t)L * sh.nchunk + c) * 81 + s) * 2;
-          const int64_t cnt = ct[1], k = lanes_below(mask);
-          T *dst = F + sd.fbase + ct[0];
-          const double *src = Wb + rho * 729 + 9 * s;
-          for (int e = 0; e < 9; ++e) dst[blk_pos(e, k, cnt)] = (T)src[e];
+      if (lane < rows) unpack(coords[sh.coord_off + r0 + 64 * c + lane], x, y, z, t);
+      __syncthreads();
+      if (wave == 0) rhos[lane] = x + lx * (y + ly * (z + lz * t));
+      for (int g = 0; g < 9; ++g) {
+        __syncthreads();   // rhos written, the previous tile read
+        for (int q = tid; q < rows * 81; q += 256) {
+          const int rr = q / 81, e = q - 81 * rr;
+          tile[q] = Wb[(long long)rhos[rr] * kWStride + 81 * g + e];
+        }
+        __syncthreads();
+        for (int j = wave; j < 9; j += 4) {
+          const int s = 9 * g + j;
+          int dx, dy, dz, dt;
+          slot_off(s, dx, dy, dz, dt);
+          const bool has = lane < rows && inside(x + dx, y + dy, z + dz, t + dt, sh.dims);
+          const unsigned long long mask = __ballot(has);
+          if (has) {
+            const int32_t *ct = ctab + sh.ct_off + (((int64_t)L * sh.nchunk + c) * 81 + s) * 2;
+            store_block(F + sd.fbase + ct[0], (int64_t)lanes_below(mask), (int64_t)ct[1], tile + 81 * lane + 9 * j);
+          }
         }
       }
     }
@@ -643,12 +1064,6 @@ __device__ inline int face_code(const SweepArgs<T> &a, int x, int y, int zc, int
   return (x == 0 ? 1 : 0) | (y == 0 ? 2 : 0) | (zc == 0 ? 4 : 0) | (t == 0 ? 8 : 0) |
          (x == a.sh.dims[0] - 1 ? 16 : 0) | (y == a.sh.dims[1] - 1 ? 32 : 0) | (zc == a.sh.dims[2] - 1 ? 64 : 0) |
          (t == a.sh.dims[3] - 1 ? 128 : 0);
-}
-
-// The faces (same bit layout) through which slot offset (dx, dy, dz, dt) leaves.
-__device__ inline int slot_faces(int dx, int dy, int dz, int dt) {
-  return (dx < 0 ? 1 : 0) | (dy < 0 ? 2 : 0) | (dz < 0 ? 4 : 0) | (dt < 0 ? 8 : 0) | (dx > 0 ? 16 : 0) |
-         (dy > 0 ? 32 : 0) | (dz > 0 ? 64 : 0) | (dt > 0 ? 128 : 0);
 }
 
 // Factor loads of all five slots of this wavefront for chunk c of phase p.
@@ -1333,6 +1748,49 @@ template <class V> static void upload(const Allocator *al, DevBuf &buf, const st
     STKKT_HIP(hipMemcpyAsync(buf.ptr, host.data(), sizeof(V) * host.size(), hipMemcpyHostToDevice, s));
 }
 
+template <int ROWS>
+static void factor_by_lines_t(const ras *R, const double *atab, const int32_t *lines, const int32_t *line_lvl, int first,
+                              int last, double *W, int *status, hipStream_t s) {
+  STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&factor_lines_kernel<ROWS>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)FlCfg<ROWS>::lds));
+  const int count = last - first, count8 = (count + 7) / 8 * 8;
+  // most workgroups any of the boxes has at a line level
+  std::vector<char> used(R->shapes.size(), 0);
+  for (int i = first; i < last; ++i) used[R->subs[i].shape] = 1;
+  std::vector<int> groups;
+  for (size_t k = 0; k < R->shapes.size(); ++k) {
+    if (!used[k]) continue;
+    const ShapeHost &sh = R->shapes[k];
+    const int per = std::min(ROWS / sh.dims[0], FlCfg<ROWS>::max_lines), nline = (int)sh.line_lvl.size() - 1;
+    if ((int)groups.size() < nline) groups.resize(nline, 0);
+    for (int L = 0; L < nline; ++L)
+      groups[L] = std::max(groups[L], (sh.line_lvl[L + 1] - sh.line_lvl[L] + per - 1) / per);
+  }
+  for (int L = 0; L < (int)groups.size(); ++L) {
+    if (groups[L] == 0) continue;
+    hipLaunchKernelGGL(factor_lines_kernel<ROWS>, dim3((unsigned)count8 * groups[L]), dim3(FlCfg<ROWS>::threads),
+                       FlCfg<ROWS>::lds, s, R->d, atab, R->d_subs.as<SubInfo>(), R->d_shapes.as<ShapeInfo>(), lines,
+                       line_lvl, first, count, count8, L, W, status);
+  }
+}
+
+// Factor the boxes [first, last) line level by line level.  27 rows per
+// workgroup (two workgroups per compute unit) unless 54 fill their places
+// better: whole x lines are taken, and a line may not fit in 27.
+static void factor_by_lines(const ras *R, const double *atab, const int32_t *lines, const int32_t *line_lvl, int first,
+                            int last, double *W, int *status, hipStream_t s) {
+  long long full27 = 0, full54 = 0;   // rows of full workgroups, in 54ths
+  bool fits27 = true;
+  for (int i = first; i < last; ++i) {
+    const int lx = R->shapes[R->subs[i].shape].dims[0];
+    fits27 = fits27 && lx <= 27;
+    full27 += 2 * (27 / lx) * lx;
+    full54 += (54 / lx) * lx;
+  }
+  if (fits27 && full27 >= full54 * 4 / 5) factor_by_lines_t<27>(R, atab, lines, line_lvl, first, last, W, status, s);
+  else factor_by_lines_t<54>(R, atab, lines, line_lvl, first, last, W, status, s);
+}
+
 ras *ras_create(const kkt_op *op, const ras_params_t *rp, hipStream_t s) {
   STKKT_REQUIRE(rp != nullptr, "ras_setup: params is NULL");
   STKKT_REQUIRE(rp->ilu_level >= 0 && rp->ilu_level <= 3, "ras_setup: ilu_level must be 0, 1, 2 or 3");
@@ -1416,6 +1874,8 @@ ras *ras_create(const kkt_op *op, const ras_params_t *rp, hipStream_t s) {
   std::vector<uint64_t> crd;
   std::vector<int32_t> ctb;
   std::vector<int32_t> tzp;
+  std::vector<int32_t> lines, line_lvl;
+  bool by_lines = true;   // every box has line tables
   for (auto &sh : R->shapes) {
     ShapeInfo si{};
     for (int d = 0; d < 4; ++d) si.dims[d] = sh.dims[d];
@@ -1427,12 +1887,18 @@ ras *ras_create(const kkt_op *op, const ras_params_t *rp, hipStream_t s) {
     si.coord_off = (int64_t)crd.size();
     si.ct_off = (int64_t)ctb.size();
     si.tz_off = (int64_t)tzp.size();
+    si.ln_off = (int64_t)lines.size();
+    si.ll_off = (int64_t)line_lvl.size();
+    si.nline = (int32_t)sh.line_lvl.size() - 1;
+    by_lines = by_lines && !sh.lines.empty();
     R->ring_rmax = std::max(R->ring_rmax, sh.rmax);
     R->ring_ltlz = std::max(R->ring_ltlz, sh.dims[3] * sh.dims[2]);
     lvl.insert(lvl.end(), sh.lvl_start.begin(), sh.lvl_start.end());
     crd.insert(crd.end(), sh.coords.begin(), sh.coords.end());
     ctb.insert(ctb.end(), sh.ctab.begin(), sh.ctab.end());
     tzp.insert(tzp.end(), sh.tzpref.begin(), sh.tzpref.end());
+    lines.insert(lines.end(), sh.lines.begin(), sh.lines.end());
+    line_lvl.insert(line_lvl.end(), sh.line_lvl.begin(), sh.line_lvl.end());
     shinfo.push_back(si);
   }
   const Allocator *al = &R->al;
@@ -1445,9 +1911,11 @@ ras *ras_create(const kkt_op *op, const ras_params_t *rp, hipStream_t s) {
   std::vector<int16_t> pstart;
   std::vector<uint8_t> pairs;
   build_pairs(pstart, pairs);
-  DevBuf d_pstart, d_pairs;
+  DevBuf d_pstart, d_pairs, d_lines, d_line_lvl;
   upload(al, d_pstart, pstart, s);
   upload(al, d_pairs, pairs, s);
+  upload(al, d_lines, lines, s);
+  upload(al, d_line_lvl, line_lvl, s);
   const size_t esz = rp->precision == STKKT_F32 ? sizeof(float) : sizeof(double);
   // trailing all-zero sentinels read for neighbours outside a box
   R->factors = DevBuf(al, esz * ((size_t)fb + 16));
@@ -1466,7 +1934,7 @@ ras *ras_create(const kkt_op *op, const ras_params_t *rp, hipStream_t s) {
     size_t used = 0;
     int last = first;
     while (last < nsub) {
-      const size_t need = (size_t)R->shapes[R->subs[last].shape].vol * 729 * sizeof(double);
+      const size_t need = (size_t)R->shapes[R->subs[last].shape].vol * kWStride * sizeof(double);
       if (last > first && used + need > budget) break;
       R->subs[last].wbase = (int64_t)(used / sizeof(double));
       used += need;
@@ -1477,18 +1945,22 @@ ras *ras_create(const kkt_op *op, const ras_params_t *rp, hipStream_t s) {
                                   hipMemcpyHostToDevice, s));
     DevBuf work(al, used);
     STKKT_REQUIRE(work.ptr != nullptr, "ras_setup: out of memory for the factorisation workspace");
-    hipLaunchKernelGGL(factor_kernel, dim3(last - first), dim3(256), 0, s, op->d, R->d_subs.as<SubInfo>(),
-                       R->d_shapes.as<ShapeInfo>(), R->d_lvl.as<int32_t>(), R->d_coords.as<uint64_t>(),
-                       d_pstart.as<int16_t>(), d_pairs.as<uint8_t>(), first, work.as<double>(),
-                       d_status.as<int>());
+    if (by_lines)
+      factor_by_lines(R.get(), op->atab.as<double>(), d_lines.as<int32_t>(), d_line_lvl.as<int32_t>(), first, last,
+                      work.as<double>(), d_status.as<int>(), s);
+    else
+      hipLaunchKernelGGL(factor_kernel, dim3(last - first), dim3(256), 0, s, op->d, R->d_subs.as<SubInfo>(),
+                         R->d_shapes.as<ShapeInfo>(), R->d_lvl.as<int32_t>(), R->d_coords.as<uint64_t>(),
+                         d_pstart.as<int16_t>(), d_pairs.as<uint8_t>(), first, work.as<double>(),
+                         d_status.as<int>());
     STKKT_HIP(hipGetLastError());
     if (rp->precision == STKKT_F32) {
-      hipLaunchKernelGGL(compact_kernel<float>, dim3(last - first), dim3(512), 0, s, R->d_subs.as<SubInfo>(),
+      hipLaunchKernelGGL(compact_kernel<float>, dim3(last - first, kCompactSplit), dim3(256), 0, s, R->d_subs.as<SubInfo>(),
                          R->d_shapes.as<ShapeInfo>(), R->d_lvl.as<int32_t>(), R->d_coords.as<uint64_t>(),
                          R->d_ctab.as<int32_t>(), first, work.as<double>(),
                          R->factors.as<float>());
     } else {
-      hipLaunchKernelGGL(compact_kernel<double>, dim3(last - first), dim3(512), 0, s, R->d_subs.as<SubInfo>(),
+      hipLaunchKernelGGL(compact_kernel<double>, dim3(last - first, kCompactSplit), dim3(256), 0, s, R->d_subs.as<SubInfo>(),
                          R->d_shapes.as<ShapeInfo>(), R->d_lvl.as<int32_t>(), R->d_coords.as<uint64_t>(),
                          R->d_ctab.as<int32_t>(), first, work.as<double>(),
                          R->factors.as<double>());

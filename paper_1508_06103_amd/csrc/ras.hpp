@@ -31,6 +31,9 @@ struct ShapeInfo {
   int64_t coord_off;   // into coords (vol entries, packed 16-bit x|y|z|t)
   int64_t ct_off;      // into the chunk table (nlev*nchunk*81 (off9, cnt) pairs)
   int64_t tz_off;      // into tzpref (nlev*lt*lz entries)
+  int64_t ln_off;      // into lines (ly*lz*lt packed (y, z, t) by line level y + 2z + 4t)
+  int64_t ll_off;      // into line_lvl (nline + 1 entries)
+  int32_t nline, pad_; // line levels
 };
 
 struct ShapeHost {
@@ -42,6 +45,7 @@ struct ShapeHost {
   int64_t nblocks = 0;         // 3x3 blocks
   int64_t felems = 0;          // factor elements including group padding
   std::vector<int32_t> tzpref;
+  std::vector<int32_t> lines, line_lvl;   // x lines (y | z << 10 | t << 20) by level y + 2z + 4t (factorisation)
 };
 
 }  // namespace stkkt

@@ -88,8 +88,9 @@ struct SpatialCoef {
   double B, K, A, N, Nt;  // N = N[j, j+d], Nt = N[j+d, j]
 };
 
-__host__ __device__ inline SpatialCoef spatial_coef(const OpDev &op, int jx, int jy, int jz, int dx, int dy,
-                                                    int dz) {
+// The coefficients with the diffusion entry A[j, j+d] given (the operator's table holds the values of stiff_var).
+__host__ __device__ inline SpatialCoef spatial_coef_with(const OpDev &op, int jx, int jy, int jz, int dx, int dy,
+                                                         int dz, double a_entry) {
   const double mx = mass1(op.h[0], jx, dx, op.nn[0]);
   const double my = mass1(op.h[1], jy, dy, op.nn[1]);
   const double mz = mass1(op.h[2], jz, dz, op.nn[2]);
@@ -104,8 +105,13 @@ __host__ __device__ inline SpatialCoef spatial_coef(const OpDev &op, int jx, int
   c.Nt = op.v[0] * conv1(jx + dx, -dx, op.nn[0]) * my * mz +
          op.v[1] * mx * conv1(jy + dy, -dy, op.nn[1]) * mz +
          op.v[2] * mx * my * conv1(jz + dz, -dz, op.nn[2]);
-  c.A = stiff_var(op, jx, jy, jz, dx, dy, dz);
+  c.A = a_entry;
   return c;
+}
+
+__host__ __device__ inline SpatialCoef spatial_coef(const OpDev &op, int jx, int jy, int jz, int dx, int dy,
+                                                    int dz) {
+  return spatial_coef_with(op, jx, jy, jz, dx, dy, dz, stiff_var(op, jx, jy, jz, dx, dy, dz));
 }
 
 // 3x3 block F_h[(n, j), (n+dt, j+d)] in row-major (row slot, column slot),
