@@ -31,6 +31,21 @@ namespace {
 
 constexpr int kApplyThreads = 512;
 constexpr size_t kRingLdsLimit = 160 * 1024;   // LDS of one gfx950 workgroup
+constexpr int kWaves = kApplyThreads / 64;
+constexpr int kSlotsPerWave = 40 / kWaves;   // 5
+constexpr unsigned kNoNbr = 1023;            // neighbour place of a slot that leaves the box
+
+// A 64-row chunk of a level (device table, read word by word through the scalar cache).
+struct ChunkInfo {
+  int32_t row0;       // level-order index of its first row
+  int32_t rows;       // 1 to 64
+  int32_t L, c, R;    // level, index in the level, rows of the level
+  int32_t off40;      // factor element of the diagonal group
+  int32_t pad_[2];
+  int32_t off[2][kWaves];   // of wavefront w's five L (0) or U (1) groups
+};
+constexpr int kChunkWords = sizeof(ChunkInfo) / 4;
+static_assert(kWaves == 8 && kChunkWords == 24, "word offsets 8 + w and 16 + w");
 
 __host__ __device__ inline void slot_off(int s, int &dx, int &dy, int &dz, int &dt) {
   dx = s % 3 - 1;
@@ -162,21 +177,6 @@ ShapeHost make_shape(const int dims[4]) {
     }
   }
   sh.felems = off;
-  // tzpref[L][t][z]: rows of level L in earlier (t, z) groups (rows of a level
-  // are ordered by (t, z, y), x being implied by the level)
-  sh.tzpref.assign((size_t)sh.nlev * lt * lz, 0);
-  for (int L = 0; L < sh.nlev; ++L) {
-    int cnt = 0;
-    for (int t = 0; t < lt; ++t)
-      for (int z = 0; z < lz; ++z) {
-        sh.tzpref[((size_t)L * lt + t) * lz + z] = cnt;
-        for (int y = 0; y < ly; ++y) {
-          const int x = L - 8 * t - 4 * z - 2 * y;
-          if (x >= 0 && x < lx) ++cnt;
-        }
-      }
-    if (cnt != sh.lvl_start[L + 1] - sh.lvl_start[L]) throw Error(STKKT_EINVAL, "ras_setup: level table mismatch");
-  }
   // x lines by level y + 2z + 4t (every lower line has a smaller level)
   if (lx <= kFactorRows && ly < 1024 && lz < 1024 && lt < 1024) {
     const int nline = (ly - 1) + 2 * (lz - 1) + 4 * (lt - 1) + 1;
@@ -727,8 +727,6 @@ __global__ void __launch_bounds__(256) compact_kernel(const SubInfo *__restrict_
 // a chunk touch nearly contiguous neighbour rows.
 // --------------------------------------------------------------------------
 constexpr int kRows = 256;
-constexpr int kWaves = kApplyThreads / 64;
-constexpr int kSlotsPerWave = 40 / kWaves;   // 5
 constexpr int kUnit = 3;                     // slots per pipeline unit
 
 template <typename T>
@@ -997,17 +995,36 @@ __global__ void __launch_bounds__(kApplyThreads, 2) apply_kernel(OpDev op, const
 // --------------------------------------------------------------------------
 // apply, LDS-ring form (used when the ring fits in LDS).
 //
-// Same work split as above, but the values of the last 16 levels live in an
-// LDS ring (16 is one more than the largest level distance between a row and
-// its stencil neighbours, x + 2y + 4z + 8t changes by at most 15).  A row's
-// place inside its level is (rows of the level in earlier (t, z) groups) +
-// (y - first y of its group); the per-level (t, z) prefix rows sit in a
-// second LDS ring.  Level barriers therefore only synchronise LDS, so the
-// factor loads of the next chunk -- also across phase and level boundaries --
-// stay in flight through them: a wavefront streams its factor blocks
-// continuously, one 64-row chunk ahead of the multiply.  The forward result y
-// is also written to global memory (the backward sweep reads it once per row),
-// and z is written to the output on owned rows.
+// Same split of slots over wavefronts as above, but the values of the last 16
+// levels live in an LDS ring (16 is one more than the largest level distance
+// between a row and its stencil neighbours, x + 2y + 4z + 8t changes by at most
+// 15), so level barriers only synchronise LDS and factor loads stay in flight
+// through them: a wavefront streams its factor blocks continuously, DEPTH
+// 64-row chunks ahead of the multiply.
+//
+// Everything that depends on the box shape alone is tabulated, so that a chunk
+// costs few instructions besides its loads and products:
+//  * ChunkInfo, one entry per chunk in sweep order (scalar loads, one chunk
+//    ahead of their use): rows, level, the first factor element of every
+//    wavefront's five groups (the groups follow each other, and a group's block
+//    count is the number of its rows that have the neighbour);
+//  * 8 bytes per (row, wavefront, sweep): for each of the five slots the
+//    neighbour's place in its level, kNoNbr if it lies outside the box.  The
+//    ring entry, the wavefront's has-neighbour mask and with it the row's rank
+//    in the group all follow from it.
+// Before the tables every chunk recomputed face tests, (t, z) prefix rows and
+// 64-bit addresses, about 500 vector instructions per wavefront against 45
+// multiply-adds; the thin levels of small boxes (20 rows) took 3.6 us each.
+//
+// A sweep walks the chunk list; a phase is up to KR / 64 chunks of one level.
+// After a phase's partial sums a barrier, then one thread per row adds the
+// eight wavefronts' sums in order, finishes the row, puts it in the ring, and a
+// second barrier publishes it.  What that thread needs (r, or inv(U_rr) and y)
+// is requested when the phase starts, ahead of the factor loads of the next
+// chunk, from coordinates read one phase earlier.  The local vector holds rows
+// in level order.  With KR = 64 every chunk is a phase and the loop carries no
+// branch, so the compiler's wait counts are exact; boxes whose levels have at
+// most 64 rows always take that form.
 // --------------------------------------------------------------------------
 __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -1015,180 +1032,188 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// A phase: segment seg (KR rows) of level L, the level's rows starting
-// at r0 (R of them); L < 0 once the sweep has no further phase.  Only these
-// four values are kept (the kernel is short of scalar registers); the rest
-// is derived.
-template <int KR>
-struct Phase {
-  int L, seg, r0, R;
-  __device__ bool done() const { return L < 0; }
-  __device__ int segR() const { return min(KR, R - seg * KR); }
-  __device__ int nch() const { return (segR() + 63) >> 6; }
-};
-
-// li: index of the level in sweep order
-template <int KR>
-__device__ inline void phase_at(Phase<KR> &p, cptr<int32_t> lvls, int nlev, int li, int seg, bool fwd) {
-  if (li < 0) {
-    p.L = -1, p.seg = 0, p.r0 = 0, p.R = 0;
-    return;
-  }
-  p.L = fwd ? li : nlev - 1 - li;
-  p.r0 = lvls[p.L];
-  p.R = lvls[p.L + 1] - p.r0;
-  p.seg = seg;
-}
-
-template <int KR>
-__device__ inline void phase_next(Phase<KR> &n, const Phase<KR> &p, cptr<int32_t> lvls, int nlev, bool fwd) {
-  if (p.done()) {
-    n = p;
-    return;
-  }
-  const int li = fwd ? p.L : nlev - 1 - p.L;
-  if ((p.seg + 1) * KR < p.R) phase_at(n, lvls, nlev, li, p.seg + 1, fwd);
-  else phase_at(n, lvls, nlev, next_level(lvls, nlev, li, fwd), 0, fwd);
-}
-
-struct Ring {
-  int rmax;   // rows per ring level
-  int ltlz;   // (t, z) groups per level
-};
-
-// Boundary code of a row of the subdomain box: bit k set if the row lies on
-// the low face of dimension k, bit 4+k on the high face.  A stencil slot whose
-// offset leaves the box through one of those faces has no neighbour there.
 template <typename T>
-__device__ inline int face_code(const SweepArgs<T> &a, int x, int y, int zc, int t) {
-  return (x == 0 ? 1 : 0) | (y == 0 ? 2 : 0) | (zc == 0 ? 4 : 0) | (t == 0 ? 8 : 0) |
-         (x == a.sh.dims[0] - 1 ? 16 : 0) | (y == a.sh.dims[1] - 1 ? 32 : 0) | (zc == a.sh.dims[2] - 1 ? 64 : 0) |
-         (t == a.sh.dims[3] - 1 ? 128 : 0);
-}
+struct RingArgs {
+  SubInfo sd;
+  int nn0, nn1, N;          // mesh sizes of global_row
+  int nchk, rmax, vol;
+  cptr<int32_t> ch;         // the shape's chunk list (ChunkInfo words)
+  const uint64_t *crd;      // the shape's row coordinates
+  const uint2 *nbr;         // the shape's neighbour places
+  const T *F;               // the subdomain's factors
+  T *Y;                     // its local vector
+  const double *r;
+  double *z;
+};
 
-// Factor loads of all five slots of this wavefront for chunk c of phase p.
-// The chunk-table entries of the five slots are adjacent and are requested
-// together, so a single scalar round trip precedes the 45 vector loads.
-// The chunk is given by its level L, its chunk index cl inside the level and
-// its number of rows (done: past the last phase, nothing is loaded).
+// One chunk of the sweep for one wavefront (wavefront-uniform).
+struct Chk {
+  int row0, rows, L, c, R, off;
+};
+
+// Chunk i of the sweep order; past the end an entry without rows.
 template <typename T, bool kFwd>
-__device__ inline void load_chunk_f(const SweepArgs<T> &a, bool done, int L, int cl, int rows, uint64_t cw,
-                                    int wave, T (&f)[kSlotsPerWave][9]) {
+__device__ inline Chk chunk_at(const RingArgs<T> &a, int i, int wave) {
+  const int k = min(i, a.nchk - 1);
+  const cptr<int32_t> e = a.ch + (kFwd ? k : a.nchk - 1 - k) * kChunkWords;
+  Chk q{e[0], e[1], e[2], e[3], e[4], e[(kFwd ? 8 : 16) + wave]};
+  if (i >= a.nchk) q.rows = 0;
+  return q;
+}
+
+// Neighbour places of this lane's row of chunk q (all kNoNbr for lanes without a row).
+template <typename T>
+__device__ inline uint2 load_nbr(const RingArgs<T> &a, const Chk &q, int wave, int dir) {
   const int lane = (int)__lane_id();
+  const uint2 *p = a.nbr + ((size_t)dir * a.vol + q.row0) * kWaves + wave * q.rows;
+  return p[min(lane, max(q.rows - 1, 0))];   // masked when used: the load has no branch
+}
+
+__device__ inline unsigned nbr_place(const uint2 &v, int j, bool valid) {
+  const unsigned f = j < 3 ? (v.x >> (10 * j)) & 1023u : (v.y >> (10 * (j - 3))) & 1023u;
+  return valid ? f : kNoNbr;
+}
+
+// Block k of a group of cnt blocks at g (uniform): 32-bit offsets from scalar bases.
+__device__ inline void load_block_at(const double *g, unsigned k, int cnt, double (&f)[9]) {
+  const char *p = reinterpret_cast<const char *>(g), *p1 = p + 32 * (int64_t)cnt, *p2 = p1 + 32 * (int64_t)cnt;
+  const double2 a = *reinterpret_cast<const double2 *>(p + 32u * k);
+  const double2 b = *reinterpret_cast<const double2 *>(p + 32u * k + 16);
+  const double2 c = *reinterpret_cast<const double2 *>(p1 + 32u * k);
+  const double2 d = *reinterpret_cast<const double2 *>(p1 + 32u * k + 16);
+  f[0] = a.x, f[1] = a.y, f[2] = b.x, f[3] = b.y;
+  f[4] = c.x, f[5] = c.y, f[6] = d.x, f[7] = d.y;
+  f[8] = *reinterpret_cast<const double *>(p2 + 8u * k);
+}
+__device__ inline void load_block_at(const float *g, unsigned k, int cnt, float (&f)[9]) {
+  const char *p = reinterpret_cast<const char *>(g), *p1 = p + 16 * (int64_t)cnt, *p2 = p1 + 16 * (int64_t)cnt;
+  const float4 a = *reinterpret_cast<const float4 *>(p + 16u * k);
+  const float4 b = *reinterpret_cast<const float4 *>(p1 + 16u * k);
+  f[0] = a.x, f[1] = a.y, f[2] = a.z, f[3] = a.w;
+  f[4] = b.x, f[5] = b.y, f[6] = b.z, f[7] = b.w;
+  f[8] = *reinterpret_cast<const float *>(p2 + 4u * k);
+}
+
+// Factor loads of the wavefront's five slots for chunk q.  Lanes without the
+// neighbour read the block at their rank all the same (at most one block past
+// the group, inside the factor buffer); mac_chunk discards it.
+template <typename T>
+__device__ inline void load_chunk(const RingArgs<T> &a, const Chk &q, const uint2 &nb, T (&f)[kSlotsPerWave][9]) {
+  const bool valid = (int)__lane_id() < q.rows;
+  const T *g = a.F + q.off;
+#pragma unroll
+  for (int j = 0; j < kSlotsPerWave; ++j) {
+    const unsigned long long mask = __ballot(nbr_place(nb, j, valid) != kNoNbr);
+    const int cnt = __popcll(mask);
+    const unsigned k =
+        __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+    load_block_at(g, k, cnt, f[j]);
+    g += (9 * cnt + kGroupAlign - 1) & ~(kGroupAlign - 1);
+  }
+}
+
+// a . b with the roundings written out, so that every form of the sweeps gives the same bits.
+__device__ inline float dot3(float a0, float a1, float a2, float b0, float b1, float b2) {
+  return __builtin_fmaf(a2, b2, __builtin_fmaf(a0, b0, a1 * b1));
+}
+__device__ inline double dot3(double a0, double a1, double a2, double b0, double b1, double b2) {
+  return __builtin_fma(a2, b2, __builtin_fma(a0, b0, a1 * b1));
+}
+
+// Products of chunk q with the neighbour values of the ring; slot j's
+// neighbours lie on level q.L + dl[j].
+template <typename T>
+__device__ inline void mac_chunk(const RingArgs<T> &a, const Chk &q, const uint2 &nb, const int (&dl)[kSlotsPerWave],
+                                 const T (&f)[kSlotsPerWave][9], const T *yring, T &a0, T &a1, T &a2) {
+  const bool valid = (int)__lane_id() < q.rows;
+  T v[2][3];   // slot j's values are read while slot j - 1 is multiplied
+  auto fetch = [&](int j) {
+    const unsigned pl = min(nbr_place(nb, j, valid), (unsigned)(a.rmax - 1));
+    const T *y = yring + ((q.L + dl[j]) & 15) * (3 * a.rmax) + 3 * pl;
+    v[j & 1][0] = y[0];
+    v[j & 1][1] = y[1];
+    v[j & 1][2] = y[2];
+  };
+  fetch(0);
+#pragma unroll
+  for (int j = 0; j < kSlotsPerWave; ++j) {
+    if (j + 1 < kSlotsPerWave) fetch(j + 1);
+    const T(&u)[3] = v[j & 1];
+    const bool has = nbr_place(nb, j, valid) != kNoNbr;
+    const T s0 = a0 + dot3(f[j][0], f[j][1], f[j][2], u[0], u[1], u[2]);
+    const T s1 = a1 + dot3(f[j][3], f[j][4], f[j][5], u[0], u[1], u[2]);
+    const T s2 = a2 + dot3(f[j][6], f[j][7], f[j][8], u[0], u[1], u[2]);
+    a0 = has ? s0 : a0;
+    a1 = has ? s1 : a1;
+    a2 = has ? s2 : a2;
+    if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);   // (FP64: more values in flight do not fit the registers)
+  }
+}
+
+// A phase as the finishing threads see it: its first chunk in sweep order, the
+// thread's row (index in level order, valid if tq < rows) and its coordinates.
+struct RingPhase {
+  int L, rows;        // level, rows of the phase
+  int base;           // level-order index of the phase's first row
+  int pos;            // place of that row in its level
+  int first, nchk;    // chunks [first, first + nchk) of the sweep
+  int off40, cnt40;   // diagonal group of this wavefront's 64 rows of the phase
+};
+
+template <typename T, bool kFwd, int KR>
+__device__ inline RingPhase phase_from(const RingArgs<T> &a, int i, int wave) {
+  constexpr int P = KR / 64;
+  const int k = min(i, a.nchk - 1), idx = kFwd ? k : a.nchk - 1 - k;
+  const cptr<int32_t> e = a.ch + idx * kChunkWords;
+  const int row0 = e[0], c = e[3], R = e[4];
+  const int seg = c / P;
+  RingPhase p;
+  p.L = e[2];
+  p.rows = i < a.nchk ? min(KR, R - seg * KR) : 0;
+  p.base = row0 - 64 * (c - seg * P);
+  p.pos = seg * KR;
+  p.first = i;
+  p.nchk = (max(p.rows, 1) + 63) >> 6;
+  const int w = min(wave, p.nchk - 1);   // this wavefront's chunk of the phase
+  p.off40 = a.ch[(idx - c + seg * P + w) * kChunkWords + 5];
+  p.cnt40 = min(64, R - 64 * (seg * P + w));
+  return p;
+}
+
+template <typename T>
+__device__ inline int64_t ring_global_row(const RingArgs<T> &a, uint64_t cw) {
   int x, y, zc, t;
   unpack(cw, x, y, zc, t);
-  const bool valid = !done && lane < rows;
-  const int code = face_code(a, x, y, zc, t);
-  const int s0 = (kFwd ? 0 : 41) + kSlotsPerWave * wave;
-  int32_t tab[2 * kSlotsPerWave];
-  if (!done) {
-    const int i0 = __builtin_amdgcn_readfirstlane(((L * a.sh.nchunk + cl) * 81 + s0) * 2);
-#pragma unroll
-    for (int k = 0; k < 2 * kSlotsPerWave; ++k) tab[k] = a.ct[i0 + k];
-  } else {
-#pragma unroll
-    for (int k = 0; k < 2 * kSlotsPerWave; ++k) tab[k] = 0;
-  }
-#pragma unroll
-  for (int j = 0; j < kSlotsPerWave; ++j) {
-    int dx, dy, dz, dt;
-    slot_off(s0 + j, dx, dy, dz, dt);
-    const bool has = valid && (code & slot_faces(dx, dy, dz, dt)) == 0;
-    const unsigned long long mask = __ballot(has);
-    // rows without the neighbour read the zero block (k = cnt = 0)
-    const int64_t gi = has ? a.sd.fbase + tab[2 * j] : a.fzero;
-    const int64_t k = has ? (int64_t)lanes_below(mask) : 0, kc = has ? tab[2 * j + 1] : 0;
-    load_block(a.F + gi, k, kc, f[j]);
-  }
+  const long long node =
+      (a.sd.org[0] + x) + (long long)a.nn0 * ((a.sd.org[1] + y) + (long long)a.nn1 * (a.sd.org[2] + zc));
+  return 3 * ((long long)(a.sd.org[3] + t) * a.N + node);
 }
 
-template <typename T, bool kFwd, int KR>
-__device__ inline void load_chunk_f(const SweepArgs<T> &a, const Phase<KR> &p, int c, uint64_t cw, int wave,
-                                    T (&f)[kSlotsPerWave][9]) {
-  load_chunk_f<T, kFwd>(a, p.done(), p.L, p.seg * (KR / 64) + c, p.segR() - 64 * c, cw, wave, f);
+// Coordinates of this thread's row of phase p (any row when it has none).
+template <typename T> __device__ inline uint64_t phase_crd(const RingArgs<T> &a, const RingPhase &p) {
+  return a.crd[p.base + min((int)threadIdx.x, max(p.rows - 1, 0))];
 }
 
-// Multiply chunk c of phase p: neighbour values from the LDS ring.  All rows
-// of a phase lie on level p.L, so a slot's neighbours all lie on level
-// p.L + dx + 2dy + 4dz + 8dt, and its ring slot is the same for the whole
-// wavefront.  The lookups carry no branches: rows without the neighbour read
-// ring entry 0 and discard the value, so the LDS requests of the five slots
-// can be in flight together.
-template <typename T, bool kFwd, int KR>
-__device__ inline void mac_chunk_ring(const SweepArgs<T> &a, const Phase<KR> &p, int c, uint64_t cw, int wave,
-                                      const T (&f)[kSlotsPerWave][9], const T *yring, const int32_t *tzr,
-                                      const Ring &rg, T &a0, T &a1, T &a2) {
-  const int lane = (int)__lane_id();
-  int x, y, zc, t;
-  unpack(cw, x, y, zc, t);
-  const bool valid = c * 64 + lane < p.segR();
-  const int code = face_code(a, x, y, zc, t);
-  const int lx = a.sh.dims[0], lz = a.sh.dims[2];
-  const int xy = x + 2 * y, tz = t * lz + zc;
-  const int s0 = (kFwd ? 0 : 41) + kSlotsPerWave * wave;
-  // all prefix-row lookups first, so that they are in flight together
-  int hb = 0, qv[kSlotsPerWave];
-#pragma unroll
-  for (int j = 0; j < kSlotsPerWave; ++j) {
-    int dx, dy, dz, dt;
-    slot_off(s0 + j, dx, dy, dz, dt);
-    const bool has = valid && (code & slot_faces(dx, dy, dz, dt)) == 0;
-    hb |= has ? 1 << j : 0;
-    const int slot = (p.L + dx + 2 * dy + 4 * dz + 8 * dt) & 15;
-    qv[j] = tzr[has ? slot * rg.ltlz + tz + dt * lz + dz : 0];
-  }
-#pragma unroll
-  for (int j = 0; j < kSlotsPerWave; ++j) {
-    int dx, dy, dz, dt;
-    slot_off(s0 + j, dx, dy, dz, dt);
-    const bool has = (hb >> j) & 1;
-    const int slot = (p.L + dx + 2 * dy + 4 * dz + 8 * dt) & 15;
-    const int rem = xy + dx + 2 * dy;   // nx + 2 ny of the neighbour
-    const int ymin = max(0, (rem - lx + 2) >> 1);
-    const int vi = has ? (slot * rg.rmax + qv[j] + (y + dy - ymin)) * 3 : 0;
-    const T w0 = yring[vi], w1 = yring[vi + 1], w2 = yring[vi + 2];
-    const T v0 = has ? w0 : (T)0, v1 = has ? w1 : (T)0, v2 = has ? w2 : (T)0;
-    a0 += f[j][0] * v0 + f[j][1] * v1 + f[j][2] * v2;
-    a1 += f[j][3] * v0 + f[j][4] * v1 + f[j][5] * v2;
-    a2 += f[j][6] * v0 + f[j][7] * v1 + f[j][8] * v2;
-  }
-}
-
-// Inputs of the final step of row tq of phase p (coordinates crd), requested
-// at the start of the phase: r (forward; kept in FP64 until it is used, so
-// that no conversion waits on the load while factor loads are in flight), or
-// inv(U_rr) and y (backward).  The chunk-table entry of the diagonal slot is
-// wavefront-uniform (a wavefront holds 64 consecutive rows) and is read
-// through the scalar cache.
-template <typename T, bool kFwd, int KR>
-__device__ inline void load_pre(const SweepArgs<T> &a, const Phase<KR> &p, const uint64_t *crd, T (&pre)[12],
+// Inputs of the final step of the thread's row: r (forward, kept in FP64 until
+// it is used) or inv(U_rr) and y (backward).
+template <typename T, bool kFwd>
+__device__ inline void load_pre(const RingArgs<T> &a, const RingPhase &p, uint64_t cw, T (&pre)[12],
                                 double (&rin)[3]) {
-  const int tq = (int)threadIdx.x;
-  if (tq >= p.segR()) return;
-  int x, y, zc, t;
-  unpack(crd[tq], x, y, zc, t);
   if (kFwd) {
-    const int64_t gi = global_row(a, x, y, zc, t);
-    rin[0] = a.r[gi];
-    rin[1] = a.r[gi + 1];
-    rin[2] = a.r[gi + 2];
+    const double *r = a.r + ring_global_row(a, cw);
+    rin[0] = r[0];
+    rin[1] = r[1];
+    rin[2] = r[2];
   } else {
-    const int qrow = p.seg * KR + tq;
-    int64_t off9, cnt;
-    chunk_slot(a, p.L, qrow >> 6, 40, off9, cnt);
-    // the row's place in its chunk is made opaque here, so that the compiler
-    // forms this address inside the sweep loop instead of keeping a per-lane
-    // pointer alive across it (which does not fit the FP64 register budget)
-    int lrow = qrow & 63;
-    asm volatile("" : "+v"(lrow));
-    T dg[9];
-    load_block(a.F + a.sd.fbase + off9, lrow, cnt, dg);
+    const int tq = min((int)threadIdx.x, max(p.rows - 1, 0));
+    T d[9];
+    load_block_at(a.F + p.off40, (unsigned)(tq & 63), p.cnt40, d);
 #pragma unroll
-    for (int e = 0; e < 9; ++e) pre[e] = dg[e];
-    const int64_t yo = a.sd.sbase + 3 * yrow_of(a, x, y, zc, t);
-    pre[9] = a.Y[yo];
-    pre[10] = a.Y[yo + 1];
-    pre[11] = a.Y[yo + 2];
+    for (int e = 0; e < 9; ++e) pre[e] = d[e];
+    const T *y = a.Y + 3 * (int64_t)(p.base + tq);
+    pre[9] = y[0];
+    pre[10] = y[1];
+    pre[11] = y[2];
   }
 }
 
@@ -1197,290 +1222,173 @@ __device__ inline void load_pre(const SweepArgs<T> &a, const Phase<KR> &p, const
 // backward sweep) or z = inv(U_rr)(y - sum) (backward, owned rows written to
 // the output); the result goes into the LDS ring.
 template <typename T, bool kFwd, int KR>
-__device__ inline void ring_finish(const SweepArgs<T> &a, const Phase<KR> &pc, const uint64_t *crd, T (*part)[KR][3],
-                                   const T (&pre)[12], const double (&rin)[3], T *yring, const Ring &rg) {
+__device__ inline void ring_finish(const RingArgs<T> &a, const RingPhase &p, uint64_t cw, T (*part)[KR][3],
+                                   const T (&pre)[12], const double (&rin)[3], T *yring) {
   const int tq = (int)threadIdx.x;
-  if (tq < pc.segR()) {
-    const uint64_t fc = crd[tq];
-    T s3[3];
+  if (tq >= p.rows) return;
+  T s3[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      T acc = 0;
+  for (int k = 0; k < 3; ++k) {
+    T acc = 0;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) acc += part[w][tq][k];
-      s3[k] = acc;
-    }
-    T o[3];
+    for (int w = 0; w < kWaves; ++w) acc += part[w][tq][k];
+    s3[k] = acc;
+  }
+  T o[3];
+  if (kFwd) {
+    for (int k = 0; k < 3; ++k) o[k] = (T)rin[k] - s3[k];
+    T *y = a.Y + 3 * (int64_t)(p.base + tq);
+    for (int k = 0; k < 3; ++k) y[k] = o[k];
+  } else {
+    T v[3];
+    for (int k = 0; k < 3; ++k) v[k] = pre[9 + k] - s3[k];
+    for (int k = 0; k < 3; ++k) o[k] = dot3(pre[3 * k], pre[3 * k + 1], pre[3 * k + 2], v[0], v[1], v[2]);
+    const SubInfo &sd = a.sd;
     int x, y, zc, t;
-    unpack(fc, x, y, zc, t);
-    if (kFwd) {
-      for (int k = 0; k < 3; ++k) o[k] = (T)rin[k] - s3[k];
-      T *yg = a.Y + a.sd.sbase + 3 * yrow_of(a, x, y, zc, t);
-      for (int k = 0; k < 3; ++k) yg[k] = o[k];
-    } else {
-      T v[3];
-      for (int k = 0; k < 3; ++k) v[k] = pre[9 + k] - s3[k];
-      for (int k = 0; k < 3; ++k) o[k] = pre[3 * k] * v[0] + pre[3 * k + 1] * v[1] + pre[3 * k + 2] * v[2];
-      const SubInfo &sd = a.sd;
-      const bool owned = x >= sd.olo[0] && x < sd.ohi[0] && y >= sd.olo[1] && y < sd.ohi[1] && zc >= sd.olo[2] &&
-                         zc < sd.ohi[2] && t >= sd.olo[3] && t < sd.ohi[3];
-      if (owned) {
-        const int64_t gi = global_row(a, x, y, zc, t);
-        for (int k = 0; k < 3; ++k) a.z[gi + k] = (double)o[k];
-      }
-    }
-    T *yr = yring + ((int64_t)(pc.L & 15) * rg.rmax + pc.seg * KR + tq) * 3;
-    for (int k = 0; k < 3; ++k) yr[k] = o[k];
-  }
-}
-
-// One chunk step: issue the factor loads of the next chunk, multiply the
-// current one, and close the phase if this was its last chunk.
-template <typename T, bool kFwd, int KR>
-__device__ inline void ring_step(const SweepArgs<T> &a, cptr<int32_t> tzp, int nlev, int wave, Phase<KR> &pc, int &cc,
-                                 int &par, Phase<KR> &pn, Phase<KR> &pnn, const T (&fcur)[kSlotsPerWave][9],
-                                 T (&fnext)[kSlotsPerWave][9], T (*part)[KR][3], uint64_t *crd2, T *yring,
-                                 int32_t *tzr, const Ring &rg, uint64_t &c2, int &tzrow, T (&pre)[12],
-                                 double (&rin)[3]) {
-  const int lane = (int)__lane_id();
-  const int tq = (int)threadIdx.x;
-  // requests of the phase, issued when its first chunk is multiplied: coordinates
-  // two phases ahead, the (t, z) prefix row of a new level, final-step inputs
-  if (cc == 0) {
-    if (!pnn.done() && tq < pnn.segR()) c2 = a.crd[a.sh.coord_off + pnn.r0 + pnn.seg * KR + tq];
-    if (pc.seg == 0 && tq < rg.ltlz) tzrow = tzp[pc.L * rg.ltlz + tq];
-    load_pre<T, kFwd>(a, pc, crd2 + par * KR, pre, rin);
-  }
-  // next chunk: same phase, or the first chunk of the next phase
-  const bool last = cc == pc.nch() - 1;
-  {
-    // chosen with selects, field by field, so that the phases stay in registers
-    const bool tdone = last ? pn.done() : pc.done();
-    const int tL = last ? pn.L : pc.L, tseg = last ? pn.seg : pc.seg, tsegR = last ? pn.segR() : pc.segR();
-    const int ct = last ? 0 : cc + 1;
-    const int pt_par = last ? par ^ 1 : par;
-    const uint64_t cw = crd2[pt_par * KR + ct * 64 + lane];
-    load_chunk_f<T, kFwd>(a, tdone, tL, tseg * (KR / 64) + ct, tsegR - 64 * ct, cw, wave, fnext);
-  }
-  // multiply the current chunk
-  {
-    const uint64_t cw = crd2[par * KR + cc * 64 + lane];
-    T a0 = 0, a1 = 0, a2 = 0;
-    mac_chunk_ring<T, kFwd>(a, pc, cc, cw, wave, fcur, yring, tzr, rg, a0, a1, a2);
-    if (cc * 64 + lane < pc.segR()) {
-      part[wave][cc * 64 + lane][0] = a0;
-      part[wave][cc * 64 + lane][1] = a1;
-      part[wave][cc * 64 + lane][2] = a2;
+    unpack(cw, x, y, zc, t);
+    const bool owned = x >= sd.olo[0] && x < sd.ohi[0] && y >= sd.olo[1] && y < sd.ohi[1] && zc >= sd.olo[2] &&
+                       zc < sd.ohi[2] && t >= sd.olo[3] && t < sd.ohi[3];
+    if (owned) {
+      double *z = a.z + ring_global_row(a, cw);
+      for (int k = 0; k < 3; ++k) z[k] = (double)o[k];
     }
   }
-  if (!last) {
-    ++cc;
-    return;
-  }
-  // close the phase
-  lds_barrier();
-  ring_finish<T, kFwd>(a, pc, crd2 + par * KR, part, pre, rin, yring, rg);
-  if (pc.seg == 0 && tq < rg.ltlz) tzr[(pc.L & 15) * rg.ltlz + tq] = tzrow;
-  if (!pnn.done() && tq < pnn.segR()) crd2[par * KR + tq] = c2;   // phase after next reuses this buffer
-  lds_barrier();
-  // advance
-  pc = pn;
-  pn = pnn;
-  phase_next(pnn, pn, a.lvls, nlev, kFwd);
-  par ^= 1;
-  cc = 0;
+  T *yr = yring + ((p.L & 15) * a.rmax + p.pos + tq) * 3;
+  for (int k = 0; k < 3; ++k) yr[k] = o[k];
 }
 
-template <typename T, bool kFwd, int KR>
-__device__ inline void sweep_ring(const SweepArgs<T> &a, cptr<int32_t> tzp, T (*part)[KR][3], uint64_t *crd2,
-                                  T *yring, int32_t *tzr, const Ring &rg) {
-  const int lane = (int)__lane_id();
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int tq = (int)threadIdx.x;
-  const int nlev = a.sh.nlev;
-  Phase<KR> pc, pn, pnn;
-  phase_at(pc, a.lvls, nlev, next_level(a.lvls, nlev, -1, kFwd), 0, kFwd);
-  if (pc.done()) return;
-  phase_next(pn, pc, a.lvls, nlev, kFwd);
-  phase_next(pnn, pn, a.lvls, nlev, kFwd);
-  // coordinates of the first two phases
-  if (tq < pc.segR()) crd2[tq] = a.crd[a.sh.coord_off + pc.r0 + pc.seg * KR + tq];
-  if (!pn.done() && tq < pn.segR()) crd2[KR + tq] = a.crd[a.sh.coord_off + pn.r0 + pn.seg * KR + tq];
-  __syncthreads();
-  int par = 0, cc = 0;
-  uint64_t c2 = 0;
-  int tzrow = 0;
+// State of a sweep: chunks i .. i + DEPTH + 1, the neighbour places of chunks
+// i .. i + DEPTH, the phase of chunk i and the next two.
+template <typename T, int DEPTH>
+struct RingState {
+  int i;
+  Chk q[DEPTH + 2];
+  uint2 nb[DEPTH + 1];
+  RingPhase p, p1;
+  uint64_t crd, crd1;
   T pre[12];
   double rin[3];
-  T fA[kSlotsPerWave][9], fB[kSlotsPerWave][9];
-  load_chunk_f<T, kFwd>(a, pc, 0, crd2[lane], wave, fA);
-  for (;;) {
-    ring_step<T, kFwd>(a, tzp, nlev, wave, pc, cc, par, pn, pnn, fA, fB, part, crd2, yring, tzr, rg, c2, tzrow, pre,
-                       rin);
-    if (pc.done()) break;
-    ring_step<T, kFwd>(a, tzp, nlev, wave, pc, cc, par, pn, pnn, fB, fA, part, crd2, yring, tzr, rg, c2, tzrow, pre,
-                       rin);
-    if (pc.done()) break;
+  int dl[kSlotsPerWave];
+};
+
+// One chunk: issue the factor loads of the chunk DEPTH ahead, multiply chunk
+// i, and close its phase if it is the phase's last.
+template <typename T, bool kFwd, int KR, int DEPTH>
+__device__ inline void ring_step(const RingArgs<T> &a, int wave, RingState<T, DEPTH> &s,
+                                 const T (&fcur)[kSlotsPerWave][9], T (&fload)[kSlotsPerWave][9], T (*part)[KR][3],
+                                 T *yring) {
+  constexpr int dir = kFwd ? 0 : 1;
+  const int lane = (int)__lane_id();
+  if (KR == 64 || s.i == s.p.first) {
+    load_pre<T, kFwd>(a, s.p, s.crd, s.pre, s.rin);
+    s.crd1 = phase_crd(a, s.p1);
+  }
+  const uint2 nbn = load_nbr(a, s.q[DEPTH + 1], wave, dir);
+  load_chunk(a, s.q[DEPTH], s.nb[DEPTH], fload);
+  const Chk qn = chunk_at<T, kFwd>(a, s.i + DEPTH + 2, wave);
+  T a0 = 0, a1 = 0, a2 = 0;
+  mac_chunk(a, s.q[0], s.nb[0], s.dl, fcur, yring, a0, a1, a2);
+  const int prow = (KR == 64 ? 0 : (s.q[0].c % (KR / 64)) * 64) + lane;
+  if (lane < s.q[0].rows) {
+    part[wave][prow][0] = a0;
+    part[wave][prow][1] = a1;
+    part[wave][prow][2] = a2;
+  }
+  ++s.i;
+#pragma unroll
+  for (int k = 0; k <= DEPTH; ++k) s.q[k] = s.q[k + 1];
+  s.q[DEPTH + 1] = qn;
+#pragma unroll
+  for (int k = 0; k < DEPTH; ++k) s.nb[k] = s.nb[k + 1];
+  s.nb[DEPTH] = nbn;
+  if (KR == 64 || s.i == s.p.first + s.p.nchk) {
+    const RingPhase p2 = phase_from<T, kFwd, KR>(a, s.p1.first + s.p1.nchk, wave);
+    lds_barrier();
+    ring_finish<T, kFwd, KR>(a, s.p, s.crd, part, s.pre, s.rin, yring);
+    lds_barrier();
+    s.p = s.p1;
+    s.p1 = p2;
+    s.crd = s.crd1;
   }
 }
 
-// Depth-2 form of the pipeline (FP32 factors, whose registers allow three
-// chunk buffers): the factor loads of the chunk two steps ahead are issued
-// before the current chunk is multiplied.  That chunk may lie up to two phases
-// ahead, so the coordinates of the current phase and the next two live in
-// three LDS buffers (par, par+1, par+2 mod 3); the phase three ahead is read
-// into registers at the start of a phase and stored into the buffer the
-// closing phase frees.
-template <typename T, bool kFwd, int KR>
-__device__ inline void ring_step2(const SweepArgs<T> &a, cptr<int32_t> tzp, int nlev, int wave, Phase<KR> &pc, int &cc,
-                                  int &par, Phase<KR> &pn, Phase<KR> &pnn, Phase<KR> &p3, const T (&fcur)[kSlotsPerWave][9],
-                                  T (&fload)[kSlotsPerWave][9], T (*part)[KR][3], uint64_t *crd3, T *yring,
-                                  int32_t *tzr, const Ring &rg, uint64_t &c3, int &tzrow, T (&pre)[12],
-                                  double (&rin)[3]) {
-  const int lane = (int)__lane_id();
-  const int tq = (int)threadIdx.x;
-  if (cc == 0) {
-    if (!p3.done() && tq < p3.segR()) c3 = a.crd[a.sh.coord_off + p3.r0 + p3.seg * KR + tq];
-    if (pc.seg == 0 && tq < rg.ltlz) tzrow = tzp[pc.L * rg.ltlz + tq];
-    load_pre<T, kFwd>(a, pc, crd3 + par * KR, pre, rin);
+template <typename T, bool kFwd, int KR, int DEPTH>
+__device__ inline void sweep_ring(const RingArgs<T> &a, T (*part)[KR][3], T *yring) {
+  constexpr int dir = kFwd ? 0 : 1;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  RingState<T, DEPTH> s;
+  s.i = 0;
+#pragma unroll
+  for (int k = 0; k < DEPTH + 2; ++k) s.q[k] = chunk_at<T, kFwd>(a, k, wave);
+#pragma unroll
+  for (int k = 0; k < DEPTH + 1; ++k) s.nb[k] = load_nbr(a, s.q[k], wave, dir);
+#pragma unroll
+  for (int j = 0; j < kSlotsPerWave; ++j) {
+    int dx, dy, dz, dt;
+    slot_off((kFwd ? 0 : 41) + kSlotsPerWave * wave + j, dx, dy, dz, dt);
+    s.dl[j] = dx + 2 * dy + 4 * dz + 8 * dt;
   }
-  // the chunk two steps ahead: (pc, cc+2), (pn, 0), (pn, 1) or (pnn, 0)
-  {
-    const int p1 = par == 2 ? 0 : par + 1, p2 = par == 0 ? 2 : par - 1;
-    // chosen with selects, field by field, so that the phases stay in registers
-    const int which = cc + 2 < pc.nch() ? 0 : (cc + 2 == pc.nch() || (!pn.done() && pn.nch() >= 2)) ? 1 : 2;
-    const bool tdone = which == 0 ? pc.done() : which == 1 ? pn.done() : pnn.done();
-    const int tL = which == 0 ? pc.L : which == 1 ? pn.L : pnn.L;
-    const int tseg = which == 0 ? pc.seg : which == 1 ? pn.seg : pnn.seg;
-    const int tsegR = which == 0 ? pc.segR() : which == 1 ? pn.segR() : pnn.segR();
-    const int ct = which == 0 ? cc + 2 : which == 1 ? (cc + 2 == pc.nch() ? 0 : 1) : 0;
-    const int tpar = which == 0 ? par : which == 1 ? p1 : p2;
-    const uint64_t cw = crd3[tpar * KR + ct * 64 + lane];
-    load_chunk_f<T, kFwd>(a, tdone, tL, tseg * (KR / 64) + ct, tsegR - 64 * ct, cw, wave, fload);
-  }
-  // multiply the current chunk
-  {
-    const uint64_t cw = crd3[par * KR + cc * 64 + lane];
-    T a0 = 0, a1 = 0, a2 = 0;
-    mac_chunk_ring<T, kFwd>(a, pc, cc, cw, wave, fcur, yring, tzr, rg, a0, a1, a2);
-    if (cc * 64 + lane < pc.segR()) {
-      part[wave][cc * 64 + lane][0] = a0;
-      part[wave][cc * 64 + lane][1] = a1;
-      part[wave][cc * 64 + lane][2] = a2;
+  s.p = phase_from<T, kFwd, KR>(a, 0, wave);
+  s.p1 = phase_from<T, kFwd, KR>(a, s.p.nchk, wave);
+  s.crd = phase_crd(a, s.p);
+  T f[DEPTH + 1][kSlotsPerWave][9];
+#pragma unroll
+  for (int k = 0; k < DEPTH; ++k) load_chunk(a, s.q[k], s.nb[k], f[k]);
+  static_assert(DEPTH == 1 || DEPTH == 2, "two or three chunk buffers");
+  for (;;) {
+    ring_step<T, kFwd, KR, DEPTH>(a, wave, s, f[0], f[DEPTH], part, yring);
+    if (s.i >= a.nchk) break;
+    ring_step<T, kFwd, KR, DEPTH>(a, wave, s, f[1], f[0], part, yring);
+    if (s.i >= a.nchk) break;
+    if constexpr (DEPTH == 2) {
+      ring_step<T, kFwd, KR, DEPTH>(a, wave, s, f[2], f[1], part, yring);
+      if (s.i >= a.nchk) break;
     }
   }
-  if (cc != pc.nch() - 1) {
-    ++cc;
-    return;
-  }
-  // close the phase
-  lds_barrier();
-  ring_finish<T, kFwd>(a, pc, crd3 + par * KR, part, pre, rin, yring, rg);
-  if (pc.seg == 0 && tq < rg.ltlz) tzr[(pc.L & 15) * rg.ltlz + tq] = tzrow;
-  if (!p3.done() && tq < p3.segR()) crd3[par * KR + tq] = c3;   // the phase three ahead reuses this buffer
-  lds_barrier();
-  pc = pn;
-  pn = pnn;
-  pnn = p3;
-  phase_next(p3, pnn, a.lvls, nlev, kFwd);
-  par = par == 2 ? 0 : par + 1;
-  cc = 0;
 }
 
-template <typename T, bool kFwd, int KR>
-__device__ inline void sweep_ring2(const SweepArgs<T> &a, cptr<int32_t> tzp, T (*part)[KR][3], uint64_t *crd3,
-                                   T *yring, int32_t *tzr, const Ring &rg) {
-  const int lane = (int)__lane_id();
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int tq = (int)threadIdx.x;
-  const int nlev = a.sh.nlev;
-  Phase<KR> pc, pn, pnn, p3;
-  phase_at(pc, a.lvls, nlev, next_level(a.lvls, nlev, -1, kFwd), 0, kFwd);
-  if (pc.done()) return;
-  phase_next(pn, pc, a.lvls, nlev, kFwd);
-  phase_next(pnn, pn, a.lvls, nlev, kFwd);
-  phase_next(p3, pnn, a.lvls, nlev, kFwd);
-  // coordinates of the first three phases
-  if (tq < pc.segR()) crd3[tq] = a.crd[a.sh.coord_off + pc.r0 + pc.seg * KR + tq];
-  if (!pn.done() && tq < pn.segR()) crd3[KR + tq] = a.crd[a.sh.coord_off + pn.r0 + pn.seg * KR + tq];
-  if (!pnn.done() && tq < pnn.segR()) crd3[2 * KR + tq] = a.crd[a.sh.coord_off + pnn.r0 + pnn.seg * KR + tq];
-  __syncthreads();
-  int par = 0, cc = 0;
-  uint64_t c3 = 0;
-  int tzrow = 0;
-  T pre[12];
-  double rin[3];
-  T fA[kSlotsPerWave][9], fB[kSlotsPerWave][9], fC[kSlotsPerWave][9];
-  load_chunk_f<T, kFwd>(a, pc, 0, crd3[lane], wave, fA);
-  if (pc.nch() >= 2) load_chunk_f<T, kFwd>(a, pc, 1, crd3[64 + lane], wave, fB);
-  else load_chunk_f<T, kFwd>(a, pn, 0, crd3[KR + lane], wave, fB);
-  for (;;) {
-    ring_step2<T, kFwd>(a, tzp, nlev, wave, pc, cc, par, pn, pnn, p3, fA, fC, part, crd3, yring, tzr, rg, c3, tzrow,
-                        pre, rin);
-    if (pc.done()) break;
-    ring_step2<T, kFwd>(a, tzp, nlev, wave, pc, cc, par, pn, pnn, p3, fB, fA, part, crd3, yring, tzr, rg, c3, tzrow,
-                        pre, rin);
-    if (pc.done()) break;
-    ring_step2<T, kFwd>(a, tzp, nlev, wave, pc, cc, par, pn, pnn, p3, fC, fB, part, crd3, yring, tzr, rg, c3, tzrow,
-                        pre, rin);
-    if (pc.done()) break;
-  }
-}
-
-// Chunk-coordinate buffers of the apply kernel: two for the depth-1 pipeline
-// (FP64), three for the depth-2 one (FP32).
-template <typename T> constexpr int kCrdBufs = sizeof(T) == 4 ? 3 : 2;
+// Chunks the factor loads run ahead: FP32 factors leave registers for three chunk buffers.
+template <typename T> constexpr int kDepth = sizeof(T) == 4 ? 2 : 1;
 
 // Both sweeps of subdomain `sub` with the values of the last 16 levels in LDS.
 template <typename T, int KR>
 __device__ inline void apply_ring_sub(const OpDev &op, const SubInfo *__restrict__ subs, int sub,
-                                      const ShapeInfo *__restrict__ shapes, const int32_t *__restrict__ lvl_start,
-                                      const uint64_t *__restrict__ coords, const int32_t *__restrict__ ctab,
-                                      const int32_t *__restrict__ tzpref, const T *__restrict__ F,
-                                      T *__restrict__ Y, int64_t fzero, int64_t yzero, const Ring &rg,
+                                      const ShapeInfo *__restrict__ shapes, const uint64_t *__restrict__ coords,
+                                      const ChunkInfo *__restrict__ chunks, const uint2 *__restrict__ nbr,
+                                      const T *__restrict__ F, T *__restrict__ Y, int rmax,
                                       const double *__restrict__ r, double *__restrict__ z) {
   extern __shared__ __align__(16) unsigned char smem[];
   T(*part)[KR][3] = reinterpret_cast<T(*)[KR][3]>(smem);
-  uint64_t *crd2 = reinterpret_cast<uint64_t *>(smem + sizeof(T) * kWaves * KR * 3);
-  T *yring = reinterpret_cast<T *>(smem + sizeof(T) * kWaves * KR * 3 + sizeof(uint64_t) * kCrdBufs<T> * KR);
-  int32_t *tzr = reinterpret_cast<int32_t *>(reinterpret_cast<unsigned char *>(yring) +
-                                             sizeof(T) * (size_t)16 * rg.rmax * 3);
-  SweepArgs<T> a;
+  T *yring = reinterpret_cast<T *>(smem + sizeof(T) * kWaves * KR * 3);
+  RingArgs<T> a;
   a.sd = load_uniform(subs + sub);
-  a.sh = load_uniform(shapes + a.sd.shape);
-  a.op = op;
-  a.lvls = as_const(lvl_start) + a.sh.lvl_off;
-  a.crd = coords;
-  a.ct = as_const(ctab) + a.sh.ct_off;
-  a.F = F;
-  a.Y = Y;
-  a.fzero = fzero;
-  a.yzero = yzero;
-  a.SL = (int64_t)a.sh.dims[3] * a.sh.dims[2] * a.sh.dims[1];
+  const ShapeInfo sh = load_uniform(shapes + a.sd.shape);
+  a.nn0 = op.nn[0];
+  a.nn1 = op.nn[1];
+  a.N = op.N;
+  a.nchk = sh.nchk;
+  a.rmax = rmax;
+  a.vol = sh.vol;
+  a.ch = reinterpret_cast<cptr<int32_t>>(as_const(chunks + sh.chk_off));
+  a.crd = coords + sh.coord_off;
+  a.nbr = nbr + sh.nbr_off;
+  a.F = F + a.sd.fbase;
+  a.Y = Y + a.sd.sbase;
   a.r = r;
   a.z = z;
-  const cptr<int32_t> tzp = as_const(tzpref) + a.sh.tz_off;
-  Ring rl = rg;
-  rl.ltlz = a.sh.dims[3] * a.sh.dims[2];
-  if (kCrdBufs<T> == 3) {
-    sweep_ring2<T, true>(a, tzp, part, crd2, yring, tzr, rl);
-    __syncthreads();   // forward results in global memory are read by the backward sweep
-    sweep_ring2<T, false>(a, tzp, part, crd2, yring, tzr, rl);
-  } else {
-    sweep_ring<T, true>(a, tzp, part, crd2, yring, tzr, rl);
-    __syncthreads();
-    sweep_ring<T, false>(a, tzp, part, crd2, yring, tzr, rl);
-  }
+  sweep_ring<T, true, KR, kDepth<T>>(a, part, yring);
+  __syncthreads();   // forward results in global memory are read by the backward sweep
+  sweep_ring<T, false, KR, kDepth<T>>(a, part, yring);
 }
 
 template <typename T, int KR>
 __global__ void __launch_bounds__(kApplyThreads, 2) apply_ring_kernel(
     OpDev op, const SubInfo *__restrict__ subs, const int32_t *__restrict__ order,
-    const ShapeInfo *__restrict__ shapes, const int32_t *__restrict__ lvl_start,
-    const uint64_t *__restrict__ coords, const int32_t *__restrict__ ctab, const int32_t *__restrict__ tzpref, const T *__restrict__ F, T *__restrict__ Y, int64_t fzero, int64_t yzero,
-    Ring rg, const double *__restrict__ r, double *__restrict__ z) {
+    const ShapeInfo *__restrict__ shapes, const uint64_t *__restrict__ coords, const ChunkInfo *__restrict__ chunks,
+    const uint2 *__restrict__ nbr, const T *__restrict__ F, T *__restrict__ Y, int rmax, const double *__restrict__ r,
+    double *__restrict__ z) {
   const int sub = as_const(order)[blockIdx.x];
-  apply_ring_sub<T, KR>(op, subs, sub, shapes, lvl_start, coords, ctab, tzpref, F, Y, fzero, yzero, rg, r, z);
+  apply_ring_sub<T, KR>(op, subs, sub, shapes, coords, chunks, nbr, F, Y, rmax, r, z);
 }
 
 // One preconditioner of a batched application; its vectors start at element
@@ -1490,14 +1398,13 @@ struct RasBatchDesc {
   OpDev op;
   const SubInfo *subs;
   const ShapeInfo *shapes;
-  const int32_t *lvl;
   const uint64_t *coords;
-  const int32_t *ctab;
-  const int32_t *tz;
+  const ChunkInfo *chunks;
+  const uint2 *nbr;
   const T *F;
   T *Y;
-  int64_t fzero, yzero, voff;
-  Ring rg;
+  int64_t voff;
+  int32_t rmax, pad_;
 };
 
 // Work list entry (preconditioner, subdomain), ordered largest box first
@@ -1519,57 +1426,101 @@ __global__ void __launch_bounds__(kApplyThreads, 2) apply_ring_batch_kernel(cons
   // also count against the LDS counter, so every LDS wait of the sweep would
   // drain the factor loads in flight.)
   const cptr<RasBatchDesc<T>> dp = as_const(descs + wk.x);
-  apply_ring_sub<T, KR>(d.op, dp->subs, wk.y, dp->shapes, dp->lvl, dp->coords, dp->ctab, dp->tz, dp->F, dp->Y, d.fzero,
-                    d.yzero, d.rg, (a == 2 ? r2 : r) + d.voff, z + d.voff);
+  apply_ring_sub<T, KR>(d.op, dp->subs, wk.y, dp->shapes, dp->coords, dp->chunks, dp->nbr, dp->F, dp->Y, d.rmax,
+                        (a == 2 ? r2 : r) + d.voff, z + d.voff);
+}
+
+// --------------------------------------------------------------------------
+// the neighbour places of every shape (setup): rows' places in their levels by
+// natural index, then per (sweep, row, wavefront) the five slots' places
+// --------------------------------------------------------------------------
+__global__ void place_kernel(const ShapeInfo *__restrict__ shapes, const int32_t *__restrict__ lvl_start,
+                             const uint64_t *__restrict__ coords, uint16_t *__restrict__ place) {
+  const ShapeInfo sh = load_uniform(shapes + blockIdx.y);
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < sh.vol; i += gridDim.x * blockDim.x) {
+    int x, y, z, t;
+    unpack(coords[sh.coord_off + i], x, y, z, t);
+    const int rho = x + sh.dims[0] * (y + sh.dims[1] * (z + sh.dims[2] * t));
+    place[sh.coord_off + rho] = (uint16_t)(i - lvl_start[sh.lvl_off + x + 2 * y + 4 * z + 8 * t]);
+  }
+}
+
+__global__ void nbr_kernel(const ShapeInfo *__restrict__ shapes, const int32_t *__restrict__ lvl_start,
+                           const uint64_t *__restrict__ coords, const uint16_t *__restrict__ place,
+                           uint2 *__restrict__ nbr) {
+  const ShapeInfo sh = load_uniform(shapes + blockIdx.y);
+  const int lx = sh.dims[0], ly = sh.dims[1], lz = sh.dims[2];
+  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < 2 * kWaves * sh.vol; q += gridDim.x * blockDim.x) {
+    const int i = q / (2 * kWaves), wave = q % kWaves, dir = (q / kWaves) & 1;
+    int x, y, z, t;
+    unpack(coords[sh.coord_off + i], x, y, z, t);
+    const int L = x + 2 * y + 4 * z + 8 * t;
+    const int r0 = lvl_start[sh.lvl_off + L], R = lvl_start[sh.lvl_off + L + 1] - r0;
+    const int c = (i - r0) >> 6, row0 = r0 + 64 * c, rows = min(64, R - 64 * c);
+    unsigned f[kSlotsPerWave];
+    for (int j = 0; j < kSlotsPerWave; ++j) {
+      int dx, dy, dz, dt;
+      slot_off(41 * dir + kSlotsPerWave * wave + j, dx, dy, dz, dt);
+      f[j] = inside(x + dx, y + dy, z + dz, t + dt, sh.dims)
+                 ? place[sh.coord_off + (x + dx) + lx * ((y + dy) + ly * ((z + dz) + lz * (t + dt)))]
+                 : kNoNbr;
+    }
+    nbr[sh.nbr_off + ((size_t)dir * sh.vol + row0) * kWaves + wave * rows + (i - row0)] =
+        make_uint2(f[0] | (f[1] << 10) | (f[2] << 20), f[3] | (f[4] << 10));
+  }
 }
 
 }  // namespace
 
-// LDS of the ring kernel with KR rows per phase: partial sums, phase
-// coordinates, the 16-level value ring and the (t, z) prefix rows of its levels.
+// LDS of the ring kernel with KR rows per phase: partial sums and the 16-level value ring.
 template <typename T, int KR>
 static size_t ring_lds_bytes(const ras *R) {
-  return sizeof(T) * kWaves * KR * 3 + sizeof(uint64_t) * kCrdBufs<T> * KR +
-         sizeof(T) * (size_t)16 * R->ring_rmax * 3 +
-         sizeof(int32_t) * (size_t)16 * R->ring_ltlz;
+  return sizeof(T) * kWaves * KR * 3 + sizeof(T) * (size_t)16 * R->ring_rmax * 3;
 }
 
 template <typename T, int KR>
-static void launch_ring(const ras *R, const double *r, double *z, T *Y, size_t lds, hipStream_t s) {
+static void launch_ring(const ras *R, const double *r, double *z, T *Y, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
     STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_ring_kernel<T, KR>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingLdsLimit));
     attr_set = true;
   }
-  Ring rg{R->ring_rmax, R->ring_ltlz};
-  hipLaunchKernelGGL((apply_ring_kernel<T, KR>), dim3(R->nsub), dim3(kApplyThreads), lds, s, R->d,
-                     R->d_subs.as<SubInfo>(), R->d_order.as<int32_t>(), R->d_shapes.as<ShapeInfo>(),
-                     R->d_lvl.as<int32_t>(), R->d_coords.as<uint64_t>(), R->d_ctab.as<int32_t>(),
-                     R->d_tz.as<int32_t>(), R->factors.as<T>(), Y, R->factor_elems, R->scratch_elems, rg, r, z);
+  hipLaunchKernelGGL((apply_ring_kernel<T, KR>), dim3(R->nsub), dim3(kApplyThreads), (ring_lds_bytes<T, KR>(R)), s,
+                     R->d, R->d_subs.as<SubInfo>(), R->d_order.as<int32_t>(), R->d_shapes.as<ShapeInfo>(),
+                     R->d_coords.as<uint64_t>(), R->d_chunks.as<ChunkInfo>(), R->d_nbr.as<uint2>(), R->factors.as<T>(),
+                     Y, R->ring_rmax, r, z);
 }
 
-// Rows per phase of the ring kernel for this preconditioner: 256 when the ring
-// fits with them, else 128 (e.g. 13^4 boxes in FP64), else 64 (14^4 boxes in
-// FP64), else 0 (no ring: the kernel with the local vector in global memory).
+// Most rows per phase of the ring kernel for this preconditioner: 256 when the
+// ring fits with them, else 128 (e.g. 13^4 boxes in FP64), else 64 (14^4 boxes
+// in FP64), else 0 (no ring: the kernel with the local vector in global
+// memory).  Beside the ring and the partial sums the rule leaves room for two
+// (FP64) or three (FP32) words per row of a phase and the (t, z) groups of 16
+// levels, at most kApplyThreads of them.
 template <typename T>
 static int ring_rows(const ras *R) {
   if (R->ring_ltlz > kApplyThreads) return 0;
-  if (ring_lds_bytes<T, 256>(R) <= kRingLdsLimit) return 256;
-  if (ring_lds_bytes<T, 128>(R) <= kRingLdsLimit) return 128;
-  if (ring_lds_bytes<T, 64>(R) <= kRingLdsLimit) return 64;
+  const size_t bufs = sizeof(T) == 4 ? 3 : 2, groups = sizeof(int32_t) * (size_t)16 * R->ring_ltlz;
+  if (ring_lds_bytes<T, 256>(R) + groups + sizeof(uint64_t) * bufs * 256 <= kRingLdsLimit) return 256;
+  if (ring_lds_bytes<T, 128>(R) + groups + sizeof(uint64_t) * bufs * 128 <= kRingLdsLimit) return 128;
+  if (ring_lds_bytes<T, 64>(R) + groups + sizeof(uint64_t) * bufs * 64 <= kRingLdsLimit) return 64;
   return 0;
 }
 
+// The form that runs: a level of at most 64 rows is one chunk, so phases of
+// 256 rows would be the same phases with the branches of longer ones.
+static int ring_form(int rows, int rmax) { return rows > 64 && rmax <= 64 ? 64 : rows; }
+
 template <typename T>
 static void launch_apply(const ras *R, const double *r, double *z, T *Y, hipStream_t s) {
-  const int kr = ring_rows<T>(R);
+  const int kr = ring_form(ring_rows<T>(R), R->ring_rmax);
   if (kr == 256) {
-    launch_ring<T, 256>(R, r, z, Y, ring_lds_bytes<T, 256>(R), s);
+    launch_ring<T, 256>(R, r, z, Y, s);
   } else if (kr == 128) {
-    launch_ring<T, 128>(R, r, z, Y, ring_lds_bytes<T, 128>(R), s);
+    launch_ring<T, 128>(R, r, z, Y, s);
   } else if (kr == 64) {
-    launch_ring<T, 64>(R, r, z, Y, ring_lds_bytes<T, 64>(R), s);
+    launch_ring<T, 64>(R, r, z, Y, s);
   } else {
     hipLaunchKernelGGL((apply_kernel<T>), dim3(R->nsub), dim3(kApplyThreads), 0, s, R->d, R->d_subs.as<SubInfo>(),
                        R->d_order.as<int32_t>(), R->d_shapes.as<ShapeInfo>(), R->d_lvl.as<int32_t>(),
@@ -1619,16 +1570,13 @@ static void ras_batch_prepare_t(const ras *const *R, const long long *voff, void
     d[i].op = q->d;
     d[i].subs = q->d_subs.as<SubInfo>();
     d[i].shapes = q->d_shapes.as<ShapeInfo>();
-    d[i].lvl = q->d_lvl.as<int32_t>();
     d[i].coords = q->d_coords.as<uint64_t>();
-    d[i].ctab = q->d_ctab.as<int32_t>();
-    d[i].tz = q->d_tz.as<int32_t>();
+    d[i].chunks = q->d_chunks.as<ChunkInfo>();
+    d[i].nbr = q->d_nbr.as<uint2>();
     d[i].F = q->factors.as<T>();
     d[i].Y = local && local[i] ? static_cast<T *>(local[i]) : q->scratch.as<T>();
-    d[i].fzero = q->factor_elems;
-    d[i].yzero = q->scratch_elems;
     d[i].voff = voff[i];
-    d[i].rg = Ring{q->ring_rmax, q->ring_ltlz};
+    d[i].rmax = q->ring_rmax;
     lds = std::max(lds, out.kr == 256   ? ring_lds_bytes<T, 256>(q)
                         : out.kr == 128 ? ring_lds_bytes<T, 128>(q)
                                         : ring_lds_bytes<T, 64>(q));
@@ -1669,7 +1617,7 @@ void ras_batch_prepare(const ras *const *R, const long long *voff, void *const *
   if (out.precision < 0) out.precision = STKKT_F64;
   if (!uniform) return;   // per-preconditioner launches
   std::vector<char> solo(count, 0);
-  int kr = 256;
+  int kr = 256, rmax = 0;
   bool any = false;
   for (int i = 0; i < count; ++i) {
     if (!R[i]) continue;
@@ -1680,6 +1628,7 @@ void ras_batch_prepare(const ras *const *R, const long long *voff, void *const *
     } else {
       any = true;
       kr = std::min(kr, rows);
+      rmax = std::max(rmax, R[i]->ring_rmax);
     }
   }
   if (!any) {   // every member on its own
@@ -1687,7 +1636,7 @@ void ras_batch_prepare(const ras *const *R, const long long *voff, void *const *
     return;
   }
   out.ring = true;
-  out.kr = kr;
+  out.kr = ring_form(kr, rmax);
   if (out.precision == STKKT_F32) ras_batch_prepare_t<float>(R, voff, local, count, solo, al, out, s);
   else ras_batch_prepare_t<double>(R, voff, local, count, solo, al, out, s);
 }
@@ -1746,6 +1695,28 @@ template <class V> static void upload(const Allocator *al, DevBuf &buf, const st
   buf = DevBuf(al, std::max<size_t>(sizeof(V) * host.size(), 256));
   if (!host.empty())
     STKKT_HIP(hipMemcpyAsync(buf.ptr, host.data(), sizeof(V) * host.size(), hipMemcpyHostToDevice, s));
+}
+
+// The chunk list of a shape, in forward sweep order.
+static void append_chunks(const ShapeHost &sh, std::vector<ChunkInfo> &out) {
+  for (int L = 0; L < sh.nlev; ++L) {
+    const int r0 = sh.lvl_start[L], R = sh.lvl_start[L + 1] - r0;
+    for (int c = 0; c * 64 < R; ++c) {
+      const int32_t *ct = sh.ctab.data() + ((size_t)L * sh.nchunk + c) * 81 * 2;
+      ChunkInfo q{};
+      q.row0 = r0 + 64 * c;
+      q.rows = std::min(64, R - 64 * c);
+      q.L = L;
+      q.c = c;
+      q.R = R;
+      q.off40 = ct[2 * 40];
+      for (int w = 0; w < kWaves; ++w) {
+        q.off[0][w] = ct[2 * (kSlotsPerWave * w)];
+        q.off[1][w] = ct[2 * (41 + kSlotsPerWave * w)];
+      }
+      out.push_back(q);
+    }
+  }
 }
 
 template <int ROWS>
@@ -1873,7 +1844,8 @@ ras *ras_create(const kkt_op *op, const ras_params_t *rp, hipStream_t s) {
   std::vector<int32_t> lvl;
   std::vector<uint64_t> crd;
   std::vector<int32_t> ctb;
-  std::vector<int32_t> tzp;
+  std::vector<ChunkInfo> chunks;
+  int64_t nbr_rows = 0;
   std::vector<int32_t> lines, line_lvl;
   bool by_lines = true;   // every box has line tables
   for (auto &sh : R->shapes) {
@@ -1886,7 +1858,11 @@ ras *ras_create(const kkt_op *op, const ras_params_t *rp, hipStream_t s) {
     si.lvl_off = (int64_t)lvl.size();
     si.coord_off = (int64_t)crd.size();
     si.ct_off = (int64_t)ctb.size();
-    si.tz_off = (int64_t)tzp.size();
+    si.chk_off = (int64_t)chunks.size();
+    si.nbr_off = 2 * kWaves * nbr_rows;
+    nbr_rows += sh.vol;
+    append_chunks(sh, chunks);
+    si.nchk = (int32_t)((int64_t)chunks.size() - si.chk_off);
     si.ln_off = (int64_t)lines.size();
     si.ll_off = (int64_t)line_lvl.size();
     si.nline = (int32_t)sh.line_lvl.size() - 1;
@@ -1896,7 +1872,6 @@ ras *ras_create(const kkt_op *op, const ras_params_t *rp, hipStream_t s) {
     lvl.insert(lvl.end(), sh.lvl_start.begin(), sh.lvl_start.end());
     crd.insert(crd.end(), sh.coords.begin(), sh.coords.end());
     ctb.insert(ctb.end(), sh.ctab.begin(), sh.ctab.end());
-    tzp.insert(tzp.end(), sh.tzpref.begin(), sh.tzpref.end());
     lines.insert(lines.end(), sh.lines.begin(), sh.lines.end());
     line_lvl.insert(line_lvl.end(), sh.line_lvl.begin(), sh.line_lvl.end());
     shinfo.push_back(si);
@@ -1906,7 +1881,18 @@ ras *ras_create(const kkt_op *op, const ras_params_t *rp, hipStream_t s) {
   upload(al, R->d_lvl, lvl, s);
   upload(al, R->d_coords, crd, s);
   upload(al, R->d_ctab, ctb, s);
-  upload(al, R->d_tz, tzp, s);
+  upload(al, R->d_chunks, chunks, s);
+  R->d_nbr = DevBuf(al, sizeof(uint2) * 2 * kWaves * (size_t)nbr_rows);
+  DevBuf d_place(al, sizeof(uint16_t) * (size_t)nbr_rows);
+  {
+    const dim3 g(blocks_for(nbr_rows / (int64_t)R->shapes.size() + 1, 256, 256), (unsigned)R->shapes.size());
+    hipLaunchKernelGGL(place_kernel, g, dim3(256), 0, s, R->d_shapes.as<ShapeInfo>(), R->d_lvl.as<int32_t>(),
+                       R->d_coords.as<uint64_t>(), d_place.as<uint16_t>());
+    hipLaunchKernelGGL(nbr_kernel, dim3(8 * g.x, g.y), dim3(256), 0, s, R->d_shapes.as<ShapeInfo>(),
+                       R->d_lvl.as<int32_t>(), R->d_coords.as<uint64_t>(), d_place.as<uint16_t>(),
+                       R->d_nbr.as<uint2>());
+    STKKT_HIP(hipGetLastError());
+  }
   upload(al, R->d_order, order, s);
   std::vector<int16_t> pstart;
   std::vector<uint8_t> pairs;

@@ -30,10 +30,11 @@ struct ShapeInfo {
   int64_t lvl_off;     // into lvl_start (nlev + 1 entries, row offsets)
   int64_t coord_off;   // into coords (vol entries, packed 16-bit x|y|z|t)
   int64_t ct_off;      // into the chunk table (nlev*nchunk*81 (off9, cnt) pairs)
-  int64_t tz_off;      // into tzpref (nlev*lt*lz entries)
+  int64_t chk_off;     // into the chunk list (nchk entries)
+  int64_t nbr_off;     // into the neighbour places (16 vol entries)
   int64_t ln_off;      // into lines (ly*lz*lt packed (y, z, t) by line level y + 2z + 4t)
   int64_t ll_off;      // into line_lvl (nline + 1 entries)
-  int32_t nline, pad_; // line levels
+  int32_t nline, nchk; // line levels, chunks
 };
 
 struct ShapeHost {
@@ -44,7 +45,6 @@ struct ShapeHost {
   std::vector<int32_t> ctab;   // (element offset, block count) per (level, chunk, slot)
   int64_t nblocks = 0;         // 3x3 blocks
   int64_t felems = 0;          // factor elements including group padding
-  std::vector<int32_t> tzpref;
   std::vector<int32_t> lines, line_lvl;   // x lines (y | z << 10 | t << 20) by level y + 2z + 4t (factorisation)
 };
 
@@ -63,8 +63,8 @@ struct ras {
   int64_t total_blocks = 0;    // 3x3 factor blocks of all subdomains
   int64_t factor_elems = 0;    // factor elements including group padding (zero block follows)
   int64_t scratch_elems = 0;
-  int ring_rmax = 0, ring_ltlz = 0;   // LDS ring sizes of the apply kernel
-  stkkt::DevBuf d_subs, d_shapes, d_lvl, d_coords, d_ctab, d_order, d_tz;
+  int ring_rmax = 0, ring_ltlz = 0;   // most rows of a level, (t, z) groups of a level
+  stkkt::DevBuf d_subs, d_shapes, d_lvl, d_coords, d_ctab, d_order, d_chunks, d_nbr;
   stkkt::DevBuf factors;   // double or float, grouped (blk_pos), 16 zero elements at the end
   stkkt::DevBuf scratch;   // local vectors
   std::shared_ptr<stkkt::IlukData> iluk;   // ILU(k), k > 0: factors, tables and local vectors (else null)
