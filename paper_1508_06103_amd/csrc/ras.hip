@@ -1061,54 +1061,86 @@ __device__ inline Chk chunk_at(const RingArgs<T> &a, int i, int wave) {
   return q;
 }
 
-// Neighbour places of this lane's row of chunk q (all kNoNbr for lanes without a row).
-template <typename T>
+// PACK = 1: lane = row, the wavefront's five slots one after the other.
+// PACK = 2 (levels of at most 32 rows): lanes 32 + i hold row i too and take
+// every second slot, so that a chunk needs three groups of loads instead of
+// five: the address unit spends 16 cycles on a 16-byte load of a wavefront
+// however few of its lanes matter, and at 20 rows a level it was busy two
+// thirds of the time.
+template <int PACK> constexpr int kSlotRegs = (kSlotsPerWave + PACK - 1) / PACK;
+template <int PACK> __device__ inline int lane_row() { return (int)__lane_id() & (64 / PACK - 1); }
+
+// Neighbour places of this lane's row of chunk q.
+template <typename T, int PACK>
 __device__ inline uint2 load_nbr(const RingArgs<T> &a, const Chk &q, int wave, int dir) {
-  const int lane = (int)__lane_id();
   const uint2 *p = a.nbr + ((size_t)dir * a.vol + q.row0) * kWaves + wave * q.rows;
-  return p[min(lane, max(q.rows - 1, 0))];   // masked when used: the load has no branch
+  return p[(unsigned)min(lane_row<PACK>(), max(q.rows - 1, 0))];   // masked when used: the load has no branch
 }
 
-__device__ inline unsigned nbr_place(const uint2 &v, int j, bool valid) {
-  const unsigned f = j < 3 ? (v.x >> (10 * j)) & 1023u : (v.y >> (10 * (j - 3))) & 1023u;
-  return valid ? f : kNoNbr;
+// Place of the neighbour through the slot this lane holds in register group g (kNoNbr: none).
+template <int PACK> __device__ inline unsigned nbr_place(const uint2 &v, int g, bool valid) {
+  auto field = [&v](int j) {
+    return j >= kSlotsPerWave ? kNoNbr : j < 3 ? (v.x >> (10 * j)) & 1023u : (v.y >> (10 * (j - 3))) & 1023u;
+  };
+  if (PACK == 1) return valid ? field(g) : kNoNbr;
+  const unsigned lo = field(2 * g), hi = field(2 * g + 1);
+  return valid ? (__lane_id() < 32 ? lo : hi) : kNoNbr;
 }
 
-// Block k of a group of cnt blocks at g (uniform): 32-bit offsets from scalar bases.
-__device__ inline void load_block_at(const double *g, unsigned k, int cnt, double (&f)[9]) {
-  const char *p = reinterpret_cast<const char *>(g), *p1 = p + 32 * (int64_t)cnt, *p2 = p1 + 32 * (int64_t)cnt;
-  const double2 a = *reinterpret_cast<const double2 *>(p + 32u * k);
-  const double2 b = *reinterpret_cast<const double2 *>(p + 32u * k + 16);
-  const double2 c = *reinterpret_cast<const double2 *>(p1 + 32u * k);
-  const double2 d = *reinterpret_cast<const double2 *>(p1 + 32u * k + 16);
+// 9 elements of a block: quads at byte offsets o and o1, the last element at o2, from a scalar base.
+__device__ inline void load_block_at(const double *base, unsigned o, unsigned o1, unsigned o2, double (&f)[9]) {
+  const char *p = reinterpret_cast<const char *>(base);
+  const double2 a = *reinterpret_cast<const double2 *>(p + o);
+  const double2 b = *reinterpret_cast<const double2 *>(p + o + 16);
+  const double2 c = *reinterpret_cast<const double2 *>(p + o1);
+  const double2 d = *reinterpret_cast<const double2 *>(p + o1 + 16);
   f[0] = a.x, f[1] = a.y, f[2] = b.x, f[3] = b.y;
   f[4] = c.x, f[5] = c.y, f[6] = d.x, f[7] = d.y;
-  f[8] = *reinterpret_cast<const double *>(p2 + 8u * k);
+  f[8] = *reinterpret_cast<const double *>(p + o2);
 }
-__device__ inline void load_block_at(const float *g, unsigned k, int cnt, float (&f)[9]) {
-  const char *p = reinterpret_cast<const char *>(g), *p1 = p + 16 * (int64_t)cnt, *p2 = p1 + 16 * (int64_t)cnt;
-  const float4 a = *reinterpret_cast<const float4 *>(p + 16u * k);
-  const float4 b = *reinterpret_cast<const float4 *>(p1 + 16u * k);
+__device__ inline void load_block_at(const float *base, unsigned o, unsigned o1, unsigned o2, float (&f)[9]) {
+  const char *p = reinterpret_cast<const char *>(base);
+  const float4 a = *reinterpret_cast<const float4 *>(p + o);
+  const float4 b = *reinterpret_cast<const float4 *>(p + o1);
   f[0] = a.x, f[1] = a.y, f[2] = a.z, f[3] = a.w;
   f[4] = b.x, f[5] = b.y, f[6] = b.z, f[7] = b.w;
-  f[8] = *reinterpret_cast<const float *>(p2 + 4u * k);
+  f[8] = *reinterpret_cast<const float *>(p + o2);
 }
 
-// Factor loads of the wavefront's five slots for chunk q.  Lanes without the
-// neighbour read the block at their rank all the same (at most one block past
-// the group, inside the factor buffer); mac_chunk discards it.
-template <typename T>
-__device__ inline void load_chunk(const RingArgs<T> &a, const Chk &q, const uint2 &nb, T (&f)[kSlotsPerWave][9]) {
-  const bool valid = (int)__lane_id() < q.rows;
-  const T *g = a.F + q.off;
+// Factor loads of the wavefront's five slots for chunk q: 32-bit byte offsets
+// from the first of the five groups.  Lanes without the neighbour read the
+// block at their rank all the same (at most one block past the group, inside
+// the factor buffer); mac_chunk discards it.
+template <typename T, int PACK>
+__device__ inline void load_chunk(const RingArgs<T> &a, const Chk &q, const uint2 &nb,
+                                  T (&f)[kSlotRegs<PACK>][9]) {
+  constexpr unsigned kQuad = 4 * sizeof(T);
+  const bool valid = lane_row<PACK>() < q.rows;
+  const T *base = a.F + q.off;
+  unsigned go = 0;   // the group's offset
+  auto group_bytes = [](unsigned cnt) {
+    return (unsigned)sizeof(T) * ((9 * cnt + kGroupAlign - 1) & ~(unsigned)(kGroupAlign - 1));
+  };
 #pragma unroll
-  for (int j = 0; j < kSlotsPerWave; ++j) {
-    const unsigned long long mask = __ballot(nbr_place(nb, j, valid) != kNoNbr);
-    const int cnt = __popcll(mask);
-    const unsigned k =
-        __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
-    load_block_at(g, k, cnt, f[j]);
-    g += (9 * cnt + kGroupAlign - 1) & ~(kGroupAlign - 1);
+  for (int g = 0; g < kSlotRegs<PACK>; ++g) {
+    const unsigned long long mask = __ballot(nbr_place<PACK>(nb, g, valid) != kNoNbr);
+    const unsigned below = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+    if (PACK == 1) {
+      const unsigned cnt = (unsigned)__popcll(mask);
+      load_block_at(base, kQuad * below + go, kQuad * below + (go + kQuad * cnt),
+                    (unsigned)sizeof(T) * below + (go + 2 * kQuad * cnt), f[g]);
+      go += group_bytes(cnt);
+    } else {
+      const unsigned c0 = (unsigned)__popc((unsigned)mask), c1 = (unsigned)__popc((unsigned)(mask >> 32));
+      const unsigned go1 = go + group_bytes(c0);
+      const bool up = __lane_id() >= 32;
+      const unsigned k = up ? below - c0 : below;
+      const unsigned b0 = up ? go1 : go, b1 = up ? go1 + kQuad * c1 : go + kQuad * c0,
+                     b2 = up ? go1 + 2 * kQuad * c1 : go + 2 * kQuad * c0;
+      load_block_at(base, kQuad * k + b0, kQuad * k + b1, (unsigned)sizeof(T) * k + b2, f[g]);
+      go = go1 + group_bytes(c1);
+    }
   }
 }
 
@@ -1120,32 +1152,52 @@ __device__ inline double dot3(double a0, double a1, double a2, double b0, double
   return __builtin_fma(a2, b2, __builtin_fma(a0, b0, a1 * b1));
 }
 
-// Products of chunk q with the neighbour values of the ring; slot j's
-// neighbours lie on level q.L + dl[j].
-template <typename T>
+// The value of lane + 32 (in lanes 0..31).
+__device__ inline unsigned upper_half(unsigned v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return r[1];
+}
+__device__ inline float upper_half(float v) { return __uint_as_float(upper_half(__float_as_uint(v))); }
+__device__ inline double upper_half(double v) {
+  return __hiloint2double((int)upper_half((unsigned)__double2hiint(v)), (int)upper_half((unsigned)__double2loint(v)));
+}
+
+// Products of chunk q with the neighbour values of the ring, added in slot
+// order (lanes below 64 / PACK); slot j's neighbours lie on level q.L + dl[j].
+template <typename T, int PACK>
 __device__ inline void mac_chunk(const RingArgs<T> &a, const Chk &q, const uint2 &nb, const int (&dl)[kSlotsPerWave],
-                                 const T (&f)[kSlotsPerWave][9], const T *yring, T &a0, T &a1, T &a2) {
-  const bool valid = (int)__lane_id() < q.rows;
-  T v[2][3];   // slot j's values are read while slot j - 1 is multiplied
-  auto fetch = [&](int j) {
-    const unsigned pl = min(nbr_place(nb, j, valid), (unsigned)(a.rmax - 1));
-    const T *y = yring + ((q.L + dl[j]) & 15) * (3 * a.rmax) + 3 * pl;
-    v[j & 1][0] = y[0];
-    v[j & 1][1] = y[1];
-    v[j & 1][2] = y[2];
+                                 const T (&f)[kSlotRegs<PACK>][9], const T *yring, T &a0, T &a1, T &a2) {
+  const bool valid = lane_row<PACK>() < q.rows;
+  T v[2][3];   // group g's values are read while group g - 1 is multiplied
+  auto fetch = [&](int g) {
+    const unsigned pl = min(nbr_place<PACK>(nb, g, valid), (unsigned)(a.rmax - 1));
+    auto level = [&](int j) { return ((q.L + dl[min(j, kSlotsPerWave - 1)]) & 15) * (3 * a.rmax); };
+    const int lv = PACK == 1 ? level(g) : __lane_id() < 32 ? level(2 * g) : level(2 * g + 1);
+    const T *y = yring + lv + 3 * pl;
+    v[g & 1][0] = y[0];
+    v[g & 1][1] = y[1];
+    v[g & 1][2] = y[2];
   };
   fetch(0);
 #pragma unroll
-  for (int j = 0; j < kSlotsPerWave; ++j) {
-    if (j + 1 < kSlotsPerWave) fetch(j + 1);
-    const T(&u)[3] = v[j & 1];
-    const bool has = nbr_place(nb, j, valid) != kNoNbr;
-    const T s0 = a0 + dot3(f[j][0], f[j][1], f[j][2], u[0], u[1], u[2]);
-    const T s1 = a1 + dot3(f[j][3], f[j][4], f[j][5], u[0], u[1], u[2]);
-    const T s2 = a2 + dot3(f[j][6], f[j][7], f[j][8], u[0], u[1], u[2]);
+  for (int g = 0; g < kSlotRegs<PACK>; ++g) {
+    if (g + 1 < kSlotRegs<PACK>) fetch(g + 1);
+    const T(&u)[3] = v[g & 1];
+    const bool has = nbr_place<PACK>(nb, g, valid) != kNoNbr;
+    const T t0 = dot3(f[g][0], f[g][1], f[g][2], u[0], u[1], u[2]);
+    const T t1 = dot3(f[g][3], f[g][4], f[g][5], u[0], u[1], u[2]);
+    const T t2 = dot3(f[g][6], f[g][7], f[g][8], u[0], u[1], u[2]);
+    const T s0 = a0 + t0, s1 = a1 + t1, s2 = a2 + t2;
     a0 = has ? s0 : a0;
     a1 = has ? s1 : a1;
     a2 = has ? s2 : a2;
+    if (PACK == 2 && 2 * g + 1 < kSlotsPerWave) {
+      const bool hup = upper_half(has ? 1u : 0u) != 0;
+      const T w0 = a0 + upper_half(t0), w1 = a1 + upper_half(t1), w2 = a2 + upper_half(t2);
+      a0 = hup ? w0 : a0;
+      a1 = hup ? w1 : a1;
+      a2 = hup ? w2 : a2;
+    }
     if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);   // (FP64: more values in flight do not fit the registers)
   }
 }
@@ -1207,7 +1259,9 @@ __device__ inline void load_pre(const RingArgs<T> &a, const RingPhase &p, uint64
   } else {
     const int tq = min((int)threadIdx.x, max(p.rows - 1, 0));
     T d[9];
-    load_block_at(a.F + p.off40, (unsigned)(tq & 63), p.cnt40, d);
+    const unsigned k = (unsigned)(tq & 63), cnt = (unsigned)p.cnt40;
+    constexpr unsigned kQuad = 4 * sizeof(T);
+    load_block_at(a.F + p.off40, kQuad * k, kQuad * k + kQuad * cnt, (unsigned)sizeof(T) * k + 2 * kQuad * cnt, d);
 #pragma unroll
     for (int e = 0; e < 9; ++e) pre[e] = d[e];
     const T *y = a.Y + 3 * (int64_t)(p.base + tq);
@@ -1258,7 +1312,7 @@ __device__ inline void ring_finish(const RingArgs<T> &a, const RingPhase &p, uin
 }
 
 // State of a sweep: chunks i .. i + DEPTH + 1, the neighbour places of chunks
-// i .. i + DEPTH, the phase of chunk i and the next two.
+// i .. i + DEPTH, the phase of chunk i and the next.
 template <typename T, int DEPTH>
 struct RingState {
   int i;
@@ -1273,21 +1327,21 @@ struct RingState {
 
 // One chunk: issue the factor loads of the chunk DEPTH ahead, multiply chunk
 // i, and close its phase if it is the phase's last.
-template <typename T, bool kFwd, int KR, int DEPTH>
+template <typename T, bool kFwd, int KR, int PACK, int DEPTH, bool kFinish>
 __device__ inline void ring_step(const RingArgs<T> &a, int wave, RingState<T, DEPTH> &s,
-                                 const T (&fcur)[kSlotsPerWave][9], T (&fload)[kSlotsPerWave][9], T (*part)[KR][3],
-                                 T *yring) {
+                                 const T (&fcur)[kSlotRegs<PACK>][9], T (&fload)[kSlotRegs<PACK>][9],
+                                 T (*part)[KR][3], T *yring) {
   constexpr int dir = kFwd ? 0 : 1;
   const int lane = (int)__lane_id();
-  if (KR == 64 || s.i == s.p.first) {
+  if (kFinish && (KR == 64 || s.i == s.p.first)) {
     load_pre<T, kFwd>(a, s.p, s.crd, s.pre, s.rin);
     s.crd1 = phase_crd(a, s.p1);
   }
-  const uint2 nbn = load_nbr(a, s.q[DEPTH + 1], wave, dir);
-  load_chunk(a, s.q[DEPTH], s.nb[DEPTH], fload);
+  const uint2 nbn = load_nbr<T, PACK>(a, s.q[DEPTH + 1], wave, dir);
+  load_chunk<T, PACK>(a, s.q[DEPTH], s.nb[DEPTH], fload);
   const Chk qn = chunk_at<T, kFwd>(a, s.i + DEPTH + 2, wave);
   T a0 = 0, a1 = 0, a2 = 0;
-  mac_chunk(a, s.q[0], s.nb[0], s.dl, fcur, yring, a0, a1, a2);
+  mac_chunk<T, PACK>(a, s.q[0], s.nb[0], s.dl, fcur, yring, a0, a1, a2);
   const int prow = (KR == 64 ? 0 : (s.q[0].c % (KR / 64)) * 64) + lane;
   if (lane < s.q[0].rows) {
     part[wave][prow][0] = a0;
@@ -1304,7 +1358,7 @@ __device__ inline void ring_step(const RingArgs<T> &a, int wave, RingState<T, DE
   if (KR == 64 || s.i == s.p.first + s.p.nchk) {
     const RingPhase p2 = phase_from<T, kFwd, KR>(a, s.p1.first + s.p1.nchk, wave);
     lds_barrier();
-    ring_finish<T, kFwd, KR>(a, s.p, s.crd, part, s.pre, s.rin, yring);
+    if (kFinish) ring_finish<T, kFwd, KR>(a, s.p, s.crd, part, s.pre, s.rin, yring);
     lds_barrier();
     s.p = s.p1;
     s.p1 = p2;
@@ -1312,16 +1366,15 @@ __device__ inline void ring_step(const RingArgs<T> &a, int wave, RingState<T, DE
   }
 }
 
-template <typename T, bool kFwd, int KR, int DEPTH>
-__device__ inline void sweep_ring(const RingArgs<T> &a, T (*part)[KR][3], T *yring) {
+template <typename T, bool kFwd, int KR, int PACK, int DEPTH, bool kFinish>
+__device__ inline void sweep_ring(const RingArgs<T> &a, int wave, T (*part)[KR][3], T *yring) {
   constexpr int dir = kFwd ? 0 : 1;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   RingState<T, DEPTH> s;
   s.i = 0;
 #pragma unroll
   for (int k = 0; k < DEPTH + 2; ++k) s.q[k] = chunk_at<T, kFwd>(a, k, wave);
 #pragma unroll
-  for (int k = 0; k < DEPTH + 1; ++k) s.nb[k] = load_nbr(a, s.q[k], wave, dir);
+  for (int k = 0; k < DEPTH + 1; ++k) s.nb[k] = load_nbr<T, PACK>(a, s.q[k], wave, dir);
 #pragma unroll
   for (int j = 0; j < kSlotsPerWave; ++j) {
     int dx, dy, dz, dt;
@@ -1330,28 +1383,38 @@ __device__ inline void sweep_ring(const RingArgs<T> &a, T (*part)[KR][3], T *yri
   }
   s.p = phase_from<T, kFwd, KR>(a, 0, wave);
   s.p1 = phase_from<T, kFwd, KR>(a, s.p.nchk, wave);
-  s.crd = phase_crd(a, s.p);
-  T f[DEPTH + 1][kSlotsPerWave][9];
+  if (kFinish) s.crd = phase_crd(a, s.p);
+  T f[DEPTH + 1][kSlotRegs<PACK>][9];
 #pragma unroll
-  for (int k = 0; k < DEPTH; ++k) load_chunk(a, s.q[k], s.nb[k], f[k]);
+  for (int k = 0; k < DEPTH; ++k) load_chunk<T, PACK>(a, s.q[k], s.nb[k], f[k]);
   static_assert(DEPTH == 1 || DEPTH == 2, "two or three chunk buffers");
   for (;;) {
-    ring_step<T, kFwd, KR, DEPTH>(a, wave, s, f[0], f[DEPTH], part, yring);
+    ring_step<T, kFwd, KR, PACK, DEPTH, kFinish>(a, wave, s, f[0], f[DEPTH], part, yring);
     if (s.i >= a.nchk) break;
-    ring_step<T, kFwd, KR, DEPTH>(a, wave, s, f[1], f[0], part, yring);
+    ring_step<T, kFwd, KR, PACK, DEPTH, kFinish>(a, wave, s, f[1], f[0], part, yring);
     if (s.i >= a.nchk) break;
     if constexpr (DEPTH == 2) {
-      ring_step<T, kFwd, KR, DEPTH>(a, wave, s, f[2], f[1], part, yring);
+      ring_step<T, kFwd, KR, PACK, DEPTH, kFinish>(a, wave, s, f[2], f[1], part, yring);
       if (s.i >= a.nchk) break;
     }
   }
 }
 
-// Chunks the factor loads run ahead: FP32 factors leave registers for three chunk buffers.
-template <typename T> constexpr int kDepth = sizeof(T) == 4 ? 2 : 1;
+// Chunks the factor loads run ahead: two where three chunk buffers fit the registers.
+template <typename T, int PACK> constexpr int kDepth = sizeof(T) == 4 || PACK == 2 ? 2 : 1;
+
+// The wavefronts that finish rows and the others run separate copies of the
+// loop, so that the others issue none of the finishing threads' loads and both
+// have exact wait counts; they meet at the same barriers.
+template <typename T, bool kFwd, int KR, int PACK>
+__device__ inline void sweep_ring(const RingArgs<T> &a, T (*part)[KR][3], T *yring) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (wave < KR / 64) sweep_ring<T, kFwd, KR, PACK, kDepth<T, PACK>, true>(a, wave, part, yring);
+  else sweep_ring<T, kFwd, KR, PACK, kDepth<T, PACK>, false>(a, wave, part, yring);
+}
 
 // Both sweeps of subdomain `sub` with the values of the last 16 levels in LDS.
-template <typename T, int KR>
+template <typename T, int KR, int PACK>
 __device__ inline void apply_ring_sub(const OpDev &op, const SubInfo *__restrict__ subs, int sub,
                                       const ShapeInfo *__restrict__ shapes, const uint64_t *__restrict__ coords,
                                       const ChunkInfo *__restrict__ chunks, const uint2 *__restrict__ nbr,
@@ -1376,19 +1439,19 @@ __device__ inline void apply_ring_sub(const OpDev &op, const SubInfo *__restrict
   a.Y = Y + a.sd.sbase;
   a.r = r;
   a.z = z;
-  sweep_ring<T, true, KR, kDepth<T>>(a, part, yring);
+  sweep_ring<T, true, KR, PACK>(a, part, yring);
   __syncthreads();   // forward results in global memory are read by the backward sweep
-  sweep_ring<T, false, KR, kDepth<T>>(a, part, yring);
+  sweep_ring<T, false, KR, PACK>(a, part, yring);
 }
 
-template <typename T, int KR>
+template <typename T, int KR, int PACK>
 __global__ void __launch_bounds__(kApplyThreads, 2) apply_ring_kernel(
     OpDev op, const SubInfo *__restrict__ subs, const int32_t *__restrict__ order,
     const ShapeInfo *__restrict__ shapes, const uint64_t *__restrict__ coords, const ChunkInfo *__restrict__ chunks,
     const uint2 *__restrict__ nbr, const T *__restrict__ F, T *__restrict__ Y, int rmax, const double *__restrict__ r,
     double *__restrict__ z) {
   const int sub = as_const(order)[blockIdx.x];
-  apply_ring_sub<T, KR>(op, subs, sub, shapes, coords, chunks, nbr, F, Y, rmax, r, z);
+  apply_ring_sub<T, KR, PACK>(op, subs, sub, shapes, coords, chunks, nbr, F, Y, rmax, r, z);
 }
 
 // One preconditioner of a batched application; its vectors start at element
@@ -1409,7 +1472,7 @@ struct RasBatchDesc {
 
 // Work list entry (preconditioner, subdomain), ordered largest box first
 // over the whole batch.
-template <typename T, int KR>
+template <typename T, int KR, int PACK>
 __global__ void __launch_bounds__(kApplyThreads, 2) apply_ring_batch_kernel(const RasBatchDesc<T> *__restrict__ descs,
                                                                             const int2 *__restrict__ work,
                                                                             const int *__restrict__ act,
@@ -1426,7 +1489,7 @@ __global__ void __launch_bounds__(kApplyThreads, 2) apply_ring_batch_kernel(cons
   // also count against the LDS counter, so every LDS wait of the sweep would
   // drain the factor loads in flight.)
   const cptr<RasBatchDesc<T>> dp = as_const(descs + wk.x);
-  apply_ring_sub<T, KR>(d.op, dp->subs, wk.y, dp->shapes, dp->coords, dp->chunks, dp->nbr, dp->F, dp->Y, d.rmax,
+  apply_ring_sub<T, KR, PACK>(d.op, dp->subs, wk.y, dp->shapes, dp->coords, dp->chunks, dp->nbr, dp->F, dp->Y, d.rmax,
                         (a == 2 ? r2 : r) + d.voff, z + d.voff);
 }
 
@@ -1478,16 +1541,16 @@ static size_t ring_lds_bytes(const ras *R) {
   return sizeof(T) * kWaves * KR * 3 + sizeof(T) * (size_t)16 * R->ring_rmax * 3;
 }
 
-template <typename T, int KR>
+template <typename T, int KR, int PACK>
 static void launch_ring(const ras *R, const double *r, double *z, T *Y, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_ring_kernel<T, KR>),
+    STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_ring_kernel<T, KR, PACK>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingLdsLimit));
     attr_set = true;
   }
-  hipLaunchKernelGGL((apply_ring_kernel<T, KR>), dim3(R->nsub), dim3(kApplyThreads), (ring_lds_bytes<T, KR>(R)), s,
-                     R->d, R->d_subs.as<SubInfo>(), R->d_order.as<int32_t>(), R->d_shapes.as<ShapeInfo>(),
+  hipLaunchKernelGGL((apply_ring_kernel<T, KR, PACK>), dim3(R->nsub), dim3(kApplyThreads), (ring_lds_bytes<T, KR>(R)),
+                     s, R->d, R->d_subs.as<SubInfo>(), R->d_order.as<int32_t>(), R->d_shapes.as<ShapeInfo>(),
                      R->d_coords.as<uint64_t>(), R->d_chunks.as<ChunkInfo>(), R->d_nbr.as<uint2>(), R->factors.as<T>(),
                      Y, R->ring_rmax, r, z);
 }
@@ -1508,19 +1571,29 @@ static int ring_rows(const ras *R) {
   return 0;
 }
 
-// The form that runs: a level of at most 64 rows is one chunk, so phases of
-// 256 rows would be the same phases with the branches of longer ones.
-static int ring_form(int rows, int rmax) { return rows > 64 && rmax <= 64 ? 64 : rows; }
+// The form that runs, for the given rows per phase and most rows of a level:
+// a level of at most 64 rows is one chunk, so phases of 256 rows would be the
+// same phases with the branches of longer ones; with at most 32 rows two slots
+// share a load.
+struct RingForm {
+  int kr, pack;
+};
+static RingForm ring_form(int rows, int rmax) {
+  if (rows >= 64 && rmax <= 32) return {64, 2};
+  return {rows > 64 && rmax <= 64 ? 64 : rows, 1};
+}
 
 template <typename T>
 static void launch_apply(const ras *R, const double *r, double *z, T *Y, hipStream_t s) {
-  const int kr = ring_form(ring_rows<T>(R), R->ring_rmax);
-  if (kr == 256) {
-    launch_ring<T, 256>(R, r, z, Y, s);
-  } else if (kr == 128) {
-    launch_ring<T, 128>(R, r, z, Y, s);
-  } else if (kr == 64) {
-    launch_ring<T, 64>(R, r, z, Y, s);
+  const RingForm fm = ring_form(ring_rows<T>(R), R->ring_rmax);
+  if (fm.pack == 2) {
+    launch_ring<T, 64, 2>(R, r, z, Y, s);
+  } else if (fm.kr == 256) {
+    launch_ring<T, 256, 1>(R, r, z, Y, s);
+  } else if (fm.kr == 128) {
+    launch_ring<T, 128, 1>(R, r, z, Y, s);
+  } else if (fm.kr == 64) {
+    launch_ring<T, 64, 1>(R, r, z, Y, s);
   } else {
     hipLaunchKernelGGL((apply_kernel<T>), dim3(R->nsub), dim3(kApplyThreads), 0, s, R->d, R->d_subs.as<SubInfo>(),
                        R->d_order.as<int32_t>(), R->d_shapes.as<ShapeInfo>(), R->d_lvl.as<int32_t>(),
@@ -1597,7 +1670,7 @@ static void ras_batch_prepare_t(const ras *const *R, const long long *voff, void
 
 // One launch covers every member whose LDS ring fits, with the largest rows
 // per phase (256, 128 or 64) that all of them allow (the per-row sums, and
-// so the results, are the same for every phase size).  Members without a ring (or with ILU(k) factors)
+// so the results, are the same for every phase size and form).  Members without a ring (or with ILU(k) factors)
 // are launched on their own after it; members of different precisions make
 // every member its own launch.
 void ras_batch_prepare(const ras *const *R, const long long *voff, void *const *local, int count,
@@ -1636,33 +1709,32 @@ void ras_batch_prepare(const ras *const *R, const long long *voff, void *const *
     return;
   }
   out.ring = true;
-  out.kr = ring_form(kr, rmax);
+  out.kr = ring_form(kr, rmax).kr;
+  out.pack = ring_form(kr, rmax).pack;
   if (out.precision == STKKT_F32) ras_batch_prepare_t<float>(R, voff, local, count, solo, al, out, s);
   else ras_batch_prepare_t<double>(R, voff, local, count, solo, al, out, s);
+}
+
+template <typename T, int KR, int PACK>
+static void ras_batch_launch_form(const RasBatch &b, const double *r, const double *r2, double *z, const int *act,
+                                  hipStream_t s) {
+  static bool attr_set = false;
+  if (!attr_set) {
+    STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_ring_batch_kernel<T, KR, PACK>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingLdsLimit));
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((apply_ring_batch_kernel<T, KR, PACK>), dim3(b.blocks), dim3(kApplyThreads), b.lds, s,
+                     b.desc.as<RasBatchDesc<T>>(), b.work.as<int2>(), act, r, r2 ? r2 : r, z);
 }
 
 template <typename T>
 static void ras_batch_launch(const RasBatch &b, const double *r, const double *r2, double *z, const int *act,
                              hipStream_t s) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_ring_batch_kernel<T, 256>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingLdsLimit));
-    STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_ring_batch_kernel<T, 128>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingLdsLimit));
-    STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_ring_batch_kernel<T, 64>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRingLdsLimit));
-    attr_set = true;
-  }
-  if (b.kr == 256)
-    hipLaunchKernelGGL((apply_ring_batch_kernel<T, 256>), dim3(b.blocks), dim3(kApplyThreads), b.lds, s,
-                       b.desc.as<RasBatchDesc<T>>(), b.work.as<int2>(), act, r, r2 ? r2 : r, z);
-  else if (b.kr == 128)
-    hipLaunchKernelGGL((apply_ring_batch_kernel<T, 128>), dim3(b.blocks), dim3(kApplyThreads), b.lds, s,
-                       b.desc.as<RasBatchDesc<T>>(), b.work.as<int2>(), act, r, r2 ? r2 : r, z);
-  else
-    hipLaunchKernelGGL((apply_ring_batch_kernel<T, 64>), dim3(b.blocks), dim3(kApplyThreads), b.lds, s,
-                       b.desc.as<RasBatchDesc<T>>(), b.work.as<int2>(), act, r, r2 ? r2 : r, z);
+  if (b.pack == 2) ras_batch_launch_form<T, 64, 2>(b, r, r2, z, act, s);
+  else if (b.kr == 256) ras_batch_launch_form<T, 256, 1>(b, r, r2, z, act, s);
+  else if (b.kr == 128) ras_batch_launch_form<T, 128, 1>(b, r, r2, z, act, s);
+  else ras_batch_launch_form<T, 64, 1>(b, r, r2, z, act, s);
 }
 
 void ras_batch_run(const RasBatch &b, const double *r, double *z, const int *act, const int *act_host,
