@@ -1107,40 +1107,36 @@ __device__ inline void load_block_at(const float *base, unsigned o, unsigned o1,
   f[8] = *reinterpret_cast<const float *>(p + o2);
 }
 
-// Factor loads of the wavefront's five slots for chunk q: 32-bit byte offsets
-// from the first of the five groups.  Lanes without the neighbour read the
-// block at their rank all the same (at most one block past the group, inside
-// the factor buffer); mac_chunk discards it.
+// Factor loads of register group g of the wavefront's five slots for chunk q:
+// 32-bit byte offsets from the first of the five groups; `go` runs through
+// them.  Lanes without the neighbour read the block at their rank all the same
+// (at most one block past the group, inside the factor buffer); mac_group
+// discards it.
 template <typename T, int PACK>
-__device__ inline void load_chunk(const RingArgs<T> &a, const Chk &q, const uint2 &nb,
-                                  T (&f)[kSlotRegs<PACK>][9]) {
+__device__ inline void load_group(const RingArgs<T> &a, const Chk &q, const uint2 &nb, int g, unsigned &go, T (&f)[9]) {
   constexpr unsigned kQuad = 4 * sizeof(T);
   const bool valid = lane_row<PACK>() < q.rows;
   const T *base = a.F + q.off;
-  unsigned go = 0;   // the group's offset
   auto group_bytes = [](unsigned cnt) {
     return (unsigned)sizeof(T) * ((9 * cnt + kGroupAlign - 1) & ~(unsigned)(kGroupAlign - 1));
   };
-#pragma unroll
-  for (int g = 0; g < kSlotRegs<PACK>; ++g) {
-    const unsigned long long mask = __ballot(nbr_place<PACK>(nb, g, valid) != kNoNbr);
-    const unsigned below = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
-    if (PACK == 1) {
-      const unsigned cnt = (unsigned)__popcll(mask);
-      load_block_at(base, kQuad * below + go, kQuad * below + (go + kQuad * cnt),
-                    (unsigned)sizeof(T) * below + (go + 2 * kQuad * cnt), f[g]);
-      go += group_bytes(cnt);
-    } else {
-      const unsigned c0 = (unsigned)__popc((unsigned)mask), c1 = (unsigned)__popc((unsigned)(mask >> 32));
-      const unsigned go1 = go + group_bytes(c0);
-      const bool up = __lane_id() >= 32;
-      const unsigned k = up ? below - c0 : below;
-      const unsigned b0 = up ? go1 : go, b1 = up ? go1 + kQuad * c1 : go + kQuad * c0,
-                     b2 = up ? go1 + 2 * kQuad * c1 : go + 2 * kQuad * c0;
-      load_block_at(base, kQuad * k + b0, kQuad * k + b1, (unsigned)sizeof(T) * k + b2, f[g]);
-      go = go1 + group_bytes(c1);
-    }
+  const unsigned long long mask = __ballot(nbr_place<PACK>(nb, g, valid) != kNoNbr);
+  const unsigned below = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+  if (PACK == 1) {
+    const unsigned cnt = (unsigned)__popcll(mask);
+    load_block_at(base, kQuad * below + go, kQuad * below + (go + kQuad * cnt),
+                  (unsigned)sizeof(T) * below + (go + 2 * kQuad * cnt), f);
+    go += group_bytes(cnt);
+  } else {
+    const unsigned c0 = (unsigned)__popc((unsigned)mask), c1 = (unsigned)__popc((unsigned)(mask >> 32));
+    const unsigned go1 = go + group_bytes(c0);
+    const bool up = __lane_id() >= 32;
+    const unsigned k = up ? below - c0 : below;
+    const unsigned b0 = up ? go1 : go, b1 = up ? go1 + kQuad * c1 : go + kQuad * c0,
+                   b2 = up ? go1 + 2 * kQuad * c1 : go + 2 * kQuad * c0;
+    load_block_at(base, kQuad * k + b0, kQuad * k + b1, (unsigned)sizeof(T) * k + b2, f);
+    go = go1 + group_bytes(c1);
   }
 }
 
@@ -1162,43 +1158,40 @@ __device__ inline double upper_half(double v) {
   return __hiloint2double((int)upper_half((unsigned)__double2hiint(v)), (int)upper_half((unsigned)__double2loint(v)));
 }
 
-// Products of chunk q with the neighbour values of the ring, added in slot
-// order (lanes below 64 / PACK); slot j's neighbours lie on level q.L + dl[j].
+// Neighbour values of register group g of chunk q from the ring; slot j's
+// neighbours lie on level q.L + dl[j].
 template <typename T, int PACK>
-__device__ inline void mac_chunk(const RingArgs<T> &a, const Chk &q, const uint2 &nb, const int (&dl)[kSlotsPerWave],
-                                 const T (&f)[kSlotRegs<PACK>][9], const T *yring, T &a0, T &a1, T &a2) {
+__device__ inline void ring_values(const RingArgs<T> &a, const Chk &q, const uint2 &nb, const int (&dl)[kSlotsPerWave],
+                                   int g, const T *yring, T (&v)[3]) {
   const bool valid = lane_row<PACK>() < q.rows;
-  T v[2][3];   // group g's values are read while group g - 1 is multiplied
-  auto fetch = [&](int g) {
-    const unsigned pl = min(nbr_place<PACK>(nb, g, valid), (unsigned)(a.rmax - 1));
-    auto level = [&](int j) { return ((q.L + dl[min(j, kSlotsPerWave - 1)]) & 15) * (3 * a.rmax); };
-    const int lv = PACK == 1 ? level(g) : __lane_id() < 32 ? level(2 * g) : level(2 * g + 1);
-    const T *y = yring + lv + 3 * pl;
-    v[g & 1][0] = y[0];
-    v[g & 1][1] = y[1];
-    v[g & 1][2] = y[2];
-  };
-  fetch(0);
-#pragma unroll
-  for (int g = 0; g < kSlotRegs<PACK>; ++g) {
-    if (g + 1 < kSlotRegs<PACK>) fetch(g + 1);
-    const T(&u)[3] = v[g & 1];
-    const bool has = nbr_place<PACK>(nb, g, valid) != kNoNbr;
-    const T t0 = dot3(f[g][0], f[g][1], f[g][2], u[0], u[1], u[2]);
-    const T t1 = dot3(f[g][3], f[g][4], f[g][5], u[0], u[1], u[2]);
-    const T t2 = dot3(f[g][6], f[g][7], f[g][8], u[0], u[1], u[2]);
-    const T s0 = a0 + t0, s1 = a1 + t1, s2 = a2 + t2;
-    a0 = has ? s0 : a0;
-    a1 = has ? s1 : a1;
-    a2 = has ? s2 : a2;
-    if (PACK == 2 && 2 * g + 1 < kSlotsPerWave) {
-      const bool hup = upper_half(has ? 1u : 0u) != 0;
-      const T w0 = a0 + upper_half(t0), w1 = a1 + upper_half(t1), w2 = a2 + upper_half(t2);
-      a0 = hup ? w0 : a0;
-      a1 = hup ? w1 : a1;
-      a2 = hup ? w2 : a2;
-    }
-    if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);   // (FP64: more values in flight do not fit the registers)
+  const unsigned pl = min(nbr_place<PACK>(nb, g, valid), (unsigned)(a.rmax - 1));
+  auto level = [&](int j) { return ((q.L + dl[min(j, kSlotsPerWave - 1)]) & 15) * (3 * a.rmax); };
+  const int lv = PACK == 1 ? level(g) : __lane_id() < 32 ? level(2 * g) : level(2 * g + 1);
+  const T *y = yring + lv + 3 * pl;
+  v[0] = y[0];
+  v[1] = y[1];
+  v[2] = y[2];
+}
+
+// Products of register group g, added in slot order (lanes below 64 / PACK).
+template <typename T, int PACK>
+__device__ inline void mac_group(const Chk &q, const uint2 &nb, int g, const T (&f)[9], const T (&u)[3], T &a0, T &a1,
+                                 T &a2) {
+  const bool valid = lane_row<PACK>() < q.rows;
+  const bool has = nbr_place<PACK>(nb, g, valid) != kNoNbr;
+  const T t0 = dot3(f[0], f[1], f[2], u[0], u[1], u[2]);
+  const T t1 = dot3(f[3], f[4], f[5], u[0], u[1], u[2]);
+  const T t2 = dot3(f[6], f[7], f[8], u[0], u[1], u[2]);
+  const T s0 = a0 + t0, s1 = a1 + t1, s2 = a2 + t2;
+  a0 = has ? s0 : a0;
+  a1 = has ? s1 : a1;
+  a2 = has ? s2 : a2;
+  if (PACK == 2 && 2 * g + 1 < kSlotsPerWave) {
+    const bool hup = upper_half(has ? 1u : 0u) != 0;
+    const T w0 = a0 + upper_half(t0), w1 = a1 + upper_half(t1), w2 = a2 + upper_half(t2);
+    a0 = hup ? w0 : a0;
+    a1 = hup ? w1 : a1;
+    a2 = hup ? w2 : a2;
   }
 }
 
@@ -1338,10 +1331,20 @@ __device__ inline void ring_step(const RingArgs<T> &a, int wave, RingState<T, DE
     s.crd1 = phase_crd(a, s.p1);
   }
   const uint2 nbn = load_nbr<T, PACK>(a, s.q[DEPTH + 1], wave, dir);
-  load_chunk<T, PACK>(a, s.q[DEPTH], s.nb[DEPTH], fload);
   const Chk qn = chunk_at<T, kFwd>(a, s.i + DEPTH + 2, wave);
+  // loads and products group by group: issued in one go, the chunk's loads
+  // would fill the address unit's queue and hold up the products behind them
   T a0 = 0, a1 = 0, a2 = 0;
-  mac_chunk<T, PACK>(a, s.q[0], s.nb[0], s.dl, fcur, yring, a0, a1, a2);
+  T v[2][3];
+  ring_values<T, PACK>(a, s.q[0], s.nb[0], s.dl, 0, yring, v[0]);
+  unsigned go = 0;
+#pragma unroll
+  for (int g = 0; g < kSlotRegs<PACK>; ++g) {
+    load_group<T, PACK>(a, s.q[DEPTH], s.nb[DEPTH], g, go, fload[g]);
+    if (g + 1 < kSlotRegs<PACK>) ring_values<T, PACK>(a, s.q[0], s.nb[0], s.dl, g + 1, yring, v[(g + 1) & 1]);
+    mac_group<T, PACK>(s.q[0], s.nb[0], g, fcur[g], v[g & 1], a0, a1, a2);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   const int prow = (KR == 64 ? 0 : (s.q[0].c % (KR / 64)) * 64) + lane;
   if (lane < s.q[0].rows) {
     part[wave][prow][0] = a0;
@@ -1386,7 +1389,11 @@ __device__ inline void sweep_ring(const RingArgs<T> &a, int wave, T (*part)[KR][
   if (kFinish) s.crd = phase_crd(a, s.p);
   T f[DEPTH + 1][kSlotRegs<PACK>][9];
 #pragma unroll
-  for (int k = 0; k < DEPTH; ++k) load_chunk<T, PACK>(a, s.q[k], s.nb[k], f[k]);
+  for (int k = 0; k < DEPTH; ++k) {
+    unsigned go = 0;
+#pragma unroll
+    for (int g = 0; g < kSlotRegs<PACK>; ++g) load_group<T, PACK>(a, s.q[k], s.nb[k], g, go, f[k][g]);
+  }
   static_assert(DEPTH == 1 || DEPTH == 2, "two or three chunk buffers");
   for (;;) {
     ring_step<T, kFwd, KR, PACK, DEPTH, kFinish>(a, wave, s, f[0], f[DEPTH], part, yring);
