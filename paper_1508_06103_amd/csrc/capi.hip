@@ -123,6 +123,7 @@ kkt_op *op_create(const kkt_problem_t *p, const kkt_alloc_t *al, hipStream_t s) 
   d.sensor = op->sensor.as<double>();
   stiff_table(d, op->atab.as<double>(), s);
   op->mv = choose_matvec_tile(d);
+  matvec_constants(op.get(), s);
   STKKT_HIP(hipStreamSynchronize(s));
   return op.release();
 }

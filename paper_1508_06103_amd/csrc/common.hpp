@@ -83,11 +83,12 @@ struct OpDev {
   const double *sensor;   // device [N], 1 at sensor nodes
 };
 
-// Launch shape of the matvec: spatial tiles of t[0] x t[1] x t[2] nodes
-// (nt[] tiles per axis) marched over time chunks of clen levels.
+// Launch shape of the matvec: tiles of t[0] x t[1] node columns (nt[] tiles
+// per axis) marched along z in nz chunks of zlen planes, one time level each;
+// threads: columns of a tile with its halo, rounded up to wavefronts.
 struct MvTile {
-  int t[3], nt[3];
-  int ntiles, halo, clen, nchunks;
+  int t[2], nt[2];
+  int ntiles, threads, zlen, nz;
 };
 
 }  // namespace stkkt
@@ -96,7 +97,9 @@ struct kkt_op {
   stkkt::Allocator al;
   stkkt::OpDev d{};
   stkkt::MvTile mv{};
-  stkkt::DevBuf a_elem, sensor, atab;   // atab: [N][27] diffusion stiffness rows
+  stkkt::DevBuf a_elem, sensor, atab;   // atab: [N][27] diffusion stiffness rows (factorisation)
+  stkkt::DevBuf mvc;                    // constants of the matvec
+  std::vector<char> mvc_host;           // their staging
   std::vector<int32_t> sensor_node;   // host copy
   double T = 1.0, len[3] = {1, 1, 1};
   std::vector<double> a_host;         // host copy of a_elem (coarse setup)
@@ -138,6 +141,7 @@ void rhs_device_noalloc(const kkt_op *op, const double *data_host, hipStream_t s
 void fill_zero(double *p, long long n, hipStream_t s);
 void stiff_table(const OpDev &d, double *tab, hipStream_t s);
 MvTile choose_matvec_tile(const OpDev &d);
+void matvec_constants(kkt_op *op, hipStream_t s);   // forms op->mvc (copied in stream order)
 void matvec_device(const kkt_op *op, const double *x, double *y, hipStream_t s);
 // Batched matvec over operators whose vectors are concatenated: operator i
 // reads x[voff_i ...] and writes y[voff_i ...]; one launch for all of them,
@@ -146,8 +150,7 @@ struct MvBatch {
   DevBuf desc;
   int count = 0;
   long long items = 0;
-  int kh = 1;
-  size_t lds = 0;
+  int threads = 64;
 };
 void matvec_batch_prepare(const kkt_op *const *ops, const long long *voff, int count, const Allocator *al,
                           MvBatch &out, hipStream_t s);
