@@ -184,7 +184,12 @@ constexpr size_t kMvLds = 2 * (3 * sizeof(double2) + 9 * sizeof(double)) * kMvTh
 struct MvConst {
   double M[2][4], K[2][4];            // mass and stiffness of a mode
   double Nx[2][2], Ny[2][2], Nz[4];   // tau/2 x convection: [z][y], [z][x], [plane] of the modes that stay
-  double ht, inv_tau, tau6, tau3, beta1, beta2;
+  // rows of the time stiffness St and mass Tt on the first, an inner and the
+  // last level: (n, n - 1), (n, n), (n, n + 1); trapezoid weight
+  struct Level {
+    double st[3], tt[3], wn, pad;
+  } lv[3];
+  double ht, beta1, beta2;
   int l2, pad;   // H1-L2 regularisation: beta2 (Tt f) joins U3 (mass) instead of T3 (stiffness)
 };
 
@@ -220,9 +225,17 @@ MvConst make_mv_const(const OpDev &d) {
       c.Ny[z][i] = -0.5 * c.ht * d.v[1] * m[0][i] * m[2][z];
     }
   for (int q = 0; q < 4; ++q) c.Nz[q] = -0.5 * c.ht * d.v[2] * m[0][q & 1] * m[1][q >> 1];
-  c.inv_tau = 1.0 / d.tau;
-  c.tau6 = d.tau / 6.0;
-  c.tau3 = d.tau / 3.0;
+  for (int e = 0; e < 3; ++e) {
+    const double it = 1.0 / d.tau;
+    MvConst::Level &l = c.lv[e];
+    l.st[0] = e == 0 ? 0.0 : -it;
+    l.st[1] = e == 1 ? 2.0 * it : it;
+    l.st[2] = e == 2 ? 0.0 : -it;
+    l.tt[0] = e == 0 ? 0.0 : d.tau / 6.0;
+    l.tt[1] = e == 1 ? 2.0 * (d.tau / 3.0) : d.tau / 3.0;
+    l.tt[2] = e == 2 ? 0.0 : d.tau / 6.0;
+    l.wn = e == 1 ? d.tau : c.ht;
+  }
   c.beta1 = d.beta1;
   c.beta2 = d.beta2;
   c.l2 = d.reg == STKKT_REG_H1L2;
@@ -252,10 +265,11 @@ __device__ inline void face_modes(double a, double b, double c, double e, double
 // One (tile, z chunk, time level) work item w of one operator.  The constants
 // are read again every plane (scalar loads): kept in scalar registers they
 // spill to vector lanes.
+template <int T>
 __device__ inline void matvec_march(const OpDev &op, const MvTile &tl, cptr<MvConst> mc, const double *__restrict__ x,
                                     double *__restrict__ y, int w) {
   extern __shared__ double2 mv_lds[];
-  const int T = (int)blockDim.x, t = (int)threadIdx.x;
+  const int t = (int)threadIdx.x;
   const int M = op.M, nlev = M + 1;
   const int n = w % nlev, item = w / nlev, tile = item % tl.ntiles, zc = item / tl.ntiles;
   const int nn0 = op.nn[0], nn1 = op.nn[1], nn2 = op.nn[2];
@@ -268,8 +282,12 @@ __device__ inline void matvec_march(const OpDev &op, const MvTile &tl, cptr<MvCo
   const bool elem = tx + 1 < hx && ty + 1 < hy && gx >= 0 && gx < op.n[0] && gy >= 0 && gy < op.n[1];
   const bool own = tx >= 1 && tx + 1 < hx && ty >= 1 && ty + 1 < hy && gx < nn0 && gy < nn1;
   const bool dto = op.variant == STKKT_DTO;
-  const bool hm = n >= 1, hp = n < M, tend = n == 0 || n == M;
+  const bool hm = n >= 1, hp = n < M;
   const bool mflag = !dto || hm;
+  const cptr<MvConst::Level> lv = &mc->lv[hm ? (hp ? 1 : 2) : 0];
+  const double st0 = lv->st[0], st1 = lv->st[1], st2 = lv->st[2], tt0 = lv->tt[0], tt1 = lv->tt[1], tt2 = lv->tt[2];
+  const double ht = mc->ht, beta1 = mc->beta1, beta2 = mc->beta2, wn = lv->wn;
+  const bool l2 = mc->l2 != 0;
   const long long plane = 3LL * nn0 * nn1, level = 3LL * op.N;
   // uniform bases of the plane at levels n - 1, n, n + 1; the thread's byte
   // offsets in a plane of x, of sensor, and in an element layer (clamped into the mesh)
@@ -291,7 +309,9 @@ __device__ inline void matvec_march(const OpDev &op, const MvTile &tl, cptr<MvCo
 
   mv_d2 rm, r0, rp;        // (c, g) of the requested plane at levels n - 1, n, n + 1
   double fm, f0, fp, a_e;  // f, and the coefficient of the element layer below it
+  double sens;             // sensor mask of the plane written when the requested one is taken
   auto request = [&](int p) {
+    sens = *reinterpret_cast<const double *>(reinterpret_cast<const char *>(op.sensor + max(p - 2, 0) * (plane / 3)) + vs);
     const int q = min(p, pb);
     const char *pm = reinterpret_cast<const char *>(bm + q * plane), *p0 = reinterpret_cast<const char *>(b0 + q * plane),
                *pp = reinterpret_cast<const char *>(bp + q * plane);
@@ -317,33 +337,28 @@ __device__ inline void matvec_march(const OpDev &op, const MvTile &tl, cptr<MvCo
   // c^{n+1} (OTD sensor term)
   double c_a = 0.0, g_a = 0.0, e_a = 0.0, c_b = 0.0, g_b = 0.0, e_b = 0.0;
   // Plane p.  kFields: its fields are needed (p <= pb); kLayer: the element
-  // layer between planes p - 1 and p exists (pa < p <= pb).
-  auto plane_step = [&](int p, auto kf, auto kl) {
+  // layer between planes p - 1 and p exists (pa < p <= pb); par: (p - pa) & 1.
+  auto plane_step = [&](int p, auto kf, auto kl, auto par) {
     constexpr bool kFields = decltype(kf)::value, kLayer = decltype(kl)::value;
     cptr<MvConst> m = mc;
     asm volatile("" : "+s"(m));
-    const int par = (p - pa) & 1;
     double2 *const fb = fb0 + par * (3 * T);
     double *const cb = cb0 + par * (9 * T);
-    const double ht = m->ht, a_l = ht * a_e;
+    const double a_l = ht * a_e, sens_o = sens;
     const double cn = r0.x, gr = r0.y, en = rp.x;
     if (kFields) {
-      // rows of the time stiffness St and mass Tt at level n
-      const double it = m->inv_tau, t6 = m->tau6, t3 = m->tau3;
-      const double stm = hm ? -it : 0.0, st0 = tend ? it : 2.0 * it, stp = hp ? -it : 0.0;
-      const double ttm = hm ? t6 : 0.0, tt0 = tend ? t3 : 2.0 * t3, ttp = hp ? t6 : 0.0;
       const bool dn = dirichlet(p);
       const double cm = hm ? rm.x : 0.0, gm = hm ? rm.y : 0.0, fmv = hm ? fm : 0.0;
       const double gn = mflag ? gr : 0.0, gp = hp ? rp.y : 0.0, fpv = hp ? fp : 0.0;
       const double S2 = dn ? 0.0 : gn + gp;
-      const double stf = stm * fmv + st0 * f0 + stp * fpv;
-      const double ttf = m->beta2 * (ttm * fmv + tt0 * f0 + ttp * fpv);
-      double U3 = m->beta1 * stf;
+      const double stf = st0 * fmv + st1 * f0 + st2 * fpv;
+      const double ttf = beta2 * (tt0 * fmv + tt1 * f0 + tt2 * fpv);
+      double U3 = beta1 * stf;
       if (dto) U3 -= ht * S2;
-      else U3 -= dn ? 0.0 : ttm * gm + tt0 * gr + ttp * gp;
+      else U3 -= dn ? 0.0 : tt0 * gm + tt1 * gr + tt2 * gp;
       fb[t] = make_double2((dn ? 0.0 : cn - cm) - ht * (fmv + f0), dn ? 0.0 : cn + cm);
       fb[T + t] = make_double2(dn ? 0.0 : gn - gp, S2);
-      fb[2 * T + t] = m->l2 ? make_double2(U3 + ttf, 0.0) : make_double2(U3, ttf);
+      fb[2 * T + t] = l2 ? make_double2(U3 + ttf, 0.0) : make_double2(U3, ttf);
     }
     // corners of plane p - 2 that belong to other columns
 #pragma unroll
@@ -354,7 +369,7 @@ __device__ inline void matvec_march(const OpDev &op, const MvTile &tl, cptr<MvCo
     const double c_o = c_b, g_o = g_b, e_o = e_b;
     c_b = c_a, g_b = g_a, e_b = e_a;
     c_a = cn, g_a = gr, e_a = en;
-    if (kFields) request(p + 1);
+    request(p + 1);
     __syncthreads();
     if (elem) {
 #pragma unroll
@@ -428,36 +443,46 @@ __device__ inline void matvec_march(const OpDev &op, const MvTile &tl, cptr<MvCo
       const double q1 = keep1 + cb[3 * T + tl1] + (cb[4 * T + td] + cb[5 * T + tdl]);
       const double q2 = keep2 + cb[6 * T + tl1] + (cb[7 * T + td] + cb[8 * T + tdl]);
       const bool dn = dirichlet(o);
-      const double sens =
-          *reinterpret_cast<const double *>(reinterpret_cast<const char *>(op.sensor + o * (plane / 3)) + vs);
       double g;
       if (dn) {
         g = g_o;
       } else if (dto) {
-        const double wn = tend ? ht : 2.0 * ht;   // trapezoid weight of level n
-        g = q1 + (n == 0 ? g_o : 0.0) + wn * sens * c_o;
+        g = q1 + (hm ? 0.0 : g_o) + wn * sens_o * c_o;
       } else {
-        g = hp ? q1 + ht * sens * (c_o + e_o) : g_o;
+        g = hp ? q1 + ht * sens_o * (c_o + e_o) : g_o;
       }
       char *ys = reinterpret_cast<char *>(y + n * level + o * plane);
-      *reinterpret_cast<mv_d2 *>(ys + vo) = mv_d2{(n == 0 || dn) ? c_o : q0, g};
+      *reinterpret_cast<mv_d2 *>(ys + vo) = mv_d2{(!hm || dn) ? c_o : q0, g};
       *reinterpret_cast<double *>(ys + vo + 16) = q2;
     }
   };
   request(pa);
-  plane_step(pa, std::true_type{}, std::false_type{});
-  for (int p = pa + 1; p <= pb; ++p) plane_step(p, std::true_type{}, std::true_type{});
-  for (int p = pb + 1; p <= z1 + 1; ++p) plane_step(p, std::false_type{}, std::false_type{});
+  using Even = std::integral_constant<int, 0>;
+  using Odd = std::integral_constant<int, 1>;
+  plane_step(pa, std::true_type{}, std::false_type{}, Even{});
+  int p = pa + 1;
+  for (; p + 1 <= pb; p += 2) {
+    plane_step(p, std::true_type{}, std::true_type{}, Odd{});
+    plane_step(p + 1, std::true_type{}, std::true_type{}, Even{});
+  }
+  if (p <= pb) {
+    plane_step(p, std::true_type{}, std::true_type{}, Odd{});
+    ++p;
+  }
+#pragma unroll 1
+  for (; p <= z1 + 1; ++p) plane_step(p, std::false_type{}, std::false_type{}, (p - pa) & 1);
 }
 
-__global__ void __launch_bounds__(kMvThreads, 2) matvec_kernel(OpDev op, MvTile tl, const MvConst *__restrict__ mc,
+template <int T>
+__global__ void __launch_bounds__(T, 2) matvec_kernel(OpDev op, MvTile tl, const MvConst *__restrict__ mc,
                                                                const double *__restrict__ x, double *__restrict__ y) {
-  matvec_march(op, tl, as_const(mc), x, y, xcd_work_index());
+  matvec_march<T>(op, tl, as_const(mc), x, y, xcd_work_index());
 }
 
 // Batched form: the work items of all operators in one grid, operator i
 // owning [w0_i, w0_i + nw_i).
-__global__ void __launch_bounds__(kMvThreads, 2) matvec_batch_kernel(const MvBatchDesc *__restrict__ descs, int count,
+template <int T>
+__global__ void __launch_bounds__(T, 2) matvec_batch_kernel(const MvBatchDesc *__restrict__ descs, int count,
                                                                      const int *__restrict__ act,
                                                                      const double *__restrict__ x,
                                                                      double *__restrict__ y) {
@@ -472,7 +497,7 @@ __global__ void __launch_bounds__(kMvThreads, 2) matvec_batch_kernel(const MvBat
   // would be generic, and generic loads also wait on the LDS counter
   d.op.a_elem = cd[i].op.a_elem;
   d.op.sensor = cd[i].op.sensor;
-  matvec_march(d.op, d.tl, &cd[i].mc, x + d.voff, y + d.voff, w - d.w0);
+  matvec_march<T>(d.op, d.tl, &cd[i].mc, x + d.voff, y + d.voff, w - d.w0);
 }
 
 }  // namespace
@@ -522,7 +547,11 @@ void matvec_device(const kkt_op *op, const double *x, double *y, hipStream_t s) 
   const OpDev &d = op->d;
   const long long grid = matvec_items(d, op->mv);
   if (grid > INT32_MAX) throw Error(STKKT_EINVAL, "kkt_matvec: mesh too large");
-  hipLaunchKernelGGL(matvec_kernel, dim3((unsigned)grid), dim3(op->mv.threads), matvec_lds(op->mv.threads), s, d, op->mv,
+  const auto kernel = op->mv.threads == 64    ? matvec_kernel<64>
+                      : op->mv.threads == 128 ? matvec_kernel<128>
+                      : op->mv.threads == 192 ? matvec_kernel<192>
+                                              : matvec_kernel<256>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(op->mv.threads), matvec_lds(op->mv.threads), s, d, op->mv,
                      op->mvc.as<MvConst>(), x, y);
   STKKT_HIP(hipGetLastError());
 }
@@ -556,7 +585,11 @@ void matvec_batch_prepare(const kkt_op *const *ops, const long long *voff, int c
 
 void matvec_batch_run(const MvBatch &b, const double *x, double *y, const int *act, hipStream_t s) {
   if (b.items == 0) return;
-  hipLaunchKernelGGL(matvec_batch_kernel, dim3((unsigned)b.items), dim3(b.threads), matvec_lds(b.threads), s,
+  const auto kernel = b.threads == 64    ? matvec_batch_kernel<64>
+                      : b.threads == 128 ? matvec_batch_kernel<128>
+                      : b.threads == 192 ? matvec_batch_kernel<192>
+                                         : matvec_batch_kernel<256>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)b.items), dim3(b.threads), matvec_lds(b.threads), s,
                      b.desc.as<MvBatchDesc>(), b.count, act, x, y);
   STKKT_HIP(hipGetLastError());
 }
