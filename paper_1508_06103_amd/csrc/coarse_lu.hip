@@ -27,6 +27,18 @@
 
 namespace stkkt {
 
+// Where a block product takes its right-hand sides from: formed already
+// (vec, value (col, c) at col vsi + c), or, one right-hand side, the chunk sums
+// of the previous product, base - sum (base == nullptr: the sum), which the
+// workgroups of the first row tile then also write to out.
+struct ProductInput {
+  const double *vec;
+  int vsi;
+  const double *base, *partial;
+  double *out;
+  int ld, nch;
+};
+
 namespace {
 
 constexpr int kPanel = 64;   // Gauss-Jordan panel width (= GEMM inner dimension)
@@ -776,60 +788,134 @@ __global__ void iota_kernel(int n, int32_t *p) {
 // ---------------------------------------------------------------------------
 // application
 // ---------------------------------------------------------------------------
-// t[i tsi + c tsc] = r_c[i] - (L y_c)[i] for the right-hand sides c =
-// blockIdx.y (r_c = r + c ldr, y_c = y + c ldy; with y == nullptr: t = r).
-// One wavefront per row: its 81 couplings spread over the lanes and summed
-// in a fixed order.
-__global__ void __launch_bounds__(256) lower_rhs_kernel(int nb, const int32_t *__restrict__ idx,
+// A block product leaves its sums over column chunks, partial[(chunk q + c) ld
+// + row] for right-hand side c < q.  With one right-hand side the next launch
+// adds them where it needs them, in chunk order, so no launch of its own does
+// only that: a level of the forward sweep is two launches, of the backward
+// sweep one.  Every workgroup of a product then adds the sums of its columns,
+// which costs (rows / 64) times the reads, so several right-hand sides keep the
+// separate sum (gemm_reduce_kernel): at nb = 2187 and six of them the added
+// form took 1300 us a correction against 1045.
+__device__ inline double chunk_sum(const double *__restrict__ partial, int ld, int nch, int row) {
+  double s = 0.0;
+#pragma unroll 6
+  for (int k = 0; k < nch; ++k) s += partial[(long long)k * ld + row];
+  return s;
+}
+
+// t[i] = r[i] - (L y)[i], y the chunk sums of `partial`, which also go to y;
+// with partial == nullptr: t = r.  One wavefront per row: its 81 couplings
+// spread over the lanes and summed in a fixed order.
+__global__ void __launch_bounds__(256) lower_rhs_kernel(int nb, int ld, int nch, const int32_t *__restrict__ idx,
                                                         const double *__restrict__ val, const double *__restrict__ r,
-                                                        long long ldr, const double *__restrict__ y, long long ldy,
-                                                        double *__restrict__ t, int tsi, int tsc) {
+                                                        const double *__restrict__ partial, double *__restrict__ y,
+                                                        double *__restrict__ t, int tsi) {
   const int lane = threadIdx.x & 63;
-  const int c = blockIdx.y;
-  const double *rc = r + c * ldr;
-  const double *yc = y ? y + c * ldy : nullptr;
   for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < nb; i += gridDim.x * 4) {
     double s = 0.0;
-    if (yc) {
+    if (partial) {
       const long long b = (long long)i * 81;
-      s = val[b + lane] * yc[idx[b + lane]];
-      if (lane < 81 - 64) s += val[b + 64 + lane] * yc[idx[b + 64 + lane]];
+      // lanes 17..63 of the second round: lane 17 forms the row's own y
+      const int j1 = lane < 81 - 64 ? idx[b + 64 + lane] : i;
+      const double v0 = val[b + lane], v1 = lane < 81 - 64 ? val[b + 64 + lane] : 0.0;
+      const double y0 = chunk_sum(partial, ld, nch, idx[b + lane]);
+      const double y1 = lane <= 81 - 64 ? chunk_sum(partial, ld, nch, j1) : 0.0;
+      if (lane == 81 - 64) y[i] = y1;
+      s = v0 * y0;
+      if (lane < 81 - 64) s += v1 * y1;
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
     }
-    if (lane == 0) t[(long long)i * tsi + (long long)c * tsc] = rc[i] - s;
+    if (lane == 0) t[(long long)i * tsi] = r[i] - s;
   }
 }
 
-constexpr int kGvRows = 256, kGvCols = 128;
-
-// partial[chunk][r] = sum over the chunk's columns of A(r, c) x(c)
-// (column-major A with leading dimension ld)
-template <typename T>
-__global__ void __launch_bounds__(kGvRows) gemv_partial_kernel(int nb, int ld, const T *__restrict__ A,
-                                                               const double *__restrict__ x,
-                                                               double *__restrict__ partial) {
-  __shared__ T xs[kGvCols];
-  const int c0 = blockIdx.y * kGvCols;
-  const int nc = min(kGvCols, nb - c0);
-  if ((int)threadIdx.x < nc) xs[threadIdx.x] = (T)x[c0 + threadIdx.x];
-  __syncthreads();
-  const int r = blockIdx.x * kGvRows + threadIdx.x;
-  if (r >= nb) return;
-  T acc = 0;
-  const T *a = A + (long long)c0 * ld + r;
-  for (int c = 0; c < nc; ++c) acc += a[(long long)c * ld] * xs[c];
-  partial[(long long)blockIdx.y * nb + r] = (double)acc;
+// The same for q right-hand sides with y_c = y + c ldy formed (nullptr: t = r):
+// t[i tsi + c] = r_c[i] - (L y_c)[i], the couplings read once for all of them.
+__global__ void __launch_bounds__(256) lower_rhs_multi_kernel(int nb, int q, const int32_t *__restrict__ idx,
+                                                              const double *__restrict__ val,
+                                                              const double *__restrict__ r, long long ldr,
+                                                              const double *__restrict__ y, long long ldy,
+                                                              double *__restrict__ t, int tsi) {
+  const int lane = threadIdx.x & 63;
+  for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < nb; i += gridDim.x * 4) {
+    const long long b = (long long)i * 81;
+    const bool two = lane < 81 - 64;
+    const int i0 = idx[b + lane], i1 = two ? idx[b + 64 + lane] : 0;
+    const double v0 = val[b + lane], v1 = two ? val[b + 64 + lane] : 0.0;
+    for (int c = 0; c < q; ++c) {
+      double s = 0.0;
+      if (y) {
+        s = v0 * y[c * ldy + i0];
+        if (two) s += v1 * y[c * ldy + i1];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+      }
+      if (lane == 0) t[(long long)i * tsi + c] = r[c * ldr + i] - s;
+    }
+  }
 }
 
-// out[r] = base[r] + sign * sum_chunks partial[chunk][r]  (fixed order)
-__global__ void gemv_reduce_kernel(int nb, int nchunk, const double *__restrict__ partial,
-                                   const double *__restrict__ base, double sign, double *__restrict__ out) {
+__device__ inline double product_input(const ProductInput &in, int col, int c, bool write) {
+  if (in.vec) return in.vec[(long long)col * in.vsi + c];
+  const double s = chunk_sum(in.partial, in.ld, in.nch, col);
+  const double v = in.base ? in.base[col] - s : s;
+  if (write) in.out[col] = v;
+  return v;
+}
+
+// Y = A X, one vector, FP32 blocks: a wavefront owns 64 rows and a chunk of
+// kGvCols columns, one row per lane; partial[chunk][row] = sum over the
+// chunk's columns in FP32, ascending.  kGvAhead columns are in flight per
+// wavefront (16 KB): at nb = 2187 the 19 MB of a block take 7.4 us, 18 us with
+// 256-row workgroups and the loads left to the compiler.
+constexpr int kGvRows = 64, kGvCols = 128, kGvAhead = 64;
+static_assert(kGvCols % kGvAhead == 0, "whole batches");
+
+__global__ void __launch_bounds__(kGvRows) gemv_partial_kernel(int nb, int ld, const float *__restrict__ A,
+                                                               ProductInput in, double *__restrict__ partial) {
+  __shared__ float xs[kGvCols];
+  const int c0 = blockIdx.y * kGvCols, nc = min(kGvCols, nb - c0);
+  const int r = blockIdx.x * kGvRows + (int)threadIdx.x;   // < ld
+  const float *a = A + (long long)c0 * ld + r;
+  float v[kGvAhead];
+#pragma unroll
+  for (int k = 0; k < kGvAhead; ++k) v[k] = a[(long long)min(k, nc - 1) * ld];
+  for (int k = threadIdx.x; k < kGvCols; k += kGvRows)
+    xs[k] = k < nc ? (float)product_input(in, c0 + k, 0, blockIdx.x == 0) : 0.0f;
+  __syncthreads();
+  float acc = 0;
+#pragma unroll
+  for (int b = 0; b < kGvCols; b += kGvAhead) {
+#pragma unroll
+    for (int k = 0; k < kGvAhead; ++k) {
+      const float u = v[k];
+      if (b + kGvAhead < kGvCols) v[k] = a[(long long)min(b + kGvAhead + k, nc - 1) * ld];
+      acc = __builtin_fmaf(u, xs[b + k], acc);   // columns past the chunk count zero times
+    }
+  }
+  if (r < nb) partial[(long long)blockIdx.y * nb + r] = (double)acc;
+}
+
+// out = base - chunk sums (base == nullptr: the sums): the end of a sweep.
+__global__ void product_finish_kernel(int nb, ProductInput in) {
+  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nb; r += gridDim.x * blockDim.x)
+    product_input(in, r, 0, true);
+}
+
+// out_c[r] = base_c[r] - sum_chunks partial[chunk][c][r] (fixed order; base ==
+// nullptr: the sum), c = blockIdx.y; the same value also goes to outT[r][c]
+__global__ void gemm_reduce_kernel(int nb, int ld, int q, int nchunk, const double *__restrict__ partial,
+                                   const double *base, long long ldb, double *out, long long ldo,
+                                   double *__restrict__ outT, int tsi) {
+  const int c = blockIdx.y;
   for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nb; r += gridDim.x * blockDim.x) {
     double s = 0.0;
 #pragma unroll 8
-    for (int q = 0; q < nchunk; ++q) s += partial[(long long)q * nb + r];
-    out[r] = (base ? base[r] : 0.0) + sign * s;
+    for (int k = 0; k < nchunk; ++k) s += partial[((long long)k * q + c) * ld + r];
+    const double v = base ? base[c * ldb + r] - s : s;
+    out[c * ldo + r] = v;
+    outT[(long long)r * tsi + c] = v;
   }
 }
 
@@ -842,10 +928,10 @@ __global__ void store_padded_kernel(int nb, int ld, const double *__restrict__ S
 }
 
 // ---------------------------------------------------------------------------
-// several right-hand sides at once.  The product inputs are kept transposed,
-// XT[col][16] (the value of right-hand side c at column col in XT[16 col + c]),
-// so that the matrix-core operands of 4 consecutive columns x 16 right-hand
-// sides are one contiguous 512-byte read.
+// several right-hand sides at once.  A workgroup keeps its chunk of the product
+// input in LDS transposed, XT[col][16] (the value of right-hand side c at
+// column col in XT[16 col + c]), so that the matrix-core operands of 4
+// consecutive columns x 16 right-hand sides are one contiguous 512-byte read.
 // ---------------------------------------------------------------------------
 constexpr int kMrRows = 64, kMrRhs = 16, kMrThreads = 256, kMrAhead = 8;
 
@@ -893,71 +979,60 @@ template <typename T> struct Rows4;
 template <> struct Rows4<float> { using type = Rows4f; };
 template <> struct Rows4<double> { using type = Rows4d; };
 
-template <typename T>
-__global__ void __launch_bounds__(kMrThreads) gemm_partial_kernel(int nb, int ld, int csplit, const T *__restrict__ A,
-                                                                  int q, const double *__restrict__ XT,
-                                                                  double *__restrict__ partial) {
-  __shared__ double red[4 * kMrRhs * kMrRows];   // [wave][rhs][row]
+constexpr int kMrBatch = 16 * kMrAhead;   // columns of one load batch (128)
+
+// BATCHES x 128 columns per chunk: a batch's loads are all in flight together,
+// the next batch's are issued as the current one is multiplied.
+template <typename T, int BATCHES>
+__global__ void __launch_bounds__(kMrThreads) gemm_partial_kernel(int nb, int ld, const T *__restrict__ A, int q,
+                                                                  ProductInput in, double *__restrict__ partial) {
+  __shared__ double lds[4 * kMrRhs * kMrRows];   // the chunk's XT, then the wavefronts' sums [wave][rhs][row]
+  static_assert(BATCHES * kMrBatch * kMrRhs <= 4 * kMrRhs * kMrRows, "XT fits");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
   const int r0 = blockIdx.x * kMrRows;
-  const int cbeg = blockIdx.y * csplit, cend = min(nb, cbeg + csplit);
-  const int nst = ((cend - cbeg + 15) / 16 + kMrAhead - 1) / kMrAhead * kMrAhead;
-  const T *arow = A + r0 + 4 * li;
+  const int cbeg = blockIdx.y * (BATCHES * kMrBatch), ncol = min(nb - cbeg, BATCHES * kMrBatch), last = ncol - 1;
+  const int c_lane = 4 * wave + lk;   // column of step 0 in the chunk
+  const T *arow = A + (long long)cbeg * ld + r0 + 4 * li;
   f64x4 acc[4];
 #pragma unroll
   for (int m = 0; m < 4; ++m) acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
   typename Rows4<T>::type raw[kMrAhead];
-  double b[kMrAhead];
-  const int c_lane = cbeg + 4 * wave + lk;   // column of step 0
-  auto fetch = [&](int p, int st) {
-    const int cc = min(c_lane + 16 * st, cend - 1);
-    raw[p].load(arow + (long long)cc * ld);
-    b[p] = XT[(long long)cc * kMrRhs + li];
-  };
 #pragma unroll
-  for (int p = 0; p < kMrAhead; ++p) fetch(p, p);
-  // the last kMrAhead fetches read the chunk's last column again (cache hits,
-  // unused): an unconditional fetch keeps the wait counts exact
-  for (int st = 0; st < nst; st += kMrAhead) {
+  for (int p = 0; p < kMrAhead; ++p) raw[p].load(arow + (long long)min(c_lane + 16 * p, last) * ld);
+  // the input, while the first columns are on their way
+  for (int k = tid; k < ncol * q; k += kMrThreads) {
+    const int c = k / ncol, col = k - c * ncol;
+    lds[col * kMrRhs + c] = product_input(in, cbeg + col, c, blockIdx.x == 0);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int bt = 0; bt < BATCHES; ++bt) {
 #pragma unroll
     for (int p = 0; p < kMrAhead; ++p) {
+      const int cc = c_lane + 16 * (bt * kMrAhead + p);
+      const double b = lds[min(cc, last) * kMrRhs + li];
       double a[4];
-      raw[p].get(c_lane + 16 * (st + p) < cend, a);
+      raw[p].get(cc <= last, a);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], b[p], acc[m], 0, 0, 0);
-      fetch(p, st + kMrAhead + p);
+      for (int m = 0; m < 4; ++m) acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], b, acc[m], 0, 0, 0);
+      if (bt + 1 < BATCHES) raw[p].load(arow + (long long)min(cc + kMrBatch, last) * ld);
     }
   }
+  __syncthreads();
 #pragma unroll
   for (int m = 0; m < 4; ++m)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) red[(wave * kMrRhs + li) * kMrRows + 4 * (lk + 4 * j) + m] = acc[m][j];
+    for (int j = 0; j < 4; ++j) lds[(wave * kMrRhs + li) * kMrRows + 4 * (lk + 4 * j) + m] = acc[m][j];
   __syncthreads();
   const int rhs = tid >> 4, rl = 4 * (tid & 15);
   if (rhs >= q) return;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int row = r0 + rl + u;
-    const double v = red[(0 * kMrRhs + rhs) * kMrRows + rl + u] + red[(1 * kMrRhs + rhs) * kMrRows + rl + u] +
-                     red[(2 * kMrRhs + rhs) * kMrRows + rl + u] + red[(3 * kMrRhs + rhs) * kMrRows + rl + u];
+    const double v = lds[(0 * kMrRhs + rhs) * kMrRows + rl + u] + lds[(1 * kMrRhs + rhs) * kMrRows + rl + u] +
+                     lds[(2 * kMrRhs + rhs) * kMrRows + rl + u] + lds[(3 * kMrRhs + rhs) * kMrRows + rl + u];
     if (row < nb) partial[((long long)blockIdx.y * q + rhs) * ld + row] = v;
-  }
-}
-
-// out_c[r] = base_c[r] + sign * sum_chunks partial[chunk][c][r] (fixed order),
-// c = blockIdx.y; the same value also goes to outT[r][c]
-__global__ void gemm_reduce_kernel(int nb, int ld, int q, int nchunk, const double *__restrict__ partial,
-                                   const double *base, long long ldb, double sign, double *out, long long ldo,
-                                   double *__restrict__ outT) {
-  const int c = blockIdx.y;
-  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nb; r += gridDim.x * blockDim.x) {
-    double s = 0.0;
-#pragma unroll 8
-    for (int k = 0; k < nchunk; ++k) s += partial[((long long)k * q + c) * ld + r];
-    const double v = (base ? base[c * ldb + r] : 0.0) + sign * s;
-    out[c * ldo + r] = v;
-    outT[(long long)r * kMrRhs + c] = v;
   }
 }
 
@@ -1157,15 +1232,15 @@ CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStr
   E_ = DevBuf(al, esz * nld * std::max(nlev_ - 1, 1));
   Lidx_ = DevBuf(al, sizeof(int32_t) * (size_t)nb_ * 81 * nlev_);
   Lval_ = DevBuf(al, sizeof(double) * (size_t)nb_ * 81 * nlev_);
-  partial_ = DevBuf(al, sizeof(double) * (size_t)nb_ * ((nb_ + kGvCols - 1) / kGvCols));
-  t_ = DevBuf(al, sizeof(double) * nb_);
-  // multi-RHS products: workgroups of 64 rows x 256 columns (two rounds of
-  // the load pipeline).  At nb 6591 (103 x 26 workgroups) a block product
-  // took 41 us in FP32 and 65 us in FP64, against 47 / 70 us with 10 column
-  // chunks and 56 / 81 us with 3.
-  nsplit_ = (nb_ + 255) / 256;
-  mpartial_ = DevBuf(al, sizeof(double) * (size_t)nsplit_ * kMrRhs * ld_);
-  mt_ = DevBuf(al, sizeof(double) * (size_t)3 * kMrRhs * nb_);   // tT, xT[0], xT[1]
+  // block products: workgroups of 64 rows x csplit_ columns, 256 of them where
+  // that gives the chip enough workgroups; at nb 6591 (103 x 26) longer chunks
+  // were slower (FP32 47 us with 10 chunks, 56 us with 3, against 41 us).
+  // Small blocks take 128.
+  csplit_ = (long long)(ld_ / kMrRows) * ((nb_ + 2 * kMrBatch - 1) / (2 * kMrBatch)) >= 1024 ? 2 * kMrBatch : kMrBatch;
+  const size_t gv = (size_t)nb_ * ((nb_ + kGvCols - 1) / kGvCols), nch = (size_t)((nb_ + csplit_ - 1) / csplit_);
+  partial_ = DevBuf(al, sizeof(double) * 2 * std::max(gv, nch * ld_ * kMrRhs / 2));
+  mt_ = DevBuf(al, sizeof(double) * 2 * (size_t)kMrRhs * nb_);
+  y_ = DevBuf(al, sizeof(double) * (size_t)nlev_ * nb_);
   // setup work buffers (FP64)
   DevBuf S(al, sizeof(double) * nn), Ed(al, sizeof(double) * nn),
       tmp(al, sizeof(double) * nn), rows(al, sizeof(double) * 2 * (size_t)kPanel * nb_), piv(al, sizeof(int32_t) * nb_),
@@ -1238,91 +1313,114 @@ CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStr
   if (st) throw Error(STKKT_EBREAKDOWN, "coarse LU: singular Schur complement block");
 }
 
+// partial = chunk sums of A times the input, q right-hand sides (one on the GEMV when `gemv`)
 template <typename T>
-static void gemv(int nb, int ld, const T *A, const double *x, const double *base, double sign, double *partial,
-                 double *out, hipStream_t s) {
-  const int nch = (nb + kGvCols - 1) / kGvCols;
-  hipLaunchKernelGGL(gemv_partial_kernel<T>, dim3((nb + kGvRows - 1) / kGvRows, nch), dim3(kGvRows), 0, s, nb, ld, A,
-                     x, partial);
-  hipLaunchKernelGGL(gemv_reduce_kernel, dim3(blocks_for(nb, 64, 4096)), dim3(64), 0, s, nb, nch, partial, base,
-                     sign, out);
+void CoarseLU::product(bool gemv, int q, const T *A, const ProductInput &in, double *partial, hipStream_t s) const {
+  if constexpr (sizeof(T) == 4) {
+    if (gemv) {
+      hipLaunchKernelGGL(gemv_partial_kernel, dim3(ld_ / kGvRows, (nb_ + kGvCols - 1) / kGvCols), dim3(kGvRows), 0, s,
+                         nb_, ld_, A, in, partial);
+      return;
+    }
+  }
+  const dim3 grid(ld_ / kMrRows, (nb_ + csplit_ - 1) / csplit_);
+  if (csplit_ == kMrBatch)
+    hipLaunchKernelGGL((gemm_partial_kernel<T, 1>), grid, dim3(kMrThreads), 0, s, nb_, ld_, A, q, in, partial);
+  else
+    hipLaunchKernelGGL((gemm_partial_kernel<T, 2>), grid, dim3(kMrThreads), 0, s, nb_, ld_, A, q, in, partial);
 }
 
-template <typename T> void CoarseLU::solve_t(const double *r, double *x, hipStream_t s) const {
+// The two sweeps for one right-hand side: forward, per level, lower_rhs_kernel
+// (t = r_k - L_k y_{k-1}, y_{k-1} from the chunk sums of the previous product)
+// and the product by S_k^{-1}; backward one launch per level, the product by
+// E_k, whose input x_{k+1} = y_{k+1} - E_{k+1} x_{k+2} its workgroups form from
+// the previous product's chunk sums.
+template <typename T> void CoarseLU::sweep_one(bool gemv, const double *r, double *x, hipStream_t s) const {
   const size_t nn = (size_t)ld_ * nb_;
   const T *Si = static_cast<const T *>(Sinv_.ptr);
   const T *E = static_cast<const T *>(E_.ptr);
-  double *t = t_.as<double>(), *part = partial_.as<double>();
-  // forward: y_k = S_k^{-1} (r_k - L_k y_{k-1}), y kept in x
+  double *t = mt_.as<double>(), *y = y_.as<double>();
+  double *part[2] = {partial_.as<double>(), partial_.as<double>() + partial_.bytes / sizeof(double) / 2};
+  ProductInput in{};
+  in.nch = gemv ? (nb_ + kGvCols - 1) / kGvCols : (nb_ + csplit_ - 1) / csplit_;
+  in.ld = gemv ? nb_ : ld_;
+  int cur = 0;   // part[cur]: the last product
   for (int k = 0; k < nlev_; ++k) {
-    const double *rk = r + (size_t)k * nb_;
-    const double *yprev = k > 0 ? x + (size_t)(k - 1) * nb_ : nullptr;
-    hipLaunchKernelGGL(lower_rhs_kernel, dim3(blocks_for(nb_, 4, 1 << 16)), dim3(256), 0, s, nb_,
-                       Lidx_.as<int32_t>() + (size_t)k * nb_ * 81, Lval_.as<double>() + (size_t)k * nb_ * 81, rk,
-                       0LL, yprev, 0LL, t, 1, 0);
-    gemv<T>(nb_, ld_, Si + (size_t)k * nn, t, nullptr, 1.0, part, x + (size_t)k * nb_, s);
+    hipLaunchKernelGGL(lower_rhs_kernel, dim3(blocks_for(nb_, 4, 1 << 16)), dim3(256), 0, s, nb_, in.ld, in.nch,
+                       Lidx_.as<int32_t>() + (size_t)k * nb_ * 81, Lval_.as<double>() + (size_t)k * nb_ * 81,
+                       r + (size_t)k * nb_, k > 0 ? part[cur] : nullptr, k > 0 ? y + (size_t)(k - 1) * nb_ : nullptr, t,
+                       1);
+    in.vec = t;
+    in.vsi = 1;
+    product(gemv, 1, Si + (size_t)k * nn, in, part[cur ^ 1], s);
+    cur ^= 1;
   }
-  // backward: x_k = y_k - E_k x_{k+1}
-  for (int k = nlev_ - 2; k >= 0; --k)
-    gemv<T>(nb_, ld_, E + (size_t)k * nn, x + (size_t)(k + 1) * nb_, x + (size_t)k * nb_, -1.0, part,
-            x + (size_t)k * nb_, s);
+  // x_M = y_M: the chunk sums of the last product; then x_k = y_k - E_k x_{k+1}
+  in.vec = nullptr;
+  for (int k = nlev_ - 1; k >= 0; --k) {
+    in.partial = part[cur];
+    in.base = k + 1 < nlev_ ? y + (size_t)k * nb_ : nullptr;
+    in.out = x + (size_t)k * nb_;
+    if (k == 0) {
+      hipLaunchKernelGGL(product_finish_kernel, dim3(blocks_for(nb_, 64, 4096)), dim3(64), 0, s, nb_, in);
+      break;
+    }
+    product(gemv, 1, E + (size_t)(k - 1) * nn, in, part[cur ^ 1], s);   // writes x_k on the way
+    cur ^= 1;
+  }
+  STKKT_HIP(hipGetLastError());
+}
+
+// The same for q <= 16 right-hand sides, the chunk sums added by a launch of
+// their own that also leaves the next product's input transposed.
+template <typename T>
+void CoarseLU::sweep_multi(int q, const double *r, long long ldr, double *x, long long ldx, hipStream_t s) const {
+  const size_t nn = (size_t)ld_ * nb_;
+  const T *Si = static_cast<const T *>(Sinv_.ptr);
+  const T *E = static_cast<const T *>(E_.ptr);
+  double *t = mt_.as<double>(), *xT = t + (size_t)kMrRhs * nb_, *part = partial_.as<double>();
+  const int nch = (nb_ + csplit_ - 1) / csplit_;
+  ProductInput in{};
+  in.vsi = q;
+  auto reduce = [&](const double *base, double *out) {
+    hipLaunchKernelGGL(gemm_reduce_kernel, dim3(blocks_for(nb_, 64, 4096), q), dim3(64), 0, s, nb_, ld_, q, nch, part,
+                       base, ldx, out, ldx, xT, q);
+  };
+  // forward: y_k kept in x (the last one also in xT)
+  for (int k = 0; k < nlev_; ++k) {
+    hipLaunchKernelGGL(lower_rhs_multi_kernel, dim3(blocks_for(nb_, 4, 1 << 16)), dim3(256), 0, s, nb_, q,
+                       Lidx_.as<int32_t>() + (size_t)k * nb_ * 81, Lval_.as<double>() + (size_t)k * nb_ * 81,
+                       r + (size_t)k * nb_, ldr, k > 0 ? x + (size_t)(k - 1) * nb_ : nullptr, ldx, t, q);
+    in.vec = t;
+    product(false, q, Si + (size_t)k * nn, in, part, s);
+    reduce(nullptr, x + (size_t)k * nb_);
+  }
+  in.vec = xT;
+  for (int k = nlev_ - 2; k >= 0; --k) {
+    product(false, q, E + (size_t)k * nn, in, part, s);
+    reduce(x + (size_t)k * nb_, x + (size_t)k * nb_);
+  }
   STKKT_HIP(hipGetLastError());
 }
 
 void CoarseLU::solve(const double *r, double *x, hipStream_t s) const {
-  if (prec_ == STKKT_F32) solve_t<float>(r, x, s);
-  else solve_t<double>(r, x, s);
+  if (prec_ == STKKT_F32) sweep_one<float>(true, r, x, s);
+  else sweep_one<double>(false, r, x, s);
 }
 
-// out_c = base_c + sign A x_c for q <= 16 right-hand sides given transposed
-// (xT, see above); out_c at stride ldo, and transposed into outT
-template <typename T>
-static void gemm(int nb, int ld, int nsplit, const T *A, int q, const double *xT, const double *base, double sign,
-                 double *partial, double *out, long long ldo, double *outT, hipStream_t s) {
-  const int steps = (nb + 15) / 16;
-  const int csplit = (steps + nsplit - 1) / nsplit * 16;
-  const int nch = (nb + csplit - 1) / csplit;
-  hipLaunchKernelGGL(gemm_partial_kernel<T>, dim3(ld / kMrRows, nch), dim3(kMrThreads), 0, s, nb, ld, csplit, A, q,
-                     xT, partial);
-  hipLaunchKernelGGL(gemm_reduce_kernel, dim3(blocks_for(nb, 64, 4096), q), dim3(64), 0, s, nb, ld, q, nch, partial,
-                     base, ldo, sign, out, ldo, outT);
-}
-
-template <typename T>
-void CoarseLU::solve_multi_t(int q, const double *r, long long ldr, double *x, long long ldx, hipStream_t s) const {
-  const size_t nn = (size_t)ld_ * nb_;
-  const T *Si = static_cast<const T *>(Sinv_.ptr);
-  const T *E = static_cast<const T *>(E_.ptr);
-  double *tT = mt_.as<double>(), *part = mpartial_.as<double>();
-  double *xT[2] = {tT + (size_t)kMrRhs * nb_, tT + (size_t)2 * kMrRhs * nb_};
+void CoarseLU::solve_multi(int q, const double *r, long long ldr, double *x, long long ldx, hipStream_t s) const {
   for (int c0 = 0; c0 < q; c0 += kMrRhs) {
     const int qq = std::min(kMrRhs, q - c0);
     const double *rg = r + c0 * ldr;
     double *xg = x + c0 * ldx;
-    // forward: y_k = S_k^{-1} (r_k - L_k y_{k-1}), y kept in x (the last one also in xT[0])
-    for (int k = 0; k < nlev_; ++k) {
-      const double *yprev = k > 0 ? xg + (size_t)(k - 1) * nb_ : nullptr;
-      hipLaunchKernelGGL(lower_rhs_kernel, dim3(blocks_for(nb_, 4, 1 << 16), qq), dim3(256), 0, s, nb_,
-                         Lidx_.as<int32_t>() + (size_t)k * nb_ * 81, Lval_.as<double>() + (size_t)k * nb_ * 81,
-                         rg + (size_t)k * nb_, ldr, yprev, ldx, tT, kMrRhs, 1);
-      gemm<T>(nb_, ld_, nsplit_, Si + (size_t)k * nn, qq, tT, nullptr, 1.0, part, xg + (size_t)k * nb_, ldx, xT[0],
-              s);
-    }
-    // backward: x_k = y_k - E_k x_{k+1}, x_{k+1} read transposed
-    int cur = 0;
-    for (int k = nlev_ - 2; k >= 0; --k) {
-      gemm<T>(nb_, ld_, nsplit_, E + (size_t)k * nn, qq, xT[cur], xg + (size_t)k * nb_, -1.0, part,
-              xg + (size_t)k * nb_, ldx, xT[1 - cur], s);
-      cur = 1 - cur;
+    if (prec_ == STKKT_F32) {
+      if (qq == 1) sweep_one<float>(false, rg, xg, s);
+      else sweep_multi<float>(qq, rg, ldr, xg, ldx, s);
+    } else {
+      if (qq == 1) sweep_one<double>(false, rg, xg, s);
+      else sweep_multi<double>(qq, rg, ldr, xg, ldx, s);
     }
   }
-  STKKT_HIP(hipGetLastError());
-}
-
-void CoarseLU::solve_multi(int q, const double *r, long long ldr, double *x, long long ldx, hipStream_t s) const {
-  if (q <= 0) return;
-  if (prec_ == STKKT_F32) solve_multi_t<float>(q, r, ldr, x, ldx, s);
-  else solve_multi_t<double>(q, r, ldr, x, ldx, s);
 }
 
 size_t CoarseLU::bytes_per_solve() const {

@@ -5,6 +5,8 @@
 
 namespace stkkt {
 
+struct ProductInput;
+
 class CoarseLU {
  public:
   // Forms and inverts every Schur complement of the coarse operator `cop`
@@ -24,14 +26,19 @@ class CoarseLU {
   bool one_vector_on_mfma() const { return prec_ == STKKT_F64; }
 
  private:
-  template <typename T> void solve_t(const double *r, double *x, hipStream_t s) const;
   template <typename T>
-  void solve_multi_t(int q, const double *r, long long ldr, double *x, long long ldx, hipStream_t s) const;
+  void product(bool gemv, int q, const T *A, const ProductInput &in, double *partial, hipStream_t s) const;
+  template <typename T> void sweep_one(bool gemv, const double *r, double *x, hipStream_t s) const;
+  template <typename T>
+  void sweep_multi(int q, const double *r, long long ldr, double *x, long long ldx, hipStream_t s) const;
   int prec_;
   int nb_ = 0, nlev_ = 0;
   int ld_ = 0;       // leading dimension of the stored blocks (nb_ rounded up to 64, zero rows below nb_)
-  int nsplit_ = 1;   // column chunks of one multi-RHS block product
-  DevBuf Sinv_, E_, Lidx_, Lval_, partial_, t_, mpartial_, mt_;
+  int csplit_ = 0;   // columns per chunk of one multi-RHS block product
+  DevBuf Sinv_, E_, Lidx_, Lval_;
+  DevBuf partial_;   // chunk sums: of two consecutive products of one vector, of one product of up to 16
+  DevBuf mt_;        // product inputs, [column][rhs]
+  DevBuf y_;         // forward results of one vector
 };
 
 }  // namespace stkkt
