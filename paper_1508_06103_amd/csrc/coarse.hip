@@ -25,7 +25,7 @@ struct coarse {
   stkkt::DevBuf xc, yc;     // coarse vectors
   stkkt::DevBuf rt[2];      // intermediate vectors of the axis-by-axis restriction
   // coarse vectors of several right-hand sides (exact coarse solve), grown on demand
-  mutable stkkt::DevBuf xcm, ycm;
+  mutable stkkt::DevBuf xcm, ycm, midm;
   mutable int mcap = 0;
   std::unique_ptr<stkkt::GmresWork> work;   // inner GMRES workspace
   std::unique_ptr<stkkt::CoarseLU> lu;       // exact coarse solve (method LU)
@@ -49,97 +49,72 @@ __device__ inline double hat(int i, int I, int f, double rf) {
   return ad >= f ? 0.0 : (double)(f - ad) * rf;
 }
 
+// Vectors of one launch of a transfer (blockIdx.y selects one).
+constexpr int kTransferVecs = 4;
+struct VecsIn {
+  const double *p[kTransferVecs];
+};
+struct VecsOut {
+  double *p[kTransferVecs];
+};
+
 // y_fine = I_c^h x_coarse: every fine node interpolates the (up to 16) coarse
 // nodes of the coarse space-time cell that contains it (the interpolation is
-// the tensor product of the 1-D hat functions).  A workgroup owns the fine
-// lines (nodes (., i1, i2, n), components innermost) of one coarse (y, z)
-// cell group at one time level: i1 in [g1 fy, g1 fy + fy), i2 in
-// [g2 fz, g2 fz + fz) (the last group of an axis is its last node alone).
-// Such lines need the coarse lines (lo1 + b1, lo2 + b2) of levels lo3 + b3,
-// b = 0, 1 (lo = g, lo3 = n / ft), and the work is done in three passes over
-// LDS:
-//   V[b1][b2][t] = sum_b3 hat_t(n, lo3 + b3) xc[lo3 + b3, lo1 + b1, lo2 + b2][t]
-//   U[line][t]   = sum_b2 hat_z(i2, lo2 + b2) sum_b1 hat_y(i1, lo1 + b1) V[b1][b2][t]
-//   y[line][3 i0 + c] = hat_x(i0, lo0) U[line][3 lo0 + c] + hat_x(i0, lo0 + 1) U[line][3 lo0 + 3 + c]
-// (t runs over the 3 x coarse-x entries of a coarse line).  The x weights and
-// U positions of the 3 nn0 fine entries, and the y / z weights of the lines,
-// are tabulated in LDS first.  The output pass runs over (line, entry) pairs
-// with the entry innermost, so that lines of consecutive i1 (adjacent in
-// memory) are written as one stream.  Lines go through U in batches of at
-// most `lb` lines.
-struct ProlongEntry {
-  double w0, w1;   // hat_x(i0, lo0), hat_x(i0, lo0 + 1) (0 when i0 sits on a coarse node)
-  int u0, pad;     // 3 lo0 + c
-};
-static_assert(sizeof(ProlongEntry) == 3 * sizeof(double), "ProlongEntry takes three doubles of LDS");
-
-__global__ void __launch_bounds__(256) prolong_kernel(OpDev fo, OpDev co, int fx, int fy, int fz, int ft, int lb,
-                                                      const double *__restrict__ xc, double *__restrict__ y) {
-  extern __shared__ double pro_lds[];
-  const int gy = (fo.nn[1] - 1) / fy + 1, gz = (fo.nn[2] - 1) / fz + 1;
-  const int g1 = blockIdx.x % gy, g2 = (blockIdx.x / gy) % gz, n = blockIdx.x / (gy * gz);
-  const int clen = 3 * co.nn[0], len = 3 * fo.nn[0];
-  const int ly = min(fy, fo.nn[1] - g1 * fy), lz = min(fz, fo.nn[2] - g2 * fz);
-  const int cy = ly > 1 ? 2 : 1, cz = lz > 1 ? 2 : 1;   // coarse y / z lines in use
-  const int nl = ly * lz;
-  const int lo3 = n / ft, ct = n % ft == 0 ? 1 : 2;
-  const double rx = 1.0 / fx, ry = 1.0 / fy, rz = 1.0 / fz, rt = 1.0 / ft;
-  const double wt0 = hat(n, lo3, ft, rt), wt1 = ct > 1 ? hat(n, lo3 + 1, ft, rt) : 0.0;
-  ProlongEntry *ent = reinterpret_cast<ProlongEntry *>(pro_lds);   // [len]
-  double *wl = pro_lds + 3 * len;   // [nl][4]: hat_y(i1, lo1 + b1), hat_z(i2, lo2 + b2)
-  double *V = wl + 4 * nl;          // [4][clen]
-  double *U = V + 4 * clen;         // [lb][clen]
-  for (int t = threadIdx.x; t < len; t += blockDim.x) {
-    const int i0 = t / 3, c = t - 3 * i0, lo0 = i0 / fx;
-    ProlongEntry e;
-    e.w0 = hat(i0, lo0, fx, rx);
-    e.w1 = i0 % fx != 0 ? hat(i0, lo0 + 1, fx, rx) : 0.0;
-    e.u0 = 3 * lo0 + c;
-    e.pad = 0;
-    ent[t] = e;
-  }
-  for (int l = threadIdx.x; l < nl; l += blockDim.x) {
-    const int i1 = g1 * fy + l % ly, i2 = g2 * fz + l / ly;
-    wl[4 * l] = hat(i1, g1, fy, ry);
-    wl[4 * l + 1] = cy > 1 ? hat(i1, g1 + 1, fy, ry) : 0.0;
-    wl[4 * l + 2] = hat(i2, g2, fz, rz);
-    wl[4 * l + 3] = cz > 1 ? hat(i2, g2 + 1, fz, rz) : 0.0;
-  }
-  for (int k = threadIdx.x; k < cy * cz * clen; k += blockDim.x) {
-    const int t = k % clen, b = k / clen, b1 = b % cy, b2 = b / cy;
-    const long long cl = (long long)co.nn[0] * ((g1 + b1) + (long long)co.nn[1] * (g2 + b2));
-    double v = wt0 * xc[3 * ((long long)lo3 * co.N + cl) + t];
-    if (ct > 1) v += wt1 * xc[3 * ((long long)(lo3 + 1) * co.N + cl) + t];
-    V[(b2 * 2 + b1) * clen + t] = v;
-  }
-  for (int l0 = 0; l0 < nl; l0 += lb) {
-    const int nb = min(lb, nl - l0);
-    __syncthreads();   // tables and V written (first batch), U free (later batches)
-    for (int k = threadIdx.x; k < nb * clen; k += blockDim.x) {
-      const int lq = k / clen, t = k - lq * clen;
-      const double *w = wl + 4 * (l0 + lq);
-      double u = w[2] * (w[0] * V[t] + (cy > 1 ? w[1] * V[clen + t] : 0.0));
-      if (cz > 1) u += w[3] * (w[0] * V[2 * clen + t] + (cy > 1 ? w[1] * V[3 * clen + t] : 0.0));
-      U[k] = u;
-    }
-    __syncthreads();
-    // (line, entry) pairs of this thread, advanced without divisions
-    const int dq = blockDim.x / len, dt = blockDim.x - dq * len;
-    int lq = threadIdx.x / len, t = threadIdx.x - lq * len;
-    for (; lq < nb;) {
-      const int l = l0 + lq;
-      const int i1 = g1 * fy + l % ly, i2 = g2 * fz + l / ly;
-      const ProlongEntry e = ent[t];
-      const double *u = U + lq * clen;
-      double v = e.w0 * u[e.u0];
-      if (e.w1 != 0.0) v += e.w1 * u[e.u0 + 3];
-      y[(((long long)n * fo.nn[2] + i2) * fo.nn[1] + i1) * len + t] = v;
-      lq += dq;
-      t += dt;
-      if (t >= len) {
-        t -= len;
-        ++lq;
+// the tensor product of the 1-D hat functions).  A thread owns one entry (x
+// node and component) of the fine lines of one coarse (y, z) cell group at one
+// time level, i1 in [g1 fy, g1 fy + fy), i2 in [g2 fz, g2 fz + fz) (the last
+// group of an axis is its last node alone): it blends the four coarse lines at
+// its x position in time and x, 16 loads from the coarse vector in L2, and
+// writes its fy fz fine values, each a bilinear blend of the four; consecutive
+// threads write consecutive entries of a line.  Bound by the fine vector
+// written: 56 MB of a 32^3 x 64 mesh in 16 us, 27 us with the lines staged in
+// LDS (tables and three barriers per 12 KB of output).
+__global__ void __launch_bounds__(256) prolong_kernel(OpDev fo, OpDev co, int fx, int fy, int fz, int ft, VecsIn xs,
+                                                      VecsOut ys) {
+  const int gy = (fo.nn[1] - 1) / fy + 1, gz = (fo.nn[2] - 1) / fz + 1, len = 3 * fo.nn[0], clen = 3 * co.nn[0];
+  const long long total = (long long)len * gy * gz * (fo.M + 1);
+  const double *__restrict__ xc = xs.p[blockIdx.y];
+  double *__restrict__ y = ys.p[blockIdx.y];
+  const double ry = 1.0 / fy, rz = 1.0 / fz;
+  for (long long q = blockIdx.x * (long long)blockDim.x + threadIdx.x; q < total;
+       q += (long long)gridDim.x * blockDim.x) {
+    const long long grp = q / len;
+    const int t = (int)(q - grp * len);
+    const int g1 = (int)(grp % gy), g2 = (int)((grp / gy) % gz), n = (int)(grp / ((long long)gy * gz));
+    const int i0 = t / 3, lo0 = i0 / fx, u0 = 3 * lo0 + (t - 3 * i0), lo3 = n / ft;
+    const double wx0 = hat(i0, lo0, fx, 1.0 / fx), wx1 = 1.0 - wx0, wt0 = hat(n, lo3, ft, 1.0 / ft), wt1 = 1.0 - wt0;
+    const int ly = min(fy, fo.nn[1] - g1 * fy), lz = min(fz, fo.nn[2] - g2 * fz);
+    // steps to the upper coarse neighbours (0 where the node sits on a coarse one: not used then)
+    const int sx = i0 % fx != 0 ? 3 : 0, sy = ly > 1 ? clen : 0;
+    const long long sz = lz > 1 ? (long long)co.nn[1] * clen : 0, st = n % ft != 0 ? 3LL * co.N : 0;
+    const double *c = xc + 3LL * lo3 * co.N + ((long long)co.nn[1] * g2 + g1) * clen + u0;
+    double W[2][2];   // [z][y]
+#pragma unroll
+    for (int b2 = 0; b2 < 2; ++b2)
+#pragma unroll
+      for (int b1 = 0; b1 < 2; ++b1) {
+        const double *p = c + b1 * sy + b2 * sz;
+        double v = wx0 * p[0];
+        if (sx) v += wx1 * p[sx];
+        v *= wt0;
+        if (st) {
+          double w = wx0 * p[st];
+          if (sx) w += wx1 * p[st + sx];
+          v += wt1 * w;
+        }
+        W[b2][b1] = v;
       }
+    double *o = y + (((long long)n * fo.nn[2] + g2 * fz) * fo.nn[1] + g1 * fy) * len + t;
+    for (int jz = 0; jz < lz; ++jz) {
+      const double wz0 = (double)(fz - jz) * rz, wz1 = (double)jz * rz;
+      double a = wz0 * W[0][0], b = wz0 * W[0][1];
+      if (jz > 0) {
+        a += wz1 * W[1][0];
+        b += wz1 * W[1][1];
+      }
+      double *ol = o + (long long)jz * fo.nn[1] * len;
+      ol[0] = a;
+      for (int jy = 1; jy < ly; ++jy) ol[(long long)jy * len] = (double)(fy - jy) * ry * a + (double)jy * ry * b;
     }
   }
 }
@@ -236,34 +211,97 @@ __global__ void __launch_bounds__(256) restrict_x_kernel(int nx, int lines, int 
   }
 }
 
+// The x and y axes together: a workgroup coarsens one (z, t) plane of the fine
+// vector, first in y, straight from memory (every fine line between two coarse
+// ones is read for both, the second time from the cache; the loads of an entry
+// do not depend on each other), then its cy lines in x, from LDS.  A 32^3 x 64
+// vector (56 MB) takes 19 us; with the whole plane staged in LDS and x first it
+// took 22, with one launch per axis 25 and 8 us.
+__global__ void __launch_bounds__(256) restrict_xy_kernel(int nx, int ny, int fx, int fy, VecsIn xs,
+                                                          double *__restrict__ out, long long ostride) {
+  extern __shared__ double rxy_lds[];   // [cy][lin]
+  const int lin = 3 * nx, cx = (nx - 1) / fx + 1, cy = (ny - 1) / fy + 1, lout = 3 * cx;
+  const double *__restrict__ src = xs.p[blockIdx.y] + (long long)blockIdx.x * ny * lin;
+  const double rx = 1.0 / fx, ry = 1.0 / fy;
+  for (int k = threadIdx.x; k < cy * lin; k += 256) {
+    const int I = k / lin, t = k - I * lin;
+    const int lo = max(0, I * fy - fy + 1), hi = min(ny - 1, I * fy + fy - 1);
+    const double *col = src + t;
+    double acc = 0.0;
+    for (int p0 = lo; p0 <= hi; p0 += 8) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = col[(long long)min(p0 + u, hi) * lin];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (p0 + u <= hi) acc += hat(p0 + u, I, fy, ry) * v[u];
+    }
+    rxy_lds[k] = acc;
+  }
+  __syncthreads();
+  double *dst = out + blockIdx.y * ostride + (long long)blockIdx.x * cy * lout;
+  for (int k = threadIdx.x; k < cy * lout; k += 256) {
+    const int l = k / lout, t = k - l * lout, I = t / 3, c = t - 3 * I;
+    const int lo = max(0, I * fx - fx + 1), hi = min(nx - 1, I * fx + fx - 1);
+    const double *row = rxy_lds + l * lin + c;
+    double acc = 0.0;
+    for (int p = lo; p <= hi; ++p) acc += hat(p, I, fx, rx) * row[3 * p];
+    dst[k] = acc;
+  }
+}
+
+// The z and t axes together, planes of pl doubles already coarsened in x and
+// y: out[I3][I2][e] = sum over t and z of hat_t hat_z in[p3][p2][e].
+__global__ void __launch_bounds__(256) restrict_zt_kernel(int pl, int nz, int nt, int fz, int ft, VecsIn xs,
+                                                          VecsOut ys) {
+  const int cz = (nz - 1) / fz + 1, ct = (nt - 1) / ft + 1;
+  const long long total = (long long)ct * cz * pl;
+  const double *__restrict__ in = xs.p[blockIdx.y];
+  const double rz = 1.0 / fz, rt = 1.0 / ft;
+  for (long long q = blockIdx.x * (long long)blockDim.x + threadIdx.x; q < total;
+       q += (long long)gridDim.x * blockDim.x) {
+    const long long g = q / pl;
+    const int e = (int)(q - g * pl), I2 = (int)(g % cz), I3 = (int)(g / cz);
+    const int z0 = max(0, I2 * fz - fz + 1), z1 = min(nz - 1, I2 * fz + fz - 1);
+    const int t0 = max(0, I3 * ft - ft + 1), t1 = min(nt - 1, I3 * ft + ft - 1);
+    double acc = 0.0;
+    for (int t = t0; t <= t1; ++t) {
+      const double *src = in + (long long)t * nz * pl + e;
+      double s = 0.0;
+#pragma unroll 4
+      for (int z = z0; z <= z1; ++z) s += hat(z, I2, fz, rz) * src[(long long)z * pl];
+      acc += hat(t, I3, ft, rt) * s;
+    }
+    ys.p[blockIdx.y][q] = acc;
+  }
+}
+
 }  // namespace
 
-// Prolongation launch: one workgroup per (y group, z group, time level); U
-// batches sized so that V and U take at most 32 KB of LDS (the x-entry and
-// line tables come on top: 24 B per fine x entry, 32 B per line).
-static void prolong(const coarse *C, const double *xc, double *y, hipStream_t s) {
-  const OpDev &fo = C->fine, &co = C->cop->d;
-  const int fy = C->fac[1], fz = C->fac[2];
-  const int gy = (fo.nn[1] - 1) / fy + 1, gz = (fo.nn[2] - 1) / fz + 1;
-  const long long blocks = (long long)gy * gz * (fo.M + 1);
-  STKKT_REQUIRE(blocks < (1LL << 31), "coarse_apply: fine mesh too large for the prolongation grid");
-  const int clen = 3 * co.nn[0], len = 3 * fo.nn[0];
-  const int lb = std::max(1, std::min(fy * fz, (int)(4096 / clen) - 4));
-  const size_t lds = sizeof(double) * ((size_t)3 * len + 4 * (size_t)fy * fz + (size_t)(4 + lb) * clen);
-  constexpr size_t kLdsMax = 160 * 1024;
-  STKKT_REQUIRE(lds <= kLdsMax, "coarse_apply: fine x line too long for the prolongation kernel");
-  static bool attr_set = false;
-  if (!attr_set) {
-    STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&prolong_kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
-    attr_set = true;
-  }
-  hipLaunchKernelGGL(prolong_kernel, dim3((unsigned)blocks), dim3(256), lds, s, fo, co, C->fac[0], fy, fz, C->fac[3],
-                     lb, xc, y);
+// y_i = I_c^h xc_i for q <= kTransferVecs vectors
+static void prolong(const coarse *C, int q, const VecsIn &xc, const VecsOut &y, hipStream_t s) {
+  const OpDev &fo = C->fine;
+  const long long threads = 3LL * fo.nn[0] * ((fo.nn[1] - 1) / C->fac[1] + 1) * ((fo.nn[2] - 1) / C->fac[2] + 1) *
+                            (fo.M + 1);
+  hipLaunchKernelGGL(prolong_kernel, dim3(blocks_for(threads, 256), q), dim3(256), 0, s, fo, C->cop->d, C->fac[0],
+                     C->fac[1], C->fac[2], C->fac[3], xc, y);
+}
+
+// LDS of restrict_xy_kernel; planes that leave room for two workgroups per
+// compute unit go through it, larger ones axis by axis.
+static size_t restrict_xy_lds(const coarse *C) {
+  return sizeof(double) * 3 * (size_t)C->fine.nn[0] * (size_t)C->cop->d.nn[1];
+}
+constexpr size_t kRestrictXyLds = 64 * 1024;
+
+// elements of one vector between restrict_xy_kernel and restrict_zt_kernel
+static long long restrict_mid(const coarse *C) {
+  const OpDev &co = C->cop->d;
+  return 3LL * co.nn[0] * co.nn[1] * C->fine.nn[2] * (C->fine.M + 1);
 }
 
 // xc = (I_c^h)^T x, axis by axis (x, y, z, t; axes with factor 1 are skipped)
-static void restrict_transpose(const coarse *C, const double *x, double *xc, hipStream_t s) {
+static void restrict_axes(const coarse *C, const double *x, double *xc, hipStream_t s) {
   const OpDev &fo = C->fine;
   Dims4 dm{{fo.nn[0], fo.nn[1], fo.nn[2], fo.M + 1}};
   int axes[4], na = 0;
@@ -293,15 +331,42 @@ static void restrict_transpose(const coarse *C, const double *x, double *xc, hip
   STKKT_HIP(hipGetLastError());
 }
 
-// xc = I_h^c x: the transposed interpolation or injection
-static void restrict_to_coarse(const coarse *C, const double *x, double *xc, hipStream_t s) {
+// xc_i = (I_c^h)^T x_i for q <= kTransferVecs vectors; mid: q times
+// restrict_mid(C) doubles (not used when x and y are not coarsened)
+static void restrict_transpose(const coarse *C, int q, const VecsIn &x, const VecsOut &xc, double *mid,
+                               hipStream_t s) {
+  const OpDev &fo = C->fine, &co = C->cop->d;
+  const bool xy = C->fac[0] > 1 || C->fac[1] > 1;
+  const size_t lds = restrict_xy_lds(C);
+  const long long planes = (long long)fo.nn[2] * (fo.M + 1);
+  if ((xy && lds > kRestrictXyLds) || planes > INT32_MAX || (!xy && C->fac[2] == 1 && C->fac[3] == 1)) {
+    for (int i = 0; i < q; ++i) restrict_axes(C, x.p[i], xc.p[i], s);
+    return;
+  }
+  VecsIn from = x;
+  if (xy) {
+    const long long step = restrict_mid(C);
+    hipLaunchKernelGGL(restrict_xy_kernel, dim3((unsigned)planes, q), dim3(256), lds, s, fo.nn[0], fo.nn[1], C->fac[0],
+                       C->fac[1], x, mid, step);
+    for (int i = 0; i < q; ++i) from.p[i] = mid + i * step;
+  }
+  const int pl = 3 * co.nn[0] * co.nn[1];
+  hipLaunchKernelGGL(restrict_zt_kernel, dim3(blocks_for(3 * co.V, 256), q), dim3(256), 0, s, pl, fo.nn[2], fo.M + 1,
+                     C->fac[2], C->fac[3], from, xc);
+  STKKT_HIP(hipGetLastError());
+}
+
+// xc_i = I_h^c x_i: the transposed interpolation or injection
+static void restrict_to_coarse(const coarse *C, int q, const VecsIn &x, const VecsOut &xc, double *mid,
+                               hipStream_t s) {
   if (C->params.restrict_kind == STKKT_RESTRICT_INJECTION) {
     const OpDev &fo = C->fine, &co = C->cop->d;
-    hipLaunchKernelGGL(inject_kernel, dim3(blocks_for(co.V, 256, 8192)), dim3(256), 0, s, fo, co, C->fac[0],
-                       C->fac[1], C->fac[2], C->fac[3], x, xc);
+    for (int i = 0; i < q; ++i)
+      hipLaunchKernelGGL(inject_kernel, dim3(blocks_for(co.V, 256, 8192)), dim3(256), 0, s, fo, co, C->fac[0],
+                         C->fac[1], C->fac[2], C->fac[3], x.p[i], xc.p[i]);
     STKKT_HIP(hipGetLastError());
   } else {
-    restrict_transpose(C, x, xc, s);
+    restrict_transpose(C, q, x, xc, mid, s);
   }
 }
 
@@ -392,8 +457,8 @@ coarse *coarse_create(const kkt_op *fine, const coarse_params_t *cp, hipStream_t
 }
 
 void coarse_apply_device(const coarse *C, const double *x, double *y, hipStream_t s) {
-  const OpDev &fo = C->fine, &co = C->cop->d;
-  restrict_to_coarse(C, x, C->xc.as<double>(), s);
+  const OpDev &co = C->cop->d;
+  restrict_to_coarse(C, 1, VecsIn{{x}}, VecsOut{{C->xc.as<double>()}}, C->rt[0].as<double>(), s);
   if (C->lu) {
     const long long nvc = 3 * co.V;
     if (C->lu->one_vector_on_mfma()) C->lu->solve_multi(1, C->xc.as<double>(), nvc, C->yc.as<double>(), nvc, s);
@@ -410,7 +475,7 @@ void coarse_apply_device(const coarse *C, const double *x, double *y, hipStream_
                                C->work.get());
     if (st != STKKT_OK && st != STKKT_NOT_CONVERGED) throw Error(st, "coarse solve failed");
   }
-  prolong(C, C->yc.as<double>(), y, s);
+  prolong(C, 1, VecsIn{{C->yc.as<double>()}}, VecsOut{{y}}, s);
   STKKT_HIP(hipGetLastError());
 }
 
@@ -420,18 +485,36 @@ void coarse_apply_multi_device(const coarse *C, int q, const double *const *x, d
     for (int i = 0; i < q; ++i) coarse_apply_device(C, x[i], y[i], s);
     return;
   }
-  const OpDev &fo = C->fine, &co = C->cop->d;
-  const long long nvc = 3 * co.V;
+  const long long nvc = 3 * C->cop->d.V;
   if (q > C->mcap) {
     STKKT_HIP(hipStreamSynchronize(s));   // launches already queued may still use the old vectors
     C->xcm = DevBuf(&C->al, sizeof(double) * (size_t)nvc * q);
     C->ycm = DevBuf(&C->al, sizeof(double) * (size_t)nvc * q);
+    C->midm = DevBuf(&C->al, sizeof(double) * (size_t)restrict_mid(C) * std::min(q, kTransferVecs));
     C->mcap = q;
   }
   double *xc = C->xcm.as<double>(), *yc = C->ycm.as<double>();
-  for (int i = 0; i < q; ++i) restrict_to_coarse(C, x[i], xc + i * nvc, s);
+  for (int i0 = 0; i0 < q; i0 += kTransferVecs) {
+    const int m = std::min(kTransferVecs, q - i0);
+    VecsIn in{};
+    VecsOut out{};
+    for (int i = 0; i < m; ++i) {
+      in.p[i] = x[i0 + i];
+      out.p[i] = xc + (i0 + i) * nvc;
+    }
+    restrict_to_coarse(C, m, in, out, C->midm.as<double>(), s);
+  }
   C->lu->solve_multi(q, xc, nvc, yc, nvc, s);
-  for (int i = 0; i < q; ++i) prolong(C, yc + i * nvc, y[i], s);
+  for (int i0 = 0; i0 < q; i0 += kTransferVecs) {
+    const int m = std::min(kTransferVecs, q - i0);
+    VecsIn in{};
+    VecsOut out{};
+    for (int i = 0; i < m; ++i) {
+      in.p[i] = yc + (i0 + i) * nvc;
+      out.p[i] = y[i0 + i];
+    }
+    prolong(C, m, in, out, s);
+  }
   STKKT_HIP(hipGetLastError());
 }
 
