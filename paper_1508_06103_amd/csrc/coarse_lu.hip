@@ -90,55 +90,100 @@ __global__ void coupling_cols_kernel(OpDev op, int n, int dt, int32_t *__restric
   }
 }
 
-// S = D_k (column-major), from the dt = 0 coupling rows
+// S = D_k (column-major, zero before), from the dt = 0 coupling rows: a thread
+// per coupling (a row's 81 place their values in 81 different columns, but for
+// those outside the mesh, which are 0 and leave no trace).
 __global__ void dense_from_rows_kernel(int nb, const int32_t *__restrict__ idx, const double *__restrict__ val,
                                        double *__restrict__ S) {
-  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nb; r += gridDim.x * blockDim.x)
-    for (int t = 0; t < 81; ++t) {
-      const double v = val[(long long)r * 81 + t];
-      if (v != 0.0) S[(long long)idx[(long long)r * 81 + t] * nb + r] += v;
-    }
-}
-
-// S(r, c) -= sum_t L(r, idx_t) E(idx_t, c)   (column-major S, E; L rows sparse)
-// A thread keeps one row's coupling entry for kSchurCols columns at a time, so
-// that the (index, value) tables are read once per eight columns instead of
-// once per column (they were three quarters of the bytes).
-constexpr int kSchurCols = 8;
-__global__ void __launch_bounds__(256) schur_update_kernel(int nb, const int32_t *__restrict__ idx,
-                                                           const double *__restrict__ val,
-                                                           const double *__restrict__ E, double *__restrict__ S) {
-  const int c0 = blockIdx.y * kSchurCols, nc = min(kSchurCols, nb - c0);
-  const double *Ec = E + (long long)c0 * nb;
-  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nb; r += gridDim.x * blockDim.x) {
-    double acc[kSchurCols];
-#pragma unroll
-    for (int q = 0; q < kSchurCols; ++q) acc[q] = 0.0;
-    const long long b = (long long)r * 81;
-    for (int t = 0; t < 81; ++t) {
-      const double v = val[b + t];
-      const int i = idx[b + t];
-#pragma unroll
-      for (int q = 0; q < kSchurCols; ++q) acc[q] += v * Ec[(long long)(q < nc ? q : 0) * nb + i];
-    }
-#pragma unroll
-    for (int q = 0; q < kSchurCols; ++q)
-      if (q < nc) S[(long long)(c0 + q) * nb + r] -= acc[q];
+  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < 81 * nb; q += gridDim.x * blockDim.x) {
+    const double v = val[q];
+    if (v != 0.0) S[(long long)idx[q] * nb + q / 81] = v;
   }
 }
 
-// E(:, c) = sum_t Sinv(:, row_t) U(row_t, c), the rows of column c of U given
-// as (row index, value) pairs
-__global__ void e_from_cols_kernel(int nb, const int32_t *__restrict__ cidx, const double *__restrict__ cval,
-                                   const double *__restrict__ Sinv, double *__restrict__ E) {
-  const int c = blockIdx.y;
-  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nb; r += gridDim.x * blockDim.x) {
-    double acc = 0.0;
-    for (int t = 0; t < 81; ++t) {
-      const double v = cval[(long long)c * 81 + t];
-      if (v != 0.0) acc += v * Sinv[(long long)cidx[(long long)c * 81 + t] * nb + r];
+// the same couplings node by node, for kernels with a thread per node: first
+// unknown of neighbour k of node j at node[k N + j] (0 outside the mesh),
+// entry (a, b) of its block at val[(9 k + 3 b + a) N + j]
+__global__ void coupling_nodes_kernel(OpDev op, int n, int dt, int32_t *__restrict__ node, double *__restrict__ val) {
+  const int N = op.N;
+  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < 27 * N; q += gridDim.x * blockDim.x) {
+    const int k = q / N, j = q - k * N;
+    const int jx = j % op.nn[0], jy = (j / op.nn[0]) % op.nn[1], jz = j / (op.nn[0] * op.nn[1]);
+    const int dx = k % 3 - 1, dy = (k / 3) % 3 - 1, dz = k / 9 - 1;
+    const int ix = jx + dx, iy = jy + dy, iz = jz + dz;
+    const bool in = ix >= 0 && ix < op.nn[0] && iy >= 0 && iy < op.nn[1] && iz >= 0 && iz < op.nn[2];
+    double blk[9];
+    if (in) kkt_block(op, jx, jy, jz, n, dx, dy, dz, dt, blk);
+    node[q] = in ? 3 * (ix + op.nn[0] * (iy + op.nn[1] * iz)) : 0;
+    for (int b = 0; b < 3; ++b)
+      for (int a = 0; a < 3; ++a) val[(long long)(9 * k + 3 * b + a) * N + j] = in ? blk[3 * a + b] : 0.0;
+  }
+}
+
+// S(r, c) -= sum_t L(r, idx_t) E(idx_t, c)   (column-major S, E; L rows sparse)
+// A thread takes the three rows of a node, which have the same columns idx_t,
+// for kSchurCols columns of S at a time: an entry of E serves three products,
+// and the tables, laid out for it, are read once per eight columns.  With a
+// thread per row, each reading its own 81 table entries one after the other,
+// the kernel took 356 us at nb = 2187, now 121.
+constexpr int kSchurCols = 8;
+__global__ void __launch_bounds__(128) schur_update_kernel(int N, const int32_t *__restrict__ node,
+                                                           const double *__restrict__ val,
+                                                           const double *__restrict__ E, double *__restrict__ S) {
+  const int nb = 3 * N, c0 = blockIdx.y * kSchurCols, nc = min(kSchurCols, nb - c0);
+  const double *Ec = E + (long long)c0 * nb;
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= N) return;
+  double acc[3][kSchurCols];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int q = 0; q < kSchurCols; ++q) acc[a][q] = 0.0;
+  for (int k = 0; k < 27; ++k) {
+    const int i = node[k * N + j];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const double *v = val + (long long)(9 * k + 3 * b) * N + j;
+      const double v0 = v[0], v1 = v[N], v2 = v[2 * N];
+#pragma unroll
+      for (int q = 0; q < kSchurCols; ++q) {
+        const double x = Ec[(long long)(q < nc ? q : 0) * nb + i + b];
+        acc[0][q] += v0 * x;
+        acc[1][q] += v1 * x;
+        acc[2][q] += v2 * x;
+      }
     }
-    E[(long long)c * nb + r] = acc;
+  }
+#pragma unroll
+  for (int q = 0; q < kSchurCols; ++q)
+    if (q < nc)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) S[(long long)(c0 + q) * nb + 3 * j + a] -= acc[a][q];
+}
+
+// E(:, c) = sum_t Sinv(:, row_t) U(row_t, c), the rows of column c of U given
+// as (row index, value) pairs; the three columns of a node have the same rows,
+// so a thread forms the three entries of its row from one read of Sinv (a
+// thread per entry took 121 us at nb = 2187, this 72).
+__global__ void __launch_bounds__(256) e_from_cols_kernel(int nb, const int32_t *__restrict__ cidx,
+                                                          const double *__restrict__ cval,
+                                                          const double *__restrict__ Sinv, double *__restrict__ E) {
+  const int i = blockIdx.y;
+  const cptr<int32_t> idx = as_const(cidx) + 243LL * i;
+  const cptr<double> val = as_const(cval) + 243LL * i;
+  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nb; r += gridDim.x * blockDim.x) {
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+#pragma unroll 9
+    for (int t = 0; t < 81; ++t) {
+      const double x = Sinv[(long long)idx[t] * nb + r];
+      a0 += val[t] * x;
+      a1 += val[81 + t] * x;
+      a2 += val[162 + t] * x;
+    }
+    double *e = E + 3LL * i * nb + r;
+    e[0] = a0;
+    e[nb] = a1;
+    e[2LL * nb] = a2;
   }
 }
 
@@ -489,125 +534,177 @@ __global__ void gje_copy_rows_kernel(int n, int k, int e, const double *__restri
 // Trailing update outside the panel columns, a rank-(e - k) product:
 //   rows outside the panel:  A[i][col] += sum_t A[i][k+t] R[t][col]
 //   panel rows:              A[i][col]  = sum_t A[i][k+t] R[t][col]
-// for the columns in [cb, ce) outside [xb, xe) (the tiles of column blocks
-// ct0, ct0 + 1, ...), so that the next panel's columns can be updated first.
 // on the FP64 matrix cores (v_mfma_f64_16x16x4: lane l supplies a = A[l%16][l/16]
 // and b = B[l/16][l%16] and holds D[l/16 + 4r][l%16], r = 0..3).  A workgroup
-// of 8 wavefronts owns a 128 x 128 output tile; wavefront (wr, wc) a 64 x 32
-// part of it, as 4 x 2 blocks of 16 x 16.  The accumulators start from the
-// tile's current values (0 for panel rows), requested first so that their
-// latency overlaps the staging; the panel is taken in two passes of 32
-// columns, each staging the A panel slice (128 rows x 32, rows padded against
-// bank conflicts) and the R slice (32 x 128) in LDS.  About 67 KB of LDS and
-// at most 128 registers let two workgroups share a compute unit, one loading
-// while the other multiplies.
+// of 8 wavefronts owns a 64 x 128 output tile; wavefront (wr, wc) a 32 x 32
+// part of it, as 2 x 2 blocks of 16 x 16.  The accumulators start from the
+// tile's current values (0 for panel rows); the panel is taken in two passes of
+// 32 columns, each staging the A panel slice (64 rows x 32) and the R slice
+// (32 x 128) in LDS, padded so that a wavefront's operand read meets every bank
+// twice.  All of the tile's loads but the second pass's are requested together
+// and those before the first pass's products.  About 54 KB of LDS and at most
+// 128 registers let two workgroups share a compute unit.  A 128 x 128 tile
+// leaves 324 tiles on 256 compute units at n = 2187, so that some take two: 38
+// us for the whole update against 29.
+constexpr int kUpdRows = 64;
 constexpr int kUpdTile = 128;
 constexpr int kUpdThreads = 512;
 constexpr int kUpdK = 32;
-constexpr size_t kUpdLds = sizeof(double) * ((size_t)kUpdTile * (kUpdK + 1) + (size_t)kUpdK * kUpdTile);
+constexpr int kUpdLdA = kUpdK + 2, kUpdLdR = kUpdTile + 16;
+constexpr size_t kUpdLds = sizeof(double) * ((size_t)kUpdRows * kUpdLdA + (size_t)kUpdK * kUpdLdR);
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-__global__ void __launch_bounds__(kUpdThreads, 4) gje_update_kernel(int n, int k, int e, int cb, int ce, int xb,
-                                                                    int xe, int ct0, double *__restrict__ A,
-                                                                    const double *__restrict__ R) {
+// The tile at (row0, col0): out = A outside the panel rows, 0 inside them, plus
+// A[:][k + t] rrow(t)[:] over the panel, for the columns `mine` accepts; the
+// columns `copied` accepts go from A to out unchanged.  A may be out: a tile
+// then reads its own entries before it writes them, and no tile writes the
+// panel columns.
+template <typename Mine, typename Copied, typename Row>
+__device__ inline void update_tile(int n, int k, int e, int row0, int col0, const double *A, double *out, Mine mine,
+                                   Copied copied, Row rrow) {
   extern __shared__ double upd_lds[];
-  double(*As)[kUpdK + 1] = reinterpret_cast<double(*)[kUpdK + 1]>(upd_lds);              // [row][t]
-  double(*Rs)[kUpdTile] = reinterpret_cast<double(*)[kUpdTile]>(upd_lds + kUpdTile * (kUpdK + 1));   // [t][col]
-  const int row0 = blockIdx.y * kUpdTile, col0 = (ct0 + blockIdx.x) * kUpdTile;
-  // columns this launch updates
-  auto mine = [&](int col) {
-    return col >= cb && col < ce && col < n && !(col >= k && col < e) && !(col >= xb && col < xe);
-  };
+  double(*As)[kUpdLdA] = reinterpret_cast<double(*)[kUpdLdA]>(upd_lds);                        // [row][t]
+  double(*Rs)[kUpdLdR] = reinterpret_cast<double(*)[kUpdLdR]>(upd_lds + kUpdRows * kUpdLdA);   // [t][col]
   const int w = e - k;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave >> 2, wc = wave & 3;
   const int li = lane & 15, lk = lane >> 4;
-  f64x4 acc[4][2];
+  constexpr int kA = kUpdRows * kUpdK / kUpdThreads, kR = kUpdK * kUpdTile / kUpdThreads;
+  constexpr int kRowsA = kUpdThreads / kUpdK, kRowsR = kUpdThreads / kUpdTile;   // rows of one round of loads
+  double ra[kA], rr[kR];
+  const int at = tid % kUpdK, ar = tid / kUpdK, rc = tid % kUpdTile;
+  const int rt = __builtin_amdgcn_readfirstlane(tid / kUpdTile);   // a wavefront stays in one row
+  auto request = [&](int kb) {
 #pragma unroll
-  for (int bi = 0; bi < 4; ++bi)
+    for (int u = 0; u < kA; ++u) {
+      const int i = row0 + ar + u * kRowsA;
+      ra[u] = (i < n && kb + at < w) ? A[(long long)i * n + k + kb + at] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < kR; ++u) {
+      const int t = kb + rt + u * kRowsR, col = col0 + rc;
+      rr[u] = (t < w && col < n && !copied(col)) ? rrow(t)[col] : 0.0;
+    }
+  };
+  auto stage = [&]() {
+#pragma unroll
+    for (int u = 0; u < kA; ++u) As[ar + u * kRowsA][at] = ra[u];
+#pragma unroll
+    for (int u = 0; u < kR; ++u) Rs[rt + u * kRowsR][rc] = rr[u];
+  };
+  if (w > 0) request(0);
+  f64x4 acc[2][2];
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
     for (int bj = 0; bj < 2; ++bj) {
       const int col = col0 + wc * 32 + bj * 16 + li;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = row0 + wr * 64 + bi * 16 + lk + 4 * r;
-        const bool acc_row = i < n && !(i >= k && i < e) && mine(col);
+        const int i = row0 + wr * 32 + bi * 16 + lk + 4 * r;
+        const bool acc_row = i < n && mine(col) && (!(i >= k && i < e) || copied(col));
         acc[bi][bj][r] = acc_row ? A[(long long)i * n + col] : 0.0;
       }
     }
   for (int kb = 0; kb < w; kb += kUpdK) {
     if (kb > 0) __syncthreads();
-    for (int q = tid; q < kUpdTile * kUpdK; q += kUpdThreads) {
-      const int rr = q / kUpdK, t = q % kUpdK;
-      const int i = row0 + rr;
-      As[rr][t] = (i < n && kb + t < w) ? A[(long long)i * n + k + kb + t] : 0.0;
-      const int t2 = q / kUpdTile, cc = q % kUpdTile;
-      const int col = col0 + cc;
-      Rs[t2][cc] = (col < n && kb + t2 < w) ? R[(long long)(kb + t2) * n + col] : 0.0;
-    }
+    stage();
     __syncthreads();
-#pragma unroll 4
-    for (int t0 = 0; t0 < kUpdK; t0 += 4) {
-      double a[4], b[2];
+    if (kb + kUpdK < w) request(kb + kUpdK);
 #pragma unroll
-      for (int bi = 0; bi < 4; ++bi) a[bi] = As[wr * 64 + bi * 16 + li][t0 + lk];
+    for (int t0 = 0; t0 < kUpdK; t0 += 4) {
+      double a[2], b[2];
+#pragma unroll
+      for (int bi = 0; bi < 2; ++bi) a[bi] = As[wr * 32 + bi * 16 + li][t0 + lk];
 #pragma unroll
       for (int bj = 0; bj < 2; ++bj) b[bj] = Rs[t0 + lk][wc * 32 + bj * 16 + li];
 #pragma unroll
-      for (int bi = 0; bi < 4; ++bi)
+      for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
         for (int bj = 0; bj < 2; ++bj)
           acc[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[bi], b[bj], acc[bi][bj], 0, 0, 0);
     }
   }
 #pragma unroll
-  for (int bi = 0; bi < 4; ++bi)
+  for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
     for (int bj = 0; bj < 2; ++bj) {
       const int col = col0 + wc * 32 + bj * 16 + li;
       if (!mine(col)) continue;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = row0 + wr * 64 + bi * 16 + lk + 4 * r;
+        const int i = row0 + wr * 32 + bi * 16 + lk + 4 * r;
         if (i >= n) continue;
-        A[(long long)i * n + col] = acc[bi][bj][r];
+        out[(long long)i * n + col] = acc[bi][bj][r];
       }
     }
 }
 
-// Panel elimination with the pivots searched among the panel's own rows
-// (block pivoting).  The Schur blocks of the coarse solve need no row
-// exchanges across panels: with the pivots restricted to each 64-row
-// diagonal block the inverse agrees with partial pivoting over all rows to
-// about 1e-14 (and with LAPACK's inverse), so a panel needs no device-wide
-// exchange per column, and one launch takes it from the previous panel's
-// state to its multipliers.  Workgroup g (eight wavefronts) owns the 64 rows
-// [64 g, 64 g + 64) and, for the panel K = [k, e), w = e - k <= 64:
-//  1. brings its rows' panel columns and, redundantly, the diagonal block
-//     D = A[K][K] up to date with the previous panel [kp, ep) (none when
-//     kp == ep): two 64 x 64 x 64 products on the matrix cores;
-//  2. inverts D: lane r holds row r, wavefront v the columns 8 v .. 8 v + 7 in
-//     registers.  Step j: the wavefront that holds column j takes the pivot
-//     row p among the rows not yet used (a lane reduction over the leading 25
-//     bits of |entry|, so a pivot is at least 1 - 2^-13 of the largest), puts
-//     the column and 1 / pivot in LDS, and after one barrier every wavefront
-//     updates its own eight columns.  Rows are not exchanged: row p_j of the
-//     result is row j of (P D)^{-1}, P the order of the pivots;
-//  3. writes -(its panel segment) (P D)^{-1} into A (one more product).
-// Every workgroup inverts the same block to the same bits; workgroup 0 also
-// writes the inverse to Dinv, the pivot rows to perm and the panel's entries
-// of piv.  Rows K of A keep the old block until gje_take_rows_kernel, since
-// the other workgroups read it.  A zero or non-finite pivot sets status 1.
+__global__ void __launch_bounds__(kUpdThreads, 4) gje_update_kernel(int n, int k, int e, int cb, int ce, int xb,
+                                                                    int xe, int ct0, double *A,
+                                                                    const double *__restrict__ R) {
+  // columns this launch updates
+  auto mine = [&](int col) {
+    return col >= cb && col < ce && col < n && !(col >= k && col < e) && !(col >= xb && col < xe);
+  };
+  update_tile(n, k, e, (int)blockIdx.y * kUpdRows, (ct0 + (int)blockIdx.x) * kUpdTile, A, A, mine,
+              [](int) { return false; }, [&](int t) { return R + (long long)t * n; });
+}
+
+// Elimination with the pivots searched among each panel's own rows (block
+// pivoting).  The Schur blocks of the coarse solve need no row exchanges
+// across panels: with the pivots restricted to each 64-row diagonal block the
+// inverse agrees with partial pivoting over all rows to about 1e-14 (and with
+// LAPACK's inverse), so a panel needs no device-wide exchange per column, and
+// one launch takes the matrix from panel to panel.  It reads `O` and writes
+// `N` (the two exchange their places for the next launch, so that nothing it
+// reads is overwritten and the panel's rows need no copy of their own):
 //
-// The 64 pivot steps are a serial chain and bound the kernel.  With the block
-// in LDS (five barriers a step) and a launch each for the inversion and the
-// multipliers the chain took 145 + 18 us at n = 2187, after 30 us of update
-// and 16 us of row exchanges; see gje_invert for the whole panel.
+// The first npan workgroups take the panel K = [k, e), w = e - k <= 64, to its
+// multipliers.  Workgroup g (eight wavefronts) owns the rows [64 g, 64 g + 64):
+//  1. brings the diagonal block D = O[K][K] (each workgroup for itself) and its
+//     own rows' panel columns up to date with the previous panel [kp, ep) (none
+//     when kp == ep): two 64 x 64 x 64 products on the matrix cores, with all
+//     their loads requested up front;
+//  2. inverts D in LDS, sixteen columns at a time: the first wavefront holds
+//     them in registers (lane r: row r).  Step j takes the pivot row p of column
+//     j among the rows not yet used (a lane reduction over the leading 25 bits
+//     of |entry|, so a pivot is at least 1 - 2^-13 of the largest) and
+//     eliminates column j from its sixteen columns.  All wavefronts then bring
+//     the other 48 columns up to date with a rank-16 product.  Rows are not
+//     exchanged: row p_j of the result is row j of (P D)^{-1}, P the order of
+//     the pivots;
+//  3. writes -(its panel segment) (P D)^{-1} into N (one more product), the
+//     workgroup that owns K (P D)^{-1} itself, and perm and the panel's
+//     entries of piv.
+// Every workgroup inverts the same block to the same bits.  A zero or
+// non-finite pivot sets status 1, and later launches do nothing.
+//
+// The other workgroups update the tiles of all columns outside K by the
+// previous panel, whose rows are read in the order of its pivots (permp); its
+// own columns are copied.
+//
+// The 64 pivot steps are a serial chain and bound the launch: 0.3 us a step,
+// 25 of the panel's 37 us at n = 2187 (8 us for the loads and products before
+// them); the launch takes 43 us, the update's tiles beside the panel.  Held in
+// one wavefront's registers a step needs no barrier and no LDS.  Spread over
+// the eight wavefronts, with launches of their own for the update (on a second
+// stream) and for the panel's rows, a panel took 81 us; with the own rows'
+// operands staged in LDS after the diagonal block's, the loads took 16 us.
 constexpr int kBpThreads = 512;
-constexpr int kBpCols = kPanel / (kBpThreads / 64);   // columns per wavefront
+constexpr int kBpCols = 16;   // columns eliminated in one wavefront's registers
 constexpr int kBpLd = kPanel + 1;
-constexpr size_t kBpLds = sizeof(double) * 3 * (size_t)kPanel * kBpLd;
+constexpr size_t kBpLds = sizeof(double) * 2 * (size_t)kPanel * kBpLd;
+// LDS of a launch.  While the update is hidden beside the panel, the panel's
+// workgroups get compute units of their own (more than half of the LDS each):
+// n = 2187 (630 tiles) 52.0 us a panel against 53.1 with two workgroups per
+// compute unit, which wait for each other's matrix instructions.  Where the
+// update takes longer than the panel two are better: n = 3993 (2016 tiles) 93
+// against 111 us.
+constexpr size_t kStepLdsTwo = kBpLds > kUpdLds ? kBpLds : kUpdLds, kStepLdsOne = 84 * 1024;
+constexpr int kStepOneTiles = 3 * 256;
+static_assert(kBpThreads == kUpdThreads, "one launch holds both kinds of workgroup");
 
 // largest value over the wavefront's lanes
 __device__ inline unsigned wave_max_u32(unsigned v) {
@@ -640,45 +737,77 @@ __device__ inline void bp_product(const double *X, const double *Y, f64x4 (&acc)
   }
 }
 
-__global__ void __launch_bounds__(kBpThreads) gje_block_panel_kernel(int n, int kp, int ep, int k, int e,
-                                                                     double *__restrict__ A,
-                                                                     const double *__restrict__ Rp,
-                                                                     double *__restrict__ Dinv,
-                                                                     int32_t *__restrict__ perm,
-                                                                     int32_t *__restrict__ piv,
-                                                                     int *__restrict__ status) {
-  extern __shared__ double bp_lds[];
-  __shared__ double fcol[2][kPanel], pinv[2];
-  __shared__ int prow[2];
-  if (*status) return;
-  double *So = bp_lds, *Sd = So + kPanel * kBpLd, *Sr = Sd + kPanel * kBpLd;
+__device__ inline void panel_rows_step(int n, int kp, int ep, int k, int e, const double *__restrict__ O,
+                                       double *__restrict__ N, const int32_t *__restrict__ permp,
+                                       int32_t *__restrict__ perm, int32_t *__restrict__ piv,
+                                       int *__restrict__ status) {
+  extern __shared__ double upd_lds[];
+  __shared__ int step_of[kPanel], row_of[kPanel];   // the step that took a row as its pivot row, and the reverse
+  double *Sa = upd_lds, *Sb = Sa + kPanel * kBpLd;
   const int w = e - k, wp = ep - kp;
   const int tid = (int)threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4, bi = wv >> 1, bj = 2 * (wv & 1);
   const int i0 = (int)blockIdx.x * kPanel;
-  // 1. own panel segment and diagonal block.  An entry (row, col) of a
-  // wavefront's blocks sits in register r of lane (li, lk): row 16 bi + lk + 4 r,
-  // column 16 (bj + u) + li.
-  f64x4 own[2], dia[2];
+  __builtin_amdgcn_s_setprio(3);   // ahead of the tiles that share the compute unit
+  // 1. An entry (row, col) of a 16 x 16 block (br, bc) sits in register r of
+  // lane (li, lk): row 16 br + lk + 4 r, column 16 bc + li.
+  constexpr int kPer = kPanel * kPanel / kBpThreads, kBpWaves = kBpThreads / 64;
+  // (a panel with a successor has 64 columns: wp is 0 or 64)
+  // loads by 32-bit byte offsets from a row's start, clamped into the matrix
+  auto at = [n](const double *base, int row, int col) {
+    return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(base) +
+                                             (unsigned)sizeof(double) * (unsigned)(row * n + col));
+  };
+  if (wp > 0) {
+    const cptr<int32_t> pp = as_const(permp);
+    double d[kPer], x[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {   // a wavefront takes whole rows
+      const int a = wv + u * kBpWaves;
+      d[u] = at(O + (long long)k * n + kp, min(a, w - 1), lane);
+      x[u] = at(O + (long long)kp * n + k, pp[a], min(lane, w - 1));
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int a = wv + u * kBpWaves;
+      Sb[a * kBpLd + lane] = a < w ? d[u] : 0.0;
+      Sa[a * kBpLd + lane] = lane < w ? x[u] : 0.0;
+    }
+  }
+  f64x4 dia[2];
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int q = 16 * bi + lk + 4 * r, c = 16 * (bj + u) + li, i = i0 + q;
-      own[u][r] = (i < n && c < w && !(i >= kp && i < ep)) ? A[(long long)i * n + k + c] : 0.0;
-      dia[u][r] = (q < w && c < w) ? A[(long long)(k + q) * n + k + c] : (q == c ? 1.0 : 0.0);
+      const int q = 16 * bi + lk + 4 * r, c = 16 * (bj + u) + li;
+      const double v = at(O + (long long)k * n + k, min(q, w - 1), min(c, w - 1));
+      dia[u][r] = q < w && c < w ? v : q == c ? 1.0 : 0.0;
+    }
+  // own rows: the panel's columns, and the previous panel's as operands
+  const int rlast = n - 1 - i0;
+  double oa[kPanel / 4];
+  f64x4 own[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int c = 16 * (bj + u) + li;
+      const double v = at(O + (long long)i0 * n + k, min(16 * bi + lk + 4 * r, rlast), min(c, w - 1));
+      own[u][r] = c < w && !(wp > 0 && i0 == kp) ? v : 0.0;   // the previous panel's rows start from 0
     }
   if (wp > 0) {
-    for (int q = tid; q < kPanel * kPanel; q += kBpThreads) {
-      const int a = q / kPanel, b = q % kPanel;
-      So[a * kBpLd + b] = (i0 + a < n && b < wp) ? A[(long long)(i0 + a) * n + kp + b] : 0.0;
-      Sd[a * kBpLd + b] = (a < w && b < wp) ? A[(long long)(k + a) * n + kp + b] : 0.0;
-      Sr[a * kBpLd + b] = (a < wp && b < w) ? Rp[(long long)a * n + k + b] : 0.0;
-    }
+#pragma unroll
+    for (int t = 0; t < kPanel / 4; ++t)
+      oa[t] = at(O + (long long)i0 * n + kp, min(16 * bi + li, rlast), 4 * t + lk);
     __syncthreads();
-    bp_product(So, Sr, own);
-    bp_product(Sd, Sr, dia);
+    bp_product(Sb, Sa, dia);
+#pragma unroll
+    for (int t = 0; t < kPanel / 4; ++t)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        own[u] =
+            __builtin_amdgcn_mfma_f64_16x16x4f64(oa[t], Sa[(4 * t + lk) * kBpLd + 16 * (bj + u) + li], own[u], 0, 0, 0);
     __syncthreads();
   }
 #pragma unroll
@@ -686,51 +815,95 @@ __global__ void __launch_bounds__(kBpThreads) gje_block_panel_kernel(int n, int 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int q = 16 * bi + lk + 4 * r, c = 16 * (bj + u) + li;
-      So[q * kBpLd + c] = own[u][r];
-      Sd[q * kBpLd + c] = dia[u][r];
+      Sa[q * kBpLd + c] = own[u][r];
+      Sb[q * kBpLd + c] = dia[u][r];
     }
   __syncthreads();
   // 2. (P D)^{-1}; rows and columns past w are those of the identity
-  double m[kBpCols];
+  int myq = -1;   // (first wavefront) the step that took this lane's row as its pivot row
+  if (wv == 0) step_of[lane] = -1;
+#pragma unroll 1
+  for (int b0 = 0; b0 < kPanel; b0 += kBpCols) {
+    if (wv == 0) {
+      double m[kBpCols];
 #pragma unroll
-  for (int c = 0; c < kBpCols; ++c) m[c] = Sd[lane * kBpLd + kBpCols * wv + c];
-  int myq = -1;   // the step that took this lane's row as its pivot row
-  for (int jb = 0; jb < kBpThreads / 64; ++jb) {
+      for (int c = 0; c < kBpCols; ++c) m[c] = Sb[lane * kBpLd + b0 + c];
 #pragma unroll
-    for (int jj = 0; jj < kBpCols; ++jj) {
-      const int par = jj & 1;
-      if (wv == jb) {
+      for (int jj = 0; jj < kBpCols; ++jj) {
         const unsigned hi = (unsigned)__double2hiint(m[jj]) & 0x7fffffffu;
         const unsigned key = myq >= 0 ? 0u : (hi & ~127u) | 64u | (unsigned)(63 - lane);
         const int p = 63 - (int)(wave_max_u32(key) & 63u);
-        const double a = lane_value(m[jj], p);
-        fcol[par][lane] = m[jj];
-        if (lane == 0) {
-          prow[par] = p;
-          pinv[par] = 1.0 / a;
-          if (!(fabs(a) > 0.0) || !std::isfinite(a)) *status = 1;
+        const double a = lane_value(m[jj], p), inv = 1.0 / a;
+        if (lane == 0 && (!(fabs(a) > 0.0) || !std::isfinite(a))) *status = 1;
+        const bool isp = lane == p;
+        const double g = isp ? inv : -m[jj] * inv;
+        if (isp) myq = b0 + jj;
+#pragma unroll
+        for (int u = 1; u < kBpCols; ++u) {   // column jj + 1 first: the next step waits for it
+          const int c = (jj + u) % kBpCols;
+          const double x = lane_value(m[c], p);
+          m[c] = __builtin_fma(g, x, isp ? 0.0 : m[c]);
         }
+        m[jj] = g;
       }
-      __syncthreads();
-      const int p = __builtin_amdgcn_readfirstlane(prow[par]);
-      const double inv = pinv[par], f = fcol[par][lane];
-      const bool isp = lane == p;
 #pragma unroll
-      for (int c = 0; c < kBpCols; ++c) {
-        const double pr = lane_value(m[c], p) * inv;
-        const double v = isp ? pr : m[c] - f * pr;
-        m[c] = (c == jj && wv == jb) ? (isp ? inv : -f * inv) : v;
+      for (int c = 0; c < kBpCols; ++c) Sb[lane * kBpLd + b0 + c] = m[c];
+      if (myq >= b0) {
+        step_of[lane] = myq;
+        row_of[myq] = lane;
       }
-      if (isp) myq = kBpCols * jb + jj;
     }
-  }
+    __syncthreads();
+    // the other column blocks: 4 x 3 tiles of 16 x 16 on eight wavefronts
+    f64x4 t[2];
+    auto tile = [&](int u, int &br, int &bc) {
+      const int q = wv + 8 * u;
+      br = q & 3;
+      bc = q >> 2;
+      bc += bc >= b0 / kBpCols;
+      return q < 12;
+    };
 #pragma unroll
-  for (int c = 0; c < kBpCols; ++c) Sr[myq * kBpLd + kBpCols * wv + c] = m[c];
+    for (int u = 0; u < 2; ++u) {
+      int br, bc;
+      if (!tile(u, br, bc)) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * br + lk + 4 * r;
+        t[u][r] = step_of[row] >= b0 ? 0.0 : Sb[row * kBpLd + 16 * bc + li];
+      }
+#pragma unroll
+      for (int s0 = 0; s0 < kBpCols; s0 += 4)
+        t[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(Sb[(16 * br + li) * kBpLd + b0 + s0 + lk],
+                                                    Sb[row_of[b0 + s0 + lk] * kBpLd + 16 * bc + li], t[u], 0, 0, 0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      int br, bc;
+      if (!tile(u, br, bc)) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) Sb[(16 * br + lk + 4 * r) * kBpLd + 16 * bc + li] = t[u][r];
+    }
+    __syncthreads();
+  }
+  {
+    // the rows in the order of the pivots
+    double v[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) v[u] = Sb[lane * kBpLd + kPer * wv + u];
+    const int q = max(step_of[lane], 0);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) Sb[q * kBpLd + kPer * wv + u] = v[u];
+  }
   __syncthreads();
-  if (blockIdx.x == 0) {
+  // 3. the multipliers; panels and row groups are both 64 wide, so one
+  // workgroup owns exactly the panel's rows
+  if (i0 == k) {
     for (int q = tid; q < kPanel * kPanel; q += kBpThreads) {
       const int a = q / kPanel, b = q % kPanel;
-      Dinv[q] = Sr[a * kBpLd + b];
+      if (a < w && b < w) N[(long long)(k + a) * n + k + b] = Sb[a * kBpLd + b];
     }
     if (wv == 0) {
       const bool real = lane < w && myq >= 0 && myq < w;   // (a row past w is a pivot row of a singular block only)
@@ -740,37 +913,37 @@ __global__ void __launch_bounds__(kBpThreads) gje_block_panel_kernel(int n, int 
         perm[myq] = lane;
       }
     }
+    return;
   }
-  // 3. the multipliers
-  if (i0 == k) return;   // the panel's own rows (panels and row groups are both 64 wide)
 #pragma unroll
-  for (int u = 0; u < 2; ++u) own[u] = f64x4{0.0, 0.0, 0.0, 0.0};
-  bp_product(So, Sr, own);
+  for (int u = 0; u < 2; ++u) dia[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+  bp_product(Sa, Sb, dia);
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = i0 + 16 * bi + lk + 4 * r, c = 16 * (bj + u) + li;
-      if (i < n && c < w) A[(long long)i * n + k + c] = -own[u][r];
+      if (i < n && c < w) N[(long long)i * n + k + c] = -dia[u][r];
     }
 }
 
-// The panel's rows in the order of its pivots, R[j][col] = A[k + perm[j]][col]
-// outside the panel columns, and the diagonal block's inverse into A[K][K].
-__global__ void gje_take_rows_kernel(int n, int k, int e, double *__restrict__ A, const double *__restrict__ Dinv,
-                                     const int32_t *__restrict__ perm, double *__restrict__ R,
-                                     const int *__restrict__ status) {
-  if (*status) return;   // perm is then incomplete
-  const int j = blockIdx.y;
-  const double *src = A + (long long)(k + perm[j]) * n;
-  for (int col = blockIdx.x * blockDim.x + threadIdx.x; col < n; col += gridDim.x * blockDim.x) {
-    if (col >= k && col < e) {
-      R[(long long)j * n + col] = 0.0;
-      A[(long long)(k + j) * n + col] = Dinv[j * kPanel + col - k];
-    } else {
-      R[(long long)j * n + col] = src[col];
-    }
+__global__ void __launch_bounds__(kBpThreads, 4) gje_block_step_kernel(int n, int npan, int kp, int ep, int k, int e,
+                                                                       const double *__restrict__ O,
+                                                                       double *__restrict__ N,
+                                                                       const int32_t *__restrict__ permp,
+                                                                       int32_t *__restrict__ perm,
+                                                                       int32_t *__restrict__ piv,
+                                                                       int *__restrict__ status) {
+  if (*status) return;   // permp is then incomplete
+  if ((int)blockIdx.x < npan) {
+    panel_rows_step(n, kp, ep, k, e, O, N, permp, perm, piv, status);
+    return;
   }
+  const int nt = (n + kUpdTile - 1) / kUpdTile, t = (int)blockIdx.x - npan;
+  update_tile(n, kp, ep, (t / nt) * kUpdRows, (t % nt) * kUpdTile, O, N,
+              [&](int col) { return col < n && !(col >= k && col < e); },
+              [&](int col) { return col >= kp && col < ep; },
+              [&](int a) { return O + (long long)(kp + permp[a]) * n; });
 }
 
 // out[i][piv[j]] = A[i][j]
@@ -1097,32 +1270,33 @@ struct LookAhead {
   LookAhead &operator=(const LookAhead &) = delete;
 };
 
-// Explicit inverse of the n x n row-major matrix in A (overwritten with the
-// inverse).  tmp: n x n scratch; rows: 2 x kPanel x n scratch (the rows of
-// two consecutive panels); pan: kPanel x n scratch (the launch-per-column
-// path's panel; with block pivoting its first kPanel x kPanel doubles hold the
-// diagonal block's inverse and swp the order of its pivots); piv: n int32; gs: candidate tables for
-// ceil(n / 64) workgroups; la: the look-ahead's side stream and events.
-static void gje_invert(int n, double *A, double *tmp, double *rows, double *pan, double *fcol, int32_t *piv,
+// Explicit inverse of the n x n row-major matrix in A; the inverse ends in A or
+// in tmp, n x n scratch (the pointer returned), the other is overwritten.
+// rows: 2 x kPanel x n scratch (the rows of two consecutive panels); pan:
+// kPanel x n scratch (the launch-per-column path's panel); swp: 2 kPanel int32
+// (with block pivoting the pivot orders of two consecutive panels); piv: n
+// int32; gs: candidate tables for ceil(n / 64) workgroups; la: the look-ahead's
+// side stream and events.
+static double *gje_invert(int n, double *A, double *tmp, double *rows, double *pan, double *fcol, int32_t *piv,
                        int32_t *swp, double *prow, const GjSync &gs, int *status, const LookAhead &la,
                        hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
     STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&gje_update_kernel),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kUpdLds));
-    STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&gje_block_panel_kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBpLds));
+    STKKT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&gje_block_step_kernel),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStepLdsOne));
     attr_set = true;
   }
   const bool block = block_pivoting();
   const int R = block ? 0 : panel_rows(n);
   hipLaunchKernelGGL(iota_kernel, dim3(blocks_for(n, 256, 64)), dim3(256), 0, s, n, piv);
   if (R > 0) hipLaunchKernelGGL(gj_reset_kernel, dim3(1), dim3(64), 0, s, gs);
-  const int nt = (n + kUpdTile - 1) / kUpdTile;
+  const int nt = (n + kUpdTile - 1) / kUpdTile, mt = (n + kUpdRows - 1) / kUpdRows;   // tiles
   // rank-(e - k) update of the columns [cb, ce) outside [xb, xe) on stream st
   auto update = [&](int k, int e, int cb, int ce, int xb, int xe, const double *Rk, hipStream_t st) {
     const int t0 = cb / kUpdTile, t1 = (ce + kUpdTile - 1) / kUpdTile;
-    hipLaunchKernelGGL(gje_update_kernel, dim3(t1 - t0, nt), dim3(kUpdThreads), kUpdLds, st, n, k, e, cb, ce, xb, xe,
+    hipLaunchKernelGGL(gje_update_kernel, dim3(t1 - t0, mt), dim3(kUpdThreads), kUpdLds, st, n, k, e, cb, ce, xb, xe,
                        t0, A, Rk);
   };
   // the panel's swaps on the other columns, then its rows into Rk
@@ -1131,37 +1305,20 @@ static void gje_invert(int n, double *A, double *tmp, double *rows, double *pan,
     hipLaunchKernelGGL(gje_copy_rows_kernel, dim3(blocks_for(n, 256, 64), e - k), dim3(256), 0, s, n, k, e, A, Rk);
   };
   if (block) {
-    // Two launches per panel on s: the panel (with the previous panel's update
-    // of its columns) and, once the side stream has finished the previous
-    // panel's update of all other columns, its rows.  The update by the panel
-    // then runs on the side stream beside the next panel's launch, which
-    // touches none of its columns.
-    auto panel = [&](int kp, int ep, int k, int e, const double *Rp) {
-      hipLaunchKernelGGL(gje_block_panel_kernel, dim3((n + kPanel - 1) / kPanel), dim3(kBpThreads), kBpLds, s, n, kp,
-                         ep, k, e, A, Rp, pan, swp, piv, status);
-    };
-    auto take_rows = [&](int k, int e, double *Rk) {
-      hipLaunchKernelGGL(gje_take_rows_kernel, dim3(blocks_for(n, 256, 64), e - k), dim3(256), 0, s, n, k, e, A, pan,
-                         swp, Rk, status);
-    };
-    panel(0, 0, 0, std::min(n, kPanel), rows);
-    take_rows(0, std::min(n, kPanel), rows);
-    for (int k = 0, p = 0; k < n; k += kPanel, ++p) {
-      const int e = std::min(n, k + kPanel);
-      double *Rk = rows + (size_t)(p & 1) * kPanel * n;
-      if (e >= n) {
-        update(k, e, 0, n, 0, 0, Rk, s);
-        break;
-      }
-      const int e2 = std::min(n, e + kPanel);
-      STKKT_HIP(hipEventRecord(la.rows_ready, s));
-      STKKT_HIP(hipStreamWaitEvent(la.side, la.rows_ready, 0));
-      update(k, e, 0, n, e, e2, Rk, la.side);
-      STKKT_HIP(hipEventRecord(la.rest_done, la.side));
-      panel(k, e, e, e2, Rk);
-      STKKT_HIP(hipStreamWaitEvent(s, la.rest_done, 0));
-      take_rows(e, e2, rows + (size_t)((p + 1) & 1) * kPanel * n);
+    // One launch per panel: the previous panel's update beside the panel.  The
+    // first only copies beside panel 0, the last only updates.
+    double *from = A, *to = tmp;
+    for (int k = 0, kp = 0, p = 0; kp < n; ++p) {
+      const int e = std::min(n, k + kPanel), npan = k < n ? (n + kPanel - 1) / kPanel : 0;
+      const size_t lds = mt * nt <= kStepOneTiles ? kStepLdsOne : kStepLdsTwo;
+      hipLaunchKernelGGL(gje_block_step_kernel, dim3(npan + mt * nt), dim3(kBpThreads), lds, s, n, npan, kp, k, k, e,
+                         from, to, swp + ((p + 1) & 1) * kPanel, swp + (p & 1) * kPanel, piv, status);
+      std::swap(from, to);
+      kp = k;
+      k = e;
     }
+    A = from;
+    tmp = to;
   } else if (R > 0) {
     // Elimination of each panel in one cooperative launch with a look-ahead:
     // the update by panel p first brings the next panel's columns up to date,
@@ -1216,7 +1373,7 @@ static void gje_invert(int n, double *A, double *tmp, double *rows, double *pan,
   }
   hipLaunchKernelGGL(gje_unpermute_kernel, dim3(blocks_for(n, 256, 64), n), dim3(256), 0, s, n, A, piv, tmp);
   STKKT_HIP(hipGetLastError());
-  STKKT_HIP(hipMemcpyAsync(A, tmp, sizeof(double) * (size_t)n * n, hipMemcpyDeviceToDevice, s));
+  return tmp;
 }
 
 CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStream_t s) : prec_(precision) {
@@ -1244,7 +1401,7 @@ CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStr
   // setup work buffers (FP64)
   DevBuf S(al, sizeof(double) * nn), Ed(al, sizeof(double) * nn),
       tmp(al, sizeof(double) * nn), rows(al, sizeof(double) * 2 * (size_t)kPanel * nb_), piv(al, sizeof(int32_t) * nb_),
-      prow(al, sizeof(double) * kPanel), swp(al, sizeof(int32_t) * kPanel), pan(al, sizeof(double) * kPanel * nb_),
+      prow(al, sizeof(double) * kPanel), swp(al, sizeof(int32_t) * 2 * kPanel), pan(al, sizeof(double) * kPanel * nb_),
       fcol(al, sizeof(double) * nb_),
       status(al, 256), ridx(al, sizeof(int32_t) * (size_t)nb_ * 81), rval(al, sizeof(double) * (size_t)nb_ * 81),
       cidx(al, sizeof(int32_t) * (size_t)nb_ * 81), cval(al, sizeof(double) * (size_t)nb_ * 81);
@@ -1260,7 +1417,7 @@ CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStr
                   bar.as<unsigned>(), reinterpret_cast<int *>(bar.as<unsigned char>() + 128), spin};
   STKKT_HIP(hipMemsetAsync(status.ptr, 0, sizeof(int), s));
   const int G = blocks_for(27LL * d.N, 128, 4096);
-  const dim3 g2(blocks_for(nb_, 256, 64), nb_);
+  const dim3 g2(blocks_for(nb_, 256, 64), d.N);
   const LookAhead la;
   for (int k = 0; k < nlev_; ++k) {
     // lower coupling of level k (to level k-1), kept for the application
@@ -1271,34 +1428,38 @@ CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStr
     fill_zero(S.as<double>(), (long long)nn, s);
     hipLaunchKernelGGL(coupling_rows_kernel, dim3(G), dim3(128), 0, s, d, k, 0, ridx.as<int32_t>(),
                        rval.as<double>());
-    hipLaunchKernelGGL(dense_from_rows_kernel, dim3(blocks_for(nb_, 256, 64)), dim3(256), 0, s, nb_,
+    hipLaunchKernelGGL(dense_from_rows_kernel, dim3(blocks_for(81LL * nb_, 256, 4096)), dim3(256), 0, s, nb_,
                        ridx.as<int32_t>(), rval.as<double>(), S.as<double>());
-    if (k > 0)
-      hipLaunchKernelGGL(schur_update_kernel, dim3(blocks_for(nb_, 256, 64), (nb_ + kSchurCols - 1) / kSchurCols),
-                         dim3(256), 0, s, nb_, Lk_idx, Lk_val, Ed.as<double>(),
-                         S.as<double>());
+    if (k > 0) {
+      // the level's couplings once more, in the tables of its D_k (used up by now)
+      hipLaunchKernelGGL(coupling_nodes_kernel, dim3(G), dim3(128), 0, s, d, k, -1, ridx.as<int32_t>(),
+                         rval.as<double>());
+      hipLaunchKernelGGL(schur_update_kernel, dim3((d.N + 127) / 128, (nb_ + kSchurCols - 1) / kSchurCols), dim3(128),
+                         0, s, d.N, ridx.as<int32_t>(), rval.as<double>(), Ed.as<double>(), S.as<double>());
+    }
     STKKT_HIP(hipGetLastError());
     // S_k^{-1} (column-major S is the row-major transpose: invert it as is)
-    gje_invert(nb_, S.as<double>(), tmp.as<double>(), rows.as<double>(), pan.as<double>(), fcol.as<double>(),
-               piv.as<int32_t>(), swp.as<int32_t>(), prow.as<double>(), gs, status.as<int>(), la, s);
+    const double *Sk = gje_invert(nb_, S.as<double>(), tmp.as<double>(), rows.as<double>(), pan.as<double>(),
+                                  fcol.as<double>(), piv.as<int32_t>(), swp.as<int32_t>(), prow.as<double>(), gs,
+                                  status.as<int>(), la, s);
     // E_k = S_k^{-1} U_k
     if (k + 1 < nlev_) {
       hipLaunchKernelGGL(coupling_cols_kernel, dim3(G), dim3(128), 0, s, d, k, +1, cidx.as<int32_t>(),
                          cval.as<double>());
       hipLaunchKernelGGL(e_from_cols_kernel, g2, dim3(256), 0, s, nb_, cidx.as<int32_t>(), cval.as<double>(),
-                         S.as<double>(), Ed.as<double>());
+                         Sk, Ed.as<double>());
       STKKT_HIP(hipGetLastError());
     }
     // store S_k^{-1} and E_k in the application precision, columns padded to ld_
     const dim3 gp(blocks_for(ld_, 256, 64), nb_);
     if (prec_ == STKKT_F32) {
-      hipLaunchKernelGGL(store_padded_kernel<float>, gp, dim3(256), 0, s, nb_, ld_, S.as<double>(),
+      hipLaunchKernelGGL(store_padded_kernel<float>, gp, dim3(256), 0, s, nb_, ld_, Sk,
                          Sinv_.as<float>() + (size_t)k * nld);
       if (k + 1 < nlev_)
         hipLaunchKernelGGL(store_padded_kernel<float>, gp, dim3(256), 0, s, nb_, ld_, Ed.as<double>(),
                            E_.as<float>() + (size_t)k * nld);
     } else {
-      hipLaunchKernelGGL(store_padded_kernel<double>, gp, dim3(256), 0, s, nb_, ld_, S.as<double>(),
+      hipLaunchKernelGGL(store_padded_kernel<double>, gp, dim3(256), 0, s, nb_, ld_, Sk,
                          Sinv_.as<double>() + (size_t)k * nld);
       if (k + 1 < nlev_)
         hipLaunchKernelGGL(store_padded_kernel<double>, gp, dim3(256), 0, s, nb_, ld_, Ed.as<double>(),
