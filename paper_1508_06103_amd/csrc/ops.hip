@@ -311,7 +311,8 @@ __device__ inline void matvec_march(const OpDev &op, const MvTile &tl, cptr<MvCo
   double fm, f0, fp, a_e;  // f, and the coefficient of the element layer below it
   double sens;             // sensor mask of the plane written when the requested one is taken
   auto request = [&](int p) {
-    sens = *reinterpret_cast<const double *>(reinterpret_cast<const char *>(op.sensor + max(p - 2, 0) * (plane / 3)) + vs);
+    const int ps = min(max(p - 2, 0), nn2 - 1);   // (the last request of a march is past the planes it writes)
+    sens = *reinterpret_cast<const double *>(reinterpret_cast<const char *>(op.sensor + ps * (plane / 3)) + vs);
     const int q = min(p, pb);
     const char *pm = reinterpret_cast<const char *>(bm + q * plane), *p0 = reinterpret_cast<const char *>(b0 + q * plane),
                *pp = reinterpret_cast<const char *>(bp + q * plane);
