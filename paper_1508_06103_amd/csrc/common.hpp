@@ -83,10 +83,17 @@ struct OpDev {
   const double *sensor;   // device [N], 1 at sensor nodes
 };
 
-// Launch shape of the matvec: tiles of t[0] x t[1] node columns (nt[] tiles
-// per axis) marched along z in nz chunks of zlen planes, one time level each;
-// threads: columns of a tile with its halo, rounded up to wavefronts.
+// Launch shape of the solvers' matvec: spatial tiles of t[0] x t[1] x t[2]
+// nodes (nt[] tiles per axis) marched over time chunks of clen levels.
 struct MvTile {
+  int t[3], nt[3];
+  int ntiles, halo, clen, nchunks;
+};
+
+// Launch shape of the public matvec: tiles of t[0] x t[1] node columns (nt[]
+// tiles per axis) marched along z in nz chunks of zlen planes, one time level
+// each; threads: columns of a tile with its halo, rounded up to wavefronts.
+struct MvMarch {
   int t[2], nt[2];
   int ntiles, threads, zlen, nz;
 };
@@ -97,8 +104,9 @@ struct kkt_op {
   stkkt::Allocator al;
   stkkt::OpDev d{};
   stkkt::MvTile mv{};
-  stkkt::DevBuf a_elem, sensor, atab;   // atab: [N][27] diffusion stiffness rows (factorisation)
-  stkkt::DevBuf mvc;                    // constants of the matvec
+  stkkt::MvMarch mvm{};
+  stkkt::DevBuf a_elem, sensor, atab;   // atab: [N][27] diffusion stiffness rows
+  stkkt::DevBuf mvc;                    // constants of the public matvec
   std::vector<char> mvc_host;           // their staging
   std::vector<int32_t> sensor_node;   // host copy
   double T = 1.0, len[3] = {1, 1, 1};
@@ -119,6 +127,14 @@ inline int blocks_for(long long n, int threads, int cap = 1 << 20) {
 // counter and with it every prefetch in flight.
 template <class V> using cptr = const __attribute__((address_space(4))) V *;
 template <class V> __device__ inline cptr<V> as_const(const V *p) { return (cptr<V>)p; }
+
+// Work item of this block such that consecutive work items run on the same
+// XCD (the dispatcher deals blocks to the 8 XCDs round robin).
+__device__ inline int xcd_work_index() {
+  const int G = gridDim.x, b = blockIdx.x;
+  const int q = G >> 3, r = G & 7, xcd = b & 7;
+  return xcd * q + min(xcd, r) + (b >> 3);
+}
 
 // Copy a table entry (a struct of 32-bit words) through scalar loads.
 template <class S> __device__ inline S load_uniform(const S *p) {
@@ -141,7 +157,9 @@ void rhs_device_noalloc(const kkt_op *op, const double *data_host, hipStream_t s
 void fill_zero(double *p, long long n, hipStream_t s);
 void stiff_table(const OpDev &d, double *tab, hipStream_t s);
 MvTile choose_matvec_tile(const OpDev &d);
+MvMarch choose_matvec_march(const OpDev &d);
 void matvec_constants(kkt_op *op, hipStream_t s);   // forms op->mvc (copied in stream order)
+void matvec_march_device(const kkt_op *op, const double *x, double *y, hipStream_t s);   // kkt_matvec
 void matvec_device(const kkt_op *op, const double *x, double *y, hipStream_t s);
 // Batched matvec over operators whose vectors are concatenated: operator i
 // reads x[voff_i ...] and writes y[voff_i ...]; one launch for all of them,
@@ -150,7 +168,8 @@ struct MvBatch {
   DevBuf desc;
   int count = 0;
   long long items = 0;
-  int threads = 64;
+  int kh = 1;
+  size_t lds = 0;
 };
 void matvec_batch_prepare(const kkt_op *const *ops, const long long *voff, int count, const Allocator *al,
                           MvBatch &out, hipStream_t s);

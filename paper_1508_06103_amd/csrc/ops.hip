@@ -3,7 +3,6 @@
 #include <climits>
 #include <mutex>
 #include <string>
-#include <type_traits>
 
 #include "common.hpp"
 #include "stencil.hpp"
@@ -151,46 +150,30 @@ void stiff_table(const OpDev &d, double *tab, hipStream_t s) {
 // and Dirichlet C/G rows, the C row of level 0 and the OTD G row of level M
 // are identity rows.
 //
-// B, A, N and K are sums over elements, and on one element each is a tensor
-// product of 2 x 2 matrices of its axes.  In the sum / difference modes of an
-// axis, s = u_0 + u_1 and d = u_0 - u_1, with results r_0 = S + D, r_1 = S - D,
-//   mass:        S = h/4 s,  D = h/12 d          stiffness:  D = d / h
-//   convection:  S = -d / 2                      its transpose:  D = -s / 2
-// so in the eight modes of an element mass and stiffness are diagonal (the
-// element coefficient multiplies seven numbers) and convection couples modes in
-// pairs.  End-of-mesh rules follow from the elements that exist.
-//
-// A workgroup owns a tile of (x, y) nodes at one time level and marches along
-// z.  A thread is one node column with its halo, and the element column to its
-// upper right.  Per plane it forms its node's six fields and puts them in LDS,
-// reads those of its element's other three columns, takes the modes in x and
-// y, pairs them with the previous plane's in z, multiplies, and turns the
-// element's results back into corner values: the lower plane's are complete
-// with the carry of the element below, and three of the four corners go
-// through LDS to the columns that own them.  Both exchanges of consecutive
-// planes share one barrier.  About 300 FP64 operations and 42 LDS doubles per
-// column and plane; summing 27 neighbours per node from LDS took 162 LDS
-// doubles and a table of 27 entries per node, and left the vector units idle
-// two thirds of the time (cube48x96 581 us).
+// One workgroup owns a TX x TY x TZ tile of spatial nodes over a chunk of
+// consecutive time levels and marches through them: every thread keeps the
+// raw (c, g, f) of up to KH halo nodes for three consecutive levels in
+// registers, loads each level once, writes the six combined fields of its
+// halo nodes to LDS, and evaluates the 27-point sums of its own node from
+// LDS.  The fields of level n + 1 go to a second buffer while level n's
+// sums read the first, so one barrier per level suffices.  The spatial 1-D factors of B, K and N are rebuilt from the node's
+// position (end-node rules); the variable-coefficient diffusion A comes from
+// the per-node table, read once per chunk into registers.  (The solvers' form;
+// the public entry point has one of its own, twice as fast but with the sums
+// in another order, see matvec.hip.)
 // --------------------------------------------------------------------------
 namespace {
 
 constexpr int kMvThreads = 256;
-// LDS per thread: two buffers of three field pairs and of nine corner values
-constexpr size_t kMvLds = 2 * (3 * sizeof(double2) + 9 * sizeof(double)) * kMvThreads;
 
-// Mesh and time constants of the matvec, formed on the host.  Mode index of a
-// plane: bit 0 the x mode, bit 1 the y mode (0 = s, 1 = d); [z mode][plane mode].
+// Mesh and time constants of the matvec, formed on the host so that the
+// kernel never evaluates a product of uniform values in vector registers.
 struct MvConst {
-  double M[2][4], K[2][4];            // mass and stiffness of a mode
-  double Nx[2][2], Ny[2][2], Nz[4];   // tau/2 x convection: [z][y], [z][x], [plane] of the modes that stay
-  // rows of the time stiffness St and mass Tt on the first, an inner and the
-  // last level: (n, n - 1), (n, n), (n, n + 1); trapezoid weight
-  struct Level {
-    double st[3], tt[3], wn, pad;
-  } lv[3];
-  double ht, beta1, beta2;
-  int l2, pad;   // H1-L2 regularisation: beta2 (Tt f) joins U3 (mass) instead of T3 (stiffness)
+  double h6[3], hinv[3];   // h/6 and 1/h per axis (off-centre mass, -stiffness)
+  double v[3];
+  double cyz[2][2][4];     // corner rows (dy, dz = +-1): myz, kyz, nyz, v0 myz
+  double ht, inv_tau, tau6, tau3, beta1, beta2;
+  int l2;   // H1-L2 regularisation: beta2 (Tt f) joins U3 (mass) instead of T3 (stiffness)
 };
 
 // One operator of a batched matvec: its vectors start at element voff of the
@@ -199,294 +182,302 @@ struct MvBatchDesc {
   OpDev op;
   MvTile tl;
   MvConst mc;
+  const double *atab;
   int64_t voff;
   int32_t w0, nw;
 };
 
 MvConst make_mv_const(const OpDev &d) {
   MvConst c{};
-  double m[3][2], k[3][2];
   for (int a = 0; a < 3; ++a) {
-    m[a][0] = d.h[a] / 4.0;
-    m[a][1] = d.h[a] / 12.0;
-    k[a][0] = 0.0;
-    k[a][1] = 1.0 / d.h[a];
+    c.h6[a] = d.h[a] / 6.0;
+    c.hinv[a] = 1.0 / d.h[a];
+    c.v[a] = d.v[a];
   }
+  for (int sy = 0; sy < 2; ++sy)
+    for (int sz = 0; sz < 2; ++sz) {
+      const double dy = sy ? 1.0 : -1.0, dz = sz ? 1.0 : -1.0;
+      const double my = c.h6[1], mz = c.h6[2], ky = -c.hinv[1], kz = -c.hinv[2];
+      c.cyz[sy][sz][0] = my * mz;
+      c.cyz[sy][sz][1] = ky * mz + my * kz;
+      c.cyz[sy][sz][2] = d.v[1] * 0.5 * dy * mz + d.v[2] * my * 0.5 * dz;
+      c.cyz[sy][sz][3] = d.v[0] * my * mz;
+    }
   c.ht = 0.5 * d.tau;
-  for (int z = 0; z < 2; ++z)
-    for (int q = 0; q < 4; ++q) {
-      const int x = q & 1, y = q >> 1;
-      c.M[z][q] = m[0][x] * m[1][y] * m[2][z];
-      c.K[z][q] = k[0][x] * m[1][y] * m[2][z] + m[0][x] * k[1][y] * m[2][z] + m[0][x] * m[1][y] * k[2][z];
-    }
-  for (int z = 0; z < 2; ++z)
-    for (int i = 0; i < 2; ++i) {
-      c.Nx[z][i] = -0.5 * c.ht * d.v[0] * m[1][i] * m[2][z];
-      c.Ny[z][i] = -0.5 * c.ht * d.v[1] * m[0][i] * m[2][z];
-    }
-  for (int q = 0; q < 4; ++q) c.Nz[q] = -0.5 * c.ht * d.v[2] * m[0][q & 1] * m[1][q >> 1];
-  for (int e = 0; e < 3; ++e) {
-    const double it = 1.0 / d.tau;
-    MvConst::Level &l = c.lv[e];
-    l.st[0] = e == 0 ? 0.0 : -it;
-    l.st[1] = e == 1 ? 2.0 * it : it;
-    l.st[2] = e == 2 ? 0.0 : -it;
-    l.tt[0] = e == 0 ? 0.0 : d.tau / 6.0;
-    l.tt[1] = e == 1 ? 2.0 * (d.tau / 3.0) : d.tau / 3.0;
-    l.tt[2] = e == 2 ? 0.0 : d.tau / 6.0;
-    l.wn = e == 1 ? d.tau : c.ht;
-  }
+  c.inv_tau = 1.0 / d.tau;
+  c.tau6 = d.tau / 6.0;
+  c.tau3 = d.tau / 3.0;
   c.beta1 = d.beta1;
   c.beta2 = d.beta2;
   c.l2 = d.reg == STKKT_REG_H1L2;
   return c;
 }
 
-// Work item of this block such that consecutive work items run on the same
-// XCD (the dispatcher deals blocks to the 8 XCDs round robin).
-__device__ inline int xcd_work_index() {
-  const int G = gridDim.x, b = blockIdx.x;
-  const int q = G >> 3, r = G & 7, xcd = b & 7;
-  return xcd * q + min(xcd, r) + (b >> 3);
+struct Centre {
+  double m, k, c;   // centre mass, stiffness and convection entries of the node on one axis
+};
+
+__device__ inline Centre axis_centre(const MvConst &mc, int a, int i, int nn) {
+  const bool end = (i == 0) || (i == nn - 1);
+  Centre r;
+  r.m = end ? 2.0 * mc.h6[a] : 4.0 * mc.h6[a];
+  r.k = end ? mc.hinv[a] : 2.0 * mc.hinv[a];
+  r.c = (i == 0) ? -0.5 : ((i == nn - 1) ? 0.5 : 0.0);
+  return r;
 }
 
-typedef double mv_d2 __attribute__((ext_vector_type(2), aligned(8)));
-
-// Modes of one field on an element's face from its nodal values at (0,0),
-// (1,0), (0,1), (1,1).
-__device__ inline void face_modes(double a, double b, double c, double e, double (&m)[4]) {
-  const double s0 = a + b, d0 = a - b, s1 = c + e, d1 = c - e;
-  m[0] = s0 + s1;
-  m[1] = d0 + d1;
-  m[2] = s0 - s1;
-  m[3] = d0 - d1;
-}
-
-// One (tile, z chunk, time level) work item w of one operator.  The constants
-// are read again every plane (scalar loads): kept in scalar registers they
-// spill to vector lanes.
-template <int T>
-__device__ inline void matvec_march(const OpDev &op, const MvTile &tl, cptr<MvConst> mc, const double *__restrict__ x,
-                                    double *__restrict__ y, int w) {
+// One (tile, time chunk) work item w of one operator.
+template <int KH>
+__device__ inline void matvec_tile_body(const OpDev &op, const MvTile &tl, const MvConst &mc,
+                                        const double *__restrict__ Atab, const double *__restrict__ x,
+                                        double *__restrict__ y, int w) {
+  // per halo node: {U1, S1}, {U2, S2}, {U3, T3} side by side (48 B)
   extern __shared__ double2 mv_lds[];
-  const int t = (int)threadIdx.x;
-  const int M = op.M, nlev = M + 1;
-  const int n = w % nlev, item = w / nlev, tile = item % tl.ntiles, zc = item / tl.ntiles;
-  const int nn0 = op.nn[0], nn1 = op.nn[1], nn2 = op.nn[2];
-  const int z0 = zc * tl.zlen, z1 = min(nn2, z0 + tl.zlen);   // planes written
-  const int pa = max(z0 - 1, 0), pb = min(z1, nn2 - 1);       // planes whose fields are needed
+  const int tile = w % tl.ntiles, chunk = w / tl.ntiles;
+  const int M = op.M;
+  const int n0 = chunk * tl.clen, n1 = min(n0 + tl.clen, M + 1);
+  const int tix = tile % tl.nt[0], tiy = (tile / tl.nt[0]) % tl.nt[1], tiz = tile / (tl.nt[0] * tl.nt[1]);
+  const int ox = tix * tl.t[0], oy = tiy * tl.t[1], oz = tiz * tl.t[2];
   const int hx = tl.t[0] + 2, hy = tl.t[1] + 2;
-  const int tx = t % hx, ty = t / hx;
-  const int gx = (tile % tl.nt[0]) * tl.t[0] - 1 + tx, gy = (tile / tl.nt[0]) * tl.t[1] - 1 + ty;
-  const int cx = min(max(gx, 0), nn0 - 1), cy = min(max(gy, 0), nn1 - 1);
-  const bool elem = tx + 1 < hx && ty + 1 < hy && gx >= 0 && gx < op.n[0] && gy >= 0 && gy < op.n[1];
-  const bool own = tx >= 1 && tx + 1 < hx && ty >= 1 && ty + 1 < hy && gx < nn0 && gy < nn1;
+  const int nn0 = op.nn[0], nn1 = op.nn[1], nn2 = op.nn[2];
+  const long long N = op.N;
+  const double ht = mc.ht;
   const bool dto = op.variant == STKKT_DTO;
-  const bool hm = n >= 1, hp = n < M;
-  const bool mflag = !dto || hm;
-  const cptr<MvConst::Level> lv = &mc->lv[hm ? (hp ? 1 : 2) : 0];
-  const double st0 = lv->st[0], st1 = lv->st[1], st2 = lv->st[2], tt0 = lv->tt[0], tt1 = lv->tt[1], tt2 = lv->tt[2];
-  const double ht = mc->ht, beta1 = mc->beta1, beta2 = mc->beta2, wn = lv->wn;
-  const bool l2 = mc->l2 != 0;
-  const long long plane = 3LL * nn0 * nn1, level = 3LL * op.N;
-  // uniform bases of the plane at levels n - 1, n, n + 1; the thread's byte
-  // offsets in a plane of x, of sensor, and in an element layer (clamped into the mesh)
-  const long long vs = 8 * ((long long)cy * nn0 + cx), vo = 3 * vs;
-  const long long vae = 8 * ((long long)min(cy, op.n[1] - 1) * op.n[0] + min(cx, op.n[0] - 1));
-  const double *b0 = x + n * level, *bm = hm ? b0 - level : b0, *bp = hp ? b0 + level : b0;
-  const long long aplane = (long long)op.n[0] * op.n[1];
-  const bool side = ((op.faces & 1u) && gx == 0) || ((op.faces & 2u) && gx == nn0 - 1) || ((op.faces & 4u) && gy == 0) ||
-                    ((op.faces & 8u) && gy == nn1 - 1);
-  auto dirichlet = [&](int p) {
-    return side || ((op.faces & 16u) && p == 0) || ((op.faces & 32u) && p == nn2 - 1);
-  };
-  // LDS: two buffers of [3][T] field pairs, two of [9][T] corner values.  The
-  // neighbours' places are clamped where there is no neighbour (unused then).
-  double2 *const fb0 = mv_lds;
-  double *const cb0 = reinterpret_cast<double *>(mv_lds + 6 * T);
-  const int tr = min(t + 1, T - 1), tu = min(t + hx, T - 1), tur = min(t + hx + 1, T - 1);
-  const int tl1 = max(t - 1, 0), td = max(t - hx, 0), tdl = max(t - hx - 1, 0);
 
-  mv_d2 rm, r0, rp;        // (c, g) of the requested plane at levels n - 1, n, n + 1
-  double fm, f0, fp, a_e;  // f, and the coefficient of the element layer below it
-  double sens;             // sensor mask of the plane written when the requested one is taken
-  auto request = [&](int p) {
-    const int ps = min(max(p - 2, 0), nn2 - 1);   // (the last request of a march is past the planes it writes)
-    sens = *reinterpret_cast<const double *>(reinterpret_cast<const char *>(op.sensor + ps * (plane / 3)) + vs);
-    const int q = min(p, pb);
-    const char *pm = reinterpret_cast<const char *>(bm + q * plane), *p0 = reinterpret_cast<const char *>(b0 + q * plane),
-               *pp = reinterpret_cast<const char *>(bp + q * plane);
-    rm = *reinterpret_cast<const mv_d2 *>(pm + vo);
-    fm = *reinterpret_cast<const double *>(pm + vo + 16);
-    r0 = *reinterpret_cast<const mv_d2 *>(p0 + vo);
-    f0 = *reinterpret_cast<const double *>(p0 + vo + 16);
-    rp = *reinterpret_cast<const mv_d2 *>(pp + vo);
-    fp = *reinterpret_cast<const double *>(pp + vo + 16);
-    a_e = *reinterpret_cast<const double *>(reinterpret_cast<const char *>(op.a_elem + max(q - 1, 0) * aplane) + vae);
-  };
-  double X[6][4];   // face modes of the last plane: U1, S1, U2, S2, U3, T3
-  double carry[3][4], corner[3][3], mine[3];
+  // own node
+  const int t = threadIdx.x;
+  const int lx = t % tl.t[0], ly = (t / tl.t[0]) % tl.t[1], lz = t / (tl.t[0] * tl.t[1]);
+  const int jx = ox + lx, jy = oy + ly, jz = oz + lz;
+  const bool own = t < tl.t[0] * tl.t[1] * tl.t[2] && jx < nn0 && jy < nn1 && jz < nn2;
+  const long long j = own ? jx + (long long)nn0 * (jy + (long long)nn1 * jz) : 0;
+  double A[27];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    mine[k] = 0.0;
+  for (int k = 0; k < 27; ++k) A[k] = own ? Atab[27 * j + k] : 0.0;
+  Centre cx = axis_centre(mc, 0, jx, nn0), cy = axis_centre(mc, 1, jy, nn1), cz = axis_centre(mc, 2, jz, nn2);
+  const bool Pj = own && !on_dirichlet(op, jx, jy, jz);
+  const double sens = own ? op.sensor[j] : 0.0;
+  const int hc = (lx + 1) + hx * ((ly + 1) + hy * (lz + 1));
+
+  // halo nodes loaded by this thread
+  long long hoff[KH];
+  double hP[KH];
+  bool hin[KH], hact[KH];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) X[2 * k][q] = X[2 * k + 1][q] = carry[k][q] = 0.0;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) corner[k][q] = 0.0;
-  }
-  // node values needed when the plane is written, two planes later: c, g, and
-  // c^{n+1} (OTD sensor term)
-  double c_a = 0.0, g_a = 0.0, e_a = 0.0, c_b = 0.0, g_b = 0.0, e_b = 0.0;
-  // Plane p.  kFields: its fields are needed (p <= pb); kLayer: the element
-  // layer between planes p - 1 and p exists (pa < p <= pb); par: (p - pa) & 1.
-  auto plane_step = [&](int p, auto kf, auto kl, auto par) {
-    constexpr bool kFields = decltype(kf)::value, kLayer = decltype(kl)::value;
-    cptr<MvConst> m = mc;
-    asm volatile("" : "+s"(m));
-    double2 *const fb = fb0 + par * (3 * T);
-    double *const cb = cb0 + par * (9 * T);
-    const double a_l = ht * a_e, sens_o = sens;
-    const double cn = r0.x, gr = r0.y, en = rp.x;
-    if (kFields) {
-      const bool dn = dirichlet(p);
-      const double cm = hm ? rm.x : 0.0, gm = hm ? rm.y : 0.0, fmv = hm ? fm : 0.0;
-      const double gn = mflag ? gr : 0.0, gp = hp ? rp.y : 0.0, fpv = hp ? fp : 0.0;
-      const double S2 = dn ? 0.0 : gn + gp;
-      const double stf = st0 * fmv + st1 * f0 + st2 * fpv;
-      const double ttf = beta2 * (tt0 * fmv + tt1 * f0 + tt2 * fpv);
-      double U3 = beta1 * stf;
-      if (dto) U3 -= ht * S2;
-      else U3 -= dn ? 0.0 : tt0 * gm + tt1 * gr + tt2 * gp;
-      fb[t] = make_double2((dn ? 0.0 : cn - cm) - ht * (fmv + f0), dn ? 0.0 : cn + cm);
-      fb[T + t] = make_double2(dn ? 0.0 : gn - gp, S2);
-      fb[2 * T + t] = l2 ? make_double2(U3 + ttf, 0.0) : make_double2(U3, ttf);
-    }
-    // corners of plane p - 2 that belong to other columns
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int q = 0; q < 3; ++q) cb[(3 * k + q) * T + t] = corner[k][q];
-    const double keep0 = mine[0], keep1 = mine[1], keep2 = mine[2];   // its own corner of plane p - 2
-    const double c_o = c_b, g_o = g_b, e_o = e_b;
-    c_b = c_a, g_b = g_a, e_b = e_a;
-    c_a = cn, g_a = gr, e_a = en;
-    request(p + 1);
-    __syncthreads();
-    if (elem) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        double tot[4];
-        if (kFields) {
-          const double2 v0 = fb[k * T + t], v1 = fb[k * T + tr], v2 = fb[k * T + tu], v3 = fb[k * T + tur];
-          double u[4], v[4];
-          face_modes(v0.x, v1.x, v2.x, v3.x, u);
-          face_modes(v0.y, v1.y, v2.y, v3.y, v);
-          if (kLayer) {
-            double O[2][4], S[2][4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              O[0][q] = m->M[0][q] * (X[2 * k][q] + u[q]);
-              O[1][q] = m->M[1][q] * (X[2 * k][q] - u[q]);
-              S[0][q] = X[2 * k + 1][q] + v[q];
-              S[1][q] = X[2 * k + 1][q] - v[q];
-            }
-#pragma unroll
-            for (int z = 0; z < 2; ++z)
-#pragma unroll
-              for (int q = 0; q < 4; ++q)
-                if (z + q > 0) {
-                  const double ks = m->K[z][q] * S[z][q];
-                  O[z][q] += k == 2 ? ks : a_l * ks;
-                }
-            // convection: k = 0 takes difference modes to sum modes, k = 1 (its transpose) the other way
-            if (k < 2) {
-#pragma unroll
-              for (int z = 0; z < 2; ++z)
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                  const int sx = 2 * i, dx = 2 * i + 1, sy = i, dy = i + 2;
-                  O[z][k == 0 ? sx : dx] += m->Nx[z][i] * S[z][k == 0 ? dx : sx];
-                  O[z][k == 0 ? sy : dy] += m->Ny[z][i] * S[z][k == 0 ? dy : sy];
-                }
-#pragma unroll
-              for (int q = 0; q < 4; ++q) O[k][q] += m->Nz[q] * S[1 - k][q];
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              tot[q] = carry[k][q] + (O[0][q] + O[1][q]);
-              carry[k][q] = O[0][q] - O[1][q];
-            }
-          }
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            X[2 * k][q] = u[q];
-            X[2 * k + 1][q] = v[q];
-          }
-        }
-        if (!kLayer) {   // first plane: nothing below it; past the last plane: nothing above it
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            tot[q] = carry[k][q];
-            carry[k][q] = 0.0;
-          }
-        }
-        // corner values of plane p - 1
-        const double ss = tot[0] + tot[2], sd = tot[0] - tot[2], ds = tot[1] + tot[3], dd = tot[1] - tot[3];
-        mine[k] = ss + ds;
-        corner[k][0] = ss - ds;   // (1, 0)
-        corner[k][1] = sd + dd;   // (0, 1)
-        corner[k][2] = sd - dd;   // (1, 1)
+  for (int s = 0; s < KH; ++s) {
+    const int h = t + kMvThreads * s;
+    hact[s] = h < tl.halo;
+    hin[s] = false;
+    hoff[s] = 0;
+    hP[s] = 0.0;
+    if (hact[s]) {
+      const int axh = h % hx, ayh = (h / hx) % hy, azh = h / (hx * hy);
+      const int gx = ox + axh - 1, gy = oy + ayh - 1, gz = oz + azh - 1;
+      if (gx >= 0 && gx < nn0 && gy >= 0 && gy < nn1 && gz >= 0 && gz < nn2) {
+        hin[s] = true;
+        hoff[s] = 3 * (gx + (long long)nn0 * (gy + (long long)nn1 * gz));
+        hP[s] = on_dirichlet(op, gx, gy, gz) ? 0.0 : 1.0;
       }
     }
-    const int o = p - 2;
-    if (own && o >= z0 && o < z1) {
-      const double q0 = keep0 + cb[tl1] + (cb[T + td] + cb[2 * T + tdl]);
-      const double q1 = keep1 + cb[3 * T + tl1] + (cb[4 * T + td] + cb[5 * T + tdl]);
-      const double q2 = keep2 + cb[6 * T + tl1] + (cb[7 * T + td] + cb[8 * T + tdl]);
-      const bool dn = dirichlet(o);
-      double g;
-      if (dn) {
-        g = g_o;
-      } else if (dto) {
-        g = q1 + (hm ? 0.0 : g_o) + wn * sens_o * c_o;
-      } else {
-        g = hp ? q1 + ht * sens_o * (c_o + e_o) : g_o;
+  }
+  // halo values (c, g, f) of three consecutive levels and a fourth in flight:
+  // the loads of a level are issued one level before its fields are formed
+  double cm[KH], c0[KH], gm[KH], g0[KH], fm[KH], f0[KH], c1[KH], g1[KH], f1[KH], c2[KH], g2[KH], f2[KH];
+#pragma unroll
+  for (int s = 0; s < KH; ++s) {
+    cm[s] = gm[s] = fm[s] = c0[s] = g0[s] = f0[s] = c1[s] = g1[s] = f1[s] = 0.0;
+    if (hin[s] && n0 >= 1) {
+      const double *p = x + 3LL * (n0 - 1) * N + hoff[s];
+      cm[s] = p[0];
+      gm[s] = p[1];
+      fm[s] = p[2];
+    }
+    if (hin[s]) {
+      const double *p = x + 3LL * n0 * N + hoff[s];
+      c0[s] = p[0];
+      g0[s] = p[1];
+      f0[s] = p[2];
+    }
+    if (hin[s] && n0 < M) {
+      const double *p = x + 3LL * (n0 + 1) * N + hoff[s];
+      c1[s] = p[0];
+      g1[s] = p[1];
+      f1[s] = p[2];
+    }
+  }
+
+  // Fields of level L from the held levels L - 1 (cm), L (c0) and L + 1 (c1)
+  // into buffer buf; then the held levels move on by one, level L + 2 (c2,
+  // requested one level earlier) taking the place of L + 1.
+  auto fields = [&](int L, double2 *buf) {
+    const bool hm = L >= 1, hp = L < M;
+    const bool tend = (L == 0) || (L == M);
+    // rows of the time stiffness St and mass Tt at level L
+    const double stm = hm ? -mc.inv_tau : 0.0, st0 = tend ? mc.inv_tau : 2.0 * mc.inv_tau,
+                 stp = hp ? -mc.inv_tau : 0.0;
+    const double ttm = hm ? mc.tau6 : 0.0, tt0 = tend ? mc.tau3 : 2.0 * mc.tau3, ttp = hp ? mc.tau6 : 0.0;
+    const bool mflag = !dto || hm;
+#pragma unroll
+    for (int s = 0; s < KH; ++s) {
+      const double cp = hp ? c1[s] : 0.0, gp = hp ? g1[s] : 0.0, fp = hp ? f1[s] : 0.0;
+      if (hact[s]) {
+        const int h = t + kMvThreads * s;
+        const double P = hP[s];
+        const double gn = mflag ? g0[s] : 0.0;
+        const double S2 = P * (gn + gp);
+        const double stf = stm * fm[s] + st0 * f0[s] + stp * fp;
+        const double ttf = ttm * fm[s] + tt0 * f0[s] + ttp * fp;
+        const double U3 = mc.beta1 * stf - (dto ? ht * S2 : P * (ttm * gm[s] + tt0 * g0[s] + ttp * gp));
+        buf[3 * h] = make_double2(P * (c0[s] - cm[s]) - ht * (fm[s] + f0[s]), P * (c0[s] + cm[s]));
+        buf[3 * h + 1] = make_double2(P * (gn - gp), S2);
+        buf[3 * h + 2] = mc.l2 ? make_double2(U3 + mc.beta2 * ttf, 0.0) : make_double2(U3, mc.beta2 * ttf);
       }
-      char *ys = reinterpret_cast<char *>(y + n * level + o * plane);
-      *reinterpret_cast<mv_d2 *>(ys + vo) = mv_d2{(!hm || dn) ? c_o : q0, g};
-      *reinterpret_cast<double *>(ys + vo + 16) = q2;
+      cm[s] = c0[s];
+      c0[s] = cp;
+      c1[s] = c2[s];
+      gm[s] = g0[s];
+      g0[s] = gp;
+      g1[s] = g2[s];
+      fm[s] = f0[s];
+      f0[s] = fp;
+      f1[s] = f2[s];
     }
   };
-  request(pa);
-  using Even = std::integral_constant<int, 0>;
-  using Odd = std::integral_constant<int, 1>;
-  plane_step(pa, std::true_type{}, std::false_type{}, Even{});
-  int p = pa + 1;
-  for (; p + 1 <= pb; p += 2) {
-    plane_step(p, std::true_type{}, std::true_type{}, Odd{});
-    plane_step(p + 1, std::true_type{}, std::true_type{}, Even{});
-  }
-  if (p <= pb) {
-    plane_step(p, std::true_type{}, std::true_type{}, Odd{});
-    ++p;
-  }
+  // level L of the halo into c2 (zero unless wanted)
+  auto request = [&](int L, bool want) {
+#pragma unroll
+    for (int s = 0; s < KH; ++s) {
+      c2[s] = g2[s] = f2[s] = 0.0;
+      if (hin[s] && want) {
+        const double *p = x + 3LL * L * N + hoff[s];
+        c2[s] = p[0];
+        g2[s] = p[1];
+        f2[s] = p[2];
+      }
+    }
+  };
+  // Two field buffers: the fields of level n + 1 are written while the
+  // outputs of level n read those of level n, so one barrier per level
+  // separates the writes of a buffer from its reads.
+  double2 *const buf0 = mv_lds, *const buf1 = mv_lds + 3 * tl.halo;
+  request(n0 + 2, n0 + 2 <= M && n0 + 1 < n1);
+  fields(n0, buf0);
+  __syncthreads();
+  for (int n = n0; n < n1; ++n) {
+    const bool hp = n < M;
+    const bool tend = (n == 0) || (n == M);
+    const double2 *const cur = ((n - n0) & 1) ? buf1 : buf0;
+    if (n + 1 < n1) {
+      // level n + 3 feeds the fields of level n + 2 (formed only while that level is in this chunk)
+      request(n + 3, n + 3 <= M && n + 2 < n1);
+      fields(n + 1, ((n - n0) & 1) ? buf0 : buf1);
+    }
+    // rebuild the node's stencil weights every level instead of keeping them live
+    asm volatile("" : "+v"(cx.m), "+v"(cx.k), "+v"(cx.c), "+v"(cy.m), "+v"(cy.k), "+v"(cy.c));
+    asm volatile("" : "+v"(cz.m), "+v"(cz.k), "+v"(cz.c));
+    if (own) {
+      // Sum factorisation: B, K and N are tensor products of 1-D factors, so
+      // each row of three x-neighbours is first contracted with the x factors
+      // (off-centre entries are the same for every node, the centre ones are
+      // the node's), then weighted by the (y, z) factors of the row.  The
+      // variable diffusion A is applied point by point.
+      double aC = 0.0, sC = 0.0, aG = 0.0, sG = 0.0, aF = 0.0;
+      // The dz planes stay a loop: unrolled, the compiler requests the LDS
+      // values of all nine rows at once and their registers leave one
+      // wavefront per SIMD.  Rolled, the diffusion table of the node goes to
+      // per-lane scratch (cached; 224 B) and two wavefronts fit
+      // (174.7 / 642 us against 187.3 / 733 us on cube32x64 / cube48x96).
 #pragma unroll 1
-  for (; p <= z1 + 1; ++p) plane_step(p, std::false_type{}, std::false_type{}, (p - pa) & 1);
+      for (int dz = -1; dz <= 1; ++dz) {
+#pragma unroll
+        for (int dy = -1; dy <= 1; ++dy) {
+          double myz, kyz, nyz, vmyz;
+          if (dy != 0 && dz != 0) {
+            const double *c4 = mc.cyz[dy > 0][dz > 0];
+            myz = c4[0];
+            kyz = c4[1];
+            nyz = c4[2];
+            vmyz = c4[3];
+          } else if (dy == 0 && dz != 0) {
+            myz = cy.m * mc.h6[2];
+            kyz = cy.k * mc.h6[2] - cy.m * mc.hinv[2];
+            nyz = mc.v[1] * mc.h6[2] * cy.c + (0.5 * dz) * mc.v[2] * cy.m;
+            vmyz = mc.v[0] * myz;
+          } else if (dy != 0 && dz == 0) {
+            myz = mc.h6[1] * cz.m;
+            kyz = -mc.hinv[1] * cz.m + mc.h6[1] * cz.k;
+            nyz = (0.5 * dy) * mc.v[1] * cz.m + mc.v[2] * mc.h6[1] * cz.c;
+            vmyz = mc.v[0] * myz;
+          } else {
+            myz = cy.m * cz.m;
+            kyz = cy.k * cz.m + cy.m * cz.k;
+            nyz = mc.v[1] * cy.c * cz.m + mc.v[2] * cy.m * cz.c;
+            vmyz = mc.v[0] * myz;
+          }
+          // N^T differs from N only in the sign of the off-centre convection entries
+          double ntyz;
+          if (dy != 0 && dz != 0) ntyz = -nyz;
+          else if (dy == 0 && dz != 0) ntyz = mc.v[1] * mc.h6[2] * cy.c - (0.5 * dz) * mc.v[2] * cy.m;
+          else if (dy != 0 && dz == 0) ntyz = -(0.5 * dy) * mc.v[1] * cz.m + mc.v[2] * mc.h6[1] * cz.c;
+          else ntyz = nyz;
+          const double2 *row = cur + 3 * (hc + hx * (dy + hy * dz));
+          const double2 w1 = row[-3], w2 = row[-2], w3 = row[-1];   // x - 1
+          const double2 c1 = row[0], c2 = row[1], c3 = row[2];      // x
+          const double2 e1 = row[3], e2 = row[4], e3 = row[5];      // x + 1
+          const int k0 = 3 * (dy + 1) + 9 * (dz + 1);
+          const double mU1 = mc.h6[0] * (w1.x + e1.x) + cx.m * c1.x;
+          const double mU2 = mc.h6[0] * (w2.x + e2.x) + cx.m * c2.x;
+          const double mU3 = mc.h6[0] * (w3.x + e3.x) + cx.m * c3.x;
+          const double mT = mc.h6[0] * (w3.y + e3.y) + cx.m * c3.y;
+          const double kT = cx.k * c3.y - mc.hinv[0] * (w3.y + e3.y);
+          const double mS1 = mc.h6[0] * (w1.y + e1.y) + cx.m * c1.y;
+          const double cS1 = 0.5 * (e1.y - w1.y) + cx.c * c1.y;
+          const double aS1 = A[k0] * w1.y + A[k0 + 1] * c1.y + A[k0 + 2] * e1.y;
+          const double mS2 = mc.h6[0] * (w2.y + e2.y) + cx.m * c2.y;
+          const double cS2 = 0.5 * (w2.y - e2.y) + cx.c * c2.y;
+          const double aS2 = A[k0] * w2.y + A[k0 + 1] * c2.y + A[k0 + 2] * e2.y;
+          aC += myz * mU1;
+          aG += myz * mU2;
+          aF += myz * (mU3 + kT) + kyz * mT;
+          sC += aS1 + vmyz * cS1 + nyz * mS1;
+          sG += aS2 + vmyz * cS2 + ntyz * mS2;
+        }
+      }
+      const long long idx = (long long)n * N + j;
+      const double *xs = x + 3 * idx;
+      double *ys = y + 3 * idx;
+      const double cj = xs[0], gj = xs[1];
+      ys[0] = (n == 0 || !Pj) ? cj : aC + ht * sC;
+      double g;
+      if (!Pj) {
+        g = gj;
+      } else if (dto) {
+        const double wn = tend ? ht : 2.0 * ht;   // trapezoid weight of level n
+        g = aG + ht * sG + (n == 0 ? gj : 0.0) + wn * sens * cj;
+      } else {
+        g = hp ? aG + ht * sG + ht * sens * (cj + xs[3 * N]) : gj;
+      }
+      ys[1] = g;
+      ys[2] = aF;
+    }
+    __syncthreads();
+  }
 }
 
-template <int T>
-__global__ void __launch_bounds__(T, 2) matvec_kernel(OpDev op, MvTile tl, const MvConst *__restrict__ mc,
-                                                               const double *__restrict__ x, double *__restrict__ y) {
-  matvec_march<T>(op, tl, as_const(mc), x, y, xcd_work_index());
+template <int KH>
+__global__ void __launch_bounds__(kMvThreads) matvec_tile_kernel(OpDev op, MvTile tl, MvConst mc,
+                                                                 const double *__restrict__ Atab,
+                                                                 const double *__restrict__ x,
+                                                                 double *__restrict__ y) {
+  matvec_tile_body<KH>(op, tl, mc, Atab, x, y, xcd_work_index());
 }
 
 // Batched form: the work items of all operators in one grid, operator i
 // owning [w0_i, w0_i + nw_i).
-template <int T>
-__global__ void __launch_bounds__(T, 2) matvec_batch_kernel(const MvBatchDesc *__restrict__ descs, int count,
-                                                                     const int *__restrict__ act,
-                                                                     const double *__restrict__ x,
-                                                                     double *__restrict__ y) {
+template <int KH>
+__global__ void __launch_bounds__(kMvThreads) matvec_batch_kernel(const MvBatchDesc *__restrict__ descs, int count,
+                                                                  const int *__restrict__ act,
+                                                                  const double *__restrict__ x,
+                                                                  double *__restrict__ y) {
   const int w = xcd_work_index();
   cptr<MvBatchDesc> cd = as_const(descs);
   int i = 0;
@@ -498,62 +489,57 @@ __global__ void __launch_bounds__(T, 2) matvec_batch_kernel(const MvBatchDesc *_
   // would be generic, and generic loads also wait on the LDS counter
   d.op.a_elem = cd[i].op.a_elem;
   d.op.sensor = cd[i].op.sensor;
-  matvec_march<T>(d.op, d.tl, &cd[i].mc, x + d.voff, y + d.voff, w - d.w0);
+  matvec_tile_body<KH>(d.op, d.tl, d.mc, cd[i].atab, x + d.voff, y + d.voff, w - d.w0);
 }
 
 }  // namespace
 
-// Tile of owned (x, y) nodes, at most kMvThreads columns with the halo: the
-// fewest wavefronts over the mesh, wide lines first.  z is cut so that about
-// 1024 workgroups exist (two per compute unit, twice), at a cost of three
-// planes of overhead per cut.
 MvTile choose_matvec_tile(const OpDev &d) {
   MvTile best{};
-  long long best_cost = -1;
-  for (int tx = 1; tx <= std::min(d.nn[0], kMvThreads / 3 - 2); ++tx)
-    for (int ty = 1; ty <= std::min(d.nn[1], kMvThreads / (tx + 2) - 2); ++ty) {
-      const int cols = (tx + 2) * (ty + 2);
-      const int ntx = (d.nn[0] + tx - 1) / tx, nty = (d.nn[1] + ty - 1) / ty;
-      // columns, counted in wavefronts
-      const long long cost = (long long)ntx * nty * ((cols + 63) / 64);
-      if (best_cost < 0 || cost <= best_cost) {
-        best_cost = cost;
-        best.t[0] = tx;
-        best.t[1] = ty;
-        best.nt[0] = ntx;
-        best.nt[1] = nty;
-        best.threads = (cols + 63) / 64 * 64;
+  double best_cost = 1e300;
+  const int cap = kMvThreads;
+  for (int tx = 1; tx <= std::min(d.nn[0], cap); ++tx)
+    for (int ty = 1; ty <= std::min(d.nn[1], cap / tx); ++ty)
+      for (int tz = 1; tz <= std::min(d.nn[2], cap / (tx * ty)); ++tz) {
+        const int halo = (tx + 2) * (ty + 2) * (tz + 2);
+        // at most three halo nodes per thread; two field buffers within 64 KB of LDS
+        if (halo > 3 * kMvThreads || sizeof(double2) * 6 * (size_t)halo > 65536) continue;
+        const long long ntiles = (long long)((d.nn[0] + tx - 1) / tx) * ((d.nn[1] + ty - 1) / ty) *
+                                 ((d.nn[2] + tz - 1) / tz);
+        const double cost = (double)ntiles * (halo + kMvThreads);
+        // ties go to the widest x extent (longer contiguous rows of x and y)
+        if (cost <= best_cost) {
+          best_cost = cost;
+          best.t[0] = tx;
+          best.t[1] = ty;
+          best.t[2] = tz;
+        }
       }
-    }
-  best.ntiles = best.nt[0] * best.nt[1];
-  const long long per = (long long)best.ntiles * (d.M + 1);
-  const int cuts = (int)std::max<long long>(1, std::min<long long>(d.nn[2], (1024 + per - 1) / per));
-  best.zlen = (d.nn[2] + cuts - 1) / cuts;
-  best.nz = (d.nn[2] + best.zlen - 1) / best.zlen;
+  for (int a = 0; a < 3; ++a) best.nt[a] = (d.nn[a] + best.t[a] - 1) / best.t[a];
+  best.ntiles = best.nt[0] * best.nt[1] * best.nt[2];
+  best.halo = (best.t[0] + 2) * (best.t[1] + 2) * (best.t[2] + 2);
+  const int levels = d.M + 1;
+  int chunks = std::max(1, std::min(levels, (1024 + best.ntiles - 1) / best.ntiles));
+  best.clen = (levels + chunks - 1) / chunks;
+  best.nchunks = (levels + best.clen - 1) / best.clen;
   return best;
 }
 
-void matvec_constants(kkt_op *op, hipStream_t s) {
-  const MvConst c = make_mv_const(op->d);
-  const char *p = reinterpret_cast<const char *>(&c);
-  op->mvc_host.assign(p, p + sizeof(c));
-  op->mvc = DevBuf(&op->al, sizeof(c));
-  STKKT_HIP(hipMemcpyAsync(op->mvc.ptr, op->mvc_host.data(), sizeof(c), hipMemcpyHostToDevice, s));
-}
-
-static long long matvec_items(const OpDev &d, const MvTile &tl) { return (long long)tl.ntiles * tl.nz * (d.M + 1); }
-static size_t matvec_lds(int threads) { return kMvLds / kMvThreads * (size_t)threads; }
-
 void matvec_device(const kkt_op *op, const double *x, double *y, hipStream_t s) {
   const OpDev &d = op->d;
-  const long long grid = matvec_items(d, op->mv);
+  const MvTile &tl = op->mv;
+  const long long grid = (long long)tl.ntiles * tl.nchunks;
   if (grid > INT32_MAX) throw Error(STKKT_EINVAL, "kkt_matvec: mesh too large");
-  const auto kernel = op->mv.threads == 64    ? matvec_kernel<64>
-                      : op->mv.threads == 128 ? matvec_kernel<128>
-                      : op->mv.threads == 192 ? matvec_kernel<192>
-                                              : matvec_kernel<256>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(op->mv.threads), matvec_lds(op->mv.threads), s, d, op->mv,
-                     op->mvc.as<MvConst>(), x, y);
+  const size_t lds = sizeof(double2) * 6 * (size_t)tl.halo;   // two buffers of 48 B per halo node
+  const int kh = (tl.halo + kMvThreads - 1) / kMvThreads;
+  const double *atab = op->atab.as<double>();
+  const MvConst mc = make_mv_const(d);
+  if (kh == 1)
+    hipLaunchKernelGGL(matvec_tile_kernel<1>, dim3((unsigned)grid), dim3(kMvThreads), lds, s, d, tl, mc, atab, x, y);
+  else if (kh == 2)
+    hipLaunchKernelGGL(matvec_tile_kernel<2>, dim3((unsigned)grid), dim3(kMvThreads), lds, s, d, tl, mc, atab, x, y);
+  else
+    hipLaunchKernelGGL(matvec_tile_kernel<3>, dim3((unsigned)grid), dim3(kMvThreads), lds, s, d, tl, mc, atab, x, y);
   STKKT_HIP(hipGetLastError());
 }
 
@@ -561,7 +547,7 @@ void matvec_batch_prepare(const kkt_op *const *ops, const long long *voff, int c
                           MvBatch &out, hipStream_t s) {
   std::vector<MvBatchDesc> d(count);
   long long w = 0;
-  int threads = 64;
+  int halo = 0;
   for (int i = 0; i < count; ++i) {
     d[i] = MvBatchDesc{};
     d[i].w0 = (int32_t)w;
@@ -569,29 +555,33 @@ void matvec_batch_prepare(const kkt_op *const *ops, const long long *voff, int c
     d[i].op = ops[i]->d;
     d[i].tl = ops[i]->mv;
     d[i].mc = make_mv_const(ops[i]->d);
+    d[i].atab = ops[i]->atab.as<double>();
     d[i].voff = voff[i];
-    const long long nw = matvec_items(ops[i]->d, ops[i]->mv);
-    STKKT_REQUIRE(w + nw <= INT32_MAX, "batched matvec: too many work items");
-    d[i].nw = (int32_t)nw;
-    w += nw;
-    threads = std::max(threads, ops[i]->mv.threads);
+    d[i].nw = ops[i]->mv.ntiles * ops[i]->mv.nchunks;
+    w += d[i].nw;
+    halo = std::max(halo, ops[i]->mv.halo);
   }
+  STKKT_REQUIRE(w <= INT32_MAX, "batched matvec: too many work items");
   out.desc = DevBuf(al, sizeof(MvBatchDesc) * (size_t)count);
   STKKT_HIP(hipMemcpyAsync(out.desc.ptr, d.data(), sizeof(MvBatchDesc) * (size_t)count, hipMemcpyHostToDevice, s));
+  halo = std::max(halo, 27);
   STKKT_HIP(hipStreamSynchronize(s));   // d is released on return
   out.count = count;
   out.items = w;
-  out.threads = threads;
+  out.lds = sizeof(double2) * 6 * (size_t)halo;
+  out.kh = (halo + kMvThreads - 1) / kMvThreads;
 }
 
 void matvec_batch_run(const MvBatch &b, const double *x, double *y, const int *act, hipStream_t s) {
   if (b.items == 0) return;
-  const auto kernel = b.threads == 64    ? matvec_batch_kernel<64>
-                      : b.threads == 128 ? matvec_batch_kernel<128>
-                      : b.threads == 192 ? matvec_batch_kernel<192>
-                                         : matvec_batch_kernel<256>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)b.items), dim3(b.threads), matvec_lds(b.threads), s,
-                     b.desc.as<MvBatchDesc>(), b.count, act, x, y);
+  const MvBatchDesc *dd = b.desc.as<MvBatchDesc>();
+  const dim3 grid((unsigned)b.items);
+  if (b.kh == 1)
+    hipLaunchKernelGGL(matvec_batch_kernel<1>, grid, dim3(kMvThreads), b.lds, s, dd, b.count, act, x, y);
+  else if (b.kh == 2)
+    hipLaunchKernelGGL(matvec_batch_kernel<2>, grid, dim3(kMvThreads), b.lds, s, dd, b.count, act, x, y);
+  else
+    hipLaunchKernelGGL(matvec_batch_kernel<3>, grid, dim3(kMvThreads), b.lds, s, dd, b.count, act, x, y);
   STKKT_HIP(hipGetLastError());
 }
 
