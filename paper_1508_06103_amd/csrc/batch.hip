@@ -459,18 +459,11 @@ void BatchEngine::bdot(const double *V, long long ldv, int k, const double *w, c
   if (nch_ == 0) return;
   const Chunk *chd = chunks_.as<Chunk>();
   double *part = partial_.as<double>();
-  if (k <= kCgsHalf)
-    hipLaunchKernelGGL(bmultidot_tiles_kernel<kCgsHalf>, dim3(nch_), dim3(kCgsThreads), 0, s_, V, ldv, k, w, chd, nch_,
-                       act, part);
-  else if (k <= 48)
-    hipLaunchKernelGGL(bmultidot_tiles_kernel<48>, dim3(nch_), dim3(kCgsThreads), 0, s_, V, ldv, k, w, chd, nch_, act,
-                       part);
-  else if (k <= 56)
-    hipLaunchKernelGGL(bmultidot_tiles_kernel<56>, dim3(nch_), dim3(kCgsThreads), 0, s_, V, ldv, k, w, chd, nch_, act,
-                       part);
-  else if (k <= kCgsMaxK)
-    hipLaunchKernelGGL(bmultidot_tiles_kernel<kCgsMaxK>, dim3(nch_), dim3(kCgsThreads), 0, s_, V, ldv, k, w, chd, nch_,
-                       act, part);
+  if (k <= kCgsMaxK)
+    with_cgs_width(k, [&](auto width) {
+      hipLaunchKernelGGL(bmultidot_tiles_kernel<decltype(width)::value>, dim3(nch_), dim3(kCgsThreads), 0, s_, V, ldv,
+                         k, w, chd, nch_, act, part);
+    });
   else
     hipLaunchKernelGGL(bmultidot_kernel, dim3(nch_), dim3(kBT), 0, s_, V, ldv, k, w, chd, nch_, act, part);
   hipLaunchKernelGGL(breduce_kernel, dim3((unsigned)slots_.size(), k), dim3(kBT), 0, s_, partial_.as<double>(), nch_,
@@ -553,28 +546,15 @@ void BatchEngine::cgs2(int j, const int *act) {
     double *part = partial_.as<double>();
     const int *cf = cfirst_.as<int>();
     const unsigned S = (unsigned)slots_.size();
-    if (j + 1 <= kCgsHalf)
-      hipLaunchKernelGGL(bupdate_dot_kernel<kCgsHalf>, dim3(nch_), dim3(kCgsThreads), 0, s_, Wd, Vd, N, j + 1, hd, hs,
-                         chd, nch_, act, part);
-    else if (j + 1 <= 48)
-      hipLaunchKernelGGL(bupdate_dot_kernel<48>, dim3(nch_), dim3(kCgsThreads), 0, s_, Wd, Vd, N, j + 1, hd, hs, chd,
-                         nch_, act, part);
-    else if (j + 1 <= 56)
-      hipLaunchKernelGGL(bupdate_dot_kernel<56>, dim3(nch_), dim3(kCgsThreads), 0, s_, Wd, Vd, N, j + 1, hd, hs, chd,
-                         nch_, act, part);
-    else
-      hipLaunchKernelGGL(bupdate_dot_kernel<kCgsMaxK>, dim3(nch_), dim3(kCgsThreads), 0, s_, Wd, Vd, N, j + 1, hd, hs,
-                         chd, nch_, act, part);
+    with_cgs_width(j + 1, [&](auto width) {
+      hipLaunchKernelGGL(bupdate_dot_kernel<decltype(width)::value>, dim3(nch_), dim3(kCgsThreads), 0, s_, Wd, Vd, N,
+                         j + 1, hd, hs, chd, nch_, act, part);
+    });
     hipLaunchKernelGGL(breduce_kernel, dim3(S, j + 1), dim3(kBT), 0, s_, part, nch_, cf, act, hs, hd + (m + 1));
-    if (j + 1 <= kCgsHalf)
-      hipLaunchKernelGGL(bupdate_norm_kernel<kCgsHalf>, dim3(nch_), dim3(kCgsThreads), 0, s_, Wd, Vd, N, j + 1,
-                         hd + (m + 1), hs, chd, act, part);
-    else if (j + 1 <= 48)
-      hipLaunchKernelGGL(bupdate_norm_kernel<48>, dim3(nch_), dim3(kCgsThreads), 0, s_, Wd, Vd, N, j + 1, hd + (m + 1),
-                         hs, chd, act, part);
-    else
-      hipLaunchKernelGGL(bupdate_norm_kernel<kCgsMaxK>, dim3(nch_), dim3(kCgsThreads), 0, s_, Wd, Vd, N, j + 1,
-                         hd + (m + 1), hs, chd, act, part);
+    with_cgs_width(j + 1, [&](auto width) {
+      hipLaunchKernelGGL(bupdate_norm_kernel<decltype(width)::value>, dim3(nch_), dim3(kCgsThreads), 0, s_, Wd, Vd, N,
+                         j + 1, hd + (m + 1), hs, chd, act, part);
+    });
     hipLaunchKernelGGL(breduce_kernel, dim3(S, 1), dim3(kBT), 0, s_, part, nch_, cf, act, hs, hd + 2 * (m + 1));
     STKKT_HIP(hipGetLastError());
   } else {

@@ -4,13 +4,44 @@
 // partial sums that a second stage adds in a fixed order.
 #pragma once
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace stkkt {
 
 constexpr int kCgsThreads = 256;
 constexpr int kCgsMaxK = 64;   // basis vectors a fused pass accepts
-constexpr int kCgsHalf = 32;
+
+// f(width) with the smallest multiple of eight >= k (1 <= k <= kCgsMaxK) as a
+// compile-time width: the passes below keep one register per basis vector.
+template <typename F> inline void with_cgs_width(int k, F f) {
+  switch ((k + 7) / 8) {
+    case 0:
+    case 1: return f(std::integral_constant<int, 8>{});
+    case 2: return f(std::integral_constant<int, 16>{});
+    case 3: return f(std::integral_constant<int, 24>{});
+    case 4: return f(std::integral_constant<int, 32>{});
+    case 5: return f(std::integral_constant<int, 40>{});
+    case 6: return f(std::integral_constant<int, 48>{});
+    case 7: return f(std::integral_constant<int, 56>{});
+    default: return f(std::integral_constant<int, 64>{});
+  }
+}
+
+// Entries e of the basis vectors 0 .. k - 1 into v[0 .. KR), zeros past k or
+// for an invalid element.  The loads carry no branch (a vector past k reads the
+// last one's entry, an invalid element the caller's in-range `e`), so that all
+// of them are in flight together.
+template <int KR>
+__device__ inline void load_basis(const double *__restrict__ V, long long ldv, int k, long long e, bool valid,
+                                  double (&v)[KR]) {
+  double x[KR];
+#pragma unroll
+  for (int j = 0; j < KR; ++j) x[j] = V[(long long)min(j, k - 1) * ldv + e];
+#pragma unroll
+  for (int j = 0; j < KR; ++j) v[j] = j < k && valid ? x[j] : 0.0;
+}
 
 __device__ inline double cgs_wave_sum(double v) {
 #pragma unroll
@@ -34,18 +65,17 @@ __device__ inline void update_dot_tiles(double *__restrict__ w, const double *__
   for (long long t = wave; t < ntiles; t += kCgsThreads / 64) {
     const long long e = lo + 64 * t + lane;
     const bool valid = e < hi;
+    const long long ec = valid ? e : hi - 1;
+    const double wold = w[ec];
     double v[KR];
-#pragma unroll
-    for (int j = 0; j < KR; ++j) v[j] = (j < k && valid) ? V[(long long)j * ldv + e] : 0.0;
-    const double wold = valid ? w[e] : 0.0;
+    load_basis<KR>(V, ldv, k, ec, valid, v);
     double s = 0.0;
 #pragma unroll
-    for (int j = 0; j < KR; ++j)
-      if (j < k) s += hc[j] * v[j];
+    for (int j = 0; j < KR; ++j) s = __builtin_fma(j < k ? hc[j] : 0.0, v[j], s);
     const double wn = valid ? wold - s : 0.0;
     if (valid) w[e] = wn;
 #pragma unroll
-    for (int j = 0; j < KR; ++j) acc[j] += v[j] * wn;
+    for (int j = 0; j < KR; ++j) acc[j] = __builtin_fma(v[j], wn, acc[j]);
   }
 #pragma unroll
   for (int j = 0; j < KR; ++j)
@@ -69,9 +99,12 @@ __device__ inline void dot_range(const double *__restrict__ w, const double *__r
   for (long long t = wave; t < ntiles; t += kCgsThreads / 64) {
     const long long e = lo + 64 * t + lane;
     const bool valid = e < hi;
-    const double we = valid ? w[e] : 0.0;
+    const long long ec = valid ? e : hi - 1;
+    const double wold = w[ec], we = valid ? wold : 0.0;
+    double v[KR];
+    load_basis<KR>(V, ldv, k, ec, valid, v);
 #pragma unroll
-    for (int j = 0; j < KR; ++j) acc[j] += ((j < k && valid) ? V[(long long)j * ldv + e] : 0.0) * we;
+    for (int j = 0; j < KR; ++j) acc[j] = __builtin_fma(v[j], we, acc[j]);
   }
 #pragma unroll
   for (int j = 0; j < KR; ++j)
@@ -90,10 +123,9 @@ __device__ inline void dot_range(const double *__restrict__ w, const double *__r
 
 // w[e] <- w[e] - sum_{g<k} h[g] V_g[e] for e in [lo, hi), then
 // out[g * ostride] = sum over the range of V_g[e] w_new[e], g < k <= KR.
-// Every wavefront works on its own tiles with no synchronisation.  Kernels
-// are instantiated with KR = 32, 48, 56 and 64 (the smallest KR >= k: more
-// registers per wavefront, fewer wavefronts per SIMD, more loads in flight
-// per wavefront).
+// Every wavefront works on its own tiles with no synchronisation.  KR is the
+// smallest multiple of eight >= k: more registers per wavefront, fewer
+// wavefronts per SIMD, more loads in flight per wavefront.
 template <int KR>
 __device__ inline void update_dot_range(double *__restrict__ w, const double *__restrict__ V, long long ldv, int k,
                                         const double *__restrict__ h, long long lo, long long hi,
@@ -120,16 +152,15 @@ __device__ inline double update_norm_range(double *__restrict__ w, const double 
   const cptr<double> hc = as_const(h);
   double acc = 0.0;
   for (long long e = lo + threadIdx.x; e < hi; e += kCgsThreads) {
+    const double wold = w[e];
     double v[KR];
-#pragma unroll
-    for (int g = 0; g < KR; ++g) v[g] = g < k ? V[(long long)g * ldv + e] : 0.0;
+    load_basis<KR>(V, ldv, k, e, true, v);
     double s = 0.0;
 #pragma unroll
-    for (int g = 0; g < KR; ++g)
-      if (g < k) s += hc[g] * v[g];
-    const double wn = w[e] - s;
+    for (int g = 0; g < KR; ++g) s = __builtin_fma(g < k ? hc[g] : 0.0, v[g], s);
+    const double wn = wold - s;
     w[e] = wn;
-    acc += wn * wn;
+    acc = __builtin_fma(wn, wn, acc);
   }
   acc = cgs_wave_sum(acc);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;

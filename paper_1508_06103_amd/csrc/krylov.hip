@@ -145,6 +145,113 @@ __global__ void __launch_bounds__(kCgsThreads) update_norm_kernel(double *__rest
   if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
+// Short vectors: at most kSmallRanges ranges of up to 4096 elements leave most
+// of the chip idle in the kernels above, each workgroup reading its tiles one
+// after the other.  The update then runs on its own over all elements and the
+// dots take kSmallDots vectors per workgroup with all of a wavefront's tiles
+// in flight; every sum is the one of the kernels above, in the same order and
+// with the same fused multiply-adds, so both forms give the same bits.  At
+// n = 37 000 and 18 vectors the three passes of a step took 21, 33 and 33 us
+// on 10 workgroups, now 6, 5 + 6 and 5 + 5.  The limit is one range per compute
+// unit: 30 steps at n = 165 000 (41 ranges) 16.0 -> 14.6 ms, 695 000 (170) 30.0
+// -> 29.7, 1 172 000 (287) no difference, 2 297 000 (561) slower by the second
+// read of V.
+constexpr int kSmallRanges = 256, kSmallDots = 4, kSmallTiles = 4096 / 64 / (kCgsThreads / 64);
+
+__global__ void __launch_bounds__(kCgsThreads) small_dots_kernel(const double *__restrict__ V, long long ldv, int k,
+                                                                 const double *__restrict__ w, long long n,
+                                                                 double *__restrict__ partial) {
+  __shared__ double red[kCgsThreads / 64][kSmallDots];
+  const int G = gridDim.x, j0 = blockIdx.y * kSmallDots;
+  const long long per = (n + G - 1) / G, lo = (long long)blockIdx.x * per, hi = lo + per < n ? lo + per : n;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double v[kSmallTiles][kSmallDots], we[kSmallTiles];
+#pragma unroll
+  for (int i = 0; i < kSmallTiles; ++i) {
+    const long long e = lo + 64 * (wave + (kCgsThreads / 64) * i) + lane;
+    const long long ec = e < hi ? e : n - 1;
+    we[i] = w[ec];
+#pragma unroll
+    for (int j = 0; j < kSmallDots; ++j) v[i][j] = V[(long long)min(j0 + j, k - 1) * ldv + ec];
+  }
+  double acc[kSmallDots];
+#pragma unroll
+  for (int j = 0; j < kSmallDots; ++j) acc[j] = 0.0;
+#pragma unroll
+  for (int i = 0; i < kSmallTiles; ++i) {
+    const bool valid = lo + 64 * (wave + (kCgsThreads / 64) * i) + lane < hi;
+#pragma unroll
+    for (int j = 0; j < kSmallDots; ++j) acc[j] = valid ? __builtin_fma(v[i][j], we[i], acc[j]) : acc[j];
+  }
+#pragma unroll
+  for (int j = 0; j < kSmallDots; ++j) {
+    const double r = cgs_wave_sum(acc[j]);
+    if (lane == 0) red[wave][j] = r;
+  }
+  __syncthreads();
+  const int j = (int)threadIdx.x;
+  if (j < kSmallDots && j0 + j < k) {
+    double s = 0.0;
+#pragma unroll
+    for (int wv = 0; wv < kCgsThreads / 64; ++wv) s += red[wv][j];
+    partial[(long long)(j0 + j) * G + blockIdx.x] = s;
+  }
+}
+
+template <int KR>
+__global__ void __launch_bounds__(kCgsThreads) small_update_kernel(double *__restrict__ w, const double *__restrict__ V,
+                                                                   long long ldv, int k, const double *__restrict__ h,
+                                                                   long long n) {
+  const long long e = blockIdx.x * (long long)kCgsThreads + threadIdx.x;
+  const bool valid = e < n;
+  const cptr<double> hc = as_const(h);
+  const double wold = w[valid ? e : n - 1];
+  double v[KR];
+  load_basis<KR>(V, ldv, k, valid ? e : n - 1, true, v);
+  double s = 0.0;
+#pragma unroll
+  for (int j = 0; j < KR; ++j) s = __builtin_fma(j < k ? hc[j] : 0.0, v[j], s);
+  if (valid) w[e] = wold - s;
+}
+
+__global__ void __launch_bounds__(kCgsThreads) small_norm_kernel(const double *__restrict__ w, long long n,
+                                                                 double *__restrict__ partial) {
+  __shared__ double red[kCgsThreads / 64];
+  const int G = gridDim.x;
+  const long long per = (n + G - 1) / G, lo = (long long)blockIdx.x * per, hi = lo + per < n ? lo + per : n;
+  double v[4096 / kCgsThreads];
+#pragma unroll
+  for (int i = 0; i < 4096 / kCgsThreads; ++i) {
+    const long long e = lo + threadIdx.x + (long long)kCgsThreads * i;
+    v[i] = w[e < hi ? e : n - 1];
+    v[i] = e < hi ? v[i] : 0.0;
+  }
+  double acc = 0.0;
+#pragma unroll
+  for (int i = 0; i < 4096 / kCgsThreads; ++i) acc = __builtin_fma(v[i], v[i], acc);
+  acc = cgs_wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int wv = 0; wv < kCgsThreads / 64; ++wv) s += red[wv];
+    partial[blockIdx.x] = s;
+  }
+}
+
+void launch_small_dots(const double *w, const double *V, long long ldv, int k, long long n, int G, double *partial,
+                       hipStream_t s) {
+  hipLaunchKernelGGL(small_dots_kernel, dim3(G, (k + kSmallDots - 1) / kSmallDots), dim3(kCgsThreads), 0, s, V, ldv, k,
+                     w, n, partial);
+}
+
+void launch_update(double *w, const double *V, long long ldv, int k, const double *h, long long n, hipStream_t s) {
+  with_cgs_width(k, [&](auto width) {
+    hipLaunchKernelGGL(small_update_kernel<decltype(width)::value>, dim3((unsigned)((n + kCgsThreads - 1) / kCgsThreads)),
+                       dim3(kCgsThreads), 0, s, w, V, ldv, k, h, n);
+  });
+}
+
 }  // namespace
 
 bool cgs2_fused_ok(int k) { return k <= kCgsMaxK; }
@@ -152,14 +259,15 @@ bool cgs2_fused_ok(int k) { return k <= kCgsMaxK; }
 void update_dot(double *w, const double *V, long long ldv, int k, const double *h, long long n, double *partial,
                 double *out, hipStream_t s) {
   const int G = reduction_blocks(n);
-  if (k <= kCgsHalf)
-    hipLaunchKernelGGL(update_dot_kernel<kCgsHalf>, dim3(G), dim3(kThreads), 0, s, w, V, ldv, k, h, n, partial);
-  else if (k <= 48)
-    hipLaunchKernelGGL(update_dot_kernel<48>, dim3(G), dim3(kThreads), 0, s, w, V, ldv, k, h, n, partial);
-  else if (k <= 56)
-    hipLaunchKernelGGL(update_dot_kernel<56>, dim3(G), dim3(kThreads), 0, s, w, V, ldv, k, h, n, partial);
-  else
-    hipLaunchKernelGGL(update_dot_kernel<kCgsMaxK>, dim3(G), dim3(kThreads), 0, s, w, V, ldv, k, h, n, partial);
+  if (G <= kSmallRanges) {
+    launch_update(w, V, ldv, k, h, n, s);
+    launch_small_dots(w, V, ldv, k, n, G, partial, s);
+  } else {
+    with_cgs_width(k, [&](auto width) {
+      hipLaunchKernelGGL(update_dot_kernel<decltype(width)::value>, dim3(G), dim3(kCgsThreads), 0, s, w, V, ldv, k, h,
+                         n, partial);
+    });
+  }
   STKKT_HIP(hipGetLastError());
   hipLaunchKernelGGL(reduce_kernel, dim3(k), dim3(kThreads), 0, s, partial, G, out);
   STKKT_HIP(hipGetLastError());
@@ -168,12 +276,15 @@ void update_dot(double *w, const double *V, long long ldv, int k, const double *
 void update_norm(double *w, const double *V, long long ldv, int k, const double *h, long long n, double *partial,
                  double *out, hipStream_t s) {
   const int G = reduction_blocks(n);
-  if (k <= kCgsHalf)
-    hipLaunchKernelGGL(update_norm_kernel<kCgsHalf>, dim3(G), dim3(kThreads), 0, s, w, V, ldv, k, h, n, partial);
-  else if (k <= 48)
-    hipLaunchKernelGGL(update_norm_kernel<48>, dim3(G), dim3(kThreads), 0, s, w, V, ldv, k, h, n, partial);
-  else
-    hipLaunchKernelGGL(update_norm_kernel<kCgsMaxK>, dim3(G), dim3(kThreads), 0, s, w, V, ldv, k, h, n, partial);
+  if (G <= kSmallRanges) {
+    launch_update(w, V, ldv, k, h, n, s);
+    hipLaunchKernelGGL(small_norm_kernel, dim3(G), dim3(kCgsThreads), 0, s, w, n, partial);
+  } else {
+    with_cgs_width(k, [&](auto width) {
+      hipLaunchKernelGGL(update_norm_kernel<decltype(width)::value>, dim3(G), dim3(kCgsThreads), 0, s, w, V, ldv, k, h,
+                         n, partial);
+    });
+  }
   STKKT_HIP(hipGetLastError());
   hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kThreads), 0, s, partial, G, out);
   STKKT_HIP(hipGetLastError());
@@ -189,14 +300,13 @@ int reduction_blocks(long long n) {
 void multidot(const double *V, long long ldv, int k, const double *w, long long n, double *partial, double *out,
               hipStream_t s) {
   const int G = reduction_blocks(n);
-  if (k <= kCgsHalf)
-    hipLaunchKernelGGL(multidot_tiles_kernel<kCgsHalf>, dim3(G), dim3(kCgsThreads), 0, s, V, ldv, k, w, n, partial);
-  else if (k <= 48)
-    hipLaunchKernelGGL(multidot_tiles_kernel<48>, dim3(G), dim3(kCgsThreads), 0, s, V, ldv, k, w, n, partial);
-  else if (k <= 56)
-    hipLaunchKernelGGL(multidot_tiles_kernel<56>, dim3(G), dim3(kCgsThreads), 0, s, V, ldv, k, w, n, partial);
+  if (G <= kSmallRanges)
+    launch_small_dots(w, V, ldv, k, n, G, partial, s);
   else if (k <= kCgsMaxK)
-    hipLaunchKernelGGL(multidot_tiles_kernel<kCgsMaxK>, dim3(G), dim3(kCgsThreads), 0, s, V, ldv, k, w, n, partial);
+    with_cgs_width(k, [&](auto width) {
+      hipLaunchKernelGGL(multidot_tiles_kernel<decltype(width)::value>, dim3(G), dim3(kCgsThreads), 0, s, V, ldv, k, w,
+                         n, partial);
+    });
   else
     hipLaunchKernelGGL(multidot_kernel, dim3(G), dim3(kThreads), 0, s, V, ldv, k, w, n, partial);
   STKKT_HIP(hipGetLastError());
