@@ -43,7 +43,7 @@ namespace stkkt {
 // planes share one barrier.  About 300 FP64 operations and 42 LDS doubles per
 // column and plane; summing 27 neighbours per node from LDS took 162 LDS
 // doubles and a table of 27 entries per node, and left the vector units idle
-// two thirds of the time (cube48x96 581 us).
+// two thirds of the time (cube48x96 581 us, this 307).
 //
 // The solvers keep matvec_device's form, the sum over 27 neighbours: a change
 // in the order of the sums comes out of a long restarted solve with FP32

@@ -304,7 +304,9 @@ __global__ void __launch_bounds__(256) factor_kernel(OpDev op, const SubInfo *__
 // What bounds it: the LDS reads (72 B per block product, about 760 a row) and
 // the waits between the 26 pieces, which the second workgroup fills; below
 // them the U blocks read, about 30 KB per row from HBM (a row's own blocks are
-// 6 KB), since a box's window of lines does not fit in L2.
+// 6 KB), since a box's window of lines does not fit in L2.  24^3 x 48 in 108
+// boxes: 19.5 ms; with a thread per row, the rows of a point level in parallel,
+// 157 ms.  Boxes over 54 nodes long keep that form (factor_kernel).
 constexpr int kFlUnits0 = 63, kFlUnits1 = 122;   // 16-byte units per row: slots 40..53, 54..80
 template <int ROWS> struct FlCfg {
   static constexpr int threads = ROWS > 28 ? 512 : 256;
@@ -655,7 +657,7 @@ __device__ inline void store_block(float *g, int64_t k, int64_t cnt, const doubl
 // coalesced reads and are turned around in LDS, where lane = row.  Bound by
 // the bytes of W read and F written.  Every box gets kCompactSplit workgroups
 // (its levels in turn): with one per box and each lane reading its own row the
-// 24^3 x 48 case (108 boxes, 14 GB) took 7.1 ms.
+// 24^3 x 48 case (108 boxes, 14 GB) took 7.1 ms, now 5.5.
 constexpr int kCompactSplit = 16;
 template <typename T>
 __global__ void __launch_bounds__(256) compact_kernel(const SubInfo *__restrict__ subs,
@@ -1581,7 +1583,9 @@ static int ring_rows(const ras *R) {
 // The form that runs, for the given rows per phase and most rows of a level:
 // a level of at most 64 rows is one chunk, so phases of 256 rows would be the
 // same phases with the branches of longer ones; with at most 32 rows two slots
-// share a load.
+// share a load (cube8x16, 20 rows a level, FP64: an apply of 390 us against 546
+// with one slot a load; of fatter boxes 64-row phases brought nothing, FP32 24^3 x
+// 48 1093 us against 1092 with 256 rows).
 struct RingForm {
   int kr, pack;
 };
