@@ -654,11 +654,12 @@ __device__ inline void store_block(float *g, int64_t k, int64_t cnt, const doubl
 
 // W (rows of 81 blocks) into the chunk-major layout.  A workgroup takes nine
 // slots of one 64-row chunk at a time: the rows' 648 bytes come in with
-// coalesced reads and are turned around in LDS, where lane = row.  Bound by
-// the bytes of W read and F written.  Every box gets kCompactSplit workgroups
-// (its levels in turn): with one per box and each lane reading its own row the
-// 24^3 x 48 case (108 boxes, 14 GB) took 7.1 ms, now 5.5.
-constexpr int kCompactSplit = 16;
+// coalesced reads, on their way while the nine slots before are stored, and are
+// turned around in LDS, where lane = row.  Bound by the bytes of W read and F
+// written (14 GB at 24^3 x 48 in 108 boxes, 3.1 ms; 5.5 with the loads after the
+// stores; 7.1 with one workgroup per box and each lane reading its own row).
+// Every box gets kCompactSplit workgroups (its levels in turn).
+constexpr int kCompactSplit = 16, kCompactLoads = (64 * 81 + 255) / 256;
 template <typename T>
 __global__ void __launch_bounds__(256) compact_kernel(const SubInfo *__restrict__ subs,
                                                       const ShapeInfo *__restrict__ shapes,
@@ -682,21 +683,33 @@ __global__ void __launch_bounds__(256) compact_kernel(const SubInfo *__restrict_
       if (lane < rows) unpack(coords[sh.coord_off + r0 + 64 * c + lane], x, y, z, t);
       __syncthreads();
       if (wave == 0) rhos[lane] = x + lx * (y + ly * (z + lz * t));
-      for (int g = 0; g < 9; ++g) {
-        __syncthreads();   // rhos written, the previous tile read
-        for (int q = tid; q < rows * 81; q += 256) {
-          const int rr = q / 81, e = q - 81 * rr;
-          tile[q] = Wb[(long long)rhos[rr] * kWStride + 81 * g + e];
+      __syncthreads();   // rhos written
+      const int n = rows * 81;
+      double pre[kCompactLoads];   // the next nine slots, on their way while the current ones are stored
+      auto request = [&](int g) {
+#pragma unroll
+        for (int i = 0; i < kCompactLoads; ++i) {
+          const int q = min(tid + 256 * i, n - 1), rr = q / 81;
+          pre[i] = Wb[(long long)rhos[rr] * kWStride + 81 * g + (q - 81 * rr)];
         }
+      };
+      request(0);
+      for (int g = 0; g < 9; ++g) {
+        __syncthreads();   // the previous tile read
+#pragma unroll
+        for (int i = 0; i < kCompactLoads; ++i)
+          if (tid + 256 * i < n) tile[tid + 256 * i] = pre[i];
         __syncthreads();
+        if (g < 8) request(g + 1);
         for (int j = wave; j < 9; j += 4) {
           const int s = 9 * g + j;
           int dx, dy, dz, dt;
           slot_off(s, dx, dy, dz, dt);
           const bool has = lane < rows && inside(x + dx, y + dy, z + dz, t + dt, sh.dims);
           const unsigned long long mask = __ballot(has);
+          // through the scalar cache: a vector load would wait for the requests ahead of it
+          const cptr<int32_t> ct = as_const(ctab) + sh.ct_off + (((int64_t)L * sh.nchunk + c) * 81 + s) * 2;
           if (has) {
-            const int32_t *ct = ctab + sh.ct_off + (((int64_t)L * sh.nchunk + c) * 81 + s) * 2;
             store_block(F + sd.fbase + ct[0], (int64_t)lanes_below(mask), (int64_t)ct[1], tile + 81 * lane + 9 * j);
           }
         }
