@@ -5,6 +5,15 @@
 
 namespace stkkt {
 
+// a . b with the roundings written out, so that every kernel that forms it
+// gives the same bits.
+__device__ inline float dot3(float a0, float a1, float a2, float b0, float b1, float b2) {
+  return __builtin_fmaf(a2, b2, __builtin_fmaf(a0, b0, a1 * b1));
+}
+__device__ inline double dot3(double a0, double a1, double a2, double b0, double b1, double b2) {
+  return __builtin_fma(a2, b2, __builtin_fma(a0, b0, a1 * b1));
+}
+
 // Inverse of a row-major 3x3 block by Gauss-Jordan elimination with partial
 // pivoting on [a | I]; ok = false for a singular block.
 __device__ inline void inv33_pivot(const double *a, double *out, bool &ok) {
@@ -34,7 +43,7 @@ __device__ inline void inv33_pivot(const double *a, double *out, bool &ok) {
     for (int r = 0; r < 3; ++r) {
       if (r == col) continue;
       const double f = m[r][col];
-      for (int c = 0; c < 6; ++c) m[r][c] -= f * m[col][c];
+      for (int c = 0; c < 6; ++c) m[r][c] = __builtin_fma(-f, m[col][c], m[r][c]);
     }
   }
   for (int r = 0; r < 3; ++r)

@@ -254,7 +254,7 @@ __global__ void __launch_bounds__(256) factor_kernel(OpDev op, const SubInfo *__
           }
           for (int a = 0; a < 3; ++a)
             for (int b = 0; b < 3; ++b)
-              acc[3 * a + b] -= l[3 * a] * u[b] + l[3 * a + 1] * u[3 + b] + l[3 * a + 2] * u[6 + b];
+              acc[3 * a + b] -= dot3(l[3 * a], l[3 * a + 1], l[3 * a + 2], u[b], u[3 + b], u[6 + b]);
         }
         if (st < 40) {
           const long long rt = rho + tx + (long long)lx * (ty + (long long)ly * (tz + (long long)lz * tt));
@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(256) factor_kernel(OpDev op, const SubInfo *__
           for (int e = 0; e < 9; ++e) d[e] = D[e];
           for (int a = 0; a < 3; ++a)
             for (int b = 0; b < 3; ++b)
-              o[3 * a + b] = acc[3 * a] * d[b] + acc[3 * a + 1] * d[3 + b] + acc[3 * a + 2] * d[6 + b];
+              o[3 * a + b] = dot3(acc[3 * a], acc[3 * a + 1], acc[3 * a + 2], d[b], d[3 + b], d[6 + b]);
           for (int e = 0; e < 9; ++e) acc[e] = o[e];
         } else if (st == 40) {
           double o[9];
@@ -331,7 +331,7 @@ __device__ inline void mul_blk(const double (&a)[9], const double (&b)[9], doubl
 #pragma unroll
   for (int r = 0; r < 3; ++r)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) o[3 * r + c] = a[3 * r] * b[c] + a[3 * r + 1] * b[3 + c] + a[3 * r + 2] * b[6 + c];
+    for (int c = 0; c < 3; ++c) o[3 * r + c] = dot3(a[3 * r], a[3 * r + 1], a[3 * r + 2], b[c], b[3 + c], b[6 + c]);
 }
 
 __device__ inline void sub_mul_blk(double (&acc)[9], const double (&l)[9], const double (&u)[9]) {
@@ -339,7 +339,7 @@ __device__ inline void sub_mul_blk(double (&acc)[9], const double (&l)[9], const
   for (int r = 0; r < 3; ++r)
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-      acc[3 * r + c] -= l[3 * r] * u[c] + l[3 * r + 1] * u[3 + c] + l[3 * r + 2] * u[6 + c];
+      acc[3 * r + c] -= dot3(l[3 * r], l[3 * r + 1], l[3 * r + 2], u[c], u[3 + c], u[6 + c]);
 }
 
 // one thread's row position in the workgroup and its target column (dx, dy)
@@ -1153,14 +1153,6 @@ __device__ inline void load_group(const RingArgs<T> &a, const Chk &q, const uint
     load_block_at(base, kQuad * k + b0, kQuad * k + b1, (unsigned)sizeof(T) * k + b2, f);
     go = go1 + group_bytes(c1);
   }
-}
-
-// a . b with the roundings written out, so that every form of the sweeps gives the same bits.
-__device__ inline float dot3(float a0, float a1, float a2, float b0, float b1, float b2) {
-  return __builtin_fmaf(a2, b2, __builtin_fmaf(a0, b0, a1 * b1));
-}
-__device__ inline double dot3(double a0, double a1, double a2, double b0, double b1, double b2) {
-  return __builtin_fma(a2, b2, __builtin_fma(a0, b0, a1 * b1));
 }
 
 // The value of lane + 32 (in lanes 0..31).

@@ -78,7 +78,9 @@ __host__ __device__ inline double stiff_var(const OpDev &op, int jx, int jy, int
           ke[a] = (lj == li ? 1.0 : -1.0) / op.h[a];
         }
         double ae = op.a_elem[(long long)ex + (long long)op.n[0] * (ey + (long long)op.n[1] * ez)];
-        s += ae * (ke[0] * me[1] * me[2] + me[0] * ke[1] * me[2] + me[0] * me[1] * ke[2]);
+        const double k = __builtin_fma(me[0] * me[1], ke[2],
+                                       __builtin_fma(me[0] * ke[1], me[2], ke[0] * me[1] * me[2]));
+        s = __builtin_fma(ae, k, s);
       }
   return s;
 }
@@ -99,12 +101,12 @@ __host__ __device__ inline SpatialCoef spatial_coef_with(const OpDev &op, int jx
   const double kz = stiff1(op.h[2], jz, dz, op.nn[2]);
   SpatialCoef c;
   c.B = mx * my * mz;
-  c.K = kx * my * mz + mx * ky * mz + mx * my * kz;
-  c.N = op.v[0] * conv1(jx, dx, op.nn[0]) * my * mz + op.v[1] * mx * conv1(jy, dy, op.nn[1]) * mz +
-        op.v[2] * mx * my * conv1(jz, dz, op.nn[2]);
-  c.Nt = op.v[0] * conv1(jx + dx, -dx, op.nn[0]) * my * mz +
-         op.v[1] * mx * conv1(jy + dy, -dy, op.nn[1]) * mz +
-         op.v[2] * mx * my * conv1(jz + dz, -dz, op.nn[2]);
+  c.K = __builtin_fma(mx * my, kz, __builtin_fma(kx * my, mz, mx * ky * mz));
+  auto conv = [&](double cx, double cy, double cz) {
+    return __builtin_fma(op.v[2] * mx * my, cz, __builtin_fma(op.v[0] * cx * my, mz, op.v[1] * mx * cy * mz));
+  };
+  c.N = conv(conv1(jx, dx, op.nn[0]), conv1(jy, dy, op.nn[1]), conv1(jz, dz, op.nn[2]));
+  c.Nt = conv(conv1(jx + dx, -dx, op.nn[0]), conv1(jy + dy, -dy, op.nn[1]), conv1(jz + dz, -dz, op.nn[2]));
   c.A = a_entry;
   return c;
 }
@@ -128,8 +130,8 @@ __host__ __device__ inline void kkt_block_c(const OpDev &op, const SpatialCoef &
   const int M = op.M;
   const double ht = 0.5 * tau;
   const double sens = same ? op.sensor[(long long)jx + (long long)op.nn[0] * (jy + (long long)op.nn[1] * jz)] : 0.0;
-  const double A1 = c.B + ht * (c.A + c.N), A2 = -c.B + ht * (c.A + c.N);
-  const double A1t = c.B + ht * (c.A + c.Nt), A2t = -c.B + ht * (c.A + c.Nt);
+  const double A1 = __builtin_fma(ht, c.A + c.N, c.B), A2 = __builtin_fma(ht, c.A + c.N, -c.B);
+  const double A1t = __builtin_fma(ht, c.A + c.Nt, c.B), A2t = __builtin_fma(ht, c.A + c.Nt, -c.B);
   const double idn = (same && dt == 0) ? 1.0 : 0.0;
   // C-slot row: state equation
   if (n == 0) {
@@ -139,8 +141,8 @@ __host__ __device__ inline void kkt_block_c(const OpDev &op, const SpatialCoef &
     if (dt == 0 || dt == -1) out[2] = -Pj * ht * c.B;
   }
   // f-slot row: regularisation block W (beta2 with K, or with B for H1-L2)
-  out[8] = op.beta1 * tstiff(tau, n, dt, M) * c.B +
-           op.beta2 * tmass(tau, n, dt, M) * (op.reg == STKKT_REG_H1L2 ? c.B : c.K);
+  out[8] = __builtin_fma(op.beta1 * tstiff(tau, n, dt, M), c.B,
+                         op.beta2 * tmass(tau, n, dt, M) * (op.reg == STKKT_REG_H1L2 ? c.B : c.K));
   if (op.variant == STKKT_DTO) {
     if (dt == 0) out[3] = wtrap(tau, n, M) * sens;
     double g = Qj * idn;
