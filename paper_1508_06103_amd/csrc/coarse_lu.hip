@@ -679,7 +679,10 @@ __global__ void __launch_bounds__(kUpdThreads, 4) gje_update_kernel(int n, int k
 //     workgroup that owns K (P D)^{-1} itself, and perm and the panel's
 //     entries of piv.
 // Every workgroup inverts the same block to the same bits.  A zero or
-// non-finite pivot sets status 1, and later launches do nothing.
+// non-finite pivot sets *failed, and later launches do nothing: the word that a
+// launch tests is the one its predecessor wrote and nobody writes meanwhile, so
+// that all wavefronts of all its workgroups decide alike (they share barriers
+// and the order of the pivots in LDS).
 //
 // The other workgroups update the tiles of all columns outside K by the
 // previous panel, whose rows are read in the order of its pivots (permp); its
@@ -740,7 +743,7 @@ __device__ inline void bp_product(const double *X, const double *Y, f64x4 (&acc)
 __device__ inline void panel_rows_step(int n, int kp, int ep, int k, int e, const double *__restrict__ O,
                                        double *__restrict__ N, const int32_t *__restrict__ permp,
                                        int32_t *__restrict__ perm, int32_t *__restrict__ piv,
-                                       int *__restrict__ status) {
+                                       int *__restrict__ failed) {
   extern __shared__ double upd_lds[];
   __shared__ int step_of[kPanel], row_of[kPanel];   // the step that took a row as its pivot row, and the reverse
   double *Sa = upd_lds, *Sb = Sa + kPanel * kBpLd;
@@ -834,7 +837,7 @@ __device__ inline void panel_rows_step(int n, int kp, int ep, int k, int e, cons
         const unsigned key = myq >= 0 ? 0u : (hi & ~127u) | 64u | (unsigned)(63 - lane);
         const int p = 63 - (int)(wave_max_u32(key) & 63u);
         const double a = lane_value(m[jj], p), inv = 1.0 / a;
-        if (lane == 0 && (!(fabs(a) > 0.0) || !std::isfinite(a))) *status = 1;
+        if (lane == 0 && (!(fabs(a) > 0.0) || !std::isfinite(a))) *failed = 1;
         const bool isp = lane == p;
         const double g = isp ? inv : -m[jj] * inv;
         if (isp) myq = b0 + jj;
@@ -933,10 +936,14 @@ __global__ void __launch_bounds__(kBpThreads, 4) gje_block_step_kernel(int n, in
                                                                        const int32_t *__restrict__ permp,
                                                                        int32_t *__restrict__ perm,
                                                                        int32_t *__restrict__ piv,
-                                                                       int *__restrict__ status) {
-  if (*status) return;   // permp is then incomplete
+                                                                       const int *__restrict__ failed_before,
+                                                                       int *__restrict__ failed) {
+  if (*failed_before) {   // permp is then incomplete
+    if (blockIdx.x == 0 && threadIdx.x == 0) *failed = 1;
+    return;
+  }
   if ((int)blockIdx.x < npan) {
-    panel_rows_step(n, kp, ep, k, e, O, N, permp, perm, piv, status);
+    panel_rows_step(n, kp, ep, k, e, O, N, permp, perm, piv, failed);
     return;
   }
   const int nt = (n + kUpdTile - 1) / kUpdTile, t = (int)blockIdx.x - npan;
@@ -1275,8 +1282,9 @@ struct LookAhead {
 // rows: 2 x kPanel x n scratch (the rows of two consecutive panels); pan:
 // kPanel x n scratch (the launch-per-column path's panel); swp: 2 kPanel int32
 // (with block pivoting the pivot orders of two consecutive panels); piv: n
-// int32; gs: candidate tables for ceil(n / 64) workgroups; la: the look-ahead's
-// side stream and events.
+// int32; gs: candidate tables for ceil(n / 64) workgroups; status: two words,
+// zero before the first of all calls, one of them not zero after a failure
+// (block pivoting alternates them); la: the look-ahead's side stream and events.
 static double *gje_invert(int n, double *A, double *tmp, double *rows, double *pan, double *fcol, int32_t *piv,
                        int32_t *swp, double *prow, const GjSync &gs, int *status, const LookAhead &la,
                        hipStream_t s) {
@@ -1306,13 +1314,15 @@ static double *gje_invert(int n, double *A, double *tmp, double *rows, double *p
   };
   if (block) {
     // One launch per panel: the previous panel's update beside the panel.  The
-    // first only copies beside panel 0, the last only updates.
+    // first only copies beside panel 0, the last only updates (and hands on a
+    // failure, so that the next call finds it in both words).
     double *from = A, *to = tmp;
     for (int k = 0, kp = 0, p = 0; kp < n; ++p) {
       const int e = std::min(n, k + kPanel), npan = k < n ? (n + kPanel - 1) / kPanel : 0;
       const size_t lds = mt * nt <= kStepOneTiles ? kStepLdsOne : kStepLdsTwo;
       hipLaunchKernelGGL(gje_block_step_kernel, dim3(npan + mt * nt), dim3(kBpThreads), lds, s, n, npan, kp, k, k, e,
-                         from, to, swp + ((p + 1) & 1) * kPanel, swp + (p & 1) * kPanel, piv, status);
+                         from, to, swp + ((p + 1) & 1) * kPanel, swp + (p & 1) * kPanel, piv, status + ((p + 1) & 1),
+                         status + (p & 1));
       std::swap(from, to);
       kp = k;
       k = e;
@@ -1415,7 +1425,7 @@ CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStr
   const unsigned spin = spin_env ? (unsigned)std::max(0, std::atoi(spin_env)) : kGjSpinLimit;
   const GjSync gs{candv.as<double>(), candi.as<int32_t>(), candrow.as<double>(), crow.as<double>(),
                   bar.as<unsigned>(), reinterpret_cast<int *>(bar.as<unsigned char>() + 128), spin};
-  STKKT_HIP(hipMemsetAsync(status.ptr, 0, sizeof(int), s));
+  STKKT_HIP(hipMemsetAsync(status.ptr, 0, 2 * sizeof(int), s));
   const int G = blocks_for(27LL * d.N, 128, 4096);
   const dim3 g2(blocks_for(nb_, 256, 64), d.N);
   const LookAhead la;
@@ -1467,11 +1477,11 @@ CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStr
     }
     STKKT_HIP(hipGetLastError());
   }
-  int st = 0;
-  STKKT_HIP(hipMemcpyAsync(&st, status.ptr, sizeof(int), hipMemcpyDeviceToHost, s));
+  int st[2] = {0, 0};
+  STKKT_HIP(hipMemcpyAsync(st, status.ptr, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
   STKKT_HIP(hipStreamSynchronize(s));   // the setup buffers are released on return
-  if (st == 2) throw Error(STKKT_EHIP, "coarse LU: panel elimination barrier timed out");
-  if (st) throw Error(STKKT_EBREAKDOWN, "coarse LU: singular Schur complement block");
+  if (st[0] == 2) throw Error(STKKT_EHIP, "coarse LU: panel elimination barrier timed out");
+  if (st[0] || st[1]) throw Error(STKKT_EBREAKDOWN, "coarse LU: singular Schur complement block");
 }
 
 // partial = chunk sums of A times the input, q right-hand sides (one on the GEMV when `gemv`)
