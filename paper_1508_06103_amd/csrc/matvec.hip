@@ -1,8 +1,11 @@
 // The operator application of the public entry point, in element modes.
+#include <cmath>
 #include <type_traits>
 #include <vector>
 
 #include "common.hpp"
+#include "matvec_rows.hpp"
+#include "stencil.hpp"
 
 namespace stkkt {
 
@@ -45,6 +48,12 @@ namespace stkkt {
 // doubles and a table of 27 entries per node, and left the vector units idle
 // two thirds of the time (cube48x96 581 us, this 307).
 //
+// In modes an infinite entry meets itself with both signs, and sums of eight
+// values overflow before their weights bring them down.  Entries that come out
+// non-finite are therefore formed again at the end of the march, as the sum
+// over the neighbours: it alone decides what is infinite and what is not a
+// number.
+//
 // The solvers keep matvec_device's form, the sum over 27 neighbours: a change
 // in the order of the sums comes out of a long restarted solve with FP32
 // preconditioners enlarged to 5e-9 of the solution (24^3 x 32, 145 steps).
@@ -67,9 +76,13 @@ struct MvModes {
   } lv[3];
   double ht, beta1, beta2;
   int l2, pad;   // H1-L2 regularisation: beta2 (Tt f) joins U3 (mass) instead of T3 (stiffness)
+  // of the sum over neighbours
+  MvConst sums;
+  OpDev op;
+  const double *atab;
 };
 
-MvModes make_mv_modes(const OpDev &d) {
+MvModes make_mv_modes(const OpDev &d, const double *atab) {
   MvModes c{};
   double m[3][2], k[3][2];
   for (int a = 0; a < 3; ++a) {
@@ -105,6 +118,9 @@ MvModes make_mv_modes(const OpDev &d) {
   c.beta1 = d.beta1;
   c.beta2 = d.beta2;
   c.l2 = d.reg == STKKT_REG_H1L2;
+  c.sums = make_mv_const(d);
+  c.op = d;
+  c.atab = atab;
   return c;
 }
 
@@ -120,13 +136,63 @@ __device__ inline void face_modes(double a, double b, double c, double e, double
   m[3] = d0 - d1;
 }
 
+// Row (n, j), j = (jx, jy, jz), of y as the sum over the neighbours; xn and yn:
+// level n of x and y.
+__device__ inline void row_by_neighbours(const OpDev &op, const MvConst &mc, const double *__restrict__ atab,
+                                         const double *__restrict__ xn, double *yn, int n, int jx, int jy,
+                                         int jz) {
+  const int M = op.M;
+  const long long N = op.N, j = jx + (long long)op.nn[0] * (jy + (long long)op.nn[1] * jz);
+  const bool dto = op.variant == STKKT_DTO, hm = n >= 1, hp = n < M, tend = !hm || !hp;
+  const double stm = hm ? -mc.inv_tau : 0.0, st0 = tend ? mc.inv_tau : 2.0 * mc.inv_tau, stp = hp ? -mc.inv_tau : 0.0;
+  const double ttm = hm ? mc.tau6 : 0.0, tt0 = tend ? mc.tau3 : 2.0 * mc.tau3, ttp = hp ? mc.tau6 : 0.0;
+  auto at = [&](int dy, int dz, double2 (&r)[9]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const int gx = jx + i - 1, gy = jy + dy, gz = jz + dz;
+      r[3 * i] = r[3 * i + 1] = r[3 * i + 2] = make_double2(0.0, 0.0);
+      if (gx < 0 || gx >= op.nn[0] || gy < 0 || gy >= op.nn[1] || gz < 0 || gz >= op.nn[2]) continue;
+      const double *p0 = xn + 3 * (gx + (long long)op.nn[0] * (gy + (long long)op.nn[1] * gz));
+      const double *pm = hm ? p0 - 3 * N : p0, *pp = hp ? p0 + 3 * N : p0;
+      const double P = on_dirichlet(op, gx, gy, gz) ? 0.0 : 1.0;
+      const double cm = hm ? pm[0] : 0.0, gm = hm ? pm[1] : 0.0, fm = hm ? pm[2] : 0.0;
+      const double gp = hp ? pp[1] : 0.0, fp = hp ? pp[2] : 0.0;
+      const double c0 = p0[0], g0 = p0[1], f0 = p0[2], gn = !dto || hm ? g0 : 0.0;
+      const double S2 = P * (gn + gp), ttf = mc.beta2 * (ttm * fm + tt0 * f0 + ttp * fp);
+      const double U3 = mc.beta1 * (stm * fm + st0 * f0 + stp * fp) -
+                        (dto ? mc.ht * S2 : P * (ttm * gm + tt0 * g0 + ttp * gp));
+      r[3 * i] = make_double2(P * (c0 - cm) - mc.ht * (fm + f0), P * (c0 + cm));
+      r[3 * i + 1] = make_double2(P * (gn - gp), S2);
+      r[3 * i + 2] = mc.l2 ? make_double2(U3 + ttf, 0.0) : make_double2(U3, ttf);
+    }
+  };
+  const RowSums q = neighbour_sums(mc, axis_centre(mc, 0, jx, op.nn[0]), axis_centre(mc, 1, jy, op.nn[1]),
+                                   axis_centre(mc, 2, jz, op.nn[2]), atab + 27 * j, at);
+  const bool Pj = !on_dirichlet(op, jx, jy, jz);
+  const double sens = op.sensor[j], cj = xn[3 * j], gj = xn[3 * j + 1];
+  double *ys = yn + 3 * j;
+  ys[0] = (n == 0 || !Pj) ? cj : q.aC + mc.ht * q.sC;
+  double g = gj;
+  if (Pj && dto) g = q.aG + mc.ht * q.sG + (n == 0 ? gj : 0.0) + (tend ? mc.ht : 2.0 * mc.ht) * sens * cj;
+  else if (Pj && hp) g = q.aG + mc.ht * q.sG + mc.ht * sens * (cj + xn[3 * (N + j)]);
+  ys[1] = g;
+  ys[2] = q.aF;
+}
+
 // One (tile, z chunk, time level) work item w of one operator.  The constants
 // are read again every plane (scalar loads): kept in scalar registers they
 // spill to vector lanes.
 template <int T>
-__device__ inline void march_item(const OpDev &op, const MvMarch &tl, cptr<MvModes> mc, const double *__restrict__ x,
-                                    double *__restrict__ y, int w) {
+__device__ inline void march_item(const OpDev &op, const MvMarch &tl, const MvModes *modes,
+                                  const double *__restrict__ x, double *y, int w) {
   extern __shared__ double2 mv_lds[];
+  // what the end of the march needs again waits in memory: scalar registers are short during it
+  __shared__ struct {
+    const double *x;
+    double *y;
+    int n, z0, z1;
+  } late;
+  const cptr<MvModes> mc = as_const(modes);
   const int t = (int)threadIdx.x;
   const int M = op.M, nlev = M + 1;
   const int n = w % nlev, item = w / nlev, tile = item % tl.ntiles, zc = item / tl.ntiles;
@@ -160,6 +226,13 @@ __device__ inline void march_item(const OpDev &op, const MvMarch &tl, cptr<MvMod
   };
   // LDS: two buffers of [3][T] field pairs, two of [9][T] corner values.  The
   // neighbours' places are clamped where there is no neighbour (unused then).
+  if (t == 0) {   // (read after the barriers of the planes)
+    late.x = x;
+    late.y = y;
+    late.n = n;
+    late.z0 = z0;
+    late.z1 = z1;
+  }
   double2 *const fb0 = mv_lds;
   double *const cb0 = reinterpret_cast<double *>(mv_lds + 6 * T);
   const int tr = min(t + 1, T - 1), tu = min(t + hx, T - 1), tur = min(t + hx + 1, T - 1);
@@ -195,6 +268,7 @@ __device__ inline void march_item(const OpDev &op, const MvMarch &tl, cptr<MvMod
   // node values needed when the plane is written, two planes later: c, g, and
   // c^{n+1} (OTD sensor term)
   double c_a = 0.0, g_a = 0.0, e_a = 0.0, c_b = 0.0, g_b = 0.0, e_b = 0.0;
+  double check = 0.0;   // not a number once a value written is not finite
   // Plane p.  kFields: its fields are needed (p <= pb); kLayer: the element
   // layer between planes p - 1 and p exists (pa < p <= pb); par: (p - pa) & 1.
   auto plane_step = [&](int p, auto kf, auto kl, auto par) {
@@ -209,14 +283,14 @@ __device__ inline void march_item(const OpDev &op, const MvMarch &tl, cptr<MvMod
       const bool dn = dirichlet(p);
       const double cm = hm ? rm.x : 0.0, gm = hm ? rm.y : 0.0, fmv = hm ? fm : 0.0;
       const double gn = mflag ? gr : 0.0, gp = hp ? rp.y : 0.0, fpv = hp ? fp : 0.0;
-      const double S2 = dn ? 0.0 : gn + gp;
+      const double P = dn ? 0.0 : 1.0, S2 = P * (gn + gp);
       const double stf = st0 * fmv + st1 * f0 + st2 * fpv;
       const double ttf = beta2 * (tt0 * fmv + tt1 * f0 + tt2 * fpv);
       double U3 = beta1 * stf;
       if (dto) U3 -= ht * S2;
-      else U3 -= dn ? 0.0 : tt0 * gm + tt1 * gr + tt2 * gp;
-      fb[t] = make_double2((dn ? 0.0 : cn - cm) - ht * (fmv + f0), dn ? 0.0 : cn + cm);
-      fb[T + t] = make_double2(dn ? 0.0 : gn - gp, S2);
+      else U3 -= P * (tt0 * gm + tt1 * gr + tt2 * gp);
+      fb[t] = make_double2(P * (cn - cm) - ht * (fmv + f0), P * (cn + cm));
+      fb[T + t] = make_double2(P * (gn - gp), S2);
       fb[2 * T + t] = l2 ? make_double2(U3 + ttf, 0.0) : make_double2(U3, ttf);
     }
     // corners of plane p - 2 that belong to other columns
@@ -311,7 +385,9 @@ __device__ inline void march_item(const OpDev &op, const MvMarch &tl, cptr<MvMod
         g = hp ? q1 + ht * sens_o * (c_o + e_o) : g_o;
       }
       char *ys = reinterpret_cast<char *>(y + n * level + o * plane);
-      *reinterpret_cast<mv_d2 *>(ys + vo) = mv_d2{(!hm || dn) ? c_o : q0, g};
+      const double c = (!hm || dn) ? c_o : q0;
+      check = __builtin_fma(c, 0.0, __builtin_fma(g, 0.0, __builtin_fma(q2, 0.0, check)));
+      *reinterpret_cast<mv_d2 *>(ys + vo) = mv_d2{c, g};
       *reinterpret_cast<double *>(ys + vo + 16) = q2;
     }
   };
@@ -330,12 +406,25 @@ __device__ inline void march_item(const OpDev &op, const MvMarch &tl, cptr<MvMod
   }
 #pragma unroll 1
   for (; p <= z1 + 1; ++p) plane_step(p, std::false_type{}, std::false_type{}, (p - pa) & 1);
+  if (check != check) {
+    const MvConst sums = load_uniform(&modes->sums);
+    const OpDev full = load_uniform(&modes->op);
+    const int nl = late.n, ze = late.z1;
+    const double *xn = late.x + nl * 3LL * full.N;
+    double *yn = late.y + nl * 3LL * full.N;
+#pragma unroll 1
+    for (int z = late.z0; z < ze; ++z) {
+      const double *ys = yn + 3 * (gx + (long long)full.nn[0] * (gy + (long long)full.nn[1] * z));
+      if (!std::isfinite(ys[0]) || !std::isfinite(ys[1]) || !std::isfinite(ys[2]))
+        row_by_neighbours(full, sums, modes->atab, xn, yn, nl, gx, gy, z);
+    }
+  }
 }
 
 template <int T>
 __global__ void __launch_bounds__(T, 2) matvec_march_kernel(OpDev op, MvMarch tl, const MvModes *__restrict__ mc,
-                                                               const double *__restrict__ x, double *__restrict__ y) {
-  march_item<T>(op, tl, as_const(mc), x, y, xcd_work_index());
+                                                            const double *__restrict__ x, double *y) {
+  march_item<T>(op, tl, mc, x, y, xcd_work_index());
 }
 
 }  // namespace
@@ -371,7 +460,7 @@ MvMarch choose_matvec_march(const OpDev &d) {
 }
 
 void matvec_constants(kkt_op *op, hipStream_t s) {
-  const MvModes c = make_mv_modes(op->d);
+  const MvModes c = make_mv_modes(op->d, op->atab.as<double>());
   const char *p = reinterpret_cast<const char *>(&c);
   op->mvc_host.assign(p, p + sizeof(c));
   op->mvc = DevBuf(&op->al, sizeof(c));
