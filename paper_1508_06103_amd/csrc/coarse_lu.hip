@@ -669,12 +669,12 @@ __global__ void __launch_bounds__(kUpdThreads, 4) gje_update_kernel(int n, int k
 //     their loads requested up front;
 //  2. inverts D in LDS, sixteen columns at a time: the first wavefront holds
 //     them in registers (lane r: row r).  Step j takes the pivot row p of column
-//     j among the rows not yet used (a lane reduction over the leading 25 bits
-//     of |entry|, so a pivot is at least 1 - 2^-13 of the largest) and
-//     eliminates column j from its sixteen columns.  All wavefronts then bring
-//     the other 48 columns up to date with a rank-16 product.  Rows are not
-//     exchanged: row p_j of the result is row j of (P D)^{-1}, P the order of
-//     the pivots;
+//     j among the rows not yet used (the largest |entry|, the smallest row on
+//     ties: a lane reduction over the high words, and one over the low words
+//     where several rows have the same) and eliminates column j from its
+//     sixteen columns.  All wavefronts then bring the other 48 columns up to
+//     date with a rank-16 product.  Rows are not exchanged: row p_j of the
+//     result is row j of (P D)^{-1}, P the order of the pivots;
 //  3. writes -(its panel segment) (P D)^{-1} into N (one more product), the
 //     workgroup that owns K (P D)^{-1} itself, and perm and the panel's
 //     entries of piv.
@@ -688,9 +688,10 @@ __global__ void __launch_bounds__(kUpdThreads, 4) gje_update_kernel(int n, int k
 // previous panel, whose rows are read in the order of its pivots (permp); its
 // own columns are copied.
 //
-// The 64 pivot steps are a serial chain and bound the launch: 0.3 us a step,
-// 25 of the panel's 37 us at n = 2187 (8 us for the loads and products before
-// them); the launch takes 43 us, the update's tiles beside the panel.  Held in
+// The inversion is a serial chain and bounds the launch: 25 of the panel's 37
+// us at n = 2187, 64 pivot steps of about 0.3 us with four rank-16 products
+// between them (8 us for the loads and products before); the launch takes 43
+// us, the update's tiles beside the panel.  Held in
 // one wavefront's registers a step needs no barrier and no LDS.  Spread over
 // the eight wavefronts, with launches of their own for the update (on a second
 // stream) and for the panel's rows, a panel took 81 us; with the own rows'
@@ -833,9 +834,15 @@ __device__ inline void panel_rows_step(int n, int kp, int ep, int k, int e, cons
       for (int c = 0; c < kBpCols; ++c) m[c] = Sb[lane * kBpLd + b0 + c];
 #pragma unroll
       for (int jj = 0; jj < kBpCols; ++jj) {
-        const unsigned hi = (unsigned)__double2hiint(m[jj]) & 0x7fffffffu;
-        const unsigned key = myq >= 0 ? 0u : (hi & ~127u) | 64u | (unsigned)(63 - lane);
-        const int p = 63 - (int)(wave_max_u32(key) & 63u);
+        const unsigned hi = (unsigned)__double2hiint(m[jj]) & 0x7fffffffu, lo = (unsigned)__double2loint(m[jj]);
+        const bool open = myq < 0;
+        const unsigned top = wave_max_u32(open ? hi : 0u);
+        unsigned long long cand = __ballot(open && hi == top);
+        if (cand & (cand - 1)) {
+          const unsigned low = wave_max_u32(open && hi == top ? lo : 0u);
+          cand = __ballot(open && hi == top && lo == low);
+        }
+        const int p = (int)__builtin_ctzll(cand);
         const double a = lane_value(m[jj], p), inv = 1.0 / a;
         if (lane == 0 && (!(fabs(a) > 0.0) || !std::isfinite(a))) *failed = 1;
         const bool isp = lane == p;
