@@ -976,13 +976,20 @@ __global__ void iota_kernel(int n, int32_t *p) {
 // application
 // ---------------------------------------------------------------------------
 // A block product leaves its sums over column chunks, partial[(chunk q + c) ld
-// + row] for right-hand side c < q.  With one right-hand side the next launch
-// adds them where it needs them, in chunk order, so no launch of its own does
-// only that: a level of the forward sweep is two launches, of the backward
-// sweep one.  Every workgroup of a product then adds the sums of its columns,
-// which costs (rows / 64) times the reads, so several right-hand sides keep the
-// separate sum (gemm_reduce_kernel): at nb = 2187 and six of them the added
-// form took 1300 us a correction against 1045.
+// + row] for right-hand side c < q.  With one right-hand side and small blocks
+// the next launch adds them where it needs them, in chunk order, so no launch of
+// its own does only that: a level of the forward sweep is two launches, of the
+// backward sweep one.  Every workgroup of a product then adds the sums of its
+// columns, rows / 64 times the reads of a separate sum, and a row of couplings
+// those of 81: against the block's bytes that grows with nb.  Both sweeps of
+// seven levels, separate / added form, FP64 and FP32:
+//   nb 1029   141 / 130 us   124 / 116 us       nb 3993   431 / 506 us   259 / 286 us
+//   nb 2187   247 / 238 us   161 / 149 us       nb 6591   892 / 940 us   540 / 705 us
+//   nb 3000   311 / 331 us   203 / 203 us
+// so the added form ends at kFoldRows.  Several right-hand sides always keep the
+// separate sum (gemm_reduce_kernel): at nb = 2187 and six of them the added form
+// took 1300 us a correction against 1045.  The order of the sums is the same.
+constexpr int kFoldRows = 2560;
 __device__ inline double chunk_sum(const double *__restrict__ partial, int ld, int nch, int row) {
   double s = 0.0;
 #pragma unroll 6
@@ -1053,31 +1060,34 @@ __device__ inline double product_input(const ProductInput &in, int col, int c, b
 
 // Y = A X, one vector, FP32 blocks: a wavefront owns 64 rows and a chunk of
 // kGvCols columns, one row per lane; partial[chunk][row] = sum over the
-// chunk's columns in FP32, ascending.  kGvAhead columns are in flight per
-// wavefront (16 KB): at nb = 2187 the 19 MB of a block take 7.4 us, 18 us with
-// 256-row workgroups and the loads left to the compiler.
-constexpr int kGvRows = 64, kGvCols = 128, kGvAhead = 64;
-static_assert(kGvCols % kGvAhead == 0, "whole batches");
+// chunk's columns in FP32, ascending.  AHEAD columns are in flight per
+// wavefront: 64 (16 KB) up to kFoldRows, where the chip has few wavefronts (nb =
+// 2187: 19 MB of a block in 7.4 us, 18 us with 256-row workgroups and the loads
+// left to the compiler), 32 above (nb = 6591, both sweeps: 536 to 542 us, 545
+// to 547 with 64).
+constexpr int kGvRows = 64, kGvCols = 128;
 
+template <int AHEAD>
 __global__ void __launch_bounds__(kGvRows) gemv_partial_kernel(int nb, int ld, const float *__restrict__ A,
                                                                ProductInput in, double *__restrict__ partial) {
+  static_assert(kGvCols % AHEAD == 0, "whole batches");
   __shared__ float xs[kGvCols];
   const int c0 = blockIdx.y * kGvCols, nc = min(kGvCols, nb - c0);
   const int r = blockIdx.x * kGvRows + (int)threadIdx.x;   // < ld
   const float *a = A + (long long)c0 * ld + r;
-  float v[kGvAhead];
+  float v[AHEAD];
 #pragma unroll
-  for (int k = 0; k < kGvAhead; ++k) v[k] = a[(long long)min(k, nc - 1) * ld];
+  for (int k = 0; k < AHEAD; ++k) v[k] = a[(long long)min(k, nc - 1) * ld];
   for (int k = threadIdx.x; k < kGvCols; k += kGvRows)
     xs[k] = k < nc ? (float)product_input(in, c0 + k, 0, blockIdx.x == 0) : 0.0f;
   __syncthreads();
   float acc = 0;
 #pragma unroll
-  for (int b = 0; b < kGvCols; b += kGvAhead) {
+  for (int b = 0; b < kGvCols; b += AHEAD) {
 #pragma unroll
-    for (int k = 0; k < kGvAhead; ++k) {
+    for (int k = 0; k < AHEAD; ++k) {
       const float u = v[k];
-      if (b + kGvAhead < kGvCols) v[k] = a[(long long)min(b + kGvAhead + k, nc - 1) * ld];
+      if (b + AHEAD < kGvCols) v[k] = a[(long long)min(b + AHEAD + k, nc - 1) * ld];
       acc = __builtin_fmaf(u, xs[b + k], acc);   // columns past the chunk count zero times
     }
   }
@@ -1496,8 +1506,9 @@ template <typename T>
 void CoarseLU::product(bool gemv, int q, const T *A, const ProductInput &in, double *partial, hipStream_t s) const {
   if constexpr (sizeof(T) == 4) {
     if (gemv) {
-      hipLaunchKernelGGL(gemv_partial_kernel, dim3(ld_ / kGvRows, (nb_ + kGvCols - 1) / kGvCols), dim3(kGvRows), 0, s,
-                         nb_, ld_, A, in, partial);
+      const dim3 grid(ld_ / kGvRows, (nb_ + kGvCols - 1) / kGvCols);
+      const auto kernel = nb_ <= kFoldRows ? gemv_partial_kernel<64> : gemv_partial_kernel<32>;
+      hipLaunchKernelGGL(kernel, grid, dim3(kGvRows), 0, s, nb_, ld_, A, in, partial);
       return;
     }
   }
@@ -1508,11 +1519,11 @@ void CoarseLU::product(bool gemv, int q, const T *A, const ProductInput &in, dou
     hipLaunchKernelGGL((gemm_partial_kernel<T, 2>), grid, dim3(kMrThreads), 0, s, nb_, ld_, A, q, in, partial);
 }
 
-// The two sweeps for one right-hand side: forward, per level, lower_rhs_kernel
-// (t = r_k - L_k y_{k-1}, y_{k-1} from the chunk sums of the previous product)
-// and the product by S_k^{-1}; backward one launch per level, the product by
-// E_k, whose input x_{k+1} = y_{k+1} - E_{k+1} x_{k+2} its workgroups form from
-// the previous product's chunk sums.
+// The two sweeps for one right-hand side and blocks of at most kFoldRows rows:
+// forward, per level, lower_rhs_kernel (t = r_k - L_k y_{k-1}, y_{k-1} from the
+// chunk sums of the previous product) and the product by S_k^{-1}; backward one
+// launch per level, the product by E_k, whose input x_{k+1} = y_{k+1} - E_{k+1}
+// x_{k+2} its workgroups form from the previous product's chunk sums.
 template <typename T> void CoarseLU::sweep_one(bool gemv, const double *r, double *x, hipStream_t s) const {
   const size_t nn = (size_t)ld_ * nb_;
   const T *Si = static_cast<const T *>(Sinv_.ptr);
@@ -1549,19 +1560,21 @@ template <typename T> void CoarseLU::sweep_one(bool gemv, const double *r, doubl
   STKKT_HIP(hipGetLastError());
 }
 
-// The same for q <= 16 right-hand sides, the chunk sums added by a launch of
-// their own that also leaves the next product's input transposed.
+// The same for q <= 16 right-hand sides (one on the GEMV when `gemv`), the
+// chunk sums added by a launch of their own that also leaves the next product's
+// input transposed.
 template <typename T>
-void CoarseLU::sweep_multi(int q, const double *r, long long ldr, double *x, long long ldx, hipStream_t s) const {
+void CoarseLU::sweep_multi(bool gemv, int q, const double *r, long long ldr, double *x, long long ldx,
+                           hipStream_t s) const {
   const size_t nn = (size_t)ld_ * nb_;
   const T *Si = static_cast<const T *>(Sinv_.ptr);
   const T *E = static_cast<const T *>(E_.ptr);
   double *t = mt_.as<double>(), *xT = t + (size_t)kMrRhs * nb_, *part = partial_.as<double>();
-  const int nch = (nb_ + csplit_ - 1) / csplit_;
+  const int nch = gemv ? (nb_ + kGvCols - 1) / kGvCols : (nb_ + csplit_ - 1) / csplit_, ldp = gemv ? nb_ : ld_;
   ProductInput in{};
   in.vsi = q;
   auto reduce = [&](const double *base, double *out) {
-    hipLaunchKernelGGL(gemm_reduce_kernel, dim3(blocks_for(nb_, 64, 4096), q), dim3(64), 0, s, nb_, ld_, q, nch, part,
+    hipLaunchKernelGGL(gemm_reduce_kernel, dim3(blocks_for(nb_, 64, 4096), q), dim3(64), 0, s, nb_, ldp, q, nch, part,
                        base, ldx, out, ldx, xT, q);
   };
   // forward: y_k kept in x (the last one also in xT)
@@ -1570,20 +1583,25 @@ void CoarseLU::sweep_multi(int q, const double *r, long long ldr, double *x, lon
                        Lidx_.as<int32_t>() + (size_t)k * nb_ * 81, Lval_.as<double>() + (size_t)k * nb_ * 81,
                        r + (size_t)k * nb_, ldr, k > 0 ? x + (size_t)(k - 1) * nb_ : nullptr, ldx, t, q);
     in.vec = t;
-    product(false, q, Si + (size_t)k * nn, in, part, s);
+    product(gemv, q, Si + (size_t)k * nn, in, part, s);
     reduce(nullptr, x + (size_t)k * nb_);
   }
   in.vec = xT;
   for (int k = nlev_ - 2; k >= 0; --k) {
-    product(false, q, E + (size_t)k * nn, in, part, s);
+    product(gemv, q, E + (size_t)k * nn, in, part, s);
     reduce(x + (size_t)k * nb_, x + (size_t)k * nb_);
   }
   STKKT_HIP(hipGetLastError());
 }
 
+template <typename T> void CoarseLU::solve_one(bool gemv, const double *r, double *x, hipStream_t s) const {
+  if (nb_ <= kFoldRows) sweep_one<T>(gemv, r, x, s);
+  else sweep_multi<T>(gemv, 1, r, 0, x, 0, s);
+}
+
 void CoarseLU::solve(const double *r, double *x, hipStream_t s) const {
-  if (prec_ == STKKT_F32) sweep_one<float>(true, r, x, s);
-  else sweep_one<double>(false, r, x, s);
+  if (prec_ == STKKT_F32) solve_one<float>(true, r, x, s);
+  else solve_one<double>(false, r, x, s);
 }
 
 void CoarseLU::solve_multi(int q, const double *r, long long ldr, double *x, long long ldx, hipStream_t s) const {
@@ -1592,11 +1610,11 @@ void CoarseLU::solve_multi(int q, const double *r, long long ldr, double *x, lon
     const double *rg = r + c0 * ldr;
     double *xg = x + c0 * ldx;
     if (prec_ == STKKT_F32) {
-      if (qq == 1) sweep_one<float>(false, rg, xg, s);
-      else sweep_multi<float>(qq, rg, ldr, xg, ldx, s);
+      if (qq == 1) solve_one<float>(false, rg, xg, s);
+      else sweep_multi<float>(false, qq, rg, ldr, xg, ldx, s);
     } else {
-      if (qq == 1) sweep_one<double>(false, rg, xg, s);
-      else sweep_multi<double>(qq, rg, ldr, xg, ldx, s);
+      if (qq == 1) solve_one<double>(false, rg, xg, s);
+      else sweep_multi<double>(false, qq, rg, ldr, xg, ldx, s);
     }
   }
 }

@@ -29,8 +29,9 @@ class CoarseLU {
   template <typename T>
   void product(bool gemv, int q, const T *A, const ProductInput &in, double *partial, hipStream_t s) const;
   template <typename T> void sweep_one(bool gemv, const double *r, double *x, hipStream_t s) const;
+  template <typename T> void solve_one(bool gemv, const double *r, double *x, hipStream_t s) const;
   template <typename T>
-  void sweep_multi(int q, const double *r, long long ldr, double *x, long long ldx, hipStream_t s) const;
+  void sweep_multi(bool gemv, int q, const double *r, long long ldr, double *x, long long ldx, hipStream_t s) const;
   int prec_;
   int nb_ = 0, nlev_ = 0;
   int ld_ = 0;       // leading dimension of the stored blocks (nb_ rounded up to 64, zero rows below nb_)
