@@ -300,12 +300,15 @@ static long long restrict_mid(const coarse *C) {
   return 3LL * co.nn[0] * co.nn[1] * C->fine.nn[2] * (C->fine.M + 1);
 }
 
-// xc = (I_c^h)^T x, axis by axis (x, y, z, t; axes with factor 1 are skipped)
-static void restrict_axes(const coarse *C, const double *x, double *xc, hipStream_t s) {
-  const OpDev &fo = C->fine;
+// xc = (I_c^h)^T x, axis by axis (x, y, z, t; axes with factor 1 are skipped),
+// or, given planes that restrict_xy_kernel has coarsened (anywhere but in
+// C->rt[1]), along the other two axes (first = 2).
+static void restrict_axes(const coarse *C, int first, const double *x, double *xc, hipStream_t s) {
+  const OpDev &fo = C->fine, &co = C->cop->d;
   Dims4 dm{{fo.nn[0], fo.nn[1], fo.nn[2], fo.M + 1}};
+  for (int d = 0; d < first; ++d) dm.n[d] = co.nn[d];
   int axes[4], na = 0;
-  for (int d = 0; d < 4; ++d)
+  for (int d = first; d < 4; ++d)
     if (C->fac[d] > 1) axes[na++] = d;
   if (na == 0) {
     STKKT_HIP(hipMemcpyAsync(xc, x, sizeof(double) * 3 * fo.V, hipMemcpyDeviceToDevice, s));
@@ -314,7 +317,7 @@ static void restrict_axes(const coarse *C, const double *x, double *xc, hipStrea
   const double *src = x;
   for (int k = 0; k < na; ++k) {
     const int d = axes[k];
-    double *dst = k == na - 1 ? xc : C->rt[k & 1].as<double>();
+    double *dst = k == na - 1 ? xc : C->rt[first > 0 ? 1 : k & 1].as<double>();
     Dims4 out = dm;
     out.n[d] = (dm.n[d] - 1) / C->fac[d] + 1;
     const int lines = out.n[1] * out.n[2] * out.n[3];
@@ -331,24 +334,43 @@ static void restrict_axes(const coarse *C, const double *x, double *xc, hipStrea
   STKKT_HIP(hipGetLastError());
 }
 
+// Which axes go together.  A thread of restrict_xy_kernel reads its entries of
+// the plane one batch after the other, and a launch has a workgroup per plane:
+// few planes with many entries are slower than an axis at a time.  Planes,
+// entries a thread and the whole restriction, together / by axes: 25, 1014 114 /
+// 38 us; 45, 361 62 / 32; 189, 266 49 / 40; 136, 105 31 / 28; 245, 60 20 / 27;
+// 427, 115 33 / 41.  A thread of restrict_zt_kernel reads a window of z and t
+// nodes: 1521 of them 105 us against 27 for a launch per axis, 225 34 against
+// 14, 121 21 against 14, 45 8 against 12.  (No rule depends on the number of
+// vectors: a vector's result is the same among others.)
+static bool fuse_xy(const coarse *C) {
+  const long long planes = (long long)C->fine.nn[2] * (C->fine.M + 1);
+  const long long entries = (3LL * C->fine.nn[0] * C->cop->d.nn[1] + 255) / 256 * (2 * C->fac[1] - 1);
+  return restrict_xy_lds(C) <= kRestrictXyLds && planes <= INT32_MAX && planes >= 2 * entries;
+}
+constexpr long long kRestrictWindow = 64;
+static bool fuse_zt(const coarse *C) { return (2LL * C->fac[2] - 1) * (2LL * C->fac[3] - 1) <= kRestrictWindow; }
+
 // xc_i = (I_c^h)^T x_i for q <= kTransferVecs vectors; mid: q times
-// restrict_mid(C) doubles (not used when x and y are not coarsened)
+// restrict_mid(C) doubles outside C->rt[1] (not used when x and y are not coarsened)
 static void restrict_transpose(const coarse *C, int q, const VecsIn &x, const VecsOut &xc, double *mid,
                                hipStream_t s) {
   const OpDev &fo = C->fine, &co = C->cop->d;
-  const bool xy = C->fac[0] > 1 || C->fac[1] > 1;
-  const size_t lds = restrict_xy_lds(C);
-  const long long planes = (long long)fo.nn[2] * (fo.M + 1);
-  if ((xy && lds > kRestrictXyLds) || planes > INT32_MAX || (!xy && C->fac[2] == 1 && C->fac[3] == 1)) {
-    for (int i = 0; i < q; ++i) restrict_axes(C, x.p[i], xc.p[i], s);
+  const bool xy = C->fac[0] > 1 || C->fac[1] > 1, zt = C->fac[2] > 1 || C->fac[3] > 1;
+  if (xy ? !fuse_xy(C) : !zt || !fuse_zt(C)) {
+    for (int i = 0; i < q; ++i) restrict_axes(C, 0, x.p[i], xc.p[i], s);
     return;
   }
   VecsIn from = x;
   if (xy) {
     const long long step = restrict_mid(C);
-    hipLaunchKernelGGL(restrict_xy_kernel, dim3((unsigned)planes, q), dim3(256), lds, s, fo.nn[0], fo.nn[1], C->fac[0],
-                       C->fac[1], x, mid, step);
+    hipLaunchKernelGGL(restrict_xy_kernel, dim3((unsigned)(fo.nn[2] * (fo.M + 1)), q), dim3(256), restrict_xy_lds(C),
+                       s, fo.nn[0], fo.nn[1], C->fac[0], C->fac[1], x, mid, step);
     for (int i = 0; i < q; ++i) from.p[i] = mid + i * step;
+    if (!fuse_zt(C)) {
+      for (int i = 0; i < q; ++i) restrict_axes(C, 2, from.p[i], xc.p[i], s);
+      return;
+    }
   }
   const int pl = 3 * co.nn[0] * co.nn[1];
   hipLaunchKernelGGL(restrict_zt_kernel, dim3(blocks_for(3 * co.V, 256), q), dim3(256), 0, s, pl, fo.nn[2], fo.M + 1,
