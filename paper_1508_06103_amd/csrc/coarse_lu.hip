@@ -28,7 +28,7 @@
 namespace stkkt {
 
 // Where a block product takes its right-hand sides from: formed already
-// (vec, value (col, c) at col vsi + c), or, one right-hand side, the chunk sums
+// (vec, value (col, c) at col vsi + c), or, for one right-hand side, the chunk sums
 // of the previous product, base - sum (base == nullptr: the sum), which the
 // workgroups of the first row tile then also write to out.
 struct ProductInput {
@@ -981,15 +981,17 @@ __global__ void iota_kernel(int n, int32_t *p) {
 // its own does only that: a level of the forward sweep is two launches, of the
 // backward sweep one.  Every workgroup of a product then adds the sums of its
 // columns, rows / 64 times the reads of a separate sum, and a row of couplings
-// those of 81: against the block's bytes that grows with nb.  Both sweeps of
-// seven levels, separate / added form, FP64 and FP32:
-//   nb 1029   141 / 130 us   124 / 116 us       nb 3993   431 / 506 us   259 / 286 us
-//   nb 2187   247 / 238 us   161 / 149 us       nb 6591   892 / 940 us   540 / 705 us
-//   nb 3000   311 / 331 us   203 / 203 us
-// so the added form ends at kFoldRows.  Several right-hand sides always keep the
+// those of 81: against the block's bytes that grows with nb, and so the added
+// form ends at fold_rows().  Both sweeps, separate / added:
+//   levels          7           7           9           7           7           5
+//   nb           1029        1536        2187        3000        3993        6591
+//   GEMV    119 / 108   119 / 102   206 / 190   200 / 202   257 / 285   376 / 490 us
+//   MFMA    120 / 120   155 / 159   276 / 296   286 / 329   403 / 506   607 / 656 us
+// (GEMV: FP32 blocks, MFMA here: FP64).  Several right-hand sides always keep the
 // separate sum (gemm_reduce_kernel): at nb = 2187 and six of them the added form
 // took 1300 us a correction against 1045.  The order of the sums is the same.
-constexpr int kFoldRows = 2560;
+constexpr int fold_rows(bool gemv) { return gemv ? 2560 : 1280; }
+
 __device__ inline double chunk_sum(const double *__restrict__ partial, int ld, int nch, int row) {
   double s = 0.0;
 #pragma unroll 6
@@ -1025,33 +1027,47 @@ __global__ void __launch_bounds__(256) lower_rhs_kernel(int nb, int ld, int nch,
 }
 
 // The same for q right-hand sides with y_c = y + c ldy formed (nullptr: t = r):
-// t[i tsi + c] = r_c[i] - (L y_c)[i], the couplings read once for all of them.
+// t[i tsi + c] = r_c[i] - (L y_c)[i], the couplings read once for VECS of them
+// (blockIdx.y: which), whose values are in flight together.  Bound by the
+// latency of the reads: at nb = 1536 sixteen vectors take 7 us, one after the
+// other 16, with a wavefront for each 9 (nb = 6591: 18, 23 and 30 us).
+template <int VECS>
 __global__ void __launch_bounds__(256) lower_rhs_multi_kernel(int nb, int q, const int32_t *__restrict__ idx,
                                                               const double *__restrict__ val,
                                                               const double *__restrict__ r, long long ldr,
                                                               const double *__restrict__ y, long long ldy,
                                                               double *__restrict__ t, int tsi) {
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, c0 = blockIdx.y * VECS, nc = min(VECS, q - c0);
   for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < nb; i += gridDim.x * 4) {
     const long long b = (long long)i * 81;
     const bool two = lane < 81 - 64;
     const int i0 = idx[b + lane], i1 = two ? idx[b + 64 + lane] : 0;
     const double v0 = val[b + lane], v1 = two ? val[b + 64 + lane] : 0.0;
-    for (int c = 0; c < q; ++c) {
+    double y0[VECS], y1[VECS], rc[VECS];
+#pragma unroll
+    for (int c = 0; c < VECS; ++c) {
+      const int cc = c0 + min(c, nc - 1);
+      y0[c] = y ? y[cc * ldy + i0] : 0.0;
+      y1[c] = y && two ? y[cc * ldy + i1] : 0.0;
+      rc[c] = r[cc * ldr + i];
+    }
+#pragma unroll
+    for (int c = 0; c < VECS; ++c) {
       double s = 0.0;
       if (y) {
-        s = v0 * y[c * ldy + i0];
-        if (two) s += v1 * y[c * ldy + i1];
+        s = v0 * y0[c];
+        if (two) s += v1 * y1[c];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
       }
-      if (lane == 0) t[(long long)i * tsi + c] = r[c * ldr + i] - s;
+      if (lane == 0 && c < nc) t[(long long)i * tsi + c0 + c] = rc[c] - s;
     }
   }
 }
 
-__device__ inline double product_input(const ProductInput &in, int col, int c, bool write) {
-  if (in.vec) return in.vec[(long long)col * in.vsi + c];
+// entry col of the one right-hand side
+__device__ inline double product_input(const ProductInput &in, int col, bool write) {
+  if (in.vec) return in.vec[(long long)col * in.vsi];
   const double s = chunk_sum(in.partial, in.ld, in.nch, col);
   const double v = in.base ? in.base[col] - s : s;
   if (write) in.out[col] = v;
@@ -1061,7 +1077,7 @@ __device__ inline double product_input(const ProductInput &in, int col, int c, b
 // Y = A X, one vector, FP32 blocks: a wavefront owns 64 rows and a chunk of
 // kGvCols columns, one row per lane; partial[chunk][row] = sum over the
 // chunk's columns in FP32, ascending.  AHEAD columns are in flight per
-// wavefront: 64 (16 KB) up to kFoldRows, where the chip has few wavefronts (nb =
+// wavefront: 64 (16 KB) up to fold_rows(), where the chip has few wavefronts (nb =
 // 2187: 19 MB of a block in 7.4 us, 18 us with 256-row workgroups and the loads
 // left to the compiler), 32 above (nb = 6591, both sweeps: 536 to 542 us, 545
 // to 547 with 64).
@@ -1079,7 +1095,7 @@ __global__ void __launch_bounds__(kGvRows) gemv_partial_kernel(int nb, int ld, c
 #pragma unroll
   for (int k = 0; k < AHEAD; ++k) v[k] = a[(long long)min(k, nc - 1) * ld];
   for (int k = threadIdx.x; k < kGvCols; k += kGvRows)
-    xs[k] = k < nc ? (float)product_input(in, c0 + k, 0, blockIdx.x == 0) : 0.0f;
+    xs[k] = k < nc ? (float)product_input(in, c0 + k, blockIdx.x == 0) : 0.0f;
   __syncthreads();
   float acc = 0;
 #pragma unroll
@@ -1097,7 +1113,7 @@ __global__ void __launch_bounds__(kGvRows) gemv_partial_kernel(int nb, int ld, c
 // out = base - chunk sums (base == nullptr: the sums): the end of a sweep.
 __global__ void product_finish_kernel(int nb, ProductInput in) {
   for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nb; r += gridDim.x * blockDim.x)
-    product_input(in, r, 0, true);
+    product_input(in, r, true);
 }
 
 // out_c[r] = base_c[r] - sum_chunks partial[chunk][c][r] (fixed order; base ==
@@ -1125,10 +1141,10 @@ __global__ void store_padded_kernel(int nb, int ld, const double *__restrict__ S
 }
 
 // ---------------------------------------------------------------------------
-// several right-hand sides at once.  A workgroup keeps its chunk of the product
-// input in LDS transposed, XT[col][16] (the value of right-hand side c at
-// column col in XT[16 col + c]), so that the matrix-core operands of 4
-// consecutive columns x 16 right-hand sides are one contiguous 512-byte read.
+// several right-hand sides at once: the product input lies transposed, [column]
+// [right-hand side], so that the matrix-core operands of 4 consecutive columns
+// are one contiguous read.  Staged in LDS first, as the form with chunk sums
+// does, a product of sixteen took 56 us at nb = 6591 in FP32, now 42.
 // ---------------------------------------------------------------------------
 constexpr int kMrRows = 64, kMrRhs = 16, kMrThreads = 256, kMrAhead = 8;
 
@@ -1179,11 +1195,13 @@ template <> struct Rows4<double> { using type = Rows4d; };
 constexpr int kMrBatch = 16 * kMrAhead;   // columns of one load batch (128)
 
 // BATCHES x 128 columns per chunk: a batch's loads are all in flight together,
-// the next batch's are issued as the current one is multiplied.
-template <typename T, int BATCHES>
+// the next batch's are issued as the current one is multiplied.  SUMS: the one
+// right-hand side is formed (from chunk sums, mostly) into LDS first; else the
+// formed right-hand sides are read as operands, beside the block's columns.
+template <typename T, int BATCHES, bool SUMS>
 __global__ void __launch_bounds__(kMrThreads) gemm_partial_kernel(int nb, int ld, const T *__restrict__ A, int q,
                                                                   ProductInput in, double *__restrict__ partial) {
-  __shared__ double lds[4 * kMrRhs * kMrRows];   // the chunk's XT, then the wavefronts' sums [wave][rhs][row]
+  __shared__ double lds[4 * kMrRhs * kMrRows];   // (the chunk's input), then the wavefronts' sums [wave][rhs][row]
   static_assert(BATCHES * kMrBatch * kMrRhs <= 4 * kMrRhs * kMrRows, "XT fits");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
@@ -1191,29 +1209,35 @@ __global__ void __launch_bounds__(kMrThreads) gemm_partial_kernel(int nb, int ld
   const int cbeg = blockIdx.y * (BATCHES * kMrBatch), ncol = min(nb - cbeg, BATCHES * kMrBatch), last = ncol - 1;
   const int c_lane = 4 * wave + lk;   // column of step 0 in the chunk
   const T *arow = A + (long long)cbeg * ld + r0 + 4 * li;
+  const double *brow = in.vec + (long long)cbeg * in.vsi + min(li, q - 1);   // (!SUMS)
   f64x4 acc[4];
 #pragma unroll
   for (int m = 0; m < 4; ++m) acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
   typename Rows4<T>::type raw[kMrAhead];
+  double b[kMrAhead];
+  auto fetch = [&](int p, int step) {
+    const int cc = min(c_lane + 16 * step, last);
+    raw[p].load(arow + (long long)cc * ld);
+    if (!SUMS) b[p] = brow[cc * in.vsi];
+  };
 #pragma unroll
-  for (int p = 0; p < kMrAhead; ++p) raw[p].load(arow + (long long)min(c_lane + 16 * p, last) * ld);
-  // the input, while the first columns are on their way
-  for (int k = tid; k < ncol * q; k += kMrThreads) {
-    const int c = k / ncol, col = k - c * ncol;
-    lds[col * kMrRhs + c] = product_input(in, cbeg + col, c, blockIdx.x == 0);
+  for (int p = 0; p < kMrAhead; ++p) fetch(p, p);
+  if (SUMS) {
+    // the input, while the first columns are on their way
+    for (int k = tid; k < ncol; k += kMrThreads) lds[k * kMrRhs] = product_input(in, cbeg + k, blockIdx.x == 0);
+    __syncthreads();
   }
-  __syncthreads();
 #pragma unroll
   for (int bt = 0; bt < BATCHES; ++bt) {
 #pragma unroll
     for (int p = 0; p < kMrAhead; ++p) {
-      const int cc = c_lane + 16 * (bt * kMrAhead + p);
-      const double b = lds[min(cc, last) * kMrRhs + li];
+      const int step = bt * kMrAhead + p, cc = c_lane + 16 * step;
+      const double bv = SUMS ? lds[min(cc, last) * kMrRhs + li] : b[p];
       double a[4];
       raw[p].get(cc <= last, a);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], b, acc[m], 0, 0, 0);
-      if (bt + 1 < BATCHES) raw[p].load(arow + (long long)min(cc + kMrBatch, last) * ld);
+      for (int m = 0; m < 4; ++m) acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], bv, acc[m], 0, 0, 0);
+      if (bt + 1 < BATCHES) fetch(p, step + kMrAhead);
     }
   }
   __syncthreads();
@@ -1417,9 +1441,10 @@ CoarseLU::CoarseLU(const Allocator *al, const kkt_op *cop, int precision, hipStr
   Lidx_ = DevBuf(al, sizeof(int32_t) * (size_t)nb_ * 81 * nlev_);
   Lval_ = DevBuf(al, sizeof(double) * (size_t)nb_ * 81 * nlev_);
   // block products: workgroups of 64 rows x csplit_ columns, 256 of them where
-  // that gives the chip enough workgroups; at nb 6591 (103 x 26) longer chunks
-  // were slower (FP32 47 us with 10 chunks, 56 us with 3, against 41 us).
-  // Small blocks take 128.
+  // that gives the chip enough workgroups (seven levels, one vector and sixteen,
+  // 128 / 256 columns, FP64: nb 1029 120 / 144 and 198 / 220 us, 3000 286 / 316
+  // and 464 / 478; five levels of nb 6591 624 / 607 and 929 / 878); longer chunks
+  // were slower there (FP32 47 us a block with 10 chunks, 56 us with 3, against 41).
   csplit_ = (long long)(ld_ / kMrRows) * ((nb_ + 2 * kMrBatch - 1) / (2 * kMrBatch)) >= 1024 ? 2 * kMrBatch : kMrBatch;
   const size_t gv = (size_t)nb_ * ((nb_ + kGvCols - 1) / kGvCols), nch = (size_t)((nb_ + csplit_ - 1) / csplit_);
   partial_ = DevBuf(al, sizeof(double) * 2 * std::max(gv, nch * ld_ * kMrRhs / 2));
@@ -1507,19 +1532,19 @@ void CoarseLU::product(bool gemv, int q, const T *A, const ProductInput &in, dou
   if constexpr (sizeof(T) == 4) {
     if (gemv) {
       const dim3 grid(ld_ / kGvRows, (nb_ + kGvCols - 1) / kGvCols);
-      const auto kernel = nb_ <= kFoldRows ? gemv_partial_kernel<64> : gemv_partial_kernel<32>;
+      const auto kernel = nb_ <= fold_rows(true) ? gemv_partial_kernel<64> : gemv_partial_kernel<32>;
       hipLaunchKernelGGL(kernel, grid, dim3(kGvRows), 0, s, nb_, ld_, A, in, partial);
       return;
     }
   }
   const dim3 grid(ld_ / kMrRows, (nb_ + csplit_ - 1) / csplit_);
-  if (csplit_ == kMrBatch)
-    hipLaunchKernelGGL((gemm_partial_kernel<T, 1>), grid, dim3(kMrThreads), 0, s, nb_, ld_, A, q, in, partial);
-  else
-    hipLaunchKernelGGL((gemm_partial_kernel<T, 2>), grid, dim3(kMrThreads), 0, s, nb_, ld_, A, q, in, partial);
+  const bool one = csplit_ == kMrBatch, sums = q == 1 && nb_ <= fold_rows(false);
+  const auto kernel = sums ? (one ? gemm_partial_kernel<T, 1, true> : gemm_partial_kernel<T, 2, true>)
+                           : (one ? gemm_partial_kernel<T, 1, false> : gemm_partial_kernel<T, 2, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kMrThreads), 0, s, nb_, ld_, A, q, in, partial);
 }
 
-// The two sweeps for one right-hand side and blocks of at most kFoldRows rows:
+// The two sweeps for one right-hand side and blocks of at most fold_rows() rows:
 // forward, per level, lower_rhs_kernel (t = r_k - L_k y_{k-1}, y_{k-1} from the
 // chunk sums of the previous product) and the product by S_k^{-1}; backward one
 // launch per level, the product by E_k, whose input x_{k+1} = y_{k+1} - E_{k+1}
@@ -1577,9 +1602,13 @@ void CoarseLU::sweep_multi(bool gemv, int q, const double *r, long long ldr, dou
     hipLaunchKernelGGL(gemm_reduce_kernel, dim3(blocks_for(nb_, 64, 4096), q), dim3(64), 0, s, nb_, ldp, q, nch, part,
                        base, ldx, out, ldx, xT, q);
   };
+  const int vecs = q == 1 ? 1 : q == 2 ? 2 : 4;
+  const auto lower_rhs = vecs == 1   ? lower_rhs_multi_kernel<1>
+                         : vecs == 2 ? lower_rhs_multi_kernel<2>
+                                     : lower_rhs_multi_kernel<4>;
   // forward: y_k kept in x (the last one also in xT)
   for (int k = 0; k < nlev_; ++k) {
-    hipLaunchKernelGGL(lower_rhs_multi_kernel, dim3(blocks_for(nb_, 4, 1 << 16)), dim3(256), 0, s, nb_, q,
+    hipLaunchKernelGGL(lower_rhs, dim3(blocks_for(nb_, 4, 1 << 16), (q + vecs - 1) / vecs), dim3(256), 0, s, nb_, q,
                        Lidx_.as<int32_t>() + (size_t)k * nb_ * 81, Lval_.as<double>() + (size_t)k * nb_ * 81,
                        r + (size_t)k * nb_, ldr, k > 0 ? x + (size_t)(k - 1) * nb_ : nullptr, ldx, t, q);
     in.vec = t;
@@ -1595,7 +1624,7 @@ void CoarseLU::sweep_multi(bool gemv, int q, const double *r, long long ldr, dou
 }
 
 template <typename T> void CoarseLU::solve_one(bool gemv, const double *r, double *x, hipStream_t s) const {
-  if (nb_ <= kFoldRows) sweep_one<T>(gemv, r, x, s);
+  if (nb_ <= fold_rows(gemv)) sweep_one<T>(gemv, r, x, s);
   else sweep_multi<T>(gemv, 1, r, 0, x, 0, s);
 }
 

@@ -18,12 +18,12 @@ def st():
     return st_mod
 
 
-# blocks of 3 x 9 x 9 x 10 = 2430 and 3 x 9 x 10 x 10 = 2700 rows, three levels
-@pytest.mark.parametrize("c", [(8, 8, 9), (8, 9, 9)])
+# blocks of 1176 and 1344 rows (the line of the matrix-core form), 2430 and 2700 (of the FP32 GEMV), three levels
+@pytest.mark.parametrize("c", [(6, 6, 7), (7, 6, 7), (8, 8, 9), (8, 9, 9)])
 def test_one_vector_against_several(st, c):
     n = tuple(2 * k for k in c)
     print(f"case {n}, {3 * (c[0] + 1) * (c[1] + 1) * (c[2] + 1)} rows", flush=True)
-    node = np.array([8 + (n[0] + 1) * (8 + (n[1] + 1) * 8)], dtype=np.int32)
+    node = np.array([6 + (n[0] + 1) * (6 + (n[1] + 1) * 6)], dtype=np.int32)
     prob = make_custom(n, 4, 41, sensors=node)
     op = st.KKTOperator(prob)
     tl = twolevel.TwoLevel(prob, None, None, (2, 2, 2, 2), coarse="lu")
@@ -41,3 +41,5 @@ def test_one_vector_against_several(st, c):
         if prec == st.F64:   # one FP64 vector takes the products of several
             assert np.array_equal(one, few[0])
         assert np.array_equal(many[16], last[1]) and np.array_equal(many[0], few[0])
+        for q in (3, 5):   # vectors in fours, with a remainder
+            assert np.array_equal(C.apply_multi(Xd[:q].contiguous()).cpu().numpy(), many[:q])
