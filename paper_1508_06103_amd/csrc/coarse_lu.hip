@@ -834,13 +834,13 @@ __device__ inline void panel_rows_step(int n, int kp, int ep, int k, int e, cons
       for (int c = 0; c < kBpCols; ++c) m[c] = Sb[lane * kBpLd + b0 + c];
 #pragma unroll
       for (int jj = 0; jj < kBpCols; ++jj) {
-        const unsigned hi = (unsigned)__double2hiint(m[jj]) & 0x7fffffffu, lo = (unsigned)__double2loint(m[jj]);
-        const bool open = myq < 0;
-        const unsigned top = wave_max_u32(open ? hi : 0u);
-        unsigned long long cand = __ballot(open && hi == top);
+        // high word of |entry| above those of the rows used already
+        const unsigned key = myq < 0 ? (unsigned)__double2hiint(m[jj]) | 0x80000000u : 0u;
+        const unsigned top = wave_max_u32(key);
+        unsigned long long cand = __ballot(key == top);
         if (cand & (cand - 1)) {
-          const unsigned low = wave_max_u32(open && hi == top ? lo : 0u);
-          cand = __ballot(open && hi == top && lo == low);
+          const unsigned lo = key == top ? (unsigned)__double2loint(m[jj]) : 0u;
+          cand &= __ballot(lo == wave_max_u32(lo));
         }
         const int p = (int)__builtin_ctzll(cand);
         const double a = lane_value(m[jj], p), inv = 1.0 / a;
