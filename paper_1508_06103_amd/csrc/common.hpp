@@ -92,10 +92,12 @@ struct MvTile {
 
 // Launch shape of the public matvec: tiles of t[0] x t[1] node columns (nt[]
 // tiles per axis) marched along z in nz chunks of zlen planes, one time level
-// each; threads: columns of a tile with its halo, rounded up to wavefronts.
+// each; threads: columns of a tile with its halo, rounded up to wavefronts;
+// sums: the solvers' form instead.
 struct MvMarch {
   int t[2], nt[2];
   int ntiles, threads, zlen, nz;
+  bool sums;
 };
 
 }  // namespace stkkt

@@ -456,6 +456,14 @@ MvMarch choose_matvec_march(const OpDev &d) {
   const int cuts = (int)std::max<long long>(1, std::min<long long>(d.nn[2], (1024 + per - 1) / per));
   best.zlen = (d.nn[2] + cuts - 1) / cuts;
   best.nz = (d.nn[2] + best.zlen - 1) / best.zlen;
+  // Thin meshes: a plane costs a wavefront about 1.8 us however few of its lanes
+  // own a node, so long marches of few columns are slower than the sum over
+  // neighbours.  Columns, planes a march: march / sum in us.  4, 3 12.4 / 9.5 (31
+  // planes, 97 levels); 9, 5 16.4 / 11.0; 12, 3 12.4 / 10.6; 16, 6 17 / 15; 16, 28
+  // 58 / 41; 20, 28 58 / 49; 25, 28 58 / 53.  The other side: 9, 2 8.3 / 9.3; 16,
+  // 5 12 / 15; 25, 17 38 / 46; 35, 28 58 / 69.
+  const int columns = d.nn[0] * d.nn[1];
+  best.sums = best.zlen > (columns <= 12 ? 2 : columns <= 16 ? 5 : columns <= 26 ? 24 : d.nn[2]);
   return best;
 }
 
@@ -471,6 +479,10 @@ static long long matvec_items(const OpDev &d, const MvMarch &tl) { return (long 
 static size_t matvec_lds(int threads) { return kMvLds / kMvThreads * (size_t)threads; }
 
 void matvec_march_device(const kkt_op *op, const double *x, double *y, hipStream_t s) {
+  if (op->mvm.sums) {
+    matvec_device(op, x, y, s);
+    return;
+  }
   const OpDev &d = op->d;
   const long long grid = matvec_items(d, op->mvm);
   if (grid > INT32_MAX) throw Error(STKKT_EINVAL, "kkt_matvec: mesh too large");

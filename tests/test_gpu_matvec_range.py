@@ -71,3 +71,16 @@ def test_one_non_finite_entry(st, n, M, variant, value):
             c = hit.copy()
             c.reshape(-1, 3)[:, 1:] = False
             assert c.any() and (y[c] == -value).all()
+
+
+# thin meshes on both sides of the lines where the sum over neighbours serves the whole call: 4 columns and marches of 2
+# and 3 planes, 16 columns and marches of 5 and 6
+@pytest.mark.parametrize("n,M,variant", [((1, 1, 9), 204, DTO), ((1, 1, 10), 204, OTD), ((3, 3, 24), 204, OTD),
+                                         ((3, 3, 29), 204, DTO)])
+def test_thin_meshes(st, n, M, variant):
+    print(f"case {n} x {M} variant {variant}", flush=True)
+    prob = make_custom(n, M, 32, variant=variant, faces=0, sensors=np.array([5], dtype=np.int32))
+    op, F = st.KKTOperator(prob), kkt.assemble(prob).tocsr()
+    x = np.random.default_rng(3).standard_normal(F.shape[0])
+    # a few hundred roundings per entry, of terms no larger than |F| |x|
+    assert np.abs(_matvec(op, x) - F @ x).max() <= 1e-13 * (abs(F) @ np.abs(x)).max()
