@@ -213,7 +213,9 @@ def oracle_full_solve(st, seed=0):
 def time_kernels(op, pre, reps, coarse=None):
     """Average ras_apply, kkt_matvec and coarse_apply durations, from HIP
     events recorded on the stream the library launches on (torch's current
-    stream)."""
+    stream).  kkt_matvec is the entry point; the solves apply the operator with
+    a kernel of their own (the sum over 27 neighbours), whose time is part of
+    the solves' only."""
     import torch
     stream = torch.cuda.current_stream()
     r = torch.randn(op.n, dtype=torch.float64, device="cuda")
@@ -706,10 +708,27 @@ def timed_solves(st, prob, cfg, op, pre, coarse, steps, warmup, flexible, tag, s
     return times, its, time.perf_counter() - t_start
 
 
+def widest_level(dims):
+    """Most rows of a wavefront level x + 2y + 4z + 8t of a box."""
+    import numpy as np
+    rows = np.ones(1, dtype=np.int64)
+    for length, stride in zip(dims, (1, 2, 4, 8)):
+        axis = np.zeros((length - 1) * stride + 1, dtype=np.int64)
+        axis[::stride] = 1
+        rows = np.convolve(rows, axis)
+    return int(rows.max())
+
+
 def apply_kernel_name(pre, prec_name):
+    """The sweep kernel that runs: rows per phase and stencil slots per load."""
     t = "double" if prec_name == "f64" else "float"
     rows = pre.apply_rows
-    return f"apply_ring_kernel<{t}, {rows}>" if rows else f"apply_kernel<{t}>"
+    if not rows:
+        return f"apply_kernel<{t}>"
+    b = pre.boxes()
+    widest = max(widest_level(d) for d in {tuple(int(v) for v in d) for d in b[:, 12:16] - b[:, 8:12]})
+    # levels of at most 64 rows are one phase; with at most 32 rows two slots share a load
+    return f"apply_ring_kernel<{t}, {64 if widest <= 64 else rows}, {2 if widest <= 32 else 1}>"
 
 
 def roofline_of(prob, pre, apply_ms, config, prec_name, copy_ms=None):

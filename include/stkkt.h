@@ -241,11 +241,13 @@ int ras_query_boxes(const ras_t *ras, int32_t *host_out);
 /* Bytes of factor data streamed by one ras_apply (all L, U and inv(D) blocks). */
 int64_t ras_factor_bytes(const ras_t *ras);
 
-/* Which sweep kernel ras_apply runs: the rows of a wavefront level handled
- * per phase, 256 or 64, when the values of the last 16 levels of every box fit
- * in the 160 KB LDS of a workgroup (64 for boxes with many rows per level,
- * e.g. 14^4 nodes with FP64 factors); 0 when they do not and the sweeps keep
- * them in the local vector in global memory.  -1 for a NULL handle. */
+/* The most rows of a wavefront level that ras_apply's sweeps may take per
+ * phase: 256, 128 or 64, as the values of the last 16 levels of every box leave
+ * room in the 160 KB LDS of a workgroup (64 for boxes with many rows per level,
+ * e.g. 14^4 nodes with FP64 factors); 0 when they do not fit and the sweeps keep
+ * them in the local vector in global memory.  Boxes whose levels all have at
+ * most 64 rows need one phase a level and run phases of 64 rows whatever this
+ * value.  -1 for a NULL handle. */
 int32_t ras_query_apply_rows(const ras_t *ras);
 
 /* Factor blocks of one subdomain (the size of ras_export_factors_csr's

@@ -318,7 +318,7 @@ class RAS:
 
     @property
     def apply_rows(self):
-        """Rows per phase of the sweep kernel: 256 or 64 (LDS ring), 0 (local vector in global memory)."""
+        """Most rows per phase of the sweep kernel: 256, 128 or 64 (LDS ring), 0 (local vector in global memory)."""
         return int(_lib.ras_query_apply_rows(self.handle))
 
     def export_factors(self, sub):

@@ -198,8 +198,9 @@ ShapeHost make_shape(const int dims[4]) {
 // setup: subdomain matrix from the operator formula, then ILU(0), one
 // workgroup per subdomain, rows of a level in parallel (one thread per row).
 // W holds the subdomain's rows padded to 81 blocks: W[rho][s][e], kWStride
-// doubles per row (rows 16-byte aligned).  This form serves boxes with more
-// than kFactorRows nodes along x; factor_lines_kernel the others.
+// doubles per row (rows 16-byte aligned).  This form serves preconditioners
+// that have a box of more than kFactorRows nodes along x (all their boxes);
+// factor_lines_kernel the others.  Both give the same bits.
 // --------------------------------------------------------------------------
 constexpr int kWStride = 730;
 
@@ -305,8 +306,9 @@ __global__ void __launch_bounds__(256) factor_kernel(OpDev op, const SubInfo *__
 // the waits between the 26 pieces, which the second workgroup fills; below
 // them the U blocks read, about 30 KB per row from HBM (a row's own blocks are
 // 6 KB), since a box's window of lines does not fit in L2.  24^3 x 48 in 108
-// boxes: 19.5 ms on one stream, 16.5 on two; with a thread per row, the rows of a point level in parallel,
-// 157 ms.  Boxes over 54 nodes long keep that form (factor_kernel).
+// boxes: 19.5 ms on one stream, 16.5 on two; with a thread per row, the rows of
+// a point level in parallel, 157 ms.  Preconditioners with a box over 54 nodes
+// long keep that form (factor_kernel).
 constexpr int kFlUnits0 = 63, kFlUnits1 = 122;   // 16-byte units per row: slots 40..53, 54..80
 template <int ROWS> struct FlCfg {
   static constexpr int threads = ROWS > 28 ? 512 : 256;
@@ -1572,9 +1574,11 @@ static void launch_ring(const ras *R, const double *r, double *z, T *Y, hipStrea
 // Most rows per phase of the ring kernel for this preconditioner: 256 when the
 // ring fits with them, else 128 (e.g. 13^4 boxes in FP64), else 64 (14^4 boxes
 // in FP64), else 0 (no ring: the kernel with the local vector in global
-// memory).  Beside the ring and the partial sums the rule leaves room for two
-// (FP64) or three (FP32) words per row of a phase and the (t, z) groups of 16
-// levels, at most kApplyThreads of them.
+// memory).  The public query reports it, and the members of a batch share the
+// smallest of theirs.  Beside the ring and the partial sums, which are all that
+// the kernel keeps, the rule leaves the room that phase coordinates (two or
+// three words a row) and the (t, z) groups of 16 levels took in an earlier
+// layout: boxes near the lines have been timed with these phases only.
 template <typename T>
 static int ring_rows(const ras *R) {
   if (R->ring_ltlz > kApplyThreads) return 0;
@@ -1588,9 +1592,10 @@ static int ring_rows(const ras *R) {
 // The form that runs, for the given rows per phase and most rows of a level:
 // a level of at most 64 rows is one chunk, so phases of 256 rows would be the
 // same phases with the branches of longer ones; with at most 32 rows two slots
-// share a load (cube8x16, 20 rows a level, FP64: an apply of 390 us against 546
-// with one slot a load; of fatter boxes 64-row phases brought nothing, FP32 24^3 x
-// 48 1093 us against 1092 with 256 rows).
+// share a load (cube8x16, 20 rows a level, FP64: an apply of 335 us against 462
+// with one slot a load and 496 with 256 rows; of fatter boxes 64-row phases bring
+// little or nothing, 24^3 x 48 FP64 2.03 ms against 1.98 with 256 rows, FP32 1.03
+// against 1.05).
 struct RingForm {
   int kr, pack;
 };
@@ -1859,9 +1864,9 @@ static void factor_by_lines_t(const ras *R, const double *atab, const int32_t *l
       groups[L] = std::max(groups[L], (sh.line_lvl[L + 1] - sh.line_lvl[L] + per - 1) / per);
   }
   // Boxes are independent: two halves on two streams fill the compute units
-  // that a launch's last workgroups leave idle (the whole setup: 108 boxes 24.3
-  // -> 21.1 ms, 512 boxes 67.2 -> 63.6; 32 boxes 7.9 either way, fewer leave
-  // compute units idle in any case).
+  // that a launch's last workgroups leave idle (ras_setup in FP64: 108 boxes of
+  // 24^3 x 48 25.0 -> 21.7 ms, 512 of 32^3 x 64 69.1 -> 65.5, 32 of 24^3 x 16
+  // 17.0 -> 15.3; fewer leave compute units idle in any case).
   const int mid = last - first >= kFlTwoStreams ? first + (last - first) / 2 : last;
   auto level = [&](int L, int b0, int b1, hipStream_t st) {
     const int count = b1 - b0, count8 = (count + 7) / 8 * 8;
