@@ -304,10 +304,10 @@ __global__ void __launch_bounds__(256) factor_kernel(OpDev op, const SubInfo *__
 //
 // What bounds it: the LDS reads (72 B per block product, about 760 a row) and
 // the waits between the 26 pieces, which the second workgroup fills; below
-// them the U blocks read, about 30 KB per row from HBM (a row's own blocks are
-// 6 KB), since a box's window of lines does not fit in L2.  24^3 x 48 in 108
-// boxes: 19.5 ms on one stream, 16.5 on two; with a thread per row, the rows of
-// a point level in parallel, 157 ms.  Preconditioners with a box over 54 nodes
+// them the U blocks read, 22 KB per row from HBM by the counters (a row's own
+// blocks are 6 KB), since a box's window of lines does not fit in L2.  24^3 x 48
+// in 108 boxes (1.34 M rows): 19.5 ms on one stream, 16.5 on two; with a thread
+// per row, the rows of a point level in parallel, 157 ms.  Preconditioners with a box over 54 nodes
 // long keep that form (factor_kernel).
 constexpr int kFlUnits0 = 63, kFlUnits1 = 122;   // 16-byte units per row: slots 40..53, 54..80
 template <int ROWS> struct FlCfg {
